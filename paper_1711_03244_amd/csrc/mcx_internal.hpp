@@ -105,7 +105,7 @@ struct LaunchParams {
   // its waves use it while they work on that simulation.
   int32_t window_cells;
   // How the kernel adds to map cells: 1 a returning 32-bit add with a carry
-  // into the cell's high word, 0 one 64-bit add (see map_add).
+  // into the cell's high word, 0 one 64-bit add (see deposit).
   int32_t map32;
 };
 
@@ -119,11 +119,8 @@ constexpr int kVariantCensus = 3;
 bool transport_variant_available(bool detect, bool diag, bool accurate, int variant);
 hipError_t transport_occupancy(int* blocks_per_cu, int block, size_t smem, bool detect,
                                bool diag, bool accurate, int variant);
-// `host` is the host copy (for the shared-memory size); `dev` must hold the
-// same bytes in device memory by the time the kernel runs.
-hipError_t launch_transport(const LaunchParams& host, const LaunchParams* dev, int grid,
-                            int block, hipStream_t s, bool detect, bool diag, bool accurate,
-                            int variant);
+hipError_t launch_transport(const LaunchParams& params, int grid, int block, hipStream_t s,
+                            bool detect, bool diag, bool accurate, int variant);
 
 // Zero `ncells` tally cells and `nsims` ledgers, counters and record counts.
 hipError_t launch_clear(uint64_t* tally, uint64_t ncells, double* ledger,

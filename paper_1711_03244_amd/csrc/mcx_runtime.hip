@@ -135,7 +135,6 @@ struct mcx_ctx {
   // estimated cost per photon of every simulation (ms); empty: home waves by
   // job counts
   std::vector<double> cost;
-  mcx::LaunchParams* d_launch = nullptr;
   float* d_stage32 = nullptr;
   double* d_stage64 = nullptr;
   // detected-photon post-processing: absorption changes, per-detector
@@ -274,7 +273,7 @@ static void release(mcx_ctx* c) {
   void* bufs[] = {c->d_labels,      c->d_tables,     c->d_tally,   c->d_ledger,
                   c->d_counts,      c->d_det_count,  c->d_reduce,  c->d_rec,
                   c->d_rec_photon,  c->d_digest,     c->d_desc,    c->d_job_start,
-                  c->d_job_counter, c->d_launch,     c->d_stage32, c->d_stage64,
+                  c->d_job_counter, c->d_stage32, c->d_stage64,
                   c->d_dmua,        c->d_post,       c->d_post_w,  c->d_post_ws,
                   c->d_home_start, c->d_wbox};
   for (void* b : bufs)
@@ -590,7 +589,6 @@ static mcx_status setup(mcx_ctx* c, const mcx_sim* sims) {
   HIP_TRY(hipMalloc(&c->d_home_start, (n + 1) * sizeof(uint64_t)));
   HIP_TRY(hipMalloc(&c->d_job_counter, n * sizeof(unsigned long long)));
   HIP_TRY(hipMalloc(&c->d_wbox, n * 2 * mcx::kMaxWinGates * sizeof(int4)));
-  HIP_TRY(hipMalloc(&c->d_launch, sizeof(mcx::LaunchParams)));
   if (recs > 0) {
     HIP_TRY(hipMalloc(&c->d_rec, recs * sizeof(float)));
     HIP_TRY(hipMalloc(&c->d_rec_photon, rec_rows * sizeof(unsigned long long)));
@@ -813,11 +811,10 @@ static mcx_status enqueue(mcx_ctx* c, const uint64_t* first, const uint64_t* n,
                          hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemcpyAsync(c->d_wbox, wbox.data(), wbox.size() * sizeof(int4),
                          hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(c->d_launch, &lp, sizeof(lp), hipMemcpyHostToDevice, st));
   HIP_TRY(mcx::launch_reset_counters(c->d_job_counter, static_cast<int>(ns), st));
   HIP_TRY(hipEventRecord(c->ev_k0, st));
   HIP_TRY(mcx::launch_transport(
-      lp, c->d_launch, c->grid, c->block, st, c->detect, c->diag, c->opt.accurate_math != 0,
+      lp, c->grid, c->block, st, c->detect, c->diag, c->opt.accurate_math != 0,
       c->force_variant >= 0 ? c->force_variant : c->opt.kernel_variant));
   HIP_TRY(hipEventRecord(c->ev_k1, st));
   HIP_TRY(hipMemsetAsync(c->d_reduce, 0, ns * 2 * sizeof(double), st));

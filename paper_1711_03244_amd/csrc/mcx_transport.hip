@@ -112,16 +112,20 @@ __device__ __forceinline__ uint32_t rank_below(uint64_t mask) {
                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
 }
 
-__device__ __forceinline__ uint32_t wave_count(bool p) {
-  return static_cast<uint32_t>(__popcll(__ballot(p)));
+// ------------------------------------------------------------------ physics
+// Distance along the direction to the face a velocity component points at:
+// the gap in the local coordinate f (in [0, 1], so never negative) times r =
+// h/|v|.  For v == 0, r is infinite, and the distance is infinite or, on the
+// face itself, NaN: neither is ever the smallest under a minimum that
+// ignores NaN.
+__device__ __forceinline__ float face_dist(float f, float v, float r) {
+  return (v > 0.f ? 1.f - f : f) * r;
 }
 
-// ------------------------------------------------------------------ physics
-// Distance along the direction to the face a velocity component points at;
-// `face` is the local coordinate gap, `r` = h/|v| (only used when v != 0).
-__device__ __forceinline__ float face_dist(float f, float v, float r) {
-  const float gap = fmaxf(v > 0.f ? 1.f - f : f, 0.f);
-  return v != 0.f ? gap * r : kInf;
+// a * b rounded on its own: never part of a fused multiply-add.
+__device__ __forceinline__ float rounded_product(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
 }
 
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -156,27 +160,32 @@ __device__ __forceinline__ float fsqrt(float x) {
 }
 
 // 1 - exp(-x) for x >= 0 without cancellation: its alternating series to the
-// x^7 term below 0.25 (truncation < 2e-9 relative), 1 - exp(-x) above.
+// x^7 term below 0.25 (truncation < 2e-9 relative), 1 - exp(-x) above.  Few
+// segments are that thick: the wave skips the exponential when none is.
 template <bool kNative>
 __device__ __forceinline__ float one_minus_exp(float x) {
   if constexpr (kNative) {
-    if (x < 0.25f) {
-      float r = fmaf(x, 1.f / 5040.f, -1.f / 720.f);
-      r = fmaf(x, r, 1.f / 120.f);
-      r = fmaf(x, r, -1.f / 24.f);
-      r = fmaf(x, r, 1.f / 6.f);
-      r = fmaf(x, r, -0.5f);
-      r = fmaf(x, r, 1.f);
-      return x * r;
+    float r = fmaf(x, 1.f / 5040.f, -1.f / 720.f);
+    r = fmaf(x, r, 1.f / 120.f);
+    r = fmaf(x, r, -1.f / 24.f);
+    r = fmaf(x, r, 1.f / 6.f);
+    r = fmaf(x, r, -0.5f);
+    r = fmaf(x, r, 1.f);
+    r = x * r;
+    const bool thick = !(x < 0.25f);
+    if (__ballot(thick) != 0) {
+      asm volatile("");  // a branch, not a speculated exponential
+      const float e = 1.f - __builtin_amdgcn_exp2f(x * -1.4426950408889634f);
+      r = thick ? e : r;
     }
-    return 1.f - __builtin_amdgcn_exp2f(x * -1.4426950408889634f);
+    return r;
   } else {
     return -expm1f(-x);
   }
 }
 
 __device__ __forceinline__ float inv_speed(float h, float v) {
-  return v != 0.f ? h * rcp(fabsf(v)) : kInf;
+  return h * rcp(fabsf(v));  // infinite for v == 0
 }
 
 // Cosine of the Henyey-Greenstein deflection from its inverse CDF, written
@@ -219,53 +228,46 @@ __device__ __forceinline__ float fresnel_r(float n1, float n2, float ci, float c
   return 0.5f * (rs * rs + rp * rp);
 }
 
-// A visit sum of more than 2^28 deposit units (256 voxel sizes of path in
-// one cell) goes to the map directly, and a window sum that reaches 2^31
-// units is moved to the map by the lane whose addition took it there, so
-// the 32-bit window sums cannot wrap.
-constexpr uint32_t kWinMaxAdd = 268435456u;
-constexpr uint32_t kWinMove = 0x80000000u;
+// A visit's addition that may still owe a carry: the 32-bit add of q to a
+// window slot or to the low word of a map cell returned `old`, and when
+// old + q wraps, 1 has to be added to the high word of map cell `cell`.
+// Every carry is seen by exactly the add that caused it, so the 64-bit sum
+// of a cell -- its map count plus what its window slots hold -- is exact
+// once the launch ends.  The test is made an iteration after the add (see
+// transport_kernel), so that no lane waits for the returned value.
+struct Owed {
+  uint32_t old = 0, q = 0, cell = 0;
+};
 
-// Add q deposit units to map cell p, exactly.  The map holds 64-bit integer
-// sums of units.  map32: a returning 32-bit add to the cell's low word, and
-// when that add carries out of it (the returned old value plus q wraps), a
-// second add of 1 to the high word -- every carry is seen by exactly the
-// add that caused it, so the 64-bit sum is exact once the launch ends, and
-// 32-bit adds execute faster at the memory side than 64-bit ones (the wave
-// waits for the returned value, which pays only when enough waves are
-// resident to cover that latency).  Otherwise one 64-bit add without a
-// return value.
-__device__ __forceinline__ void map_add(MCX_GLOBAL uint64_t* p, uint32_t q, bool map32) {
-  if (map32) {
-    MCX_GLOBAL uint32_t* w = reinterpret_cast<MCX_GLOBAL uint32_t*>(p);
-    const uint32_t old = __hip_atomic_fetch_add(w, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old + q < old) __hip_atomic_fetch_add(w + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  } else {
-    __hip_atomic_fetch_add(p, static_cast<uint64_t>(q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void settle(MCX_GLOBAL uint64_t* tally, const Owed& o) {
+  if (o.old + o.q < o.q) {
+    MCX_GLOBAL uint32_t* w = reinterpret_cast<MCX_GLOBAL uint32_t*>(tally + o.cell);
+    __hip_atomic_fetch_add(w + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
-// Add a finished cell visit to the map; returns the number of global
-// atomics issued (0 or 1).  The visit's sum v is first rounded to a whole
-// number q of the simulation's deposit unit u (a power of two, 2^-20 of the
-// voxel size or just below): the map holds integer counts of u, so every
-// sum is exact and the map does not depend on the order of the additions
-// -- any launch shape, batch or photon split gives the same bits.  A visit
-// into the workgroup's LDS window adds q to that cell's 32-bit integer sum
-// (the lane that takes it to 2^31 or more exchanges it with zero and adds
-// what it took to the map); any other is added to the map by map_add.
+// Add a finished cell visit; returns the number of global atomics issued (0
+// or 1).  The visit's sum v is first rounded to a whole number q of the
+// simulation's deposit unit u (a power of two, 2^-20 of the voxel size or
+// just below): the map holds integer counts of u, so every sum is exact and
+// the map does not depend on the order of the additions -- any launch shape,
+// batch or photon split gives the same bits.  A visit into the workgroup's
+// LDS window adds q to that cell's 32-bit integer sum; any other adds to the
+// map, with map32 by a returning 32-bit add to the cell's low word (faster
+// at the memory side), else by one 64-bit add without a return value.  The
+// 32-bit adds leave in `owed` what settle() needs.
 // kRacy: a plain read, add and write of the map cell instead of the atomic
 // -- the paper's non-atomic benchmark variant (B2), where concurrent updates
 // of one cell can be lost.  kCensus: 1 per visit instead (the flush census).
 template <bool kRacy, bool kCensus = false>
-__device__ __forceinline__ int deposit(CSim* D, uint32_t* s_win, uint32_t cell, int slot,
-                                      float v, bool map32) {
-  MCX_GLOBAL uint64_t* p = as_global(D->tally) + cell;
+__device__ __forceinline__ int deposit(MCX_GLOBAL uint64_t* tally, float q_inv, uint32_t* s_win,
+                                       uint32_t cell, int slot, float v, bool map32, Owed& owed) {
+  MCX_GLOBAL uint64_t* p = tally + cell;
   if constexpr (kCensus) {
-    map_add(p, 1u, false);
+    __hip_atomic_fetch_add(p, static_cast<uint64_t>(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return 1;
   }
-  const float qf = rintf(v * D->q_inv);  // an exact scaling by a power of two
+  const float qf = rintf(v * q_inv);  // an exact scaling by a power of two
   if (qf >= 4294967296.f) {  // 2^32 units or more in one visit: one 64-bit add
     if constexpr (kRacy)
       *p = *p + static_cast<uint64_t>(qf);
@@ -275,19 +277,25 @@ __device__ __forceinline__ int deposit(CSim* D, uint32_t* s_win, uint32_t cell, 
     return 1;
   }
   const uint32_t q = static_cast<uint32_t>(qf);
-  if (slot >= 0 && q <= kWinMaxAdd) {
-    if (atomicAdd(s_win + slot, q) + q < kWinMove) return 0;
-    map_add(p, atomicExch(s_win + slot, 0u), map32);
-    return 1;
+  if (slot >= 0) {
+    owed.old = atomicAdd(s_win + slot, q);
+    owed.q = q;
+    owed.cell = cell;
+    return 0;
   }
-  if constexpr (kRacy)
+  if constexpr (kRacy) {
     *p = *p + q;
-  else
-    map_add(p, q, map32);
+  } else if (map32) {
+    owed.old = __hip_atomic_fetch_add(reinterpret_cast<MCX_GLOBAL uint32_t*>(p), q,
+                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    owed.q = q;
+    owed.cell = cell;
+  } else {
+    __hip_atomic_fetch_add(p, static_cast<uint64_t>(q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   return 1;
 }
 
-enum : int { kEvTime = 0, kEvScat = 1, kEvCross = 2 };
 enum : int { kAlive = 0, kEndEscape = 1, kEndTime = 2, kEndRoulette = 3, kEndCapped = 4 };
 
 // Event-loop variants (the paper's benchmark study, Fig. 2): the default
@@ -306,7 +314,7 @@ __device__ __forceinline__ int window_slot(const int4* s_wbox, int wng, int gate
   const uint32_t uz = static_cast<uint32_t>(iz - a.z);
   if (ux < static_cast<uint32_t>(b.x) && uy < static_cast<uint32_t>(b.y) &&
       uz < static_cast<uint32_t>(b.z))
-    return a.w + static_cast<int>((uz * b.y + uy) * b.x + ux);
+    return a.w + static_cast<int>(__umul24(__umul24(uz, b.y) + uy, b.x) + ux);
   return -1;
 }
 
@@ -325,14 +333,61 @@ __device__ __forceinline__ uint32_t window_cell(const int4* s_wbox, int wng, CSi
          DW->stride_z * static_cast<uint32_t>(a.z + z);
 }
 
+// The event loop is bound by instruction issue (a full wave runs the
+// scattering and the face path of nearly every iteration) and, with few
+// photons left, by the chain of waits of one iteration.  So: launch
+// parameters come with the kernel's arguments and the simulation's hot fields
+// stay in scalar registers (no round trip each), the label across the
+// nearest face is loaded ahead of the deposit, additions that return a value
+// are settled an iteration later, small divergent steps are selections, the
+// steps only a change of label needs sit behind one branch, and events are
+// counted when a photon ends.  Measured against loads where used, waited-for
+// returning adds, branches per axis and ballots per count: homogeneous cube,
+// 1e4 photons 7.2 -> 5.1 ms; sphere benchmark, 1e6 photons 20.4 -> 14.0 ms,
+// 3e7 photons 162.5 -> 149.5 ms (bound by the map's atomics); head phantom,
+// 1e7 photons 100.9 -> 87.3 ms.
+//
+// What the event loop reads of its simulation in every iteration, held in
+// scalar registers while the wave stays on that simulation (a scalar load
+// where each is used costs the wave a round trip to the scalar cache).
+struct Hot {
+  const MCX_GLOBAL uint8_t* labels;
+  MCX_GLOBAL uint64_t* tally;
+  int nx, ny, nz;
+  uint32_t nvox, stride_y, stride_z;
+  float h, inv_h, t0, inv_dt, t_end, n_out, q_inv;
+  int gate_max, reflect;
+  uint32_t key0, key1;
+};
+
+__device__ __forceinline__ Hot load_hot(CSim* D) {
+  Hot H;
+  H.labels = as_global(D->labels);
+  H.tally = as_global(D->tally);
+  H.nx = D->nx;
+  H.ny = D->ny;
+  H.nz = D->nz;
+  H.nvox = D->nvox;
+  H.stride_y = D->stride_y;
+  H.stride_z = D->stride_z;
+  H.h = D->h;
+  H.inv_h = D->inv_h;
+  H.t0 = D->t0;
+  H.inv_dt = D->inv_dt;
+  H.t_end = D->t_end;
+  H.n_out = D->n_out;
+  H.q_inv = D->q_inv;
+  H.gate_max = D->ngates - 1;
+  H.reflect = D->reflect;
+  H.key0 = D->key0;
+  H.key1 = D->key1;
+  return H;
+}
+
 template <bool kDetect, bool kDiag, bool kNative, int kVar>
-__global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* params) {
+__global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams L) {
   constexpr bool kRacy = kVar == kVarRacy;
   constexpr bool kCensus = kVar == kVarCensus;
-  // Launch and simulation parameters live in device memory and are read
-  // where used (scalar loads that hit the scalar cache) rather than held in
-  // scalar registers for the whole persistent loop.
-  const LaunchParams& L = *params;
   extern __shared__ float4 s_dyn[];
   __shared__ double s_led[kMaxWavesPerBlock][kLedgerN];
   __shared__ unsigned long long s_cnt[kMaxWavesPerBlock][kCountN];
@@ -344,7 +399,13 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
   const int rows = L.table_rows;
   float4* s_tab = s_dyn + wid * rows;  // this wave's copy of its simulation's tables
   const int wcells = kCensus ? 0 : L.window_cells;
-  const bool map32 = L.map32 != 0;  // how map cells are added to (map_add)
+  // the launch parameters the loop reads, each a scalar register of its own
+  // (read as they lie they would be one wide register block, kept or spilled
+  // as a whole)
+  uint32_t max_events = L.max_events, map32_word = static_cast<uint32_t>(L.map32);
+  float rr_threshold = L.rr_threshold, rr_p = L.rr_p, rr_m = L.rr_m;
+  asm volatile("" : "+s"(max_events), "+s"(map32_word), "+s"(rr_threshold), "+s"(rr_p), "+s"(rr_m));
+  const bool map32 = map32_word != 0;  // how map cells are added to (deposit)
   uint32_t* s_win = reinterpret_cast<uint32_t*>(s_dyn + (bdim >> 6) * rows);
   float* s_len = reinterpret_cast<float*>(s_win + wcells) + threadIdx.x;  // [m * blockDim]
 
@@ -381,12 +442,11 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
   if (lane < kLedgerN) s_led[wid][lane] = 0.0;
   if (lane < kCountN) s_cnt[wid][lane] = 0ull;
   __syncthreads();
-  const float4* s_med = s_tab;  // (mua, mus, g, n); the other tables follow at nmedia offsets
 
   // photon state
   bool alive = false;
-  int ix = 0, iy = 0, iz = 0, m = 0;
-  uint32_t lin = 0;
+  int ix = 0, iy = 0, iz = 0;
+  uint32_t lin = 0, m = 0;
   float fx = 0.f, fy = 0.f, fz = 0.f, vx = 0.f, vy = 0.f, vz = 1.f;
   float rx = kInf, ry = kInf, rz = kInf;
   float w = 0.f, t = 0.f, s = 0.f;
@@ -395,44 +455,52 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
   uint32_t acc_cell = 0xffffffffu, old_cell = 0xffffffffu;
   int acc_slot = -1, old_slot = -1;
   float acc = 0.f, old_acc = 0.f;
+  Owed owed;  // of the lane's last addition
 
   // wave-uniform state: current simulation, its photon pool [pool_next,
   // pool_end) (offsets from its first photon), and a job taken but not yet
   // started because the wave was still busy with another simulation
   int cur = -1;
+  int wng_cur = 0;  // gates of the window the wave's simulation may use
   CSim* D = as_const(L.sims);
+  Hot H = load_hot(D);
   uint64_t pool_next = 0, pool_end = 0;
   bool has_pend = false, dry = false;
   int pend_sim = 0;
   uint64_t pend_first = 0, pend_end = 0;
-  // per-wave counts of frequent events (scalar registers); rare events are
-  // counted in the wave's LDS slice by the lanes they happen to
-  uint32_t c_launch = 0, c_scat = 0, c_face = 0, c_fres = 0, c_ev = 0, c_slots = 0, c_flush = 0;
+  // Counts: photons launched and lane slots per wave, in scalar registers;
+  // events, scatterings, random blocks and flushes per lane, added up when a
+  // photon ends (a lane's 32-bit sums would need a photon of 2^32 events,
+  // an hour's work, to wrap between two spills); rare events in the wave's
+  // LDS slice by the lanes they happen to.
+  uint32_t c_launch = 0, c_slots = 0;
+  uint32_t c_ev = 0, c_scat = 0, c_blk = 0, c_flush = 0;
 
-  // add the wave's tallies of simulation `cur` to its totals and clear them
-  // move the 32-bit register counts to the wave's 64-bit LDS counters
+  // move the register counts to the wave's 64-bit LDS counters
   auto spill_counts = [&]() {
+    unsigned long long* C = s_cnt[wid];
     if (lane == 0) {
-      s_cnt[wid][kCntLaunched] += c_launch;
-      s_cnt[wid][kCntScatters] += c_scat;
-      s_cnt[wid][kCntFaceEvents] += c_face;
-      s_cnt[wid][kCntFresnel] += c_fres;
-      s_cnt[wid][kCntEvents] += c_ev;
-      s_cnt[wid][kCntLaneSlots] += c_slots;
-      s_cnt[wid][kCntFlushes] += c_flush;
+      C[kCntLaunched] += c_launch;
+      C[kCntLaneSlots] += c_slots;
     }
-    c_launch = c_scat = c_face = c_fres = c_ev = c_slots = c_flush = 0;
+    atomicAdd(C + kCntEvents, static_cast<unsigned long long>(c_ev));
+    atomicAdd(C + kCntScatters, static_cast<unsigned long long>(c_scat));
+    // each block is a scattering's or a Fresnel test's
+    atomicAdd(C + kCntFresnel, static_cast<unsigned long long>(c_blk - c_scat));
+    atomicAdd(C + kCntFlushes, static_cast<unsigned long long>(c_flush));
+    c_launch = c_slots = c_ev = c_scat = c_blk = c_flush = 0;
   };
+  // add the wave's tallies of simulation `cur` (none of its photons is
+  // alive) to its totals and clear them
   auto flush_wave = [&]() {
     spill_counts();
+    if (lane == 0)  // a segment ends in a scattering, a face or the last gate's end
+      s_cnt[wid][kCntFaceEvents] =
+          s_cnt[wid][kCntEvents] - s_cnt[wid][kCntScatters] - s_cnt[wid][kCntTimeout];
     if (cur >= 0) {
-      if (lane == 0) {
-        unsigned long long* C = D->counts;
-        for (int i = 0; i < kCountN; ++i)
-          if (s_cnt[wid][i]) atomicAdd(C + i, s_cnt[wid][i]);
-        for (int i = 0; i < kLedgerN; ++i)
-          if (s_led[wid][i] != 0.0) unsafeAtomicAdd(D->ledger + i, s_led[wid][i]);
-      }
+      if (lane < kCountN && s_cnt[wid][lane]) atomicAdd(D->counts + lane, s_cnt[wid][lane]);
+      if (lane < kLedgerN && s_led[wid][lane] != 0.0)
+        unsafeAtomicAdd(D->ledger + lane, s_led[wid][lane]);
     }
     if (lane < kLedgerN) s_led[wid][lane] = 0.0;
     if (lane < kCountN) s_cnt[wid][lane] = 0ull;
@@ -443,7 +511,6 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
     // its descriptor is read with scalar loads.
     D = uniform_sim(D);
     // ---------------------------------------------------------------- refill
-    bool launched = false;
     const uint64_t dead = __ballot(!alive);
     if (dead != 0 && !dry) {
       if (pool_next == pool_end && !has_pend) {
@@ -480,10 +547,15 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
         if (pend_sim != cur) {
           // every lane is idle: move the wave to the job's simulation
           flush_wave();
+          settle(H.tally, owed);  // of the simulation the lane leaves
+          owed = Owed{};
           cur = pend_sim;
           D = uniform_sim(as_const(L.sims) + cur);
-          const int nrow = 3 * D->nmedia + D->ndet;
-          for (int i = lane; i < nrow; i += 64) s_tab[i] = D->tables[i];
+          H = load_hot(D);
+          const int nm = D->nmedia, nrow = 3 * nm + D->ndet;
+          for (int i = lane; i < nrow; i += 64)
+            s_tab[i < 3 * nm ? 3 * (i % nm) + i / nm : i] = D->tables[i];
+          wng_cur = cur == wsim ? wng : 0;
           __builtin_amdgcn_wave_barrier();
         }
         pool_next = pend_first;
@@ -499,7 +571,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
           const uint64_t k = D->first + pool_next + rank;
           klo = static_cast<uint32_t>(k);
           khi = static_cast<uint32_t>(k >> 32);
-          const Words r = philox4x32_10(klo, khi, 0u, 0u, D->key0, D->key1);
+          const Words r = philox4x32_10(klo, khi, 0u, 0u, H.key0, H.key1);
           s = neg_log<kNative>(unit_open(r.x));
           blk = 1;
           ix = D->src_ix;
@@ -513,11 +585,11 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
           vx = D->src_vx;
           vy = D->src_vy;
           vz = D->src_vz;
-          rx = inv_speed(D->h, vx);
-          ry = inv_speed(D->h, vy);
-          rz = inv_speed(D->h, vz);
+          rx = inv_speed(H.h, vx);
+          ry = inv_speed(H.h, vy);
+          rz = inv_speed(H.h, vz);
           w = 1.f;
-          t = D->t0;
+          t = H.t0;
           nev = 0;
           nscat = 0;
           acc_cell = 0xffffffffu;
@@ -530,122 +602,106 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
             for (int mm = 0; mm < L.nmedia_max; ++mm) s_len[mm * bdim] = 0.f;
           }
           alive = true;
-          launched = true;
         }
       }
       pool_next += give;
+      c_launch += static_cast<uint32_t>(give);
+      if (give == 0 && dead == ~0ull) {
+        if (dry) break;
+        continue;  // the wave's lanes just finished: take the pending job next
+      }
+    } else if (dead == ~0ull) {
+      break;
     }
-    c_launch += wave_count(launched);
-    if (__ballot(alive) == 0) {
-      if (dry) break;
-      continue;  // the wave's lanes just finished: take the pending job next
-    }
-    D = uniform_sim(D);
     if (c_slots >= (1u << 30)) spill_counts();  // keeps every 32-bit count from wrapping
     c_slots += 64;
-    c_ev += wave_count(alive);
 
     // ----------------------------------------------------------------- event
     int end = kAlive;
     int det_hit = -1;
-    bool f_scat = false, f_face = false, f_fres = false;
-    int n_flush = 0;  // global atomics this lane issued in this iteration (at most 3)
+    // a visit that left the lane's cell cache, added at the end of the iteration
+    uint32_t out_cell = 0;
+    int out_slot = -1;
+    float out_acc = 0.f;
     if (alive) {
-      if (nev >= L.max_events) {
+      if (nev >= max_events) {
         end = kEndCapped;
       } else {
         ++nev;
-        const int nm = D->nmedia;
-        const float4 md = s_med[m];        // mua, mus, g, n
-        const float4 dd = s_med[nm + m];   // 1/mus, n/c, c/n, 1/mua
-        const float ds = md.y > 0.f ? s * dd.x : kInf;
+        const float4* row = s_tab + __umul24(m, 3u);
+        const float4 md = row[0];  // mua, mus, g, n
+        const float4 dd = row[1];  // 1/mus, n/c, c/n, 1/mua
         const float dx = face_dist(fx, vx, rx), dy = face_dist(fy, vy, ry),
                     dz = face_dist(fz, vz, rz);
-        int ax;
-        float dv;
-        if (dx <= dy && dx <= dz) {
-          ax = 0;
-          dv = dx;
-        } else if (dy <= dz) {
-          ax = 1;
-          dv = dy;
-        } else {
-          ax = 2;
-          dv = dz;
-        }
-        const float dtime = fmaxf((D->t_end - t) * dd.z, 0.f);
-        int ev;
-        float l;
-        if (dtime < fminf(ds, dv)) {
-          ev = kEvTime;
-          l = dtime;
-        } else if (ds <= dv) {
-          ev = kEvScat;
-          l = ds;
-        } else {
-          ev = kEvCross;
-          l = dv;
-        }
+        const float dv = fminf(fminf(dx, dy), dz);
+        const bool is_x = dx == dv, is_y = !is_x && dy == dv;  // the lowest axis wins ties
+        // the voxel across the nearest face: its label is loaded now, whether
+        // or not the segment ends there, so that the load is in flight while
+        // the segment's deposit is computed
+        const float va = is_x ? vx : (is_y ? vy : vz);
+        const bool up = va > 0.f;
+        const int step = up ? 1 : -1;
+        const uint32_t qa = static_cast<uint32_t>((is_x ? ix : (is_y ? iy : iz)) + step);
+        const uint32_t na = static_cast<uint32_t>(is_x ? H.nx : (is_y ? H.ny : H.nz));
+        const uint32_t stride = is_x ? 1u : (is_y ? H.stride_y : H.stride_z);
+        const bool inside = qa < na;
+        uint32_t qlin = lin + (up ? stride : 0u - stride);
+        qlin = inside ? qlin : lin;
+        const uint32_t qlab =
+            __hip_atomic_load(H.labels + qlin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 
-        // absorption along the segment, booked at the segment-start gate
-        int gate = static_cast<int>(floorf((t - D->t0) * D->inv_dt));
-        gate = min(max(gate, 0), D->ngates - 1);
-        const uint32_t cell = static_cast<uint32_t>(gate) * D->nvox + lin;
-        const float q = one_minus_exp<kNative>(md.x * l);  // 1 - exp(-mua l)
-        const float dep = md.x > 0.f ? w * q * dd.w : w * l;
-        if constexpr (kVar == kVarFlat) {
-          // the same two-entry update by selection: a hit on the current
-          // entry adds to it; a hit on the previous one swaps the entries;
-          // a miss flushes the previous entry and shifts the current one
-          const bool hit_a = cell == acc_cell;
-          const bool hit_o = !hit_a && cell == old_cell;
-          const bool miss = !hit_a && !hit_o;
-          if (miss && old_cell != 0xffffffffu && old_acc != 0.f) {
-            n_flush += deposit<kRacy, kCensus>(D, s_win, old_cell, old_slot, old_acc, map32);
-          }
-          const int slot = cur == wsim ? window_slot(s_wbox, wng, gate, ix, iy, iz) : -1;
-          const float a_new = hit_a ? acc : (hit_o ? old_acc : 0.f);
-          const int s_new = hit_a ? acc_slot : (hit_o ? old_slot : slot);
-          old_acc = hit_a ? old_acc : acc;
-          old_slot = hit_a ? old_slot : acc_slot;
-          old_cell = hit_a ? old_cell : acc_cell;
-          acc = miss ? dep : a_new + dep;
-          acc_slot = s_new;
-          acc_cell = cell;
-        } else if (cell == acc_cell) {
-          acc += dep;
-        } else if (cell == old_cell) {
-          // back in the previous cell: swap the two entries
-          const float ta = acc;
-          const int ts = acc_slot;
-          acc = old_acc + dep;
-          acc_slot = old_slot;
-          old_acc = ta;
-          old_slot = ts;
-          old_cell = acc_cell;
-          acc_cell = cell;
-        } else {
-          if (old_cell != 0xffffffffu && old_acc != 0.f) {
-            n_flush += deposit<kRacy, kCensus>(D, s_win, old_cell, old_slot, old_acc, map32);
-          }
-          old_cell = acc_cell;
-          old_slot = acc_slot;
-          old_acc = acc;
-          const int slot = cur == wsim ? window_slot(s_wbox, wng, gate, ix, iy, iz) : -1;
-          acc_slot = slot;
-          acc_cell = cell;
-          acc = dep;
+        const float ds = md.y > 0.f ? s * dd.x : kInf;
+        const float dtime = fmaxf((H.t_end - t) * dd.z, 0.f);
+        const float dsv = fminf(ds, dv);
+        const bool is_time = dtime < dsv;
+        const bool is_scat = !is_time && ds <= dv;
+        const bool is_cross = !is_time && !is_scat;
+        const float l = is_time ? dtime : dsv;
+
+        // absorption along the segment, booked at the segment-start gate (t
+        // never falls below t0, so the gate's quotient is not negative)
+        uint32_t gate = 0;
+        uint32_t cell = lin;
+        if (H.gate_max > 0) {
+          gate = static_cast<uint32_t>((t - H.t0) * H.inv_dt);
+          gate = min(gate, static_cast<uint32_t>(H.gate_max));
+          cell += gate * H.nvox;
         }
-        w = w - w * q;
+        const float q = one_minus_exp<kNative>(md.x * l);  // 1 - exp(-mua l)
+        // the absorbed weight is rounded once, for the deposit and the decay
+        const float wq = rounded_product(w, q);
+        const float dep = md.x > 0.f ? wq * dd.w : w * l;
+        // The two most recent cells by selection: a hit on the current entry
+        // adds to it; a hit on the previous one swaps the entries (a photon
+        // crossing back and forth over one face costs nothing extra); a miss
+        // sends the previous entry out and shifts the current one.
+        const bool hit_a = cell == acc_cell;
+        const bool hit_o = cell == old_cell;
+        const bool miss = !hit_a && !hit_o;
+        out_cell = old_cell;
+        out_slot = old_slot;
+        out_acc = miss ? old_acc : 0.f;
+        const float a_new = hit_a ? acc : (hit_o ? old_acc : 0.f);
+        int s_new = hit_a ? acc_slot : old_slot;
+        if (miss)
+          s_new = window_slot(s_wbox, wng_cur, static_cast<int>(gate), ix, iy, iz);
+        old_acc = hit_a ? old_acc : acc;
+        old_slot = hit_a ? old_slot : acc_slot;
+        old_cell = hit_a ? old_cell : acc_cell;
+        acc = a_new + dep;
+        acc_slot = s_new;
+        acc_cell = cell;
+        w = w - wq;
 
         // move
-        const float lh = l * D->inv_h;
+        const float lh = l * H.inv_h;
         fx = __builtin_amdgcn_fmed3f(fmaf(lh, vx, fx), 0.f, 1.f);
         fy = __builtin_amdgcn_fmed3f(fmaf(lh, vy, fy), 0.f, 1.f);
         fz = __builtin_amdgcn_fmed3f(fmaf(lh, vz, fz), 0.f, 1.f);
         t = fmaf(l, dd.y, t);
-        s = ev == kEvScat ? 0.f : fmaxf(fmaf(-md.y, l, s), 0.f);
-        if constexpr (kDetect) s_len[m * bdim] += l;
+        s = fmaxf(fmaf(-md.y, l, s), 0.f);  // a scattering draws the next one below
+        if constexpr (kDetect)
+          unsafeAtomicAdd(s_len + __umul24(m, bdim), l);  // no wait for the old value
 
         if constexpr (kVar == kVarFlat) {
           // Every lane that did not time out runs the same instructions:
@@ -654,47 +710,39 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
           // its own event by selection.  Only the label read of the
           // neighbour, the counters of rare events and the bookkeeping of a
           // photon's end stay conditional.
-          const bool is_scat = ev == kEvScat, is_cross = ev == kEvCross;
-          if (ev == kEvTime) end = kEndTime;
-          const float va = ax == 0 ? vx : (ax == 1 ? vy : vz);
-          const float vb1 = ax == 0 ? vy : (ax == 1 ? vz : vx);
-          const float vb2 = ax == 0 ? vz : (ax == 1 ? vx : vy);
-          const int step = va > 0.f ? 1 : -1;
-          const int qa = (ax == 0 ? ix : (ax == 1 ? iy : iz)) + step;
-          const int na = ax == 0 ? D->nx : (ax == 1 ? D->ny : D->nz);
-          const uint32_t stride = ax == 0 ? 1u : (ax == 1 ? D->stride_y : D->stride_z);
-          const uint32_t qlin = step > 0 ? lin + stride : lin - stride;
-          int m2 = 0;
-          if (is_cross && qa >= 0 && qa < na) m2 = as_global(D->labels)[qlin];
+          if (is_time) end = kEndTime;
+          const float vb1 = is_x ? vy : (is_y ? vz : vx);
+          const float vb2 = is_x ? vz : (is_y ? vx : vy);
+          const uint32_t m2 = inside ? qlab : 0u;
           const float n1 = md.w;
-          const float n2 = m2 != 0 ? s_med[m2].w : D->n_out;
-          const bool fres = is_cross && D->reflect && n2 != n1;
+          const float n2 = m2 != 0 ? s_tab[3 * m2].w : H.n_out;
+          const bool fres = is_cross && H.reflect && n2 != n1;
           const float eta = fres ? n1 * rcp(n2) : 1.f;
           const float st2 = eta * eta * (vb1 * vb1 + vb2 * vb2);
           const bool tir = fres && st2 >= 1.f;
           const float cos_t = fsqrt<kNative>(fmaxf(1.f - st2, 0.f));
           const float refl_p = fresnel_r(n1, n2, fabsf(va), cos_t);
           const bool need_rng = is_scat || (fres && !tir);
-          const Words r = philox4x32_10(klo, khi, blk, 0u, D->key0, D->key1);
+          const Words r = philox4x32_10(klo, khi, blk, 0u, H.key0, H.key1);
           blk += need_rng ? 1u : 0u;
 
           // scattering candidate
           float sx = vx, sy = vy, sz = vz;
-          const float ct = hg_cos(md.z, s_med[2 * nm + m], unit_open(r.x));
+          const float ct = hg_cos(md.z, s_tab[3 * m + 2], unit_open(r.x));
           scatter_dir<kNative>(sx, sy, sz, ct, unit_open(r.y));
           const float s_scat = neg_log<kNative>(unit_open(r.z));
-          const bool rr_test = is_scat && w < L.rr_threshold;
-          const bool rr_live = rr_test && unit_open(r.w) < L.rr_p;
+          const bool rr_test = is_scat && w < rr_threshold;
+          const bool rr_live = rr_test && unit_open(r.w) < rr_p;
           if (rr_test) {
             atomicAdd(&s_cnt[wid][kCntRrTests], 1ull);
             if (rr_live) {
               atomicAdd(&s_cnt[wid][kCntRrSurvived], 1ull);
-              atomicAdd(&s_led[wid][kLedRrGain], static_cast<double>((L.rr_m - 1.f) * w));
+              atomicAdd(&s_led[wid][kLedRrGain], static_cast<double>((rr_m - 1.f) * w));
             } else {
               end = kEndRoulette;
             }
           }
-          w = rr_live ? w * L.rr_m : w;
+          w = rr_live ? w * rr_m : w;
 
           // crossing outcome
           const bool refl = is_cross && (tir || (need_rng && unit_open(r.x) < refl_p));
@@ -707,17 +755,17 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
           const float fa = enter ? entry : face;
           const float va2 = refl ? -va : (refr ? vna : va);
           const float vb1b = refr ? vb1 * eta : vb1, vb2b = refr ? vb2 * eta : vb2;
-          // back to x, y, z: axis ax holds va2, the next ones vb1b, vb2b
-          float cx = ax == 0 ? va2 : (ax == 1 ? vb2b : vb1b);
-          float cy = ax == 0 ? vb1b : (ax == 1 ? va2 : vb2b);
-          float cz = ax == 0 ? vb2b : (ax == 1 ? vb1b : va2);
+          // back to x, y, z: the face's axis holds va2, the next ones vb1b, vb2b
+          float cx = is_x ? va2 : (is_y ? vb2b : vb1b);
+          float cy = is_x ? vb1b : (is_y ? va2 : vb2b);
+          float cz = is_x ? vb2b : (is_y ? vb1b : va2);
           if (is_cross) {
-            if (ax == 0) fx = fa; else if (ax == 1) fy = fa; else fz = fa;
+            if (is_x) fx = fa; else if (is_y) fy = fa; else fz = fa;
           }
           const int di = enter ? step : 0;
-          ix += ax == 0 ? di : 0;
-          iy += ax == 1 ? di : 0;
-          iz += ax == 2 ? di : 0;
+          ix += is_x ? di : 0;
+          iy += is_y ? di : 0;
+          iz += is_x || is_y ? 0 : di;
           lin = enter ? qlin : lin;
           m = enter ? m2 : m;
           // the new direction of each event and its h/|v|
@@ -726,122 +774,117 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
           vy = is_scat ? sy : (is_cross ? cy : vy);
           vz = is_scat ? sz : (is_cross ? cz : vz);
           if (newdir) {
-            rx = inv_speed(D->h, vx);
-            ry = inv_speed(D->h, vy);
-            rz = inv_speed(D->h, vz);
+            rx = inv_speed(H.h, vx);
+            ry = inv_speed(H.h, vy);
+            rz = inv_speed(H.h, vz);
           }
           s = is_scat ? s_scat : s;
           nscat += is_scat ? 1u : 0u;
-          f_scat = is_scat;
-          f_face = is_cross;
-          f_fres = is_cross && need_rng;
-        } else if (ev == kEvTime) {
-          end = kEndTime;
         } else {
-          // crossing set-up: neighbour voxel, its medium, Fresnel terms
-          bool need_rng = ev == kEvScat;
+          // Where the label changes: the far side's index and the Fresnel
+          // terms (a wave whose lanes all stay in their medium skips this).
+          if (is_time) end = kEndTime;
+          const uint32_t m2 = inside ? qlab : 0u;
+          const bool border = is_cross && m2 != m;
           bool tir = false, fres = false;
-          float va = 0.f, vb1 = 0.f, vb2 = 0.f, eta = 1.f, cos_t = 0.f, refl_p = 0.f;
-          int step = 0, m2 = 0;
-          uint32_t qlin = 0;
-          if (ev == kEvCross) {
-            va = ax == 0 ? vx : (ax == 1 ? vy : vz);
-            vb1 = ax == 0 ? vy : (ax == 1 ? vz : vx);
-            vb2 = ax == 0 ? vz : (ax == 1 ? vx : vy);
-            step = va > 0.f ? 1 : -1;
-            const int qa = (ax == 0 ? ix : (ax == 1 ? iy : iz)) + step;
-            const int na = ax == 0 ? D->nx : (ax == 1 ? D->ny : D->nz);
-            const uint32_t stride = ax == 0 ? 1u : (ax == 1 ? D->stride_y : D->stride_z);
-            qlin = step > 0 ? lin + stride : lin - stride;
-            m2 = (qa >= 0 && qa < na) ? as_global(D->labels)[qlin] : 0;
+          float eta = 1.f, cos_t = 0.f, refl_p = 0.f;
+          if (border && H.reflect) {
             const float n1 = md.w;
-            const float n2 = m2 != 0 ? s_med[m2].w : D->n_out;
-            fres = D->reflect && n2 != n1;
+            const float n2 = m2 != 0 ? s_tab[__umul24(m2, 3u)].w : H.n_out;
+            fres = n2 != n1;
             if (fres) {
+              const float vb1 = is_x ? vy : (is_y ? vz : vx);
+              const float vb2 = is_x ? vz : (is_y ? vx : vy);
               eta = n1 * rcp(n2);
               const float st2 = eta * eta * (vb1 * vb1 + vb2 * vb2);
-              if (st2 >= 1.f) {
-                tir = true;
-              } else {
+              tir = st2 >= 1.f;
+              if (!tir) {
                 cos_t = fsqrt<kNative>(1.f - st2);
                 refl_p = fresnel_r(n1, n2, fabsf(va), cos_t);
-                need_rng = true;
               }
             }
           }
           Words r = {0u, 0u, 0u, 0u};
-          if (need_rng) {
-            r = philox4x32_10(klo, khi, blk, 0u, D->key0, D->key1);
+          if (is_scat || (fres && !tir)) {
+            r = philox4x32_10(klo, khi, blk, 0u, H.key0, H.key1);
             ++blk;
           }
 
-          if (ev == kEvScat) {
-            f_scat = true;
+          if (is_scat) {
             ++nscat;
-            const float ct = hg_cos(md.z, s_med[2 * nm + m], unit_open(r.x));
+            const float ct = hg_cos(md.z, row[2], unit_open(r.x));
             scatter_dir<kNative>(vx, vy, vz, ct, unit_open(r.y));
-            rx = inv_speed(D->h, vx);
-            ry = inv_speed(D->h, vy);
-            rz = inv_speed(D->h, vz);
+            rx = inv_speed(H.h, vx);
+            ry = inv_speed(H.h, vy);
+            rz = inv_speed(H.h, vz);
             s = neg_log<kNative>(unit_open(r.z));
-            if (w < L.rr_threshold) {
+            if (w < rr_threshold) {
               atomicAdd(&s_cnt[wid][kCntRrTests], 1ull);
-              if (unit_open(r.w) < L.rr_p) {
+              if (unit_open(r.w) < rr_p) {
                 atomicAdd(&s_cnt[wid][kCntRrSurvived], 1ull);
-                atomicAdd(&s_led[wid][kLedRrGain], static_cast<double>((L.rr_m - 1.f) * w));
-                w *= L.rr_m;
+                atomicAdd(&s_led[wid][kLedRrGain], static_cast<double>((rr_m - 1.f) * w));
+                w *= rr_m;
               } else {
                 end = kEndRoulette;
               }
             }
-          } else {
-            // CROSS on axis ax: the photon sits on the face
-            f_face = true;
-            f_fres = need_rng;
-            const float face = step > 0 ? 1.f : 0.f;
-            if (ax == 0) fx = face; else if (ax == 1) fy = face; else fz = face;
-            const bool reflect = tir || (need_rng && unit_open(r.x) < refl_p);
+          }
+          bool enter = is_cross;
+          if (border) {
+            const bool reflect = tir || (fres && unit_open(r.x) < refl_p);
+            enter = !reflect && m2 != 0;
             if (reflect) {
               atomicAdd(&s_cnt[wid][kCntReflections], 1ull);
-              if (ax == 0) vx = -vx; else if (ax == 1) vy = -vy; else vz = -vz;
+              vx = is_x ? -vx : vx;
+              vy = is_y ? -vy : vy;
+              vz = is_x || is_y ? vz : -vz;
             } else if (m2 == 0) {
               end = kEndEscape;
             } else {
               if (fres) {
                 // refraction: tangential components scale by n1/n2
-                const float na_ = static_cast<float>(step) * cos_t;
-                if (ax == 0) {
-                  vy *= eta; vz *= eta; vx = na_;
-                } else if (ax == 1) {
-                  vz *= eta; vx *= eta; vy = na_;
-                } else {
-                  vx *= eta; vy *= eta; vz = na_;
-                }
-                rx = inv_speed(D->h, vx);
-                ry = inv_speed(D->h, vy);
-                rz = inv_speed(D->h, vz);
+                const float vn = static_cast<float>(step) * cos_t;
+                vx = is_x ? vn : vx * eta;
+                vy = is_y ? vn : vy * eta;
+                vz = is_x || is_y ? vz * eta : vn;
+                rx = inv_speed(H.h, vx);
+                ry = inv_speed(H.h, vy);
+                rz = inv_speed(H.h, vz);
               }
-              const float enter = step > 0 ? 0.f : 1.f;
-              if (ax == 0) {
-                ix += step; fx = enter;
-              } else if (ax == 1) {
-                iy += step; fy = enter;
-              } else {
-                iz += step; fz = enter;
-              }
-              lin = qlin;
               m = m2;
             }
+          }
+          if (is_cross) {
+            // the photon sits on the face: of the voxel it enters, or its own
+            const float fa = up != enter ? 1.f : 0.f;
+            fx = is_x ? fa : fx;
+            fy = is_y ? fa : fy;
+            fz = is_x || is_y ? fz : fa;
+            const int di = enter ? step : 0;
+            ix += is_x ? di : 0;
+            iy += is_y ? di : 0;
+            iz += is_x || is_y ? 0 : di;
+            lin = enter ? qlin : lin;
           }
         }
       }
 
+      // the visit that left the cache (an entry without a cell holds 0)
+      if (out_acc != 0.f) {
+        settle(H.tally, owed);
+        c_flush += deposit<kRacy, kCensus>(H.tally, H.q_inv, s_win, out_cell, out_slot, out_acc,
+                                           map32, owed);
+      }
       if (end != kAlive) {
-        if (acc != 0.f && acc_cell != 0xffffffffu) {
-          n_flush += deposit<kRacy, kCensus>(D, s_win, acc_cell, acc_slot, acc, map32);
+        if (acc != 0.f) {
+          settle(H.tally, owed);
+          c_flush += deposit<kRacy, kCensus>(H.tally, H.q_inv, s_win, acc_cell, acc_slot, acc,
+                                             map32, owed);
         }
-        if (old_acc != 0.f && old_cell != 0xffffffffu) {
-          n_flush += deposit<kRacy, kCensus>(D, s_win, old_cell, old_slot, old_acc, map32);
+        if (old_acc != 0.f) {
+          settle(H.tally, owed);
+          c_flush += deposit<kRacy, kCensus>(H.tally, H.q_inv, s_win, old_cell, old_slot, old_acc,
+                                             map32, owed);
         }
         const double wd = static_cast<double>(w);
         const int end_slot = end == kEndEscape ? kCntEscaped
@@ -851,11 +894,11 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
         if (end == kEndEscape) {
           atomicAdd(&s_led[wid][kLedEscaped], wd);
           if constexpr (kDetect) {
-            const float h = D->h;
+            const float h = H.h;
             const float px = h * (static_cast<float>(ix) + fx);
             const float py = h * (static_cast<float>(iy) + fy);
             const float pz = h * (static_cast<float>(iz) + fz);
-            const float4* s_det = s_med + 3 * D->nmedia;
+            const float4* s_det = s_tab + 3 * D->nmedia;
             for (int d = 0; d < D->ndet; ++d) {
               const float4 Dt = s_det[d];
               const float ex = px - Dt.x, ey = py - Dt.y, ez = pz - Dt.z;
@@ -901,22 +944,23 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams* par
           }
         }
         alive = false;
+        c_ev += nev;
+        c_scat += nscat;
+        c_blk += blk - 1u;  // block 0 launched the photon
       }
     }
 
-    c_scat += wave_count(f_scat);
-    c_face += wave_count(f_face);
-    c_fres += wave_count(f_fres);
-    c_flush += wave_count(n_flush >= 1) + wave_count(n_flush >= 2) +
-               wave_count(n_flush >= 3);
   }
+  settle(H.tally, owed);
   flush_wave();
 
   __syncthreads();
   // add the workgroup's window sums to the map of its window's simulation
   for (int i = threadIdx.x; i < wcount; i += bdim) {
     const uint32_t v = s_win[i];
-    if (v != 0u) map_add(as_global(DW->tally) + window_cell(s_wbox, wng, DW, i), v, map32);
+    if (v != 0u)
+      __hip_atomic_fetch_add(as_global(DW->tally) + window_cell(s_wbox, wng, DW, i),
+                             static_cast<uint64_t>(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -983,15 +1027,14 @@ hipError_t transport_occupancy(int* blocks_per_cu, int block, size_t smem, bool 
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn, block, smem);
 }
 
-hipError_t launch_transport(const LaunchParams& host, const LaunchParams* dev, int grid,
-                            int block, hipStream_t st, bool detect, bool diag, bool accurate,
-                            int variant) {
+hipError_t launch_transport(const LaunchParams& host, int grid, int block, hipStream_t st,
+                            bool detect, bool diag, bool accurate, int variant) {
   const int wcells = host.window_cells;
   const size_t smem =
       transport_smem_bytes(host.table_rows, host.nmedia_max, block, detect, wcells);
   const void* fn = pick(detect, diag, accurate, variant);
   if (!fn) return hipErrorInvalidDeviceFunction;
-  void* args[] = {const_cast<LaunchParams**>(&dev)};
+  void* args[] = {const_cast<LaunchParams*>(&host)};
   return hipLaunchKernel(fn, dim3(grid), dim3(block), args, smem, st);
 }
 
