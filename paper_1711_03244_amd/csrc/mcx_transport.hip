@@ -239,10 +239,11 @@ struct Owed {
   uint32_t old = 0, q = 0, cell = 0;
 };
 
-__device__ __forceinline__ void settle(MCX_GLOBAL uint64_t* tally, const Owed& o) {
+__device__ __forceinline__ void settle(MCX_GLOBAL uint64_t* tally, Owed& o) {
   if (o.old + o.q < o.q) {
     MCX_GLOBAL uint32_t* w = reinterpret_cast<MCX_GLOBAL uint32_t*>(tally + o.cell);
     __hip_atomic_fetch_add(w + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    o.q = 0;  // owed once: an addition that owes nothing leaves `o` as it is
   }
 }
 
