@@ -177,8 +177,10 @@ typedef struct {
  * atomic add per visit.  MCX_MAP_ADDS_32: a 32-bit atomic add to the low
  * word whose returned value tells whether it carried into the high word
  * (then one more add); faster at the memory side, but the wave waits for
- * the returned value.  MCX_MAP_ADDS_AUTO: 32-bit adds when at least 16
- * waves per compute unit are resident.  The maps are bit-identical. */
+ * the returned value.  MCX_MAP_ADDS_AUTO: 32-bit adds where the memory
+ * side's rate of atomics binds: large launches (16 waves per compute unit,
+ * eight photons per lane) of simulations whose voxels are thin (mean mus h
+ * below 2).  The maps are bit-identical. */
 enum { MCX_MAP_ADDS_AUTO = 0, MCX_MAP_ADDS_64 = 1, MCX_MAP_ADDS_32 = 2 };
 
 /* Output kinds for mcx_fluence*. */
@@ -235,8 +237,9 @@ mcx_status mcx_batch_detected(mcx_ctx *ctx, int32_t sim, float *host_rec, uint64
 mcx_status mcx_batch_digest(mcx_ctx *ctx, int32_t sim, double *host_out, uint64_t nrows);
 
 /* Launch shape: threads per workgroup (0 = the size that keeps the most waves
- * resident), photons per job (0 = default 256), LDS window cells (0 = default
- * 16384, < 0 = none, at most 36864; in a batch each workgroup keeps the window
+ * resident, with fewer waves for launches of few photons per lane), photons
+ * per job (0 = 64, in a batch 256, fewer for launches of fewer photons than
+ * lanes), LDS window cells (0 = default 16384, < 0 = none, at most 36864; in a batch each workgroup keeps the window
  * of the simulation its first wave starts on).  The window covers, per early
  * gate, a box of cells: by default one box round the source over the gates of
  * the first ~0.5 ns; after mcx_autotune on a single simulation, the boxes
@@ -300,7 +303,8 @@ mcx_status mcx_fit_runtime(mcx_ctx *ctx, const uint64_t *n1, const uint64_t *n2,
  * S2 partition, shares proportional to the work estimated from 1/a): with
  * cost_per_photon[i] = a_i (e.g. from mcx_fit_runtime), every later launch
  * spreads the waves' home simulations in proportion to a_i n_i instead of
- * the job counts; NULL restores job counts.  Only the schedule changes:
+ * the library's own estimate of each simulation's segments; NULL restores
+ * that estimate.  Only the schedule changes:
  * every photon's history and every result stay the same.  MCX_EINVAL for a
  * negative or non-finite cost. */
 mcx_status mcx_set_balance(mcx_ctx *ctx, const double *cost_per_photon);

@@ -76,6 +76,9 @@ struct SimDesc {
   // all.  The window holds 32-bit integer sums of deposit units.
   const int4* wbox;
   int32_t wng, wcount;
+  // How the kernel adds to this simulation's map cells: 1 a returning 32-bit
+  // add with a carry into the cell's high word, 0 one 64-bit add.
+  int32_t map32;
 };
 
 // One launch over `nsims` simulations.  Photons are handed out in jobs of
@@ -92,8 +95,8 @@ struct LaunchParams {
   uint32_t chunk;
   unsigned long long* job_counters;  // nsims entries, zero at launch
   // Shares of the home simulations: prefix sums (nsims + 1 entries) of each
-  // simulation's job count, or of its estimated work a_i n_i scaled to
-  // integers; nhome = home_start[nsims] (> 0).
+  // simulation's estimated work a_i n_i scaled to integers (one simulation:
+  // its job count); nhome = home_start[nsims] (> 0).
   const uint64_t* home_start;
   uint64_t nhome;
   float rr_threshold, rr_p, rr_m;
@@ -104,9 +107,6 @@ struct LaunchParams {
   // window of one simulation -- the home simulation of its first wave -- and
   // its waves use it while they work on that simulation.
   int32_t window_cells;
-  // How the kernel adds to map cells: 1 a returning 32-bit add with a carry
-  // into the cell's high word, 0 one 64-bit add (see deposit).
-  int32_t map32;
 };
 
 size_t transport_smem_bytes(int table_rows, int nmedia_max, int block, bool detect,

@@ -26,7 +26,9 @@
 namespace {
 
 constexpr double kCmmPerNs = 299.792458;  // speed of light in vacuum, mm/ns
-constexpr int kDefaultChunk = 256;
+constexpr int kDefaultChunk = 64;  // photons per job of a launch that fills the lanes
+constexpr int kBatchChunk = 256;   // the same in contexts of several simulations
+constexpr int kMinChunk = 8;       // and of the smallest launches
 constexpr int kDefaultWindow = 16384;      // FP32 cells, 64 KB of LDS
 constexpr int kMaxWindow = 36864;          // 144 KB of the 160 KB of LDS per CU
 constexpr uint64_t kMaxLaunchPhotons = 1ull << 31;  // per simulation and launch
@@ -83,6 +85,11 @@ struct SimHost {
   float src_f[3] = {0, 0, 0};
   float src_dir[3] = {0, 0, 1};
   int src_label = 0;
+  // mean scattering depth of a voxel (mus h over the labelled voxels) below
+  // kThinDepth: photons cross faces about as often as they scatter, and the
+  // map's atomics bind rather than instruction issue
+  bool thin = false;
+  double events = 1.0;  // estimated segments per photon (describe)
   int rec_len = 0;
   uint64_t label_off = 0, tally_off = 0, table_off = 0;
   uint64_t rec_off = 0;    // first record row (photon-index array)
@@ -105,7 +112,11 @@ struct mcx_ctx {
   mcx_options opt{};
   std::vector<SimHost> sims;
   bool detect = false, diag = false;
-  int block = 256, grid = 0, cus = 0, chunk = kDefaultChunk;
+  int block = 256, grid = 0, cus = 0;
+  int chunk = 0;             // photons per job; 0: by the launch's photons
+  bool fit_shape = true;     // no block size asked for: small launches use fewer waves
+  bool full_shape = false;   // pilots that stand for large launches: no such fit
+  int last_block = 0, last_grid = 0;  // the last launch's shape
   int window_budget = 0;
   int win_cells = 0;  // LDS window capacity: the largest window of any simulation
   // window boxes shaped from a flush census (single-simulation contexts):
@@ -133,7 +144,7 @@ struct mcx_ctx {
   int4* d_wbox = nullptr;  // per simulation 2 * kMaxWinGates rows
   unsigned long long* d_job_counter = nullptr;  // one per simulation
   // estimated cost per photon of every simulation (ms); empty: home waves by
-  // job counts
+  // the library's own estimate of its segments
   std::vector<double> cost;
   float* d_stage32 = nullptr;
   double* d_stage64 = nullptr;
@@ -285,6 +296,8 @@ static void release(mcx_ctx* c) {
   delete c;
 }
 
+constexpr double kThinDepth = 2.0;
+
 static void describe(SimHost& sh, const mcx_sim& sm) {
   const mcx_volume* vol = &sm.vol;
   sh.nx = vol->nx;
@@ -326,6 +339,30 @@ static void describe(SimHost& sh, const mcx_sim& sm) {
     sh.src_i[a] = static_cast<int>(fl);
     sh.src_f[a] = static_cast<float>(x - fl);
     sh.src_dir[a] = sm.src.dir[a];
+  }
+  // mean depth over a sample of at most about 4096 voxels (an odd stride)
+  const uint64_t every = (sh.nvox / 4096) | 1;
+  double depth = 0.0, absorb = 0.0, index = 0.0;
+  uint64_t seen = 0;
+  for (uint64_t i = 0; i < sh.nvox; i += every) {
+    const int m = vol->labels[i];
+    if (m == 0) continue;
+    depth += static_cast<double>(vol->media[m].mus) * sh.h;
+    absorb += vol->media[m].mua;
+    index += vol->media[m].n;
+    ++seen;
+  }
+  if (seen > 0) {
+    // segments per mm (scatterings, and three faces per two voxel edges of
+    // path) over the rates at which paths end: absorption, leaving the grid,
+    // the last gate.  Over the 256 cubes of the batched workload (343 to 7000
+    // segments per photon) the estimate is off by a factor of 1.4 (one
+    // standard deviation), a constant by 1.9.
+    const double k = static_cast<double>(seen);
+    const double side = sh.h * std::min(sh.nx, std::min(sh.ny, sh.nz));
+    const double reach = kCmmPerNs * k / index * sh.dt * sh.ngates;
+    sh.thin = depth < kThinDepth * k;
+    sh.events = (depth / k + 1.5) / sh.h / (absorb / k + 1.0 / side + 10.0 / reach);
   }
   sh.src_label =
       vol->labels[sh.src_i[0] + sh.nx * (sh.src_i[1] + static_cast<int64_t>(sh.ny) * sh.src_i[2])];
@@ -501,15 +538,64 @@ static mcx_status set_shape(mcx_ctx* c, int block) {
   return MCX_OK;
 }
 
-// Whether launches add to map cells with 32-bit returning adds (plus a
-// carry) rather than 64-bit adds: by the context's setting, or, for
-// MCX_MAP_ADDS_AUTO, when at least 16 waves per compute unit are resident,
-// enough to cover the returned value's latency (measured: 32-bit adds win
-// with 16 waves of 1024-thread workgroups and lose with 12 of 768-thread
-// ones on the sphere benchmark).
-static bool map32(const mcx_ctx* c) {
+// One launch's shape and kinds of map add.
+struct LaunchShape {
+  int grid, block, chunk;
+  bool many;  // enough photons that the map's atomics, not latency, may bind
+};
+
+// The shape of a launch of `photons` photons in all, of which `thin` are in
+// simulations of thin voxels.  A launch ends with its longest photons, and
+// while other waves on their SIMD still hold live photons every event of
+// theirs takes longer; a launch of few photons per lane is mostly that end,
+// so it gets fewer waves per CU (measured, ms with 4 / 8 / 16 waves per CU:
+// homogeneous cube 1e4 photons 3.2 / 3.6 / 3.4, 3e5 3.8 / 3.8 / 5.0, 1e6 6.8
+// / 5.3 / 5.8; sphere benchmark 1e5 7.0 / 7.2 / 6.9, 1e6 14.4 / 11.2 / 12.1,
+// 3e6 33 / 23.6 / 24.1; head 3e5 11.4 / 10.5 / 12.6, 1e6 24.7 / 17.1 /
+// 15.7): 4 below half a photon per lane of a full launch, 8 below eight (thin
+// voxels) or two.  Jobs of 64 photons, smaller where there are fewer photons
+// than lanes.
+static LaunchShape launch_shape(const mcx_ctx* c, uint64_t photons, uint64_t thin) {
+  LaunchShape s{c->grid, c->block, c->chunk, true};
+  const double lanes = c->cus * 1024.0;
+  const double per_lane = static_cast<double>(photons) / lanes;
+  const bool mostly_thin = 2 * thin > photons;
+  if (!c->full_shape) {
+    s.many = per_lane >= 8.0;
+    if (c->fit_shape) {
+      const int waves = per_lane < 0.5 ? 4 : (per_lane < (mostly_thin ? 8.0 : 2.0) ? 8 : 16);
+      if (waves < (c->grid / c->cus) * (c->block / 64)) {
+        s.block = std::min(c->block, waves * 64);
+        s.grid = std::max(1, waves * 64 / s.block) * c->cus;
+      }
+    }
+  }
+  if (s.chunk == 0) {
+    const uint64_t nw = static_cast<uint64_t>(s.grid) * (s.block / 64);
+    s.chunk = static_cast<int>(std::max<uint64_t>(
+        kMinChunk, std::min<uint64_t>(c->sims.size() > 1 ? kBatchChunk : kDefaultChunk,
+                                      (photons + nw - 1) / nw)));
+  }
+  return s;
+}
+
+// Whether a launch of that shape adds to the map cells of a simulation of
+// thin (or other) voxels with 32-bit returning adds (plus a carry) rather
+// than 64-bit adds: by the context's setting, or, for MCX_MAP_ADDS_AUTO,
+// where the memory side's rate of atomics binds -- thin voxels, at least
+// eight photons per lane of a full launch, and 16 waves per compute unit to
+// cover the returned value's latency.  Measured, ms with 64- / 32-bit adds:
+// sphere benchmark 1e6 photons 12.4 / 12.8, 3e6 24.3 / 22.9, 1e7 63.7 / 57.5;
+// homogeneous cube 1e6 5.8 / 6.3, 1e7 25.2 / 23.2; head (thick voxels) 1e7
+// 71.7 / 79.6.
+static bool map32(const mcx_ctx* c, const LaunchShape& s, bool thin) {
   if (c->map_adds != MCX_MAP_ADDS_AUTO) return c->map_adds == MCX_MAP_ADDS_32;
-  return c->cus > 0 && (c->grid / c->cus) * (c->block / 64) >= 16;
+  return thin && s.many && c->cus > 0 && (s.grid / c->cus) * (s.block / 64) >= 16;
+}
+
+// The same for the context's shape and large launches of its simulations.
+static bool map32_large(const mcx_ctx* c) {
+  return map32(c, LaunchShape{c->grid, c->block, c->chunk, true}, c->sims[0].thin);
 }
 
 // Make stream st wait for the context's last clear or launch.
@@ -604,7 +690,8 @@ static mcx_status setup(mcx_ctx* c, const mcx_sim* sims) {
   }
   MCX_TRY(clear_all(c, c->stream));
   set_window(c, c->opt.lds_window_cells == 0 ? kDefaultWindow : c->opt.lds_window_cells);
-  c->chunk = c->opt.refill_chunk > 0 ? c->opt.refill_chunk : kDefaultChunk;
+  c->chunk = c->opt.refill_chunk;
+  c->fit_shape = c->opt.block_size == 0;
   MCX_TRY(set_shape(c, c->opt.block_size));
   HIP_TRY(hipStreamSynchronize(c->stream));
   return MCX_OK;
@@ -703,6 +790,12 @@ static mcx_status enqueue(mcx_ctx* c, const uint64_t* first, const uint64_t* n,
   std::vector<mcx::SimDesc> desc(ns);
   std::vector<uint64_t> job_start(ns + 1, 0);
   std::vector<int4> wbox(ns * 2 * mcx::kMaxWinGates, make_int4(0, 0, 0, 0));
+  uint64_t photons = 0, thin = 0;
+  for (size_t i = 0; i < ns; ++i) {
+    photons += n[i];
+    if (c->sims[i].thin) thin += n[i];
+  }
+  const LaunchShape shape = launch_shape(c, photons, thin);
   for (size_t i = 0; i < ns; ++i) {
     const SimHost& sh = c->sims[i];
     mcx::SimDesc& d = desc[i];
@@ -764,18 +857,25 @@ static mcx_status enqueue(mcx_ctx* c, const uint64_t* first, const uint64_t* n,
     d.q_inv = 1.f / d.q_unit;
     std::copy(sh.wbox.begin(), sh.wbox.end(),
               reinterpret_cast<int32_t*>(wbox.data() + i * 2 * mcx::kMaxWinGates));
-    job_start[i + 1] = job_start[i] + (n[i] + c->chunk - 1) / c->chunk;
+    d.map32 = map32(c, shape, sh.thin) ? 1 : 0;
+    job_start[i + 1] = job_start[i] + (n[i] + shape.chunk - 1) / shape.chunk;
   }
-  // Home-wave shares: the job counts, or -- once per-simulation costs are
-  // set (device-level balancing by throughput) -- each simulation's
-  // estimated work cost_i n_i, scaled to integers summing to about 2^40.
+  // Home-wave shares: each simulation's estimated work, scaled to integers
+  // summing to about 2^40 -- cost_i n_i once per-simulation costs are set
+  // (device-level balancing by throughput), else the estimated segments.  A
+  // wave that runs out of its home's jobs first waits for its longest photon,
+  // so shares by job counts cost the batch of 24 cubes (5.2e6 photons) 83 ms
+  // against 64 ms.
   std::vector<uint64_t> home_start(job_start);
-  if (!c->cost.empty()) {
+  if (ns > 1) {
+    auto work = [&](size_t i) {
+      return (c->cost.empty() ? c->sims[i].events : c->cost[i]) * static_cast<double>(n[i]);
+    };
     double total = 0.0;
-    for (size_t i = 0; i < ns; ++i) total += c->cost[i] * static_cast<double>(n[i]);
+    for (size_t i = 0; i < ns; ++i) total += work(i);
     if (total > 0.0) {
       for (size_t i = 0; i < ns; ++i) {
-        const double share = c->cost[i] * static_cast<double>(n[i]) / total;
+        const double share = work(i) / total;
         home_start[i + 1] = home_start[i] + static_cast<uint64_t>(std::llround(share * 0x1p40));
       }
       if (home_start[ns] == 0) home_start = job_start;
@@ -788,7 +888,7 @@ static mcx_status enqueue(mcx_ctx* c, const uint64_t* first, const uint64_t* n,
   lp.njobs = job_start[ns];
   lp.home_start = c->d_home_start;
   lp.nhome = home_start[ns];
-  lp.chunk = static_cast<uint32_t>(c->chunk);
+  lp.chunk = static_cast<uint32_t>(shape.chunk);
   lp.job_counters = c->d_job_counter;
   lp.rr_threshold = c->opt.rr_threshold;
   lp.rr_p = static_cast<float>(1.0 / c->opt.rr_m);
@@ -797,8 +897,9 @@ static mcx_status enqueue(mcx_ctx* c, const uint64_t* first, const uint64_t* n,
   lp.table_rows = c->table_rows;
   lp.nmedia_max = c->nmedia_max;
   lp.window_cells = c->win_cells;
-  lp.map32 = map32(c) ? 1 : 0;
-  c->last_map32 = lp.map32 != 0;
+  c->last_map32 = desc[0].map32 != 0;
+  c->last_grid = shape.grid;
+  c->last_block = shape.block;
 
   // Parameter blocks are copied in stream order before the launch that reads
   // them (pageable sources are staged by the runtime before the call returns).
@@ -814,7 +915,7 @@ static mcx_status enqueue(mcx_ctx* c, const uint64_t* first, const uint64_t* n,
   HIP_TRY(mcx::launch_reset_counters(c->d_job_counter, static_cast<int>(ns), st));
   HIP_TRY(hipEventRecord(c->ev_k0, st));
   HIP_TRY(mcx::launch_transport(
-      lp, c->grid, c->block, st, c->detect, c->diag, c->opt.accurate_math != 0,
+      lp, shape.grid, shape.block, st, c->detect, c->diag, c->opt.accurate_math != 0,
       c->force_variant >= 0 ? c->force_variant : c->opt.kernel_variant));
   HIP_TRY(hipEventRecord(c->ev_k1, st));
   HIP_TRY(hipMemsetAsync(c->d_reduce, 0, ns * 2 * sizeof(double), st));
@@ -1012,8 +1113,8 @@ static mcx_status stats_of(mcx_ctx* c, int32_t sim, mcx_run_stats* o) {
     if (hipEventElapsedTime(&ms, c->ev_k0, c->ev_k1) == hipSuccess) o->kernel_ms = ms;
     if (hipEventElapsedTime(&ms, c->ev_begin, c->ev_end) == hipSuccess) o->run_ms = ms;
   }
-  o->grid_blocks = c->grid;
-  o->block_size = c->block;
+  o->grid_blocks = c->last_grid ? c->last_grid : c->grid;
+  o->block_size = c->last_block ? c->last_block : c->block;
   o->map_adds = c->last_map32 ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64;
   return MCX_OK;
 }
@@ -1287,7 +1388,8 @@ mcx_status mcx_set_launch(mcx_ctx* c, int32_t block_size, int32_t refill_chunk,
   HIP_TRY(hipSetDevice(c->device));
   MCX_TRY(host_wait(c));
   set_window(c, lds_window_cells == 0 ? kDefaultWindow : lds_window_cells);
-  c->chunk = refill_chunk > 0 ? refill_chunk : kDefaultChunk;
+  c->chunk = refill_chunk;
+  c->fit_shape = block_size == 0;
   return set_shape(c, block_size);
 }
 
@@ -1366,7 +1468,10 @@ mcx_status mcx_autotune(mcx_ctx* c, const uint64_t* pilot_photons, const uint64_
 
   auto pilot = [&](const uint64_t* n, float* ms) -> mcx_status {
     MCX_TRY(clear_all(c, c->stream));
-    MCX_TRY(enqueue_all(c, zero.data(), n, seed, c->stream));
+    c->full_shape = true;  // pilots stand for larger launches
+    const mcx_status r = enqueue_all(c, zero.data(), n, seed, c->stream);
+    c->full_shape = false;
+    MCX_TRY(r);
     HIP_TRY(hipStreamSynchronize(c->stream));
     HIP_TRY(hipEventElapsedTime(ms, c->ev_k0, c->ev_k1));
     return MCX_OK;
@@ -1392,14 +1497,15 @@ mcx_status mcx_autotune(mcx_ctx* c, const uint64_t* pilot_photons, const uint64_
     int block, chunk, window, adds;
   };
   std::vector<Cand> timed;
-  timed.push_back({ms, c->block, c->chunk, kDefaultWindow, map32(c) ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64});
+  timed.push_back({ms, c->block, kDefaultChunk, kDefaultWindow,
+                   map32_large(c) ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64});
   for (int wi = 0; wi < nwin; ++wi) {
     for (int b : blocks) {
       for (int ch : chunks) {
         if (mcx_set_launch(c, b, ch, windows[wi]) != MCX_OK) continue;
         MCX_TRY(pilot(pilot_photons, &ms));
         timed.push_back({ms, c->block, ch, windows[wi],
-                         map32(c) ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64});
+                         map32_large(c) ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64});
       }
     }
   }
@@ -1425,7 +1531,7 @@ mcx_status mcx_autotune(mcx_ctx* c, const uint64_t* pilot_photons, const uint64_
   // rule's kind stays unless the other is more than 10 % faster
   if (mcx_set_launch(c, best.block, best.chunk, best.window) == MCX_OK) {
     c->map_adds = MCX_MAP_ADDS_AUTO;
-    const int rule = map32(c) ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64;
+    const int rule = map32_large(c) ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64;
     const int other = rule == MCX_MAP_ADDS_32 ? MCX_MAP_ADDS_64 : MCX_MAP_ADDS_32;
     float t_rule = 3.4e38f, t_other = 3.4e38f;
     for (int rep = 0; rep < 3; ++rep) {
@@ -1509,7 +1615,10 @@ mcx_status mcx_fit_runtime(mcx_ctx* c, const uint64_t* n1, const uint64_t* n2,
     std::fill(n.begin(), n.end(), 0);
     n[i] = count;
     MCX_TRY(clear_all(c, c->stream));
-    MCX_TRY(enqueue(c, zero.data(), n.data(), seed, c->stream));
+    c->full_shape = true;  // both pilots in the shape of a large launch
+    const mcx_status r = enqueue(c, zero.data(), n.data(), seed, c->stream);
+    c->full_shape = false;
+    MCX_TRY(r);
     HIP_TRY(hipStreamSynchronize(c->stream));
     HIP_TRY(hipEventElapsedTime(ms, c->ev_k0, c->ev_k1));
     return MCX_OK;

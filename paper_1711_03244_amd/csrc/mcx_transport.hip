@@ -358,7 +358,7 @@ struct Hot {
   int nx, ny, nz;
   uint32_t nvox, stride_y, stride_z;
   float h, inv_h, t0, inv_dt, t_end, n_out, q_inv;
-  int gate_max, reflect;
+  int gate_max, reflect, map32;
   uint32_t key0, key1;
 };
 
@@ -381,6 +381,7 @@ __device__ __forceinline__ Hot load_hot(CSim* D) {
   H.q_inv = D->q_inv;
   H.gate_max = D->ngates - 1;
   H.reflect = D->reflect;
+  H.map32 = D->map32;
   H.key0 = D->key0;
   H.key1 = D->key1;
   return H;
@@ -404,10 +405,9 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams L) {
   // the launch parameters the loop reads, each a scalar register of its own
   // (read as they lie they would be one wide register block, kept or spilled
   // as a whole)
-  uint32_t max_events = L.max_events, map32_word = static_cast<uint32_t>(L.map32);
+  uint32_t max_events = L.max_events;
   float rr_threshold = L.rr_threshold, rr_p = L.rr_p, rr_m = L.rr_m;
-  asm volatile("" : "+s"(max_events), "+s"(map32_word), "+s"(rr_threshold), "+s"(rr_p), "+s"(rr_m));
-  const bool map32 = map32_word != 0;  // how map cells are added to (deposit)
+  asm volatile("" : "+s"(max_events), "+s"(rr_threshold), "+s"(rr_p), "+s"(rr_m));
   uint32_t* s_win = reinterpret_cast<uint32_t*>(s_dyn + (bdim >> 6) * rows);
   float* s_len = reinterpret_cast<float*>(s_win + wcells) + threadIdx.x;  // [m * blockDim]
 
@@ -875,18 +875,18 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams L) {
       if (out_acc != 0.f) {
         settle(H.tally, owed);
         c_flush += deposit<kRacy, kCensus>(H.tally, H.q_inv, s_win, out_cell, out_slot, out_acc,
-                                           map32, owed);
+                                           H.map32 != 0, owed);
       }
       if (end != kAlive) {
         if (acc != 0.f) {
           settle(H.tally, owed);
           c_flush += deposit<kRacy, kCensus>(H.tally, H.q_inv, s_win, acc_cell, acc_slot, acc,
-                                             map32, owed);
+                                             H.map32 != 0, owed);
         }
         if (old_acc != 0.f) {
           settle(H.tally, owed);
           c_flush += deposit<kRacy, kCensus>(H.tally, H.q_inv, s_win, old_cell, old_slot, old_acc,
-                                             map32, owed);
+                                             H.map32 != 0, owed);
         }
         const double wd = static_cast<double>(w);
         const int end_slot = end == kEndEscape ? kCntEscaped

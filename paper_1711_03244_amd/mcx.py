@@ -345,7 +345,7 @@ def mcx_fit_runtime(ctx, n1=None, n2=None, seed=None):
 
 
 def mcx_set_balance(ctx, cost_per_photon=None):
-    """Home waves by estimated work cost_i n_i (None: by job counts)."""
+    """Home waves by estimated work cost_i n_i (None: by the library's estimate)."""
     if cost_per_photon is None:
         _check(lib().mcx_set_balance(ctx, None))
         return
