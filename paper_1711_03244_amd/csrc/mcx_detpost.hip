@@ -81,18 +81,33 @@ __global__ void __launch_bounds__(kBlock)
   for (int i = threadIdx.x; i < hist_len; i += blockDim.x) mine[i] = hist[i];
 }
 
-// out[det_lo * cols + i] = scale(i) * sum over workgroups b (in order) of
-// partial[b][i]; column 0 (record count) is not scaled, column 1 by
-// 1 / nphoton, columns 2.. by 1 / (nphoton dt).
+// out[det_lo * cols + i] = scale(i) * sum over workgroups b of
+// partial[b][i]; column 0 (record count) is not scaled, column 1 by 1 /
+// nphoton, columns 2.. by 1 / (nphoton dt).  A workgroup takes kFinalE
+// consecutive i; its kFinalL threads per i sum b = q, q + kFinalL, ... and
+// a tree of fixed shape adds those, so a launch shape always sums in the same
+// order.  Bound by latency: one thread per i added its 977 partials (250k
+// records) in a row, 226 us; 64 threads per i take 7 us.
+constexpr int kFinalL = 64, kFinalE = kBlock / kFinalL;
 __global__ void __launch_bounds__(kBlock)
     detpost_final_kernel(const double* __restrict__ partial, int nparts, int hist_len, int cols,
                          double s_sum, double s_gate, double* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= hist_len) return;
+  __shared__ double sh[kFinalL][kFinalE];
+  const int il = threadIdx.x % kFinalE, q = threadIdx.x / kFinalE;
+  const int i = blockIdx.x * kFinalE + il;
   double acc = 0.0;
-  for (int b = 0; b < nparts; ++b) acc += partial[static_cast<int64_t>(b) * hist_len + i];
+  if (i < hist_len)
+    for (int b = q; b < nparts; b += kFinalL)
+      acc += partial[static_cast<int64_t>(b) * hist_len + i];
+  sh[q][il] = acc;
+  __syncthreads();
+  for (int off = kFinalL / 2; off > 0; off >>= 1) {
+    if (q < off) sh[q][il] += sh[q + off][il];
+    __syncthreads();
+  }
+  if (q != 0 || i >= hist_len) return;
   const int c = i % cols;
-  out[i] = c == 0 ? acc : acc * (c == 1 ? s_sum : s_gate);
+  out[i] = c == 0 ? sh[0][il] : sh[0][il] * (c == 1 ? s_sum : s_gate);
 }
 
 }  // namespace
@@ -138,7 +153,7 @@ hipError_t launch_detpost(const DetpostArgs& a, double* partial, int nblocks, in
   const double n = static_cast<double>(a.nphoton);
   const double s_sum = a.nphoton > 0 ? 1.0 / n : 1.0;
   const double s_gate = a.nphoton > 0 ? 1.0 / (n * static_cast<double>(a.dt)) : 1.0;
-  hipLaunchKernelGGL(detpost_final_kernel, dim3((hist_len + kBlock - 1) / kBlock), dim3(kBlock),
+  hipLaunchKernelGGL(detpost_final_kernel, dim3((hist_len + kFinalE - 1) / kFinalE), dim3(kBlock),
                      0, s, partial, nblocks, hist_len, cols, s_sum, s_gate,
                      a.out + static_cast<uint64_t>(det_lo) * cols);
   return hipGetLastError();
