@@ -397,8 +397,9 @@ typedef struct {
  * and, when dev_weight is not NULL, the re-weighted weight of every record
  * (nrec doubles, device, record order).  dev_dmua: npath floats in device
  * memory, or NULL.  Enqueued on hip_stream (NULL = the null stream); the
- * per-workgroup partial sums go to a workspace the call allocates, and it
- * waits for the stream before returning to free it.  Errors: MCX_EINVAL for
+ * per-workgroup partial sums go to scratch memory that later calls reuse
+ * (at most 256 MB stay idle; given back when any context is destroyed), and
+ * the call waits for the stream before returning.  Errors: MCX_EINVAL for
  * a bad spec or NULL buffers (checked before any HIP call), MCX_ENOMEM,
  * MCX_EDEVICE. */
 mcx_status mcx_detpost_device(const float *dev_rec, uint64_t nrec, const mcx_detpost *spec,

@@ -160,8 +160,10 @@ mcx_status mcx_nn_mirror_xy(const float *in, float *out, int32_t nx, int32_t ny,
  * gradient gy of the layer output (after any ReLU mask) and overwrites gx
  * (FP32 [input voxel][cin], may be NULL), gw and gb (may be NULL).
  * Temporary weight packs (and, for 3x3x3 layers whose reductions are
- * split over workgroups, FP32 workspaces of partial sums) are allocated
- * per call; both wait for the stream before returning. */
+ * split over workgroups, FP32 workspaces of partial sums) are scratch
+ * memory that later calls reuse (at most 256 MB stay idle; given back when
+ * any network or context is destroyed); both calls wait for the stream
+ * before returning. */
 mcx_status mcx_nn_layer_forward(int32_t kind, int32_t nx, int32_t ny, int32_t nz, int32_t cin,
                                 int32_t cout, const uint16_t *x, const float *w, const float *b,
                                 const uint16_t *skip, int32_t relu, int32_t y_f32, void *y,

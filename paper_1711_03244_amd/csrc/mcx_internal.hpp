@@ -11,6 +11,40 @@ namespace mcx {
 // Set the calling thread's mcx_last_error message; returns st.
 mcx_status report(mcx_status st, const char* message);
 
+// Device scratch memory of calls that need it only while they run and wait
+// for their stream before they return (the single-layer calls, the
+// post-processing): blocks are kept for the next call instead of allocated
+// and freed each time (hipMalloc and hipFree of a few buffers cost such a
+// call 15 to 60 us).  At most kScratchIdleBytes and kScratchIdleBlocks stay
+// idle over all devices; they are given back when memory runs out and when
+// any context or network is destroyed.  Safe from several threads: a block
+// belongs to one call at a time, and that call's work on it has ended before
+// it is released.
+constexpr size_t kScratchIdleBytes = size_t(256) << 20;
+constexpr size_t kScratchIdleBlocks = 16;
+class Scratch {
+ public:
+  Scratch() = default;
+  ~Scratch();
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
+  // at least `bytes` on the current device; once per object
+  hipError_t acquire(size_t bytes);
+  // the next `bytes` of the block (256-byte aligned); never more than acquired
+  void* take(size_t bytes);
+  static size_t rounded(size_t bytes) { return (bytes + 255) & ~size_t(255); }
+  // the work on the block may not have ended: free it instead of keeping it
+  void discard() { keep_ = false; }
+
+ private:
+  void* p_ = nullptr;
+  size_t size_ = 0, used_ = 0;
+  int device_ = 0;
+  bool keep_ = true;
+};
+// Free every idle block.
+void scratch_trim();
+
 // Ledger slots (FP64 weight sums) and counter slots accumulated per simulation.
 enum LedgerSlot {
   kLedEscaped = 0, kLedDetected, kLedTimeout, kLedRrGain, kLedRrLoss, kLedCapped,

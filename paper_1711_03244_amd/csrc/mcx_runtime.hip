@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <array>
 #include <cmath>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -51,6 +52,87 @@ mcx_status fail(mcx_status st, const char* fmt, ...) {
 mcx_status mcx::report(mcx_status st, const char* message) {
   g_error = message;
   return st;
+}
+
+// ------------------------------------------------------------ scratch
+
+namespace {
+struct IdleBlock {
+  int device;
+  void* p;
+  size_t size;
+};
+std::mutex g_scratch_mu;
+std::vector<IdleBlock> g_scratch;  // under g_scratch_mu
+size_t g_scratch_bytes = 0;
+}  // namespace
+
+void mcx::scratch_trim() {
+  std::vector<IdleBlock> all;
+  {
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    all.swap(g_scratch);
+    g_scratch_bytes = 0;
+  }
+  for (const IdleBlock& b : all) (void)hipFree(b.p);
+}
+
+hipError_t mcx::Scratch::acquire(size_t bytes) {
+  hipError_t e = hipGetDevice(&device_);
+  if (e != hipSuccess) return e;
+  {
+    // the smallest idle block that fits, unless it is far too large
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    size_t best = g_scratch.size();
+    for (size_t i = 0; i < g_scratch.size(); ++i) {
+      const IdleBlock& b = g_scratch[i];
+      if (b.device == device_ && b.size >= bytes && b.size / 16 <= std::max<size_t>(bytes, 1 << 16) &&
+          (best == g_scratch.size() || b.size < g_scratch[best].size))
+        best = i;
+    }
+    if (best < g_scratch.size()) {
+      p_ = g_scratch[best].p;
+      size_ = g_scratch[best].size;
+      g_scratch_bytes -= size_;
+      g_scratch.erase(g_scratch.begin() + static_cast<std::ptrdiff_t>(best));
+      return hipSuccess;
+    }
+  }
+  size_ = std::max<size_t>(rounded(bytes), 1 << 16);
+  e = hipMalloc(&p_, size_);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    scratch_trim();
+    e = hipMalloc(&p_, size_);
+  }
+  if (e != hipSuccess) {
+    p_ = nullptr;
+    size_ = 0;
+  }
+  return e;
+}
+
+void* mcx::Scratch::take(size_t bytes) {
+  if (!p_ || used_ + rounded(bytes) > rounded(size_)) return nullptr;
+  void* q = static_cast<char*>(p_) + used_;
+  used_ += rounded(bytes);
+  return q;
+}
+
+mcx::Scratch::~Scratch() {
+  if (!p_) return;
+  if (keep_) {
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    if (g_scratch.size() < kScratchIdleBlocks && g_scratch_bytes + size_ <= kScratchIdleBytes) {
+      try {
+        g_scratch.push_back(IdleBlock{device_, p_, size_});
+        g_scratch_bytes += size_;
+        return;
+      } catch (const std::bad_alloc&) {  // no room to remember it: free it
+      }
+    }
+  }
+  (void)hipFree(p_);
 }
 
 namespace {
@@ -294,6 +376,7 @@ static void release(mcx_ctx* c) {
     if (e) (void)hipEventDestroy(e);
   if (c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
+  mcx::scratch_trim();
 }
 
 constexpr double kThinDepth = 2.0;
@@ -1284,11 +1367,12 @@ mcx_status mcx_detpost_device(const float* dev_rec, uint64_t nrec, const mcx_det
   hipStream_t st = static_cast<hipStream_t>(stream);
   const mcx::DetpostArgs a = detpost_args(dev_rec, nrec, *spec, dev_dmua, dev_out, dev_weight);
   const int nblocks = mcx::detpost_blocks(nrec);
-  double* ws = nullptr;
-  HIP_TRY(hipMalloc(&ws, detpost_workspace(a, nblocks) * sizeof(double)));
-  mcx_status r = detpost_passes(a, ws, nblocks, st);
+  mcx::Scratch ws;
+  const size_t bytes = detpost_workspace(a, nblocks) * sizeof(double);
+  HIP_TRY(ws.acquire(bytes));
+  mcx_status r = detpost_passes(a, static_cast<double*>(ws.take(bytes)), nblocks, st);
   const hipError_t e = hipStreamSynchronize(st);
-  (void)hipFree(ws);
+  if (e != hipSuccess) ws.discard();
   if (r != MCX_OK) return r;
   if (e != hipSuccess) return fail(MCX_EDEVICE, "post-processing: %s", hipGetErrorString(e));
   return MCX_OK;

@@ -60,6 +60,7 @@ struct WgradArgs {
   float* gw;                  // FP32 [taps][cin][cout], accumulated
   float* part;                // FP32 workspace for per-workgroup partial sums, or null
   int64_t part_cap;           // its size in floats
+  bool overwrite = false;     // gw receives the sum instead (wgrad_overwrites)
 };
 
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
@@ -69,13 +70,28 @@ int64_t conv_workspace_floats(const ConvArgs& a);
 hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s);
 // floats of workspace launch_wgrad uses for `a` (0: it needs none)
 int64_t wgrad_workspace_floats(const WgradArgs& a);
-// pack w[taps][cin][cout] (FP32) into BF16 rows: forward Bt[n][t * cin + ci]
-// (rows >= cout) or transposed Bt[ci][t * cout + n] (rows >= cin); with
-// `clear` the rows x kpad buffer is zeroed first (the padding outside the
-// weights never changes, so later packs of the same buffer skip it)
-hipError_t launch_pack(const float* w, int taps, int cin, int cout, int rows, int kpad,
-                       bool transposed, uint16_t* bt, hipStream_t s, bool clear = true);
+// whether launch_wgrad with its workspace can store to gw instead of adding
+bool wgrad_overwrites(const WgradArgs& a);
+// One layer's weights w[taps][cin][cout] (FP32) to pack into BF16 rows:
+// forward Bt[n][t * cin + ci] (cout rows rounded up to 64) and transposed
+// Bt[ci][t * cout + n] (cin rows rounded up to 64), each kpad columns; what
+// lies outside the weights is zeroed.  Either target may be null.
+struct PackJob {
+  const float* w = nullptr;
+  uint16_t* fwd = nullptr;
+  uint16_t* bwd = nullptr;
+  int32_t taps = 0, cin = 0, cout = 0;
+  int32_t fwd_kpad = 0, bwd_kpad = 0;
+  // 32-wide tiles along `c` channels, up to a multiple of 64
+  __host__ __device__ static int side(int c) { return (c + 63) / 64 * 2; }
+  __host__ __device__ int tiles() const { return taps * side(cin) * side(cout); }
+};
+// all jobs of a device array (`tiles` in all), or one given by value
+hipError_t launch_pack(const PackJob* dev_jobs, int njobs, int tiles, hipStream_t s);
+hipError_t launch_pack(const PackJob& job, hipStream_t s);
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t s);
+// zero p[0, n) and q[0, m) in one launch (none when both are empty)
+hipError_t launch_fill2(float* p, int64_t n, float* q, int64_t m, hipStream_t s);
 hipError_t launch_to_log(const float* phi, int64_t n, float* u, uint16_t* u16, hipStream_t s);
 hipError_t launch_mirror_xy(const float* in, float* out, int nx, int ny, int nz, int op,
                             hipStream_t s);

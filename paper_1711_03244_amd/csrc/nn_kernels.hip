@@ -1225,21 +1225,22 @@ __global__ void __launch_bounds__(256) wgrad_onechannel_kernel(WgradArgs a) {
 }
 
 // the same for fewer than 8 workgroups: one thread per i
-__global__ void wgrad_reduce_few_kernel(const float* part, int groups, int64_t n, float* gw) {
+__global__ void wgrad_reduce_few_kernel(const float* part, int groups, int64_t n, float* gw,
+                                        int overwrite) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     float v = part[i];
     for (int k = 1; k < groups; ++k) v += part[k * n + i];
-    gw[i] += v;
+    gw[i] = overwrite ? v : gw[i] + v;
   }
 }
 
-// gw[i] += sum over the workgroups k < groups of part[k][i]: a workgroup
+// gw[i] += (overwrite: =) sum over the workgroups k < groups of part[k][i]: a workgroup
 // takes E = 256 / KL consecutive i; thread (q, il) sums k = q, q + KL, ...
 // for i = E blockIdx.x + il, and the KL sums of each i are added in q order
 template <int KL>
 __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float* part, int groups,
-                                                           int64_t n, float* gw) {
+                                                           int64_t n, float* gw, int overwrite) {
   constexpr int E = 256 / KL;
   __shared__ float sh[KL][E + 1];
   const int il = threadIdx.x % E, q = threadIdx.x / E;
@@ -1253,35 +1254,63 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float* part, in
     float t = sh[0][il];
 #pragma unroll
     for (int k = 1; k < KL; ++k) t += sh[k][il];
-    gw[i] += t;
+    gw[i] = overwrite ? t : gw[i] + t;
   }
 }
 
 // ------------------------------------------------------------ element-wise
 
-// Bt[n][koff(t) + ci] from w[t][ci][n] (forward packing) or
-// Bt[ci][t * cout + n] from w[t][ci][n] (transposed packing); rows and
-// columns beyond the matrix stay zero (the buffer is cleared first).
-__global__ void pack_kernel(const float* w, int taps, int cin, int cout, int kpad, int transposed,
-                            uint16_t* bt) {
-  const int64_t total = static_cast<int64_t>(taps) * cin * cout;
-  for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < total;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const int n = static_cast<int>(i % cout);
-    const int ci = static_cast<int>((i / cout) % cin);
-    const int t = static_cast<int>(i / (static_cast<int64_t>(cout) * cin));
-    const uint16_t v = to_bf16(w[i]);
-    if (transposed)
-      bt[static_cast<int64_t>(ci) * kpad + t * cout + n] = v;
-    else
-      bt[static_cast<int64_t>(n) * kpad + t * cin + ci] = v;
+// Bt[n][t * cin + ci] (fwd) and Bt[ci][t * cout + n] (bwd, transposed) from
+// w[t][ci][n], for every job in one launch: a workgroup takes one 32 x 32
+// tile (ci, n) of one tap, reads it once and writes it to both (either may
+// be null); tiles cover the rows up to a multiple of 64, zero beyond the
+// weights, and the tiles at the end of the last tap also zero the columns up
+// to kpad.  Bound by launches and by 2-byte scattered writes before: two
+// launches per layer, one thread per weight, 130 us for the 16 layers of the
+// (32, 64, 128, 256) network, 21 us as one launch.
+__global__ void __launch_bounds__(256) pack_kernel(const PackJob* jobs, int njobs, PackJob one) {
+  __shared__ uint16_t sh[32][34];
+  int b = static_cast<int>(blockIdx.x);
+  PackJob J = one;
+  if (jobs) {
+    int k = 0;
+    while (k + 1 < njobs && b >= jobs[k].tiles()) b -= jobs[k++].tiles();
+    J = jobs[k];
   }
-}
-
-__global__ void fill_u16_kernel(uint16_t* p, int64_t n) {
-  for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    p[i] = 0;
+  const int tn = PackJob::side(J.cout), tc = PackJob::side(J.cin);
+  const int n0 = (b % tn) * 32, c0 = (b / tn % tc) * 32, t = b / (tn * tc);
+  const int col = static_cast<int>(threadIdx.x) & 31, row = static_cast<int>(threadIdx.x) >> 5;
+  const float* w = J.w + static_cast<int64_t>(t) * J.cin * J.cout;
+#pragma unroll
+  for (int i = row; i < 32; i += 8)
+    sh[i][col] = c0 + i < J.cin && n0 + col < J.cout
+                     ? to_bf16(w[static_cast<int64_t>(c0 + i) * J.cout + n0 + col]) : 0;
+  __syncthreads();
+  const bool last = t == J.taps - 1;
+  if (J.fwd && c0 < J.cin) {
+    const int k = t * J.cin + c0 + col;
+    const bool end = last && c0 + 32 >= J.cin;  // up to 31 columns of zeros follow
+    const bool here = c0 + col < J.cin || (end && k < J.fwd_kpad);
+    const bool past = end && k + 32 < J.fwd_kpad;
+#pragma unroll
+    for (int i = row; i < 32; i += 8) {
+      uint16_t* p = J.fwd + static_cast<int64_t>(n0 + i) * J.fwd_kpad + k;
+      if (here) p[0] = sh[col][i];
+      if (past) p[32] = 0;
+    }
+  }
+  if (J.bwd && n0 < J.cout) {
+    const int k = t * J.cout + n0 + col;
+    const bool end = last && n0 + 32 >= J.cout;  // up to 31 columns of zeros follow
+    const bool here = n0 + col < J.cout || (end && k < J.bwd_kpad);
+    const bool past = end && k + 32 < J.bwd_kpad;
+#pragma unroll
+    for (int i = row; i < 32; i += 8) {
+      uint16_t* p = J.bwd + static_cast<int64_t>(c0 + i) * J.bwd_kpad + k;
+      if (here) p[0] = sh[i][col];
+      if (past) p[32] = 0;
+    }
+  }
 }
 
 __global__ void zero2_kernel(double* acc, float* fmax) {
@@ -1294,6 +1323,16 @@ __global__ void fill_f32_kernel(float* p, int64_t n, float v) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x)
     p[i] = v;
+}
+
+__global__ void fill2_f32_kernel(float* p, int64_t n, float* q, int64_t m) {
+  for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n + m;
+       i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+    if (i < n)
+      p[i] = 0.f;
+    else
+      q[i - n] = 0.f;
+  }
 }
 
 // u = (ln max(phi, eps) - shift) / scale, in FP32 and as BF16
@@ -1491,28 +1530,55 @@ __global__ void scale_grad_kernel(float* g, int64_t n, const double* acc) {
     g[i] *= s;
 }
 
-// gb[n] += sum over voxels of gy[m][n]: each block sums a range of rows,
-// its threads split as (channel, row phase), then one atomic per channel
+// gb[n] += sum over voxels of gy[m][n]: each block sums a range of rows and
+// ends with one atomic per channel.  The memory side takes atomics on one
+// address one at a time, so launch_bias_grad keeps the blocks few; with
+// cout a multiple of 8 (kVec) a thread reads 8 channels of a row at once.
+// 64^3 x 32: 21.7 us with 1024 blocks of 2-byte loads, 10 us.
+template <bool kVec>
 __global__ void __launch_bounds__(256) bias_grad_kernel(const uint16_t* gy, int64_t m, int cout,
                                                         int64_t rows_per_block, float* gb) {
-  __shared__ float sh[256];
-  const int lanes_c = cout < 256 ? cout : 256;       // threads per row
+  constexpr int W = kVec ? 8 : 1;  // channels per thread
+  __shared__ float sh[256][W + 1];
+  const int groups = cout / W;                       // threads' worth of channels in a row
+  const int lanes_c = groups < 256 ? groups : 256;   // threads per row
   const int phases = 256 / lanes_c;                  // rows in flight
   const int tid = threadIdx.x;
   const int64_t r0 = blockIdx.x * rows_per_block;
   const int64_t r1 = r0 + rows_per_block < m ? r0 + rows_per_block : m;
-  for (int c0 = 0; c0 < cout; c0 += lanes_c) {
-    float s = 0.f;
+  for (int c0 = 0; c0 < groups; c0 += lanes_c) {
+    float s[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) s[k] = 0.f;
     const int c = c0 + tid % lanes_c;
     const int ph = tid / lanes_c;
-    if (ph < phases && c < cout)
-      for (int64_t r = r0 + ph; r < r1; r += phases) s += from_bf16(gy[r * cout + c]);
-    sh[tid] = s;
+    if (ph < phases && c < groups) {
+#pragma unroll 4
+      for (int64_t r = r0 + ph; r < r1; r += phases) {
+        if constexpr (kVec) {
+          const uint4 v = *reinterpret_cast<const uint4*>(gy + r * cout + c * 8);
+          const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            s[2 * k] += __uint_as_float(w4[k] << 16);
+            s[2 * k + 1] += __uint_as_float(w4[k] & 0xffff0000u);
+          }
+        } else {
+          s[0] += from_bf16(gy[r * cout + c]);
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < W; ++k) sh[tid][k] = s[k];
     __syncthreads();
-    if (tid < lanes_c && c0 + tid < cout) {
+    // thread i adds channel i % W of the row's group i / W over the phases
+    for (int i = tid; i < lanes_c * W; i += 256) {
+      const int g = i / W, k = i % W;
+      if (c0 + g >= groups) break;
       float t = 0.f;
-      for (int p = 0; p < phases; ++p) t += sh[p * lanes_c + tid];
-      unsafeAtomicAdd(gb + c0 + tid, t);
+#pragma unroll 8
+      for (int p = 0; p < phases; ++p) t += sh[p * lanes_c + g][k];
+      unsafeAtomicAdd(gb + (c0 + g) * W + k, t);
     }
     __syncthreads();
   }
@@ -1531,16 +1597,23 @@ __global__ void __launch_bounds__(256) sumsq_kernel(const float* g, int64_t n, d
 
 // Adam with bias-corrected moments on g * scale, where scale also clips
 // the global norm: scale = gs * min(1, max_norm / (gs * |g|)) when
-// max_norm > 0 (|g|^2 = sum of the `blocks` partial sums)
-__global__ void adam_kernel(float* p, const float* g, float* m, float* v, int64_t n, float lr,
+// max_norm > 0 (|g|^2 = sum of the `blocks` partial sums, which every block
+// adds for itself: by all its threads -- one thread adding the 1024 in a row
+// made a step of 5.4e6 parameters 187 us, 28 us now).  The update is
+// bound by memory: seven floats per parameter.
+__global__ void __launch_bounds__(256) adam_kernel(float* p, const float* g, float* m, float* v, int64_t n, float lr,
                             float b1, float b2, float eps, float c1, float c2, float gs,
                             float max_norm, const double* partial, int blocks) {
   __shared__ float s_scale;
+  __shared__ double sh[4];
+  double ss = 0.0;
+  if (max_norm > 0.f) {
+    for (int b = threadIdx.x; b < blocks; b += blockDim.x) ss += partial[b];
+    ss = block_sum(ss, sh);
+  }
   if (threadIdx.x == 0) {
     float sc = gs;
     if (max_norm > 0.f) {
-      double ss = 0.0;
-      for (int b = 0; b < blocks; ++b) ss += partial[b];
       const double norm = gs * sqrt(ss);
       if (norm > max_norm) sc = static_cast<float>(gs * (max_norm / norm));
     }
@@ -1783,13 +1856,15 @@ int slab_groups(const WgradArgs& a, int64_t cap) {
 namespace {
 
 // the reduction of G partial sums of n floats into gw
-hipError_t launch_wgrad_reduce(const float* part, int G, int64_t n, float* gw, hipStream_t s) {
+hipError_t launch_wgrad_reduce(const float* part, int G, int64_t n, float* gw, bool overwrite,
+                               hipStream_t s) {
+  const int ow = overwrite ? 1 : 0;
   if (G < 8)
-    wgrad_reduce_few_kernel<<<blocks_for(n), 256, 0, s>>>(part, G, n, gw);
+    wgrad_reduce_few_kernel<<<blocks_for(n), 256, 0, s>>>(part, G, n, gw, ow);
   else if (G >= 64 && n < 8192)  // fewer than 256 workgroups with 8 lanes per i
-    wgrad_reduce_kernel<32><<<static_cast<unsigned>((n + 7) / 8), 256, 0, s>>>(part, G, n, gw);
+    wgrad_reduce_kernel<32><<<static_cast<unsigned>((n + 7) / 8), 256, 0, s>>>(part, G, n, gw, ow);
   else
-    wgrad_reduce_kernel<8><<<static_cast<unsigned>((n + 31) / 32), 256, 0, s>>>(part, G, n, gw);
+    wgrad_reduce_kernel<8><<<static_cast<unsigned>((n + 31) / 32), 256, 0, s>>>(part, G, n, gw, ow);
   return hipGetLastError();
 }
 
@@ -1800,6 +1875,10 @@ int64_t wgrad_workspace_floats(const WgradArgs& a) {
     return onechannel_groups(a, kSlabMaxPart) * static_cast<int64_t>(a.taps) * a.cin * a.cout;
   if (!uses_slab(a)) return 0;
   return slab_groups(a, kSlabMaxPart) * static_cast<int64_t>(a.taps) * a.cin * a.cout;
+}
+
+bool wgrad_overwrites(const WgradArgs& a) {
+  return (uses_onechannel(a) || uses_slab(a)) && wgrad_workspace_floats(a) <= kSlabMaxPart;
 }
 
 hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
@@ -1813,7 +1892,7 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
         wgrad_onechannel_kernel<true><<<grid, 256, 0, s>>>(a);
       else
         wgrad_onechannel_kernel<false><<<grid, 256, 0, s>>>(a);
-      return launch_wgrad_reduce(a.part, G, per, a.gw, s);
+      return launch_wgrad_reduce(a.part, G, per, a.gw, a.overwrite, s);
     }
   }
   if (uses_slab(a) && a.part) {
@@ -1827,7 +1906,7 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
         wgrad_slab_kernel<2><<<grid, 256, 0, s>>>(a);
       else
         wgrad_slab_kernel<1><<<grid, 256, 0, s>>>(a);
-      return launch_wgrad_reduce(a.part, G, per, a.gw, s);
+      return launch_wgrad_reduce(a.part, G, per, a.gw, a.overwrite, s);
     }
   }
   const int64_t M = static_cast<int64_t>(a.d) * a.h * a.w;
@@ -1848,18 +1927,24 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_pack(const float* w, int taps, int cin, int cout, int rows, int kpad,
-                       bool transposed, uint16_t* bt, hipStream_t s, bool clear) {
-  if (clear)
-    fill_u16_kernel<<<blocks_for(static_cast<int64_t>(rows) * kpad), 256, 0, s>>>(
-        bt, static_cast<int64_t>(rows) * kpad);
-  pack_kernel<<<blocks_for(static_cast<int64_t>(taps) * cin * cout), 256, 0, s>>>(
-      w, taps, cin, cout, kpad, transposed ? 1 : 0, bt);
+hipError_t launch_pack(const PackJob* dev_jobs, int njobs, int tiles, hipStream_t s) {
+  pack_kernel<<<tiles, 256, 0, s>>>(dev_jobs, njobs, PackJob{});
+  return hipGetLastError();
+}
+
+hipError_t launch_pack(const PackJob& job, hipStream_t s) {
+  pack_kernel<<<job.tiles(), 256, 0, s>>>(nullptr, 1, job);
   return hipGetLastError();
 }
 
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t s) {
   fill_f32_kernel<<<blocks_for(n), 256, 0, s>>>(p, n, v);
+  return hipGetLastError();
+}
+
+hipError_t launch_fill2(float* p, int64_t n, float* q, int64_t m, hipStream_t s) {
+  if (n + m == 0) return hipSuccess;
+  fill2_f32_kernel<<<blocks_for(n + m), 256, 0, s>>>(p, n, q, m);
   return hipGetLastError();
 }
 
@@ -1910,9 +1995,12 @@ hipError_t launch_mse(const float* out, const float* target_u, const float* targ
 }
 
 hipError_t launch_bias_grad(const uint16_t* gy, int64_t m, int cout, float* gb, hipStream_t s) {
-  const int64_t blocks = m < 512 ? 1 : (m / 256 < 1024 ? m / 256 : 1024);
+  const int64_t blocks = m < 512 ? 1 : (m / 256 < 256 ? m / 256 : 256);
   const int64_t per = (m + blocks - 1) / blocks;
-  bias_grad_kernel<<<static_cast<int>(blocks), 256, 0, s>>>(gy, m, cout, per, gb);
+  if (cout % 8 == 0)
+    bias_grad_kernel<true><<<static_cast<int>(blocks), 256, 0, s>>>(gy, m, cout, per, gb);
+  else
+    bias_grad_kernel<false><<<static_cast<int>(blocks), 256, 0, s>>>(gy, m, cout, per, gb);
   return hipGetLastError();
 }
 
@@ -1957,7 +2045,7 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, 
     blocks = blocks_for(n, 256, kNormBlocks);
     sumsq_kernel<<<blocks, 256, 0, s>>>(g, n, partial);
   }
-  adam_kernel<<<blocks_for(n), 256, 0, s>>>(p, g, m, v, n, lr, 0.9f, 0.999f, 1e-8f,
+  adam_kernel<<<blocks_for(n, 256, 2048), 256, 0, s>>>(p, g, m, v, n, lr, 0.9f, 0.999f, 1e-8f,
                                             static_cast<float>(c1), static_cast<float>(c2),
                                             grad_scale, max_norm, partial, blocks);
   return hipGetLastError();

@@ -81,6 +81,10 @@ void describe_layer(Layer& L, int kind, int cin, int cout, Grid in) {
   L.bwd_kpad = round_up(L.taps * cout, 32);
 }
 
+PackJob pack_job(const Layer& L, const float* w, uint16_t* fwd, uint16_t* bwd) {
+  return PackJob{w, fwd, bwd, L.taps, L.cin, L.cout, L.fwd_kpad, L.bwd_kpad};
+}
+
 // y = [relu](layer(x) + b [+ skip]); x BF16 with cin channels on L.in
 ConvArgs forward_args(const Layer& L, const uint16_t* x, const float* b, const uint16_t* skip,
                       bool relu, bool y_f32, void* y) {
@@ -213,7 +217,8 @@ struct mcx_nn {
   float* adam_v = nullptr;
   int step = 0;
   bool packed = false;       // packs hold the current parameters
-  bool pads_clear = false;   // pack padding has been zeroed once
+  PackJob* pack_jobs = nullptr;  // device table, one per layer
+  int pack_tiles = 0;
   float* u = nullptr;        // input in u space (FP32)
   uint16_t* u16 = nullptr;   // and as BF16
   float* r = nullptr;        // output layer result (FP32)
@@ -259,6 +264,7 @@ void nn_release(mcx_nn* nn) {
   for (void* p : nn->owned) (void)hipFree(p);
   if (nn->stream) (void)hipStreamDestroy(nn->stream);
   delete nn;
+  mcx::scratch_trim();
 }
 
 // NULL is the null stream, as for any HIP call (and torch's default stream)
@@ -266,14 +272,8 @@ hipStream_t pick(mcx_nn*, void* s) { return static_cast<hipStream_t>(s); }
 
 mcx_status pack_all(mcx_nn* nn, hipStream_t s) {
   if (nn->packed) return MCX_OK;
-  for (Layer& L : nn->layers) {
-    NN_HIP(launch_pack(nn->params + L.woff, L.taps, L.cin, L.cout, L.fwd_rows, L.fwd_kpad, false,
-                       L.fwd, s, !nn->pads_clear));
-    NN_HIP(launch_pack(nn->params + L.woff, L.taps, L.cin, L.cout, L.bwd_rows, L.bwd_kpad, true,
-                       L.bwd, s, !nn->pads_clear));
-  }
+  NN_HIP(launch_pack(nn->pack_jobs, static_cast<int>(nn->layers.size()), nn->pack_tiles, s));
   nn->packed = true;
-  nn->pads_clear = true;
   return MCX_OK;
 }
 
@@ -437,6 +437,14 @@ mcx_status mcx_nn_create(const int32_t* channels, int32_t nlevels, int32_t nx, i
       max_act = std::max(max_act, Ly.out.vox() * Ly.cout);
       max_in = std::max(max_in, Ly.in.vox() * Ly.cin);
     }
+    std::vector<PackJob> packs;
+    for (const Layer& Ly : nn->layers) {
+      packs.push_back(pack_job(Ly, nn->params + Ly.woff, Ly.fwd, Ly.bwd));
+      nn->pack_tiles += packs.back().tiles();
+    }
+    NN_TRY(nn_alloc(nn, &nn->pack_jobs, packs.size()));
+    NN_HIP(hipMemcpy(nn->pack_jobs, packs.data(), packs.size() * sizeof(PackJob),
+                     hipMemcpyHostToDevice));
     NN_TRY(nn_alloc(nn, &nn->u, n0));
     NN_TRY(nn_alloc(nn, &nn->u16, n0));
     NN_TRY(nn_alloc(nn, &nn->r, n0));
@@ -678,20 +686,22 @@ mcx_status mcx_nn_layer_forward(int32_t kind, int32_t nx, int32_t ny, int32_t nz
   Layer L;
   describe_layer(L, kind, cin, cout, Grid{nz, ny, nx});
   hipStream_t s = static_cast<hipStream_t>(stream);
-  NN_HIP(hipMalloc(&L.fwd, static_cast<size_t>(L.fwd_rows) * L.fwd_kpad * sizeof(uint16_t)));
   ConvArgs a = forward_args(L, x, b, skip, relu != 0, y_f32 != 0, y);
   a.part_cap = conv_workspace_floats(a);
-  hipError_t e = hipSuccess;
-  if (a.part_cap > 0) e = hipMalloc(&a.part, static_cast<size_t>(a.part_cap) * sizeof(float));
-  mcx_status st = MCX_OK;
-  if (e == hipSuccess)
-    e = launch_pack(w, L.taps, cin, cout, L.fwd_rows, L.fwd_kpad, false, L.fwd, s);
+  const size_t pack_bytes = static_cast<size_t>(L.fwd_rows) * L.fwd_kpad * sizeof(uint16_t);
+  const size_t part_bytes = static_cast<size_t>(a.part_cap) * sizeof(float);
+  mcx::Scratch ws;
+  NN_HIP(ws.acquire(mcx::Scratch::rounded(pack_bytes) + mcx::Scratch::rounded(part_bytes)));
+  L.fwd = static_cast<uint16_t*>(ws.take(pack_bytes));
+  a.bt = L.fwd;
+  if (part_bytes > 0) a.part = static_cast<float*>(ws.take(part_bytes));
+  hipError_t e = launch_pack(pack_job(L, w, L.fwd, nullptr), s);
   if (e == hipSuccess) e = launch_conv(a, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) st = nfail(MCX_EDEVICE, "layer forward: %s", hipGetErrorString(e));
-  (void)hipFree(L.fwd);
-  if (a.part) (void)hipFree(a.part);
-  return st;
+  const hipError_t w8 = hipStreamSynchronize(s);
+  if (w8 != hipSuccess) ws.discard();
+  if (e == hipSuccess) e = w8;
+  if (e != hipSuccess) return nfail(MCX_EDEVICE, "layer forward: %s", hipGetErrorString(e));
+  return MCX_OK;
 }
 
 mcx_status mcx_nn_layer_backward(int32_t kind, int32_t nx, int32_t ny, int32_t nz, int32_t cin,
@@ -703,29 +713,34 @@ mcx_status mcx_nn_layer_backward(int32_t kind, int32_t nx, int32_t ny, int32_t n
   Layer L;
   describe_layer(L, kind, cin, cout, Grid{nz, ny, nx});
   hipStream_t s = static_cast<hipStream_t>(stream);
-  NN_HIP(hipMalloc(&L.bwd, static_cast<size_t>(L.bwd_rows) * L.bwd_kpad * sizeof(uint16_t)));
-  mcx_status st = MCX_OK;
-  hipError_t e = launch_fill(gw, static_cast<int64_t>(L.taps) * cin * cout, 0.f, s);
-  if (e == hipSuccess && gb) e = launch_fill(gb, cout, 0.f, s);
   WgradArgs wa = wgrad_args(L, x, gy, gw);
   wa.part_cap = wgrad_workspace_floats(wa);
-  if (e == hipSuccess && wa.part_cap > 0)
-    e = hipMalloc(&wa.part, static_cast<size_t>(wa.part_cap) * sizeof(float));
-  if (e == hipSuccess) e = launch_wgrad(wa, s);
-  if (e == hipSuccess && gb) e = launch_bias_grad(gy, L.out.vox(), cout, gb, s);
-  if (e == hipSuccess && gx)
-    e = launch_pack(w, L.taps, cin, cout, L.bwd_rows, L.bwd_kpad, true, L.bwd, s);
+  wa.overwrite = wgrad_overwrites(wa);
   ConvArgs da = dgrad_args(L, gy, gx);
   da.part_cap = gx ? conv_workspace_floats(da) : 0;
-  if (e == hipSuccess && da.part_cap > 0)
-    e = hipMalloc(&da.part, static_cast<size_t>(da.part_cap) * sizeof(float));
+  const size_t pack_bytes =
+      gx ? static_cast<size_t>(L.bwd_rows) * L.bwd_kpad * sizeof(uint16_t) : 0;
+  // the two products run one after the other and share their workspace
+  const size_t part_bytes =
+      static_cast<size_t>(std::max(wa.part_cap, da.part_cap)) * sizeof(float);
+  mcx::Scratch ws;
+  NN_HIP(ws.acquire(mcx::Scratch::rounded(pack_bytes) + mcx::Scratch::rounded(part_bytes)));
+  L.bwd = static_cast<uint16_t*>(ws.take(pack_bytes));
+  da.bt = L.bwd;
+  float* part = part_bytes > 0 ? static_cast<float*>(ws.take(part_bytes)) : nullptr;
+  wa.part = wa.part_cap > 0 ? part : nullptr;
+  da.part = da.part_cap > 0 ? part : nullptr;
+  const int64_t nw = wa.overwrite ? 0 : static_cast<int64_t>(L.taps) * cin * cout;
+  hipError_t e = launch_fill2(gw, nw, gb, gb ? cout : 0, s);
+  if (e == hipSuccess) e = launch_wgrad(wa, s);
+  if (e == hipSuccess && gb) e = launch_bias_grad(gy, L.out.vox(), cout, gb, s);
+  if (e == hipSuccess && gx) e = launch_pack(pack_job(L, w, nullptr, L.bwd), s);
   if (e == hipSuccess && gx) e = launch_conv(da, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) st = nfail(MCX_EDEVICE, "layer backward: %s", hipGetErrorString(e));
-  (void)hipFree(L.bwd);
-  if (da.part) (void)hipFree(da.part);
-  if (wa.part) (void)hipFree(wa.part);
-  return st;
+  const hipError_t w8 = hipStreamSynchronize(s);
+  if (w8 != hipSuccess) ws.discard();
+  if (e == hipSuccess) e = w8;
+  if (e != hipSuccess) return nfail(MCX_EDEVICE, "layer backward: %s", hipGetErrorString(e));
+  return MCX_OK;
 }
 
 }  // extern "C"

@@ -39,3 +39,84 @@ def test_window_carries_beside_direct_adds(window, adds):
     expect = (-math.expm1(-mua)) / mua
     for k in range(4):
         assert maps[0][0, k, 1, 1] / N == pytest.approx(math.exp(-k * mua) * expect, rel=2e-6)
+
+
+def layer_forward_backward(kind, shape, ci, co, seed):
+    """One layer forward (FP32 output) and backward on the GPU against the
+    FP64 oracle on the same BF16 inputs, within 1e-5 of the sums of absolute
+    terms: FP32 accumulation of random signs errs by about sqrt(K) 2^-24 of
+    them, 2.5e-6 for the longest reduction (K = 1755), and by K 2^-24 at
+    most."""
+    import test_gpu_nn as T
+    t = T.torch()
+    x, w, b = T.layer_case(kind, shape, ci, co, seed)
+    wq = T.O.bf16(w)
+    oshape = T.out_shape(kind, shape)
+    xd, wd, bd = T.dev_bf16(x), T.dev_f32(w), T.dev_f32(b)
+    y = t.empty(oshape + (co,), dtype=t.float32, device="cuda")
+    T.nn.mcx_nn_layer_forward(T.KIND[kind], shape, ci, co, xd, wd, bd, None, relu=False, y=y,
+                              y_f32=True)
+    scale = T.abs_terms(kind, x, wq) + np.abs(b)
+    assert np.all(np.abs(T.host(y) - T.FWD[kind](x, wq, b)) <= 1e-5 * scale + 1e-30)
+    gy = T.O.bf16(np.random.default_rng(seed + 1).normal(size=oshape + (co,)))
+    gx = t.empty(tuple(shape) + (ci,), dtype=t.float32, device="cuda")
+    gw = t.full(w.shape, float("nan"), dtype=t.float32, device="cuda")
+    gb = t.full((co,), float("nan"), dtype=t.float32, device="cuda")
+    T.nn.mcx_nn_layer_backward(T.KIND[kind], shape, ci, co, xd, wd, T.dev_bf16(gy), gx, gw, gb)
+    ref = T.BWD[kind](x, wq, gy)
+    lim = T.BWD[kind](np.abs(x), np.abs(wq), np.abs(gy))[:2] + (np.abs(gy).reshape(-1, co).sum(0),)
+    for got, want, sc in zip((gx, gw, gb), ref, lim):
+        assert np.all(np.abs(T.host(got) - want) <= 1e-5 * sc + 1e-30)
+
+
+@pytest.mark.parametrize("kind,ci,co", [("conv3", 33, 65), ("conv3", 64, 31), ("conv3", 1, 63),
+                                        ("down", 5, 63), ("down", 32, 33), ("up", 65, 7)])
+def test_weight_packs_at_tile_edges(kind, ci, co):
+    """Channel counts around the packs' 32- and 64-wide tiles, after a call of
+    a larger layer left NaN weights in the scratch memory they reuse: the
+    packs' padding must be zero, not what was there."""
+    import test_gpu_nn as T
+    t = T.torch()
+    x = t.zeros((4, 4, 4, 96), dtype=t.bfloat16, device="cuda")
+    nan = t.full((27, 96, 128), float("nan"), device="cuda")
+    y = t.empty((4, 4, 4, 128), dtype=t.float32, device="cuda")
+    T.nn.mcx_nn_layer_forward(T.nn.MCX_NN_CONV3, (4, 4, 4), 96, 128, x, nan, None, y=y, y_f32=True)
+    say("[gpu] layer", kind, ci, co)
+    layer_forward_backward(kind, (4, 6, 4), ci, co, 11)
+
+
+def test_scratch_is_shared_between_threads():
+    """Two threads on streams of their own call layers of different sizes
+    again and again: each call's scratch memory is its own while it runs."""
+    import threading
+
+    import test_gpu_nn as T
+    t = T.torch()
+    jobs = []
+    for k, (ci, co) in enumerate([(64, 64), (32, 96)]):
+        x, w, b = T.layer_case("conv3", (6, 8, 8), ci, co, 20 + k)
+        jobs.append((T.dev_bf16(x), T.dev_f32(w), T.dev_f32(b), ci, co))
+    want = []
+    for x, w, b, ci, co in jobs:
+        y = t.empty((6, 8, 8, co), device="cuda")
+        T.nn.mcx_nn_layer_forward(T.nn.MCX_NN_CONV3, (6, 8, 8), ci, co, x, w, b, y=y, y_f32=True)
+        want.append(y.clone())
+    t.cuda.synchronize()
+    bad = []
+
+    def work(k):
+        x, w, b, ci, co = jobs[k]
+        s = t.cuda.Stream()
+        y = t.empty((6, 8, 8, co), device="cuda")
+        for _ in range(30):
+            T.nn.mcx_nn_layer_forward(T.nn.MCX_NN_CONV3, (6, 8, 8), ci, co, x, w, b, y=y,
+                                      y_f32=True, stream=s)
+            if not t.equal(y, want[k]):
+                bad.append(k)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in (0, 1)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not bad
