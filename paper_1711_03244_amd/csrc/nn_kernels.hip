@@ -246,86 +246,210 @@ __global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
 }
 
 // ------------------------------------------------- 3x3x3 conv from an LDS brick
+// The source of the zero padding of direct global-to-LDS loads: 64 KB of
+// zeros, each lane reading its own 16 bytes (offset by workgroup and load),
+// so that zero chunks spread over many cache lines instead of sending every
+// compute unit to one address.
+constexpr int kZeroChunks = 4096;
+__device__ __align__(16) uint4 g_zero16[kZeroChunks];
+
+__device__ __forceinline__ void load_lds16(const void* src, void* dst) {
+  __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)(src),
+                                   (__attribute__((address_space(3))) void*)(dst), 16, 0, 0);
+}
+
+// Wait until at most N of this wave's global memory operations are
+// outstanding (they complete in order); other counters are not waited for.
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "six bits");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
+// A workgroup barrier that waits for this wave's LDS operations but not, as
+// __syncthreads does, for all its global loads: those in flight towards LDS
+// are waited for by count (wait_vm) where they are due.
+__device__ __forceinline__ void barrier_lds() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // kConv3 / kConv3T with cin a multiple of 32: a workgroup owns a 4 x 4 x 4MZ
-// tile of output voxels (wave w: the z-slices MZ w .. MZ w + MZ - 1, one
-// 16-row MFMA block each) and 16 NB output channels.  Per chunk of 32 input
-// channels it stages the 6 x 6 x (4MZ + 2) input brick (tile plus halo, zero
-// outside the volume) in LDS once, and per plane of 9 taps the weights of
-// those taps for its channels; every tap then reads its A fragments from
-// the brick and its B fragments from the staged weights, so each weight
-// fragment feeds MZ NB matrix instructions.
+// tile of output voxels and 16 NB output channels.  Per chunk of 32 input
+// channels the 6 x 6 x (4MZ + 2) input brick (tile plus halo, zero outside
+// the volume) is staged in LDS, and the chunk's weights pass through a ring
+// of stages of three taps (one dz, dy).  Four compute waves, kWN of them side
+// by side along the channels, take their A fragments from the brick and their
+// B fragments from the stage and issue no global memory operation; two
+// loader waves stream the weights (three stages ahead) and the next chunk's
+// brick by direct global-to-LDS loads, each waiting only for the loads of
+// the stage that is due.  One barrier per stage.
+// What bounds it: staging.  Loading a plane's weights, a barrier, 9 taps,
+// a barrier left the waves waiting for loads 54-74 % of their cycles; with
+// the loads ahead the LDS reads of the fragments are next (two waves side by
+// side read 4 fragments for 4 matrix instructions, four in a column 5).
+// 32^3 64 -> 64: 30 -> BRICK32 us, 16^3 128 -> 128 and 8^3 256 -> 256 (with
+// their split reductions) 19 -> BRICK16 and 17 -> BRICK8 us.
+// Layouts as in the resident kernel: brick voxel v at v * 64 bytes, its
+// 16-byte chunk j in slot j ^ (y & 3); weight row n at n * 64 bytes, chunk j
+// in slot j ^ ((n >> 2) & 3).
 // With gridDim.z = S > 1 the chunks are split into S equal ranges, one per
 // grid z index, and each workgroup stores its raw sums to the workspace
 // part[z][out voxel][cout] for split_reduce_kernel to finish.
 template <int NB, int MZ>
-__global__ void __launch_bounds__(256) conv3_brick_kernel(ConvArgs a) {
-  constexpr int BZ = 4 * MZ + 2;
-  constexpr int BV = 36 * BZ;
-  __shared__ uint16_t sBr[BV][kBK + kPadK];
-  __shared__ uint16_t sW[9][16 * NB][kBK + kPadK];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
+struct Brick {
+  static constexpr int kBZ = 4 * MZ + 2;
+  static constexpr int kPieces = 36 * kBZ * 4;               // 16-byte pieces of a brick
+  static constexpr int kBrickLoads = (kPieces + 63) / 64;    // wave loads of a brick
+  static constexpr int kBrickBytes = kBrickLoads * 1024;
+  static constexpr int kStageLoads = 3 * NB;                 // wave loads of a stage
+  static constexpr int kStageBytes = kStageLoads * 1024;
+  static constexpr int kRing = 4;
+  static constexpr int kWN = NB >= 2 ? 2 : 1;                // compute waves along the channels
+  static constexpr int kSW = 4 * MZ * kWN / 4;               // z-slices per wave
+  static constexpr int kCW = NB / kWN;                       // 16-channel blocks per wave
+};
+
+// Loader wave LW (0 or 1) of a workgroup: every other wave load.
+template <int NB, int MZ, int LW>
+__device__ __forceinline__ void brick_loader(const ConvArgs& a, char* s_br, char* s_w, int lane,
+                                             int bx, int by, int bz, int n0, int c_begin,
+                                             int nchunks) {
+  using K = Brick<NB, MZ>;
+  constexpr int kB = (K::kBrickLoads + 1 - LW) / 2;  // this wave's loads of a brick
+  constexpr int kW = (K::kStageLoads + 1 - LW) / 2;  // and of a stage
+  // brick: source of this lane's piece of each load at the first chunk
+  const uint16_t* zero = reinterpret_cast<const uint16_t*>(g_zero16);
+  const uint16_t* src[kB];
+  uint32_t inside = 0;
+#pragma unroll
+  for (int k = 0; k < kB; ++k) {
+    const int p = (2 * k + LW) * 64 + lane;
+    const int v = p >> 2, vx = v % 6, vy = (v / 6) % 6, vz = v / 36;
+    const int gx = bx + vx - 1, gy = by + vy - 1, gz = bz + vz - 1;
+    const bool in = p < K::kPieces && gx >= 0 && gy >= 0 && gz >= 0 && gx < a.in_w &&
+                    gy < a.in_h && gz < a.in_d;
+    const int j = (p & 3) ^ (vy & 3);
+    src[k] = in ? a.x + ((static_cast<int64_t>(gz) * a.in_h + gy) * a.in_w + gx) * a.cin +
+                      c_begin + j * 8
+                : zero + ((blockIdx.x * 192 + k * 64 + lane) & (kZeroChunks - 1)) * 8;
+    inside |= in ? 1u << k : 0u;
+  }
+  auto load_brick = [&](int chunk) {
+    char* dst = s_br + (chunk & 1) * K::kBrickBytes;
+#pragma unroll
+    for (int k = 0; k < kB; ++k)
+      load_lds16(src[k] + ((inside >> k) & 1u ? chunk * 32 : 0), dst + (2 * k + LW) * 1024);
+  };
+  // weights: rows 16 rb + lane / 4 of the workgroup's 16 NB rows
+  const int row = lane >> 2, j = (lane & 3) ^ ((row >> 2) & 3);
+  uint32_t off[NB];
+#pragma unroll
+  for (int rb = 0; rb < NB; ++rb)
+    off[rb] = static_cast<uint32_t>(n0 + 16 * rb + row) * static_cast<uint32_t>(a.kpad) + j * 8;
+  auto load_stage = [&](int s) {
+    const int chunk = s / 9, t0 = (s - chunk * 9) * 3;
+    char* dst = s_w + (s & (K::kRing - 1)) * K::kStageBytes;
+#pragma unroll
+    for (int k = 0; k < kW; ++k) {
+      const int b = 2 * k + LW, dx = b / NB, rb = b % NB;
+      const uint16_t* base = a.bt + (t0 + dx) * a.cin + c_begin + chunk * 32;
+      load_lds16(base + off[rb], dst + b * 1024);
+    }
+  };
+  const int S = 9 * nchunks;
+  load_brick(0);
+#pragma unroll
+  for (int s = 0; s < 3; ++s) load_stage(s);
+  int chunk = 0, js = 0;  // s = 9 chunk + js
+  for (int s = 0; s < S; ++s) {
+    // stage s has landed once at most the loads of the two stages after it,
+    // and of a brick asked for after it (at js == 0), are outstanding
+    if (s + 2 >= S) {
+      if (s + 1 < S) wait_vm<kW>(); else wait_vm<0>();
+    } else if ((js == 1 || js == 2) && chunk + 1 < nchunks) {
+      wait_vm<2 * kW + kB>();
+    } else {
+      wait_vm<2 * kW>();
+    }
+    barrier_lds();
+    if (js == 0 && chunk + 1 < nchunks) load_brick(chunk + 1);
+    if (s + 3 < S) load_stage(s + 3);
+    if (++js == 9) {
+      js = 0;
+      ++chunk;
+    }
+  }
+}
+
+template <int NB, int MZ>
+__global__ void __launch_bounds__(384) conv3_brick_kernel(ConvArgs a) {
+  using K = Brick<NB, MZ>;
+  __shared__ __align__(16) char s_br[2 * K::kBrickBytes];
+  __shared__ __align__(16) char s_w[K::kRing * K::kStageBytes];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tx_n = (a.w + 3) >> 2, ty_n = (a.h + 3) >> 2;
   const int tile = blockIdx.x;
   const int bx = (tile % tx_n) * 4;
   const int by = ((tile / tx_n) % ty_n) * 4;
   const int bz = (tile / (tx_n * ty_n)) * (4 * MZ);
   const int n0 = blockIdx.y * 16 * NB;
+  const int split_len = a.cin / static_cast<int>(gridDim.z);  // a multiple of kBK
+  const int c_begin = static_cast<int>(blockIdx.z) * split_len;
+  const int nchunks = split_len / kBK;
+  if (wave == 4) {
+    brick_loader<NB, MZ, 0>(a, s_br, s_w, lane, bx, by, bz, n0, c_begin, nchunks);
+    return;
+  }
+  if (wave == 5) {
+    brick_loader<NB, MZ, 1>(a, s_br, s_w, lane, bx, by, bz, n0, c_begin, nchunks);
+    return;
+  }
+
   const int sgn = a.geo == kConv3 ? 1 : -1;
   const int r = lane & 15;            // A row of this lane: voxel (r & 3, r >> 2) of a slice
   const int ox = r & 3, oy = r >> 2;
-  const int kq = (lane >> 4) * 8;     // this lane's 8 reduction (channel) positions
+  const int kq = lane >> 4;           // this lane's 16-byte chunk of the 32 channels
+  const int z0 = wave / K::kWN * K::kSW;          // the wave's first slice
+  const int cb = wave % K::kWN * K::kCW;          // and 16-channel block
+  floatx4 acc[K::kSW][K::kCW];
+#pragma unroll
+  for (int q = 0; q < K::kSW; ++q)
+#pragma unroll
+    for (int c = 0; c < K::kCW; ++c) acc[q][c] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  floatx4 acc[MZ][NB];
+  int s = 0;
+  for (int chunk = 0; chunk < nchunks; ++chunk) {
+    const char* br = s_br + (chunk & 1) * K::kBrickBytes;
+    for (int row = 0; row < 9; ++row, ++s) {  // taps 3 row .. 3 row + 2
+      barrier_lds();  // stage s (and the chunk's brick) has landed
+      const char* wst = s_w + (s & (K::kRing - 1)) * K::kStageBytes;
+      const int dz = sgn * (row / 3 - 1), dy = sgn * (row % 3 - 1);
+      const int yy = oy + 1 + dy;
+      const char* ab = br + (((z0 + 1 + dz) * 6 + yy) * 6 + ox + 1) * 64 + ((kq ^ (yy & 3)) << 4);
+      const char* bb = wst + (16 * cb + r) * 64 + ((kq ^ ((r >> 2) & 3)) << 4);
+      bf16x8 af[3][K::kSW], bf[3][K::kCW];
 #pragma unroll
-  for (int q = 0; q < MZ; ++q)
+      for (int t = 0; t < 3; ++t) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) acc[q][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  const int split_len = a.cin / static_cast<int>(gridDim.z);  // a multiple of kBK
-  const int c_begin = static_cast<int>(blockIdx.z) * split_len;
-  for (int c0 = c_begin; c0 < c_begin + split_len; c0 += kBK) {
-    __syncthreads();  // the previous chunk's fragments have been read
-    for (int i = tid; i < BV * 4; i += 256) {
-      const int v = i >> 2, cc = (i & 3) * 8;
-      const int vx = v % 6, vy = (v / 6) % 6, vz = v / 36;
-      const int gx = bx + vx - 1, gy = by + vy - 1, gz = bz + vz - 1;
-      uint4 val = make_uint4(0u, 0u, 0u, 0u);
-      if (gx >= 0 && gy >= 0 && gz >= 0 && gx < a.in_w && gy < a.in_h && gz < a.in_d)
-        val = *reinterpret_cast<const uint4*>(
-            a.x + ((static_cast<int64_t>(gz) * a.in_h + gy) * a.in_w + gx) * a.cin + c0 + cc);
-      *reinterpret_cast<uint4*>(&sBr[v][cc]) = val;
-    }
-    for (int pz = 0; pz < 3; ++pz) {
-      if (pz > 0) __syncthreads();  // the previous plane's weights have been read
-      // weights of taps 9 pz .. 9 pz + 8: rows n0 .. n0 + 16 NB - 1 of bt (the
-      // packed rows extend to a multiple of 64 >= n0 + 16 NB), 32 columns each
-      for (int i = tid; i < 9 * 16 * NB * 4; i += 256) {
-        const int tt = i / (16 * NB * 4), rem = i % (16 * NB * 4);
-        const int row = rem >> 2, cc = (rem & 3) * 8;
-        *reinterpret_cast<uint4*>(&sW[tt][row][cc]) = *reinterpret_cast<const uint4*>(
-            a.bt + static_cast<int64_t>(n0 + row) * a.kpad + (9 * pz + tt) * a.cin + c0 + cc);
+        for (int c = 0; c < K::kCW; ++c)
+          bf[t][c] = *reinterpret_cast<const bf16x8*>(bb + (t * 16 * NB + 16 * c) * 64);
+#pragma unroll
+        for (int q = 0; q < K::kSW; ++q)
+          af[t][q] = *reinterpret_cast<const bf16x8*>(ab + (q * 36 + sgn * (t - 1)) * 64);
       }
-      __syncthreads();
-      const int dz = sgn * (pz - 1);
+      __builtin_amdgcn_sched_barrier(0);  // all reads ahead of the matrix instructions
 #pragma unroll
-      for (int tt = 0; tt < 9; ++tt) {
-        const int dy = sgn * (tt / 3 - 1), dx = sgn * (tt % 3 - 1);
-        bf16x8 bc[NB];
+      for (int t = 0; t < 3; ++t)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
-          bc[j] = *reinterpret_cast<const bf16x8*>(&sW[tt][16 * j + r][kq]);
+        for (int q = 0; q < K::kSW; ++q)
 #pragma unroll
-        for (int q = 0; q < MZ; ++q) {
-          const int oz = wave * MZ + q;
-          const int v = ((oz + 1 + dz) * 6 + (oy + 1 + dy)) * 6 + (ox + 1 + dx);
-          const bf16x8 af = *reinterpret_cast<const bf16x8*>(&sBr[v][kq]);
-#pragma unroll
-          for (int j = 0; j < NB; ++j)
-            acc[q][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bc[j], acc[q][j], 0, 0, 0);
-        }
-      }
+          for (int c = 0; c < K::kCW; ++c)
+            acc[q][c] =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[t][q], bf[t][c], acc[q][c], 0, 0, 0);
     }
   }
 
@@ -334,23 +458,23 @@ __global__ void __launch_bounds__(256) conv3_brick_kernel(ConvArgs a) {
   float* part = split ? a.part + static_cast<int64_t>(blockIdx.z) * a.d * a.h * a.w * a.cout
                       : nullptr;
 #pragma unroll
-  for (int q = 0; q < MZ; ++q)
+  for (int q = 0; q < K::kSW; ++q)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int n = n0 + j * 16 + (lane & 15);
+    for (int c = 0; c < K::kCW; ++c) {
+      const int n = n0 + (cb + c) * 16 + (lane & 15);
       if (n >= a.cout) continue;
       const float bias = a.bias ? a.bias[n] : 0.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int rr = (lane >> 4) * 4 + e;
-        const int x = bx + (rr & 3), y = by + (rr >> 2), z = bz + wave * MZ + q;
+        const int x = bx + (rr & 3), y = by + (rr >> 2), z = bz + z0 + q;
         if (x >= a.w || y >= a.h || z >= a.d) continue;
         const int64_t o = (static_cast<int64_t>(z) * a.h + y) * a.w + x;
         if (split) {
-          part[o * a.cout + n] = acc[q][j][e];
+          part[o * a.cout + n] = acc[q][c][e];
           continue;
         }
-        float v = acc[q][j][e] + bias;
+        float v = acc[q][c][e] + bias;
         if (a.skip) v += from_bf16(a.skip[o * a.cout + n]);
         if (a.relu) v = fmaxf(v, 0.f);
         if (a.y_f32)
@@ -383,12 +507,6 @@ __global__ void __launch_bounds__(256) conv3_brick_kernel(ConvArgs a) {
 // weights of output channel n likewise at n * 64 bytes, chunk j in slot
 // j ^ ((n >> 2) & 3).
 constexpr int kResPlane = 36 * 64;  // bytes per plane slot
-// The source of the zero padding: 64 KB of zeros, each lane reading its
-// own 16 bytes (offset by workgroup and load), so that the zero chunks --
-// whole planes at z = -1 and z = d, and the volume's sides -- spread over
-// many cache lines instead of sending every compute unit to one address.
-constexpr int kZeroChunks = 4096;
-__device__ __align__(16) uint4 g_zero16[kZeroChunks];
 
 // Byte offset of byte `byte` of local voxel vl's outputs in an output tile
 // of the resident kernel (rows of NB 16 outputs of ES bytes).  For NB == 2
@@ -1785,9 +1903,9 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t s) {
                     static_cast<unsigned>(brick_ngroups(a)), static_cast<unsigned>(sp));
 #define MCX_BRICK(NB)                                                  \
   if (mz == 2)                                                         \
-    conv3_brick_kernel<NB, 2><<<grid, 256, 0, s>>>(a);                 \
+    conv3_brick_kernel<NB, 2><<<grid, 384, 0, s>>>(a);                 \
   else                                                                 \
-    conv3_brick_kernel<NB, 1><<<grid, 256, 0, s>>>(a);
+    conv3_brick_kernel<NB, 1><<<grid, 384, 0, s>>>(a);
     if (nb == 4) { MCX_BRICK(4) } else if (nb == 2) { MCX_BRICK(2) } else { MCX_BRICK(1) }
 #undef MCX_BRICK
     if (sp > 1) split_reduce_kernel<<<blocks_for(M * a.cout), 256, 0, s>>>(a, sp);
