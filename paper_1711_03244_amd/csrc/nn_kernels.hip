@@ -500,7 +500,13 @@ __global__ void __launch_bounds__(384) conv3_brick_kernel(ConvArgs a) {
 // write the previous tile's outputs from LDS to global memory.  The compute
 // waves issue no global memory operation; each data wave waits only for its
 // own transfers (the plane wave for all but the newest A - 1 tiles' loads,
-// which complete in issue order): one barrier per tile.  Plane layout: voxel
+// which complete in issue order): one barrier per tile, which does not wait
+// for transfers (barrier_lds).  What bounds a tile are the compute waves'
+// fragment reads from LDS, 4 KB per 4 matrix instructions with both operands
+// read for every tap, so the weights of most taps stay in registers.  Measured
+// at 64^3, 32 -> 32 channels: 24.5 -> 21.6 us (BF16 out), 26.1 -> 22.2 (input
+// gradient, FP32 out); 32 -> 16: 19.0 -> 17.0; kGrad 26.5 -> 26.7: there the
+// output waves' work is the longer.  Plane layout: voxel
 // (y, x) of the plane at (y * 6 + x) * 64 bytes, its 16-byte chunk j
 // (channels 8j .. 8j + 7) in slot j ^ (y & 3), so that the 16 rows of an A
 // fragment (a 4 x 4 patch of voxels) fall on 16 different bank groups; the
@@ -539,6 +545,9 @@ __device__ __forceinline__ void pin(const uint4& v) {
 // tiles of planes in flight: all that fit in LDS beside the weights and
 // two output tiles (three, or two for 32 FP32 output columns)
 constexpr int res_ahead(int nb, bool f32) { return nb == 2 && f32 ? 2 : 3; }
+// taps whose weights the compute waves hold in registers: what 256 registers
+// per lane leave room for
+constexpr int res_taps(int nb) { return nb == 2 ? 22 : 27; }
 
 // kGrad: an input gradient with the next backward step folded in
 // (ConvArgs::gmask): the compute waves leave FP32 sums in LDS, the output
@@ -728,28 +737,26 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
     }
   };
 
-  const int sgn = a.geo == kConv3 ? 1 : -1;
-  const int r = lane & 15;
-  const int ox = r & 3, oy = r >> 2;
-  const int kq = lane >> 4;  // this lane's 16-byte chunk of the 32 channels
-  for (int col = blockIdx.x; col < ncol; col += gridDim.x) {
-    const int bx = (col % tx_n) * 4, by = (col / tx_n) * 4;
-    // planes -1 .. 8 min(tz_n, A): the first A tiles; wait for tile 0's
-    // (all loads but those of the tiles after it, 24 per tile)
-    if (wave == 4) {
+  // The three kinds of wave meet at the same barriers: one before the first
+  // column (the weights have landed), per column one once the first tile's
+  // planes have, one per tile, and one after the column's last outputs.
+  barrier_lds();
+  if (wave == 4) {
+    for (int col = blockIdx.x; col < ncol; col += gridDim.x) {
+      const int bx = (col % tx_n) * 4, by = (col / tx_n) * 4;
+      // planes -1 .. 8 min(tz_n, A): the first A tiles; wait for tile 0's
+      // (all loads but those of the tiles after it, 24 per tile)
       const int zend = 8 * min(tz_n, A);
       for (int z = -1; z <= zend; ++z) load_plane(bx, by, z);
-      const int pending = min(tz_n, A) - 1;
-      if (pending >= 2)
-        __builtin_amdgcn_s_waitcnt(0xCF70);  // vmcnt(48), other counters not waited
-      else if (pending == 1)
-        __builtin_amdgcn_s_waitcnt(0x4F78);  // vmcnt(24)
+      const int first = min(tz_n, A) - 1;
+      if (first >= 2)
+        wait_vm<48>();
+      else if (first == 1)
+        wait_vm<24>();
       else
-        __builtin_amdgcn_s_waitcnt(0);
-    }
-    __syncthreads();
-    for (int k = 0; k < tz_n; ++k) {
-      if (wave == 4) {
+        wait_vm<0>();
+      barrier_lds();
+      for (int k = 0; k < tz_n; ++k) {
         // the eight new planes of tile k + A (their slots held planes no tile
         // from k on needs); then wait until tile k + 1's planes have arrived:
         // all loads but those of the tiles after it (24 per tile)
@@ -758,29 +765,58 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
           for (int z = 8 * (k + A) + 1; z <= 8 * (k + A) + 8; ++z) load_plane(bx, by, z);
         const int pending = last - (k + 1);  // tiles whose loads may stay in flight
         if (pending >= 2)
-          __builtin_amdgcn_s_waitcnt(0xCF70);  // vmcnt(48), other counters not waited
+          wait_vm<48>();
         else if (pending == 1)
-          __builtin_amdgcn_s_waitcnt(0x4F78);  // vmcnt(24)
+          wait_vm<24>();
         else
-          __builtin_amdgcn_s_waitcnt(0);
-      } else if (wave >= 5) {
+          wait_vm<0>();
+        barrier_lds();
+      }
+      barrier_lds();
+    }
+  } else if (wave >= 5) {
+    for (int col = blockIdx.x; col < ncol; col += gridDim.x) {
+      const int bx = (col % tx_n) * 4, by = (col / tx_n) * 4;
+      barrier_lds();
+      for (int k = 0; k < tz_n; ++k) {
         if (k > 0) store_out(bx, by, 8 * (k - 1), (k - 1) & 1);
         if constexpr (kGrad) load_mask(bx, by, 8 * k);  // for the store of tile k
-      } else {
+        barrier_lds();
+      }
+      // the column's last tile; the ring and the output tiles are reused next
+      store_out(bx, by, 8 * (tz_n - 1), (tz_n - 1) & 1);
+      barrier_lds();
+    }
+  } else {
+    const int sgn = a.geo == kConv3 ? 1 : -1;
+    const int r = lane & 15;
+    const int ox = r & 3, oy = r >> 2;
+    const int kq = lane >> 4;  // this lane's 16-byte chunk of the 32 channels
+    const char* ring = reinterpret_cast<const char*>(sRing);
+    // The fragment reads bound the tile (4 KB per 4 matrix instructions of
+    // a wave), so the B fragments of the first kRT taps stay in registers for
+    // every tile, as many as fit beside the sums and the fragments in
+    // flight; only the other taps' are read with each tile.
+    constexpr int kRT = res_taps(NB);
+    bf16x8 breg[kRT][NB];
+#pragma unroll
+    for (int tt = 0; tt < kRT; ++tt)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        breg[tt][j] = *reinterpret_cast<const bf16x8*>(&sW[tt][16 * j + r][kq ^ ((r >> 2) & 3)]);
+    for (int col = blockIdx.x; col < ncol; col += gridDim.x) {
+      barrier_lds();
+      for (int k = 0; k < tz_n; ++k) {
         floatx4 acc[2][NB];
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
           for (int j = 0; j < NB; ++j) acc[q][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-        const char* ring = reinterpret_cast<const char*>(sRing);
-        // fragments of tap tt: B from the weights, A from the planes (voxel
-        // of row r shifted by the tap); the next tap's are read while this
+        // fragments of tap tt: A from the planes (voxel of row r shifted by
+        // the tap), B from the weights; the next tap's are read while this
         // tap's matrix instructions run
-        auto frags = [&](int tt, bf16x8 (&bc)[NB], bf16x8 (&af)[2]) {
+        auto read_a = [&](int tt, bf16x8 (&af)[2]) {
           const int dz = sgn * (tt / 9 - 1), dy = sgn * ((tt / 3) % 3 - 1), dx = sgn * (tt % 3 - 1);
-#pragma unroll
-          for (int j = 0; j < NB; ++j)
-            bc[j] = *reinterpret_cast<const bf16x8*>(&sW[tt][16 * j + r][kq ^ ((r >> 2) & 3)]);
           const int yy = oy + 1 + dy;
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
@@ -789,19 +825,28 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
                 ring + zs * kResPlane + (yy * 6 + ox + 1 + dx) * 64 + ((kq ^ (yy & 3)) << 4));
           }
         };
+        auto read_b = [&](int tt, bf16x8 (&bc)[NB]) {
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            bc[j] = *reinterpret_cast<const bf16x8*>(&sW[tt][16 * j + r][kq ^ ((r >> 2) & 3)]);
+        };
         bf16x8 bc[2][NB], af[2][2];
-        frags(0, bc[0], af[0]);
+        read_a(0, af[0]);
+        if constexpr (kRT == 0) read_b(0, bc[0]);
 #pragma unroll
         for (int tt = 0; tt < 27; ++tt) {
           const int cur = tt & 1;
-          if (tt + 1 < 27) frags(tt + 1, bc[cur ^ 1], af[cur ^ 1]);
+          if (tt + 1 < 27) {
+            read_a(tt + 1, af[cur ^ 1]);
+            if (tt + 1 >= kRT) read_b(tt + 1, bc[cur ^ 1]);
+          }
           __builtin_amdgcn_sched_barrier(0);  // keep those reads ahead of the MFMAs below
 #pragma unroll
           for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int j = 0; j < NB; ++j)
-              acc[q][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[cur][q], bc[cur][j],
-                                                                  acc[q][j], 0, 0, 0);
+              acc[q][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  af[cur][q], tt < kRT ? breg[tt < kRT ? tt : 0][j] : bc[cur][j], acc[q][j], 0, 0, 0);
         }
         // epilogue into sOut: row 4 (lane >> 4) + e of slice 2 wave + q is
         // local voxel (x, y, z) = (rr & 3, rr >> 2, 2 wave + q)
@@ -840,12 +885,10 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
               }
             }
           }
+        barrier_lds();
       }
-      __syncthreads();
+      barrier_lds();
     }
-    // the column's last tile; the ring and the output tiles are reused next
-    if (wave >= 5) store_out(bx, by, 8 * (tz_n - 1), (tz_n - 1) & 1);
-    __syncthreads();
   }
   if constexpr (kGrad) {
     // the workgroup's channel sums, added in a fixed order
