@@ -31,8 +31,10 @@ struct ConvArgs {
   const uint16_t* skip;       // BF16 [out voxel][cout] added before ReLU, or null
   void* y;                    // BF16 or FP32 [out voxel][cout]
   int32_t y_f32, relu;
-  float* part;                // FP32 workspace for split reductions, or null (no split)
+  float* part;                // FP32 workspace for split reductions, or null
   int64_t part_cap;           // its size in floats
+  int32_t batch = 1;          // images: x, skip and y hold that many volumes one after another
+  int32_t ranges = 1;         // ranges of the reduction, added in order (set by launch_conv)
   // An input gradient with the next step of the backward pass folded in
   // (conv_folds_grad): when gmask is set, y receives the BF16 gradient of
   // the layer below's pre-activation, bf16(sum * (gmask > 0)), and
@@ -64,8 +66,8 @@ struct WgradArgs {
 };
 
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
-// floats of split-reduction workspace launch_conv would use for `a` given an
-// unlimited workspace (0: it does not split this product)
+// floats of split-reduction workspace launch_conv would use for `a` (0: none;
+// the results are the same without it)
 int64_t conv_workspace_floats(const ConvArgs& a);
 hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s);
 // floats of workspace launch_wgrad uses for `a` (0: it needs none)
@@ -95,12 +97,16 @@ hipError_t launch_fill2(float* p, int64_t n, float* q, int64_t m, hipStream_t s)
 hipError_t launch_to_log(const float* phi, int64_t n, float* u, uint16_t* u16, hipStream_t s);
 hipError_t launch_mirror_xy(const float* in, float* out, int nx, int ny, int nz, int op,
                             hipStream_t s);
-// acc (= when first, else +=) the symmetry op of in (as launch_mirror_xy)
-hipError_t launch_mirror_acc(const float* in, float* acc, int nx, int ny, int nz, int op,
-                             bool first, hipStream_t s);
-// out_u = acc / nsym and phi = its fluence (either may be null)
-hipError_t launch_sym_finish(const float* acc, int64_t n, int nsym, float* out_u, float* phi,
-                             hipStream_t s);
+// BF16 log-space inputs u16[k][voxel] of phi under the symmetries op0 + k, k < nop
+// (as launch_mirror_xy), and for op 0 phi's own in FP32, u
+hipError_t launch_sym_inputs(const float* phi, int nx, int ny, int nz, int op0, int nop, float* u,
+                             uint16_t* u16, hipStream_t s);
+// The network outputs r[k][voxel] of those inputs plus u, mapped back and
+// added to acc (which the first op starts); when op0 + nop == nsym instead
+// out_u = the sum / nsym and phi = its fluence (either may be null).
+hipError_t launch_sym_outputs(const float* r, const float* u, int nx, int ny, int nz, int op0,
+                              int nop, int nsym, float* acc, float* out_u, float* phi,
+                              hipStream_t s);
 hipError_t launch_from_log(const float* r, const float* u, int64_t n, float* out_u, float* phi,
                            hipStream_t s);
 // g16 = bf16((g + skip16) * (y16 > 0)) over n = voxels * cout values;

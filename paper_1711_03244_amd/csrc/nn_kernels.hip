@@ -100,22 +100,28 @@ __global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
   const int64_t m0 = static_cast<int64_t>(blockIdx.x) * kBM;
   const int n0 = blockIdx.y * 16 * NB;
   const int cls = blockIdx.z;  // parity class of kUp, else 0
-  const int64_t M = static_cast<int64_t>(a.d) * a.h * a.w;
+  const int64_t M = static_cast<int64_t>(a.batch) * a.d * a.h * a.w;  // the images' rows
   const int koff = a.geo == kUp ? cls * a.cin : 0;
 
   // this thread's A row and 8-wide k chunk for the loads
   const int lr = tid >> 2, lc = (tid & 3) * 8;
   const int64_t lm = m0 + lr;
   int lz = 0, ly = 0, lx = 0;
+  const uint16_t* x_img = a.x;  // the row's image
   if (lm < M) {
     lx = static_cast<int>(lm % a.w);
     ly = static_cast<int>((lm / a.w) % a.h);
     lz = static_cast<int>(lm / (static_cast<int64_t>(a.w) * a.h));
+    if (a.batch > 1) {
+      const int img = lz / a.d;
+      lz -= img * a.d;
+      x_img += static_cast<int64_t>(img) * a.in_d * a.in_h * a.in_w * a.cin;
+    }
   }
 
-  floatx4 acc[NB];
+  floatx4 acc[NB], tot[NB];  // the current range's sums, those of the ranges before it
 #pragma unroll
-  for (int j = 0; j < NB; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < NB; ++j) acc[j] = tot[j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   // this thread's 8 k of row lr of the A tile at reduction step k0
   auto load_a = [&](int k0) -> uint4 {
@@ -126,7 +132,7 @@ __global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
       if (k < a.k) {
         const int t = k / a.cin, ci = k - t * a.cin;
         const int64_t src = gather_at(a, lz, ly, lx, t);
-        if (src >= 0) v = *reinterpret_cast<const uint4*>(a.x + src * a.cin + ci);
+        if (src >= 0) v = *reinterpret_cast<const uint4*>(x_img + src * a.cin + ci);
       }
     } else {
       uint16_t e[8];
@@ -137,7 +143,7 @@ __global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
         if (kk < a.k) {
           const int t = kk / a.cin, ci = kk - t * a.cin;
           const int64_t src = gather_at(a, lz, ly, lx, t);
-          if (src >= 0) e[j] = a.x[src * a.cin + ci];
+          if (src >= 0) e[j] = x_img[src * a.cin + ci];
         }
       }
       v = make_uint4(e[0] | (uint32_t(e[1]) << 16), e[2] | (uint32_t(e[3]) << 16),
@@ -162,14 +168,17 @@ __global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
   // software pipeline: the next stage's global loads are in flight while
   // the matrix cores work on the current stage's tiles
   constexpr int kStage = KS * kBK;
-  // kDown with gridDim.z = S > 1: this workgroup's reduction range (a
-  // multiple of kStage; the last range ends at a.k)
-  int k_begin = 0, k_end = a.k;
-  if (a.geo != kUp && gridDim.z > 1) {
-    const int len = (a.k / static_cast<int>(gridDim.z) + kStage - 1) / kStage * kStage;
-    k_begin = static_cast<int>(blockIdx.z) * len;
-    k_end = min(a.k, k_begin + len);
+  // kDown in a.ranges > 1 ranges (each a multiple of kStage; the last ends at
+  // a.k): all of them, or with gridDim.z = a.ranges this workgroup's
+  int k_begin = 0, k_end = a.k, range_len = a.k;
+  if (a.geo != kUp && a.ranges > 1) {
+    range_len = (a.k / a.ranges + kStage - 1) / kStage * kStage;
+    if (gridDim.z > 1) {
+      k_begin = static_cast<int>(blockIdx.z) * range_len;
+      k_end = min(a.k, k_begin + range_len);
+    }
   }
+  int range_end = k_begin + range_len;
   uint4 va[KS], vb[KS];
 #pragma unroll
   for (int q = 0; q < KS; ++q) {
@@ -204,7 +213,19 @@ __global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
         acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, acc[j], 0, 0, 0);
       }
     }
+    if (k0 + kStage == range_end && range_end < k_end) {  // the next range starts from zero
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        tot[j] = k0 + kStage == range_len ? acc[j] : tot[j] + acc[j];
+        acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
+      range_end += range_len;
+    }
     __syncthreads();
+  }
+  if (k_end > k_begin + range_len) {  // several ranges, added in order
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[j] = tot[j] + acc[j];
   }
 
   // epilogue: bias, skip, ReLU, store; with gridDim.z = S > 1 (kDown only)
@@ -290,14 +311,16 @@ __device__ __forceinline__ void barrier_lds() {
 // a barrier left the waves waiting for loads 54-74 % of their cycles; with
 // the loads ahead the LDS reads of the fragments are next (two waves side by
 // side read 4 fragments for 4 matrix instructions, four in a column 5).
-// 32^3 64 -> 64: 30 -> BRICK32 us, 16^3 128 -> 128 and 8^3 256 -> 256 (with
-// their split reductions) 19 -> BRICK16 and 17 -> BRICK8 us.
+// 32^3 64 -> 64: 30 -> 20 us (eight images in a launch: 17 us each), 16^3
+// 128 -> 128 and 8^3 256 -> 256 17 and 15 us (eight: 8 and 4 us each).
 // Layouts as in the resident kernel: brick voxel v at v * 64 bytes, its
 // 16-byte chunk j in slot j ^ (y & 3); weight row n at n * 64 bytes, chunk j
 // in slot j ^ ((n >> 2) & 3).
-// With gridDim.z = S > 1 the chunks are split into S equal ranges, one per
-// grid z index, and each workgroup stores its raw sums to the workspace
-// part[z][out voxel][cout] for split_reduce_kernel to finish.
+// The chunks are reduced in a.ranges equal ranges whose sums are added in
+// order.  With gridDim.z = a.ranges > 1 each grid z index takes one of them
+// and stores its raw sums to the workspace part[z][out voxel][cout] for
+// split_reduce_kernel to finish; with gridDim.z == 1 a workgroup takes all.
+// Tiles of a.batch images follow one another along the grid.
 template <int NB, int MZ>
 struct Brick {
   static constexpr int kBZ = 4 * MZ + 2;
@@ -314,9 +337,9 @@ struct Brick {
 
 // Loader wave LW (0 or 1) of a workgroup: every other wave load.
 template <int NB, int MZ, int LW>
-__device__ __forceinline__ void brick_loader(const ConvArgs& a, char* s_br, char* s_w, int lane,
-                                             int bx, int by, int bz, int n0, int c_begin,
-                                             int nchunks) {
+__device__ __forceinline__ void brick_loader(const ConvArgs& a, const uint16_t* x, char* s_br,
+                                             char* s_w, int lane, int bx, int by, int bz, int n0,
+                                             int c_begin, int nchunks) {
   using K = Brick<NB, MZ>;
   constexpr int kB = (K::kBrickLoads + 1 - LW) / 2;  // this wave's loads of a brick
   constexpr int kW = (K::kStageLoads + 1 - LW) / 2;  // and of a stage
@@ -332,7 +355,7 @@ __device__ __forceinline__ void brick_loader(const ConvArgs& a, char* s_br, char
     const bool in = p < K::kPieces && gx >= 0 && gy >= 0 && gz >= 0 && gx < a.in_w &&
                     gy < a.in_h && gz < a.in_d;
     const int j = (p & 3) ^ (vy & 3);
-    src[k] = in ? a.x + ((static_cast<int64_t>(gz) * a.in_h + gy) * a.in_w + gx) * a.cin +
+    src[k] = in ? x + ((static_cast<int64_t>(gz) * a.in_h + gy) * a.in_w + gx) * a.cin +
                       c_begin + j * 8
                 : zero + ((blockIdx.x * 192 + k * 64 + lane) & (kZeroChunks - 1)) * 8;
     inside |= in ? 1u << k : 0u;
@@ -392,7 +415,8 @@ __global__ void __launch_bounds__(384) conv3_brick_kernel(ConvArgs a) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tx_n = (a.w + 3) >> 2, ty_n = (a.h + 3) >> 2;
-  const int tile = blockIdx.x;
+  const int ntile = tx_n * ty_n * ((a.d + 4 * MZ - 1) / (4 * MZ));
+  const int img = blockIdx.x / ntile, tile = blockIdx.x - img * ntile;
   const int bx = (tile % tx_n) * 4;
   const int by = ((tile / tx_n) % ty_n) * 4;
   const int bz = (tile / (tx_n * ty_n)) * (4 * MZ);
@@ -400,12 +424,13 @@ __global__ void __launch_bounds__(384) conv3_brick_kernel(ConvArgs a) {
   const int split_len = a.cin / static_cast<int>(gridDim.z);  // a multiple of kBK
   const int c_begin = static_cast<int>(blockIdx.z) * split_len;
   const int nchunks = split_len / kBK;
+  const uint16_t* x_img = a.x + static_cast<int64_t>(img) * a.in_d * a.in_h * a.in_w * a.cin;
   if (wave == 4) {
-    brick_loader<NB, MZ, 0>(a, s_br, s_w, lane, bx, by, bz, n0, c_begin, nchunks);
+    brick_loader<NB, MZ, 0>(a, x_img, s_br, s_w, lane, bx, by, bz, n0, c_begin, nchunks);
     return;
   }
   if (wave == 5) {
-    brick_loader<NB, MZ, 1>(a, s_br, s_w, lane, bx, by, bz, n0, c_begin, nchunks);
+    brick_loader<NB, MZ, 1>(a, x_img, s_br, s_w, lane, bx, by, bz, n0, c_begin, nchunks);
     return;
   }
 
@@ -415,14 +440,27 @@ __global__ void __launch_bounds__(384) conv3_brick_kernel(ConvArgs a) {
   const int kq = lane >> 4;           // this lane's 16-byte chunk of the 32 channels
   const int z0 = wave / K::kWN * K::kSW;          // the wave's first slice
   const int cb = wave % K::kWN * K::kCW;          // and 16-channel block
-  floatx4 acc[K::kSW][K::kCW];
+  // the current range's sums, those of the ranges before it
+  floatx4 acc[K::kSW][K::kCW], tot[K::kSW][K::kCW];
 #pragma unroll
   for (int q = 0; q < K::kSW; ++q)
 #pragma unroll
-    for (int c = 0; c < K::kCW; ++c) acc[q][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < K::kCW; ++c) acc[q][c] = tot[q][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int range_chunks = gridDim.z > 1 ? nchunks : nchunks / a.ranges;
 
-  int s = 0;
+  int s = 0, range_left = range_chunks;
   for (int chunk = 0; chunk < nchunks; ++chunk) {
+    if (range_left == 0) {  // the next range starts from zero
+#pragma unroll
+      for (int q = 0; q < K::kSW; ++q)
+#pragma unroll
+        for (int c = 0; c < K::kCW; ++c) {
+          tot[q][c] = chunk == range_chunks ? acc[q][c] : tot[q][c] + acc[q][c];
+          acc[q][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+      range_left = range_chunks;
+    }
+    --range_left;
     const char* br = s_br + (chunk & 1) * K::kBrickBytes;
     for (int row = 0; row < 9; ++row, ++s) {  // taps 3 row .. 3 row + 2
       barrier_lds();  // stage s (and the chunk's brick) has landed
@@ -454,9 +492,15 @@ __global__ void __launch_bounds__(384) conv3_brick_kernel(ConvArgs a) {
   }
 
   // epilogue: rows 4 (lane >> 4) + e of each of the wave's slices
+  if (range_chunks < nchunks) {  // several ranges, added in order
+#pragma unroll
+    for (int q = 0; q < K::kSW; ++q)
+#pragma unroll
+      for (int c = 0; c < K::kCW; ++c) acc[q][c] = tot[q][c] + acc[q][c];
+  }
   const bool split = gridDim.z > 1;
-  float* part = split ? a.part + static_cast<int64_t>(blockIdx.z) * a.d * a.h * a.w * a.cout
-                      : nullptr;
+  const int64_t vox = static_cast<int64_t>(a.d) * a.h * a.w, o_img = img * vox;
+  float* part = split ? a.part + static_cast<int64_t>(blockIdx.z) * a.batch * vox * a.cout : nullptr;
 #pragma unroll
   for (int q = 0; q < K::kSW; ++q)
 #pragma unroll
@@ -469,7 +513,7 @@ __global__ void __launch_bounds__(384) conv3_brick_kernel(ConvArgs a) {
         const int rr = (lane >> 4) * 4 + e;
         const int x = bx + (rr & 3), y = by + (rr >> 2), z = bz + z0 + q;
         if (x >= a.w || y >= a.h || z >= a.d) continue;
-        const int64_t o = (static_cast<int64_t>(z) * a.h + y) * a.w + x;
+        const int64_t o = o_img + (static_cast<int64_t>(z) * a.h + y) * a.w + x;
         if (split) {
           part[o * a.cout + n] = acc[q][c][e];
           continue;
@@ -490,7 +534,7 @@ __global__ void __launch_bounds__(384) conv3_brick_kernel(ConvArgs a) {
 // the reduction is one chunk of 32 channels, so a workgroup's weights (27
 // taps x 16 NB output channels) fit in LDS and stay there while the
 // workgroup walks its columns of tiles (columns blockIdx.x, blockIdx.x +
-// gridDim.x, ... of 4 x 4 x 8-voxel tiles stacked along z).  Waves 0-3
+// gridDim.x, ... of all images, each of 4 x 4 x 8-voxel tiles stacked along z).  Waves 0-3
 // compute (wave w: z-slices 2w, 2w + 1 of the tile, NB 16-column MFMA blocks
 // each) and leave each tile's outputs in LDS; wave 4 streams the input
 // planes of the column (6 x 6 voxels of 32 channels, z = -1 .. 8 per tile
@@ -567,7 +611,9 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int tx_n = (a.w + 3) >> 2, ty_n = (a.h + 3) >> 2, tz_n = (a.d + 7) >> 3;
-  const int ncol = tx_n * ty_n;
+  const int ncol = tx_n * ty_n;  // columns of an image
+  const int64_t in_vox = static_cast<int64_t>(a.in_d) * a.in_h * a.in_w;
+  const int64_t out_vox = static_cast<int64_t>(a.d) * a.h * a.w;
   const int n0 = blockIdx.y * NC;
   const int ncols = min(NC, a.cout - n0);
 
@@ -605,9 +651,8 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
     pos[k] = c < 144 ? (x | y << 4) : -1;
   }
   const uint16_t* zero = reinterpret_cast<const uint16_t*>(g_zero16);
-  auto load_plane = [&](int bx, int by, int z) {
-    const int64_t base = (static_cast<int64_t>(z) * a.in_h + by) * a.in_w * 32 +
-                         static_cast<int64_t>(bx) * 32;
+  auto load_plane = [&](int64_t v0, int bx, int by, int z) {
+    const int64_t base = (v0 + (static_cast<int64_t>(z) * a.in_h + by) * a.in_w + bx) * 32;
     const bool zin = z >= 0 && z < a.in_d;
     const bool xyin = bx >= 1 && by >= 1 && bx + 5 <= a.in_w && by + 5 <= a.in_h;
     char* slot = reinterpret_cast<char*>(sRing) + ((z + 1) % kRing) * kResPlane;
@@ -635,22 +680,22 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
   constexpr int kGP = NC * 2 / 16;  // 16-byte BF16 pieces per voxel
   float gsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   uint4 gm[kGP];
-  auto piece = [&](int bx, int by, int bz, int mm, int64_t& e0) {
+  auto piece = [&](int64_t v0, int bx, int by, int bz, int mm, int64_t& e0) {
     const int i = s0 + 128 * mm;
     const int vl = i / kGP, k = i % kGP;
     const int x = bx + (vl & 3), y = by + ((vl >> 2) & 3), z = bz + (vl >> 4);
-    e0 = ((static_cast<int64_t>(z) * a.h + y) * a.w + x) * a.cout + n0 + k * 8;
+    e0 = (v0 + (static_cast<int64_t>(z) * a.h + y) * a.w + x) * a.cout + n0 + k * 8;
     return x < a.w && y < a.h && z < a.d;
   };
-  auto load_mask = [&](int bx, int by, int bz) {
+  auto load_mask = [&](int64_t v0, int bx, int by, int bz) {
 #pragma unroll
     for (int mm = 0; mm < kGP; ++mm) {
       int64_t e0;
-      gm[mm] = piece(bx, by, bz, mm, e0) ? *reinterpret_cast<const uint4*>(a.gmask + e0)
+      gm[mm] = piece(v0, bx, by, bz, mm, e0) ? *reinterpret_cast<const uint4*>(a.gmask + e0)
                                           : make_uint4(0u, 0u, 0u, 0u);
     }
   };
-  auto store_out = [&](int bx, int by, int bz, int b) {
+  auto store_out = [&](int64_t v0, int bx, int by, int bz, int b) {
     const char* src = reinterpret_cast<const char*>(sOut[b]);
     if constexpr (kGrad) {
       // 16-byte BF16 pieces of 8 channels (NC == cout): a lane always has
@@ -672,7 +717,7 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
 #pragma unroll
       for (int mm = 0; mm < kGP; ++mm) {
         int64_t e0;
-        if (!piece(bx, by, bz, mm, e0)) continue;
+        if (!piece(v0, bx, by, bz, mm, e0)) continue;
         const float* f = fv[mm];
         const uint16_t* mh = reinterpret_cast<const uint16_t*>(&gm[mm]);
         uint4 o;
@@ -707,7 +752,7 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
         const int vl = i / per, k = i % per;
         const int x = bx + (vl & 3), y = by + ((vl >> 2) & 3), z = bz + (vl >> 4);
         if (x >= a.w || y >= a.h || z >= a.d) continue;
-        const int64_t o = (static_cast<int64_t>(z) * a.h + y) * a.w + x;
+        const int64_t o = v0 + (static_cast<int64_t>(z) * a.h + y) * a.w + x;
         *reinterpret_cast<uint4*>(static_cast<char*>(a.y) + (o * a.cout + n0) * ES + k * 16) =
             v[mm];
       }
@@ -717,7 +762,7 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
         const int vl = i / per, k = i % per;
         const int x = bx + (vl & 3), y = by + ((vl >> 2) & 3), z = bz + (vl >> 4);
         if (x >= a.w || y >= a.h || z >= a.d) continue;
-        const int64_t o = (static_cast<int64_t>(z) * a.h + y) * a.w + x;
+        const int64_t o = v0 + (static_cast<int64_t>(z) * a.h + y) * a.w + x;
         *reinterpret_cast<uint4*>(static_cast<char*>(a.y) + (o * a.cout + n0) * ES + k * 16) =
             *reinterpret_cast<const uint4*>(src + sout_off<NB, ES>(vl, k * 16));
       }
@@ -726,7 +771,7 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
         const int vl = i / ncols, n = i % ncols;
         const int x = bx + (vl & 3), y = by + ((vl >> 2) & 3), z = bz + (vl >> 4);
         if (x >= a.w || y >= a.h || z >= a.d) continue;
-        const int64_t o = (static_cast<int64_t>(z) * a.h + y) * a.w + x;
+        const int64_t o = v0 + (static_cast<int64_t>(z) * a.h + y) * a.w + x;
         if constexpr (kF32)
           static_cast<float*>(a.y)[o * a.cout + n0 + n] =
               *reinterpret_cast<const float*>(src + sout_off<NB, ES>(vl, n * 4));
@@ -742,12 +787,14 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
   // planes have, one per tile, and one after the column's last outputs.
   barrier_lds();
   if (wave == 4) {
-    for (int col = blockIdx.x; col < ncol; col += gridDim.x) {
+    for (int gc = blockIdx.x; gc < ncol * a.batch; gc += gridDim.x) {
+      const int img = gc / ncol, col = gc - img * ncol;
       const int bx = (col % tx_n) * 4, by = (col / tx_n) * 4;
+      const int64_t v0 = img * in_vox;
       // planes -1 .. 8 min(tz_n, A): the first A tiles; wait for tile 0's
       // (all loads but those of the tiles after it, 24 per tile)
       const int zend = 8 * min(tz_n, A);
-      for (int z = -1; z <= zend; ++z) load_plane(bx, by, z);
+      for (int z = -1; z <= zend; ++z) load_plane(v0, bx, by, z);
       const int first = min(tz_n, A) - 1;
       if (first >= 2)
         wait_vm<48>();
@@ -762,7 +809,7 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
         // all loads but those of the tiles after it (24 per tile)
         const int last = min(k + A, tz_n - 1);  // the newest tile loaded
         if (k + A < tz_n)
-          for (int z = 8 * (k + A) + 1; z <= 8 * (k + A) + 8; ++z) load_plane(bx, by, z);
+          for (int z = 8 * (k + A) + 1; z <= 8 * (k + A) + 8; ++z) load_plane(v0, bx, by, z);
         const int pending = last - (k + 1);  // tiles whose loads may stay in flight
         if (pending >= 2)
           wait_vm<48>();
@@ -775,16 +822,18 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
       barrier_lds();
     }
   } else if (wave >= 5) {
-    for (int col = blockIdx.x; col < ncol; col += gridDim.x) {
+    for (int gc = blockIdx.x; gc < ncol * a.batch; gc += gridDim.x) {
+      const int img = gc / ncol, col = gc - img * ncol;
       const int bx = (col % tx_n) * 4, by = (col / tx_n) * 4;
+      const int64_t v0 = img * out_vox;
       barrier_lds();
       for (int k = 0; k < tz_n; ++k) {
-        if (k > 0) store_out(bx, by, 8 * (k - 1), (k - 1) & 1);
-        if constexpr (kGrad) load_mask(bx, by, 8 * k);  // for the store of tile k
+        if (k > 0) store_out(v0, bx, by, 8 * (k - 1), (k - 1) & 1);
+        if constexpr (kGrad) load_mask(v0, bx, by, 8 * k);  // for the store of tile k
         barrier_lds();
       }
       // the column's last tile; the ring and the output tiles are reused next
-      store_out(bx, by, 8 * (tz_n - 1), (tz_n - 1) & 1);
+      store_out(v0, bx, by, 8 * (tz_n - 1), (tz_n - 1) & 1);
       barrier_lds();
     }
   } else {
@@ -804,7 +853,7 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
 #pragma unroll
       for (int j = 0; j < NB; ++j)
         breg[tt][j] = *reinterpret_cast<const bf16x8*>(&sW[tt][16 * j + r][kq ^ ((r >> 2) & 3)]);
-    for (int col = blockIdx.x; col < ncol; col += gridDim.x) {
+    for (int gc = blockIdx.x; gc < ncol * a.batch; gc += gridDim.x) {
       barrier_lds();
       for (int k = 0; k < tz_n; ++k) {
         floatx4 acc[2][NB];
@@ -921,18 +970,21 @@ __global__ void __launch_bounds__(256) conv3_scalar_kernel(ConvArgs a) {
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int tx_n = (a.w + 3) >> 2, ty_n = (a.h + 3) >> 2;
-  const int tile = blockIdx.x;
+  const int ntile = tx_n * ty_n * ((a.d + 3) >> 2);
+  const int img = blockIdx.x / ntile, tile = blockIdx.x - img * ntile;
   const int bx = (tile % tx_n) * 4;
   const int by = ((tile / tx_n) % ty_n) * 4;
   const int bz = (tile / (tx_n * ty_n)) * 4;
   const int n0 = blockIdx.y * 16 * NB;
   const int sgn = a.geo == kConv3 ? 1 : -1;
   const int r = lane & 15, g = lane >> 4;
+  const uint16_t* x_img = a.x + static_cast<int64_t>(img) * a.in_d * a.in_h * a.in_w;
+  const int64_t o_img = static_cast<int64_t>(img) * a.d * a.h * a.w;
   for (int v = tid; v < 216; v += 256) {
     const int gx = bx + v % 6 - 1, gy = by + (v / 6) % 6 - 1, gz = bz + v / 36 - 1;
     uint16_t val = 0;
     if (gx >= 0 && gy >= 0 && gz >= 0 && gx < a.in_w && gy < a.in_h && gz < a.in_d)
-      val = a.x[(static_cast<int64_t>(gz) * a.in_h + gy) * a.in_w + gx];
+      val = x_img[(static_cast<int64_t>(gz) * a.in_h + gy) * a.in_w + gx];
     sB[v] = val;
   }
   bf16x8 bf[NB];
@@ -968,7 +1020,7 @@ __global__ void __launch_bounds__(256) conv3_scalar_kernel(ConvArgs a) {
       const int rr = 4 * g + e;
       const int x = bx + (rr & 3), y = by + (rr >> 2), z = bz + wave;
       if (x >= a.w || y >= a.h || z >= a.d) continue;
-      const int64_t o = (static_cast<int64_t>(z) * a.h + y) * a.w + x;
+      const int64_t o = o_img + (static_cast<int64_t>(z) * a.h + y) * a.w + x;
       float v = acc[j][e] + bias;
       if (a.skip) v += from_bf16(a.skip[o * a.cout + n]);
       if (a.relu) v = fmaxf(v, 0.f);
@@ -983,7 +1035,7 @@ __global__ void __launch_bounds__(256) conv3_scalar_kernel(ConvArgs a) {
 // Finish a split product: y[o][n] = [relu](sum over splits of part[s][o][n]
 // + bias[n] [+ skip[o][n]]), splits summed in order.
 __global__ void __launch_bounds__(256) split_reduce_kernel(ConvArgs a, int nsplit) {
-  const int64_t n_out = static_cast<int64_t>(a.d) * a.h * a.w * a.cout;
+  const int64_t n_out = static_cast<int64_t>(a.batch) * a.d * a.h * a.w * a.cout;
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n_out;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     const int n = static_cast<int>(i % a.cout);
@@ -1507,6 +1559,15 @@ __global__ void to_log_kernel(const float* phi, int64_t n, float eps, float shif
   }
 }
 
+// the input voxel of output voxel (x, y, z) under the symmetry op (see mirror_xy_kernel)
+__device__ __forceinline__ int64_t mirror_source(int x, int y, int64_t z, int nx, int ny, int op) {
+  int sx = (op & 4) ? y : x;
+  int sy = (op & 4) ? x : y;
+  if (op & 1) sx = nx - 1 - sx;
+  if (op & 2) sy = ny - 1 - sy;
+  return (z * ny + sy) * nx + sx;
+}
+
 // out[z][y][x] = in[z][y'][x'], (x', y') = (op & 4 ? (y, x) : (x, y)) with
 // x' mirrored when op & 1 and y' when op & 2: the eight symmetries of a
 // square cross-section (the swap needs nx == ny)
@@ -1517,39 +1578,61 @@ __global__ void mirror_xy_kernel(const float* in, float* out, int nx, int ny, in
     const int64_t r = i / nx;
     const int y = static_cast<int>(r % ny);
     const int64_t z = r / ny;
-    int sx = (op & 4) ? y : x;
-    int sy = (op & 4) ? x : y;
-    if (op & 1) sx = nx - 1 - sx;
-    if (op & 2) sy = ny - 1 - sy;
-    out[i] = in[(z * ny + sy) * nx + sx];
+    out[i] = in[mirror_source(x, y, z, nx, ny, op)];
   }
 }
 
-// acc[i] (= when first, else +=) in[src(i)]: the gather of mirror_xy_kernel
-// for the symmetry op, accumulated
-__global__ void mirror_acc_kernel(const float* in, float* acc, int nx, int ny, int64_t n, int op,
-                                  int first) {
+// The network's inputs for the symmetries op0 .. op0 + nop - 1, one image
+// each: to_log_kernel of mirror_xy_kernel's images.  u (FP32): that of the
+// volume itself.
+__global__ void __launch_bounds__(256) sym_inputs_kernel(const float* phi, int nx, int ny,
+                                                         int64_t n, int op0, float eps, float shift,
+                                                         float inv_scale, float* u,
+                                                         uint16_t* u16) {
+  const int op = op0 + blockIdx.y;
+  uint16_t* out = u16 + blockIdx.y * n;
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     const int x = static_cast<int>(i % nx);
     const int64_t r = i / nx;
     const int y = static_cast<int>(r % ny);
-    const int64_t z = r / ny;
-    int sx = (op & 4) ? y : x;
-    int sy = (op & 4) ? x : y;
-    if (op & 1) sx = nx - 1 - sx;
-    if (op & 2) sy = ny - 1 - sy;
-    const float v = in[(z * ny + sy) * nx + sx];
-    acc[i] = first ? v : acc[i] + v;
+    const float v = (logf(fmaxf(phi[mirror_source(x, y, r / ny, nx, ny, op)], eps)) - shift) *
+                    inv_scale;
+    out[i] = to_bf16(v);
+    if (op == 0) u[i] = v;
   }
 }
 
-// the mean of nsym outputs in u space and its fluence
-__global__ void sym_finish_kernel(const float* acc, int64_t n, float inv_nsym, float scale,
-                                  float shift, float* out_u, float* phi) {
+// The outputs r + u of the symmetries op0 .. op0 + nop - 1, mapped back to
+// the volume and added in order (an image's u, mapped back, is the volume's);
+// acc holds the sum of the symmetries before op0, and receives the sum unless
+// `last`: then the mean in u space and its fluence are written.
+__global__ void __launch_bounds__(256) sym_outputs_kernel(const float* r, const float* u, int nx,
+                                                          int ny, int64_t n, int op0, int nop,
+                                                          float* acc, int last, float inv_nsym,
+                                                          float scale, float shift, float* out_u,
+                                                          float* phi) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const float v = acc[i] * inv_nsym;
+    const int x = static_cast<int>(i % nx);
+    const int64_t t = i / nx;
+    const int y = static_cast<int>(t % ny);
+    const int64_t z = t / ny;
+    const float ui = u[i];
+    float sum = op0 > 0 ? acc[i] : 0.f;
+    for (int k = 0; k < nop; ++k) {
+      // the inverse of op: a flip is its own inverse; with the swap, the
+      // flips of x and y exchange
+      const int op = op0 + k;
+      const int inv = (op & 4) ? (4 | ((op & 1) << 1) | ((op & 2) >> 1)) : op;
+      const float v = r[k * n + mirror_source(x, y, z, nx, ny, inv)] + ui;
+      sum = op == 0 ? v : sum + v;
+    }
+    if (!last) {
+      acc[i] = sum;
+      continue;
+    }
+    const float v = sum * inv_nsym;
     if (out_u) out_u[i] = v;
     if (phi) phi[i] = expf(v * scale + shift);
   }
@@ -1825,9 +1908,9 @@ bool uses_resident(const ConvArgs& a) {
          brick_tiles(a, 2) >= kResidentTiles;
 }
 
-// 4 x 4 columns of the grid, each a workgroup's unit of work
+// 4 x 4 columns of all images, each a workgroup's unit of work
 int64_t resident_columns(const ConvArgs& a) {
-  return static_cast<int64_t>((a.w + 3) / 4) * ((a.h + 3) / 4);
+  return static_cast<int64_t>(a.batch) * ((a.w + 3) / 4) * ((a.h + 3) / 4);
 }
 
 // compute units of the current device (queried once)
@@ -1843,8 +1926,10 @@ int device_cus() {
   return cus;
 }
 
+// tiles of all images
 int64_t brick_tiles(const ConvArgs& a, int mz) {
-  return static_cast<int64_t>((a.w + 3) / 4) * ((a.h + 3) / 4) * ((a.d + 4 * mz - 1) / (4 * mz));
+  return static_cast<int64_t>(a.batch) * ((a.w + 3) / 4) * ((a.h + 3) / 4) *
+         ((a.d + 4 * mz - 1) / (4 * mz));
 }
 
 int64_t brick_ngroups(const ConvArgs& a) {
@@ -1858,18 +1943,46 @@ int brick_mz(const ConvArgs& a) {
   return brick_tiles(a, 2) * brick_ngroups(a) >= kDeepTileGroups ? 2 : 1;
 }
 
-// splits of the brick kernel's input-channel chunks: for launches of fewer
-// than two workgroups per CU, enough to fill the chip, a divisor of the
-// chunk count, within `cap` floats (measured: on 8^3 and 16^3 grids the
-// split runs 6x and 1.8x faster; at 512 workgroups it gains nothing)
-int brick_splits(const ConvArgs& a, int64_t cap) {
+// Ranges of the brick kernel's input-channel chunks, whose sums are added in
+// order: chosen from one image, so that an image's results do not depend on
+// how many share the launch.  For products of fewer than two workgroups per
+// CU, enough ranges to fill the chip, a divisor of the chunk count.
+int brick_ranges(ConvArgs a) {
+  a.batch = 1;
   const int64_t groups = brick_tiles(a, brick_mz(a)) * brick_ngroups(a);
   if (groups >= kSplitBelowGroups) return 1;
   const int chunks = a.cin / kBK;
   int sp = static_cast<int>(std::min<int64_t>(chunks, (kSplitTargetGroups + groups - 1) / groups));
-  const int64_t per = static_cast<int64_t>(a.d) * a.h * a.w * a.cout;
-  while (sp > 1 && (chunks % sp != 0 || sp * per > cap)) --sp;
-  return sp < 1 ? 1 : sp;
+  while (sp > 1 && chunks % sp != 0) --sp;
+  return sp;
+}
+
+// the same for the generic kernel's reduction of kDown products (the other
+// geometries have one range), at least one stage of 128 each
+int generic_ranges(ConvArgs a) {
+  if (a.geo != kDown || a.cin % 8 != 0) return 1;
+  const int64_t M = static_cast<int64_t>(a.d) * a.h * a.w;
+  const int64_t groups = (M + kBM - 1) / kBM * ((a.cout + 16 * conv_nb(a) - 1) / (16 * conv_nb(a)));
+  if (groups >= kSplitBelowGroups) return 1;
+  return std::max(1, static_cast<int>(std::min<int64_t>(
+                         a.k / (4 * kBK), (kSplitTargetGroups + groups - 1) / groups)));
+}
+
+int64_t out_floats(const ConvArgs& a) {
+  return static_cast<int64_t>(a.batch) * a.d * a.h * a.w * a.cout;
+}
+
+// Whether the ranges go to workgroups of their own (and their sums through
+// the workspace): only where the launch has few workgroups without that.
+// Measured: 16^3 128 -> 128 (128 workgroups, 4 ranges) 15.1 + 4.6 us spread,
+// 17.0 not; 8^3 (32 workgroups, 8 ranges) 10.8 + 4.6 us spread, and the two
+// 256 -> 256 layers with the down layer before them 34 us longer if not; the
+// generic kernel with 128 workgroups (4 ranges) 7.0 + 4.6 us and 13.4.
+bool spread_ranges(const ConvArgs& a, int ranges) {
+  if (ranges <= 1) return false;
+  if (uses_brick(a)) return brick_tiles(a, brick_mz(a)) * brick_ngroups(a) < 128;
+  const int nc = 16 * conv_nb(a);
+  return (out_floats(a) / a.cout + kBM - 1) / kBM * ((a.cout + nc - 1) / nc) < 256;
 }
 
 }  // namespace
@@ -1884,32 +1997,13 @@ int conv_fold_rows(const ConvArgs& a) {
   return static_cast<int>(std::min<int64_t>(resident_columns(a), device_cus()));
 }
 
-// splits of the generic kernel's reduction for kDown products (the other
-// geometries are not split): for launches of fewer than two workgroups per
-// CU, enough to fill the chip, at least one stage of 128 per split, within
-// `cap` floats
-int generic_splits(const ConvArgs& a, int64_t cap) {
-  if (a.geo != kDown || a.cin % 8 != 0) return 1;
-  const int64_t M = static_cast<int64_t>(a.d) * a.h * a.w;
-  const int64_t groups = (M + kBM - 1) / kBM * ((a.cout + 16 * conv_nb(a) - 1) / (16 * conv_nb(a)));
-  if (groups >= kSplitBelowGroups) return 1;
-  int sp = static_cast<int>(std::min<int64_t>(a.k / (4 * kBK), (kSplitTargetGroups + groups - 1) / groups));
-  while (sp > 1 && sp * M * a.cout > cap) --sp;
-  return sp < 1 ? 1 : sp;
-}
-
 int64_t conv_workspace_floats(const ConvArgs& a) {
-  const int64_t per = static_cast<int64_t>(a.d) * a.h * a.w * a.cout;
-  if (!uses_brick(a)) {
-    const int sp = generic_splits(a, INT64_MAX);
-    return sp > 1 ? sp * per : 0;
-  }
-  const int sp = brick_splits(a, INT64_MAX);
-  return sp > 1 ? sp * per : 0;
+  const int ranges = uses_brick(a) ? brick_ranges(a) : generic_ranges(a);
+  return spread_ranges(a, ranges) ? ranges * out_floats(a) : 0;
 }
 
-hipError_t launch_conv(const ConvArgs& a, hipStream_t s) {
-  const int64_t M = static_cast<int64_t>(a.d) * a.h * a.w;
+hipError_t launch_conv(const ConvArgs& args, hipStream_t s) {
+  ConvArgs a = args;
   const int nb = conv_nb(a);
   if ((a.geo == kConv3 || a.geo == kConv3T) && a.cin == 1) {
     const dim3 grid(static_cast<unsigned>(brick_tiles(a, 1)),
@@ -1941,7 +2035,10 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t s) {
   }
   if (uses_brick(a)) {
     const int mz = brick_mz(a);
-    const int sp = a.part ? brick_splits(a, a.part_cap) : 1;
+    a.ranges = brick_ranges(a);
+    const int sp = spread_ranges(a, a.ranges) && a.part && a.part_cap >= a.ranges * out_floats(a)
+                       ? a.ranges
+                       : 1;
     const dim3 grid(static_cast<unsigned>(brick_tiles(a, mz)),
                     static_cast<unsigned>(brick_ngroups(a)), static_cast<unsigned>(sp));
 #define MCX_BRICK(NB)                                                  \
@@ -1951,10 +2048,14 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t s) {
     conv3_brick_kernel<NB, 1><<<grid, 384, 0, s>>>(a);
     if (nb == 4) { MCX_BRICK(4) } else if (nb == 2) { MCX_BRICK(2) } else { MCX_BRICK(1) }
 #undef MCX_BRICK
-    if (sp > 1) split_reduce_kernel<<<blocks_for(M * a.cout), 256, 0, s>>>(a, sp);
+    if (sp > 1) split_reduce_kernel<<<blocks_for(out_floats(a)), 256, 0, s>>>(a, sp);
     return hipGetLastError();
   }
-  const int sp = a.part ? generic_splits(a, a.part_cap) : 1;
+  a.ranges = generic_ranges(a);
+  const int sp = spread_ranges(a, a.ranges) && a.part && a.part_cap >= a.ranges * out_floats(a)
+                     ? a.ranges
+                     : 1;
+  const int64_t M = static_cast<int64_t>(a.batch) * a.d * a.h * a.w;
   const dim3 grid(static_cast<unsigned>((M + kBM - 1) / kBM),
                   static_cast<unsigned>((a.cout + 16 * nb - 1) / (16 * nb)),
                   a.geo == kUp ? 8 : static_cast<unsigned>(sp));
@@ -1969,7 +2070,7 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t s) {
     conv_kernel<NB, false, 1><<<grid, 256, 0, s>>>(a);
   if (nb == 4) { MCX_CONV(4) } else if (nb == 2) { MCX_CONV(2) } else { MCX_CONV(1) }
 #undef MCX_CONV
-  if (sp > 1) split_reduce_kernel<<<blocks_for(M * a.cout), 256, 0, s>>>(a, sp);
+  if (sp > 1) split_reduce_kernel<<<blocks_for(out_floats(a)), 256, 0, s>>>(a, sp);
   return hipGetLastError();
 }
 
@@ -2121,17 +2222,22 @@ hipError_t launch_mirror_xy(const float* in, float* out, int nx, int ny, int nz,
   return hipGetLastError();
 }
 
-hipError_t launch_mirror_acc(const float* in, float* acc, int nx, int ny, int nz, int op,
-                             bool first, hipStream_t s) {
+hipError_t launch_sym_inputs(const float* phi, int nx, int ny, int nz, int op0, int nop, float* u,
+                             uint16_t* u16, hipStream_t s) {
   const int64_t n = static_cast<int64_t>(nx) * ny * nz;
-  mirror_acc_kernel<<<blocks_for(n), 256, 0, s>>>(in, acc, nx, ny, n, op, first ? 1 : 0);
+  const dim3 grid(static_cast<unsigned>(blocks_for(n)), static_cast<unsigned>(nop), 1);
+  sym_inputs_kernel<<<grid, 256, 0, s>>>(phi, nx, ny, n, op0, kEps, kLogShift, 1.f / kLogScale, u,
+                                         u16);
   return hipGetLastError();
 }
 
-hipError_t launch_sym_finish(const float* acc, int64_t n, int nsym, float* out_u, float* phi,
-                             hipStream_t s) {
-  sym_finish_kernel<<<blocks_for(n), 256, 0, s>>>(acc, n, 1.f / static_cast<float>(nsym),
-                                                  kLogScale, kLogShift, out_u, phi);
+hipError_t launch_sym_outputs(const float* r, const float* u, int nx, int ny, int nz, int op0,
+                              int nop, int nsym, float* acc, float* out_u, float* phi,
+                              hipStream_t s) {
+  const int64_t n = static_cast<int64_t>(nx) * ny * nz;
+  sym_outputs_kernel<<<blocks_for(n), 256, 0, s>>>(
+      r, u, nx, ny, n, op0, nop, acc, op0 + nop == nsym, 1.f / static_cast<float>(nsym), kLogScale,
+      kLogShift, out_u, phi);
   return hipGetLastError();
 }
 

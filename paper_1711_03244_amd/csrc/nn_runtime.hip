@@ -59,6 +59,7 @@ struct Layer {
   uint16_t* fwd = nullptr;
   uint16_t* bwd = nullptr;
   uint16_t* act = nullptr;           // BF16 output [out voxel][cout] (null for the output layer)
+  uint16_t* acts = nullptr;          // the same of mcx_nn::batch images
   int skip_level = -1;               // conv3 whose output is a skip (level), or -1
   int up_level = -1;                 // up layer adding the skip of this level, or -1
 };
@@ -241,6 +242,9 @@ struct mcx_nn {
   std::vector<char> fold;
   bool fuse = true;                // use the folds
   double* norm_partial = nullptr; // per-block sums of squares of the gradients
+  int batch = 1;                  // images that share a launch (alloc_images):
+  uint16_t* u16s = nullptr;       // their inputs u16
+  float* rs = nullptr;            // and outputs r
   float* part = nullptr;          // split-reduction workspace of the convolutions
   int64_t part_cap = 0;           // its size in floats
   std::vector<void*> owned;
@@ -254,6 +258,40 @@ mcx_status nn_alloc(mcx_nn* nn, T** p, size_t count) {
   NN_HIP(hipMalloc(&q, std::max<size_t>(count, 1) * sizeof(T)));
   nn->owned.push_back(q);
   *p = static_cast<T*>(q);
+  return MCX_OK;
+}
+
+// Activations, inputs and outputs of images that share each layer's launch:
+// as many of the eight symmetries as fit in kBatchBytes (all eight of a 64^3
+// volume with 32 to 256 channels take 0.7 GB) and in an eighth of the memory
+// that is free.
+// They are apart from those of one image, which training and plain inference
+// use, so that these stay close together.
+constexpr int64_t kBatchBytes = int64_t(2) << 30;
+mcx_status alloc_images(mcx_nn* nn) {
+  const int64_t n0 = nn->g0.vox();
+  int64_t bytes = n0 * (sizeof(uint16_t) + sizeof(float));
+  for (const Layer& L : nn->layers) bytes += L.out.vox() * L.cout * sizeof(uint16_t);
+  nn->batch = 8;
+  size_t free = 0, total = 0;
+  if (hipMemGetInfo(&free, &total) != hipSuccess) free = 0;
+  const int64_t room = std::min<int64_t>(kBatchBytes, static_cast<int64_t>(free / 8));
+  while (nn->batch > 1 && nn->batch * bytes > room) nn->batch /= 2;
+  if (nn->batch == 1) return MCX_OK;
+  const size_t kept = nn->owned.size();
+  auto alloc = [&]() -> mcx_status {
+    for (size_t i = 0; i + 1 < nn->layers.size(); ++i) {
+      Layer& L = nn->layers[i];
+      NN_TRY(nn_alloc(nn, &L.acts, static_cast<size_t>(nn->batch * L.out.vox() * L.cout)));
+    }
+    NN_TRY(nn_alloc(nn, &nn->u16s, static_cast<size_t>(nn->batch * n0)));
+    return nn_alloc(nn, &nn->rs, static_cast<size_t>(nn->batch * n0));
+  };
+  if (alloc() != MCX_OK) {  // no room: one image at a time
+    (void)hipGetLastError();
+    for (; nn->owned.size() > kept; nn->owned.pop_back()) (void)hipFree(nn->owned.back());
+    nn->batch = 1;
+  }
   return MCX_OK;
 }
 
@@ -281,26 +319,36 @@ const uint16_t* layer_input(const mcx_nn* nn, size_t i) {
   return i == 0 ? nn->u16 : nn->layers[i - 1].act;
 }
 
-mcx_status run_forward(mcx_nn* nn, const float* phi_in, hipStream_t s) {
-  NN_TRY(pack_all(nn, s));
-  const int64_t n0 = nn->g0.vox();
-  NN_HIP(launch_to_log(phi_in, n0, nn->u, nn->u16, s));
+// the layers: r from u16, or for several images rs from u16s
+mcx_status run_layers(mcx_nn* nn, int images, hipStream_t s) {
+  const bool many = images > 1;
   const size_t last = nn->layers.size() - 1;
+  const uint16_t* x = many ? nn->u16s : nn->u16;
   for (size_t i = 0; i <= last; ++i) {
     const Layer& L = nn->layers[i];
     const uint16_t* skip = nullptr;
     if (L.kind == MCX_NN_UP) {
       for (const Layer& S : nn->layers)
-        if (S.skip_level == L.up_level) skip = S.act;
+        if (S.skip_level == L.up_level) skip = many ? S.acts : S.act;
     }
     const bool out = i == last;
-    ConvArgs a = forward_args(L, layer_input(nn, i), nn->params + L.boff, skip, !out, out,
-                              out ? static_cast<void*>(nn->r) : static_cast<void*>(L.act));
+    uint16_t* y = many ? L.acts : L.act;
+    ConvArgs a = forward_args(L, x, nn->params + L.boff, skip, !out, out,
+                              out ? static_cast<void*>(many ? nn->rs : nn->r)
+                                  : static_cast<void*>(y));
     a.part = nn->part;
     a.part_cap = nn->part_cap;
+    a.batch = images;
     NN_HIP(launch_conv(a, s));
+    x = y;
   }
   return MCX_OK;
+}
+
+mcx_status run_forward(mcx_nn* nn, const float* phi_in, hipStream_t s) {
+  NN_TRY(pack_all(nn, s));
+  NN_HIP(launch_to_log(phi_in, nn->g0.vox(), nn->u, nn->u16, s));
+  return run_layers(nn, 1, s);
 }
 
 // the gradient of layer i's output skip connection, or null
@@ -497,10 +545,11 @@ mcx_status mcx_nn_create(const int32_t* channels, int32_t nlevels, int32_t nx, i
     }
     NN_TRY(nn_alloc(nn, &nn->norm_partial, static_cast<size_t>(kNormBlocks)));
     NN_TRY(nn_alloc(nn, &nn->phimax, 1));
+    NN_TRY(alloc_images(nn));
     for (const Layer& Ly : nn->layers) {
-      nn->part_cap = std::max(nn->part_cap, conv_workspace_floats(
-                                                forward_args(Ly, nullptr, nullptr, nullptr, false,
-                                                             false, nullptr)));
+      ConvArgs fa = forward_args(Ly, nullptr, nullptr, nullptr, false, false, nullptr);
+      for (fa.batch = 1; fa.batch <= nn->batch; fa.batch *= 2)
+        nn->part_cap = std::max(nn->part_cap, conv_workspace_floats(fa));
       nn->part_cap = std::max(nn->part_cap, conv_workspace_floats(dgrad_args(Ly, nullptr, nullptr)));
       nn->part_cap =
           std::max(nn->part_cap, wgrad_workspace_floats(wgrad_args(Ly, nullptr, nullptr, nullptr)));
@@ -595,22 +644,17 @@ mcx_status mcx_nn_forward_sym(mcx_nn* nn, const float* phi_in, float* phi_out, f
   if (nsym == 1) return mcx_nn_forward(nn, phi_in, phi_out, u_out, stream);
   NN_HIP(hipSetDevice(nn->device));
   hipStream_t s = pick(nn, stream);
-  // the loss buffers are idle outside mcx_nn_loss_grad: tgt_u holds the
-  // transformed input, gout the sum of the outputs mapped back
-  for (int op = 0; op < nsym; ++op) {
-    const float* x = phi_in;
-    if (op > 0) {
-      NN_HIP(launch_mirror_xy(phi_in, nn->tgt_u, g.w, g.h, g.d, op, s));
-      x = nn->tgt_u;
-    }
-    NN_TRY(run_forward(nn, x, s));
-    NN_HIP(launch_from_log(nn->r, nn->u, g.vox(), nn->out_u, nullptr, s));
-    // the inverse of op: a flip is its own inverse; with the swap, the flips
-    // of x and y exchange
-    const int inv = (op & 4) ? (4 | ((op & 1) << 1) | ((op & 2) >> 1)) : op;
-    NN_HIP(launch_mirror_acc(nn->out_u, nn->gout, g.w, g.h, g.d, inv, op == 0, s));
+  NN_TRY(pack_all(nn, s));
+  // groups of symmetries share each layer's launch; gout, idle outside
+  // mcx_nn_loss_grad, holds the sum of the groups' outputs mapped back
+  const int group = std::min<int>(nsym, nn->batch);
+  for (int op = 0; op < nsym; op += group) {
+    NN_HIP(launch_sym_inputs(phi_in, g.w, g.h, g.d, op, group, nn->u,
+                             group > 1 ? nn->u16s : nn->u16, s));
+    NN_TRY(run_layers(nn, group, s));
+    NN_HIP(launch_sym_outputs(group > 1 ? nn->rs : nn->r, nn->u, g.w, g.h, g.d, op, group, nsym,
+                              nn->gout, u_out, phi_out, s));
   }
-  NN_HIP(launch_sym_finish(nn->gout, g.vox(), nsym, u_out, phi_out, s));
   return MCX_OK;
 }
 

@@ -120,3 +120,37 @@ def test_scratch_is_shared_between_threads():
     for th in threads:
         th.join()
     assert not bad
+
+
+@pytest.mark.parametrize("channels,shape,nsym", [
+    ((8, 16), (6, 8, 8), 8),            # the generic kernel's gathers of several images
+    ((16, 128), (16, 16, 16), 8),       # ranges spread over workgroups for one image only
+    ((32, 64), (32, 32, 32), 4),        # resident weights for several images only
+    ((5, 33, 64), (12, 20, 20), 8),     # odd channels, remainders of tiles
+    ((16, 32), (10, 6, 14), 2),         # nx != ny
+    ((32, 64), (104, 104, 104), 8),     # two groups of images
+])
+def test_images_in_one_launch_equal_one_by_one(channels, shape, nsym):
+    """The symmetries' images share each layer's launch: the same bits as
+    the network applied to one image after another, mapped back and added in
+    order."""
+    import test_gpu_nn as T
+    t = T.torch()
+    say("[gpu] symmetries", channels, shape, nsym)
+    _, flat = T.make_net(channels, shape, 31)
+    noisy, _ = T.fluence_pair(shape, 32)
+    with T.nn.Denoiser(channels, shape) as d:
+        d.set_params(flat)
+        x = T.dev_f32(noisy)
+        acc = None
+        for op in range(nsym):
+            u = t.empty_like(x)
+            d.forward(x if op == 0 else T.nn.mcx_nn_mirror_xy(x, op), u_out=u)
+            inv = (4 | (op & 1) << 1 | (op & 2) >> 1) if op & 4 else op
+            if inv:
+                u = T.nn.mcx_nn_mirror_xy(u, inv)
+            acc = u if acc is None else acc + u
+        u_sym = t.empty_like(x)
+        d.forward(x, u_out=u_sym, symmetries=nsym)
+        t.cuda.synchronize()
+    assert t.equal(u_sym, acc / nsym)
