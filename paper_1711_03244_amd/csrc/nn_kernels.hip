@@ -266,6 +266,120 @@ __global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
   }
 }
 
+// ------------------------------------------------------- 2x2x2 stride-2 up
+// kUp with cin a multiple of 32 and cout one of 8: a wave owns 16 R voxels of
+// the small grid, 32 output channels and a range of the parity classes.  The
+// voxels are the columns of the matrix product and the channels its rows,
+// so a lane's sums are 8 channels of one output voxel (row 4 g + i of the two
+// products is channel 8 g + 4 j + i): bias, skip and ReLU are applied and 16
+// bytes stored from registers, and the two x classes fill whole cache lines.
+// The voxels' channels (KC chunks of 32; 0: any number, read again for each
+// class) stay in registers for all classes; weights come from L1 and L2.
+// No LDS, no barrier.
+// What bounds it: at full resolution the bytes of skip and output, 3.6 of
+// the 4.8 TB/s that a large copy reaches.  Measured: eight images of 32^3
+// 64 -> 32 224 -> 84 us, one 22.8 -> 12.4 (the generic kernel stored 2 bytes a
+// lane and each class half lines), 16^3 128 -> 64 12.2 -> 7.7.
+template <int KC, int R>
+__global__ void __launch_bounds__(256) up_kernel(ConvArgs a) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, g = lane >> 4;
+  const int64_t M = static_cast<int64_t>(a.batch) * a.d * a.h * a.w;
+  const int64_t m0 = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * (16 * R);
+  if (m0 >= M) return;
+  const int n0 = blockIdx.y * 32, n = n0 + 8 * g;
+  const bool has_n = n < a.cout;
+  const int nc = 8 / static_cast<int>(gridDim.z);
+  const int chunks = KC > 0 ? KC : a.cin / kBK;
+
+  const uint16_t* xp[R];
+  int64_t ob[R];  // output voxel of class 0, or -1 past the rows
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int64_t m = m0 + 16 * q + r;
+    const uint32_t mm = static_cast<uint32_t>(m < M ? m : M - 1);  // at most 2^30 voxels
+    const uint32_t x = mm % static_cast<uint32_t>(a.w), t = mm / static_cast<uint32_t>(a.w);
+    const uint32_t y = t % static_cast<uint32_t>(a.h), z = t / static_cast<uint32_t>(a.h);
+    xp[q] = a.x + static_cast<int64_t>(mm) * a.cin + 8 * g;
+    ob[q] = m < M && has_n
+                ? (static_cast<int64_t>(2 * z) * (2 * a.h) + 2 * y) * (2 * a.w) + 2 * x
+                : -1;
+  }
+  bf16x8 xf[KC > 0 ? KC : 1][R];
+  if constexpr (KC > 0) {
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int q = 0; q < R; ++q) xf[c][q] = *reinterpret_cast<const bf16x8*>(xp[q] + c * kBK);
+  }
+  const uint16_t* wp[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    wp[j] = a.bt + static_cast<int64_t>(n0 + 8 * (r >> 2) + 4 * j + (r & 3)) * a.kpad + 8 * g;
+  float bias[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) bias[i] = a.bias && has_n ? a.bias[n + i] : 0.f;
+
+  for (int cls = blockIdx.z * nc; cls < (static_cast<int>(blockIdx.z) + 1) * nc; ++cls) {
+    const int64_t oc = (static_cast<int64_t>(cls >> 2) * (2 * a.h) + ((cls >> 1) & 1)) * (2 * a.w) +
+                       (cls & 1);
+    uint4 sk[R];
+    if (a.skip) {
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+        sk[q] = ob[q] >= 0 ? *reinterpret_cast<const uint4*>(a.skip + (ob[q] + oc) * a.cout + n)
+                           : make_uint4(0u, 0u, 0u, 0u);
+    }
+    floatx4 acc[R][2];
+#pragma unroll
+    for (int q = 0; q < R; ++q) acc[q][0] = acc[q][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto step = [&](int c, const bf16x8 (&v)[R]) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const bf16x8 wf = *reinterpret_cast<const bf16x8*>(wp[j] + cls * a.cin + c * kBK);
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+          acc[q][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, v[q], acc[q][j], 0, 0, 0);
+      }
+    };
+    if constexpr (KC > 0) {
+#pragma unroll
+      for (int c = 0; c < KC; ++c) step(c, xf[c]);
+    } else {
+      for (int c = 0; c < chunks; ++c) {
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+          xf[0][q] = *reinterpret_cast<const bf16x8*>(xp[q] + c * kBK);
+        step(c, xf[0]);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      if (ob[q] < 0) continue;
+      const int64_t e0 = (ob[q] + oc) * a.cout + n;
+      float v[8];
+      const uint16_t* sh = reinterpret_cast<const uint16_t*>(&sk[q]);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        v[i] = acc[q][i >> 2][i & 3] + bias[i];
+        if (a.skip) v[i] += from_bf16(sh[i]);
+        if (a.relu) v[i] = fmaxf(v[i], 0.f);
+      }
+      if (a.y_f32) {
+        float4* y = reinterpret_cast<float4*>(static_cast<float*>(a.y) + e0);
+        y[0] = make_float4(v[0], v[1], v[2], v[3]);
+        y[1] = make_float4(v[4], v[5], v[6], v[7]);
+      } else {
+        uint4 o;
+        uint16_t* oh = reinterpret_cast<uint16_t*>(&o);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) oh[i] = to_bf16(v[i]);
+        *reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.y) + e0) = o;
+      }
+    }
+  }
+}
+
 // ------------------------------------------------- 3x3x3 conv from an LDS brick
 // The source of the zero padding of direct global-to-LDS loads: 64 KB of
 // zeros, each lane reading its own 16 bytes (offset by workgroup and load),
@@ -1893,8 +2007,36 @@ constexpr int64_t kDeepTileGroups = 1024;     // 4 x 4 x 8 tiles when at least t
 
 int conv_nb(const ConvArgs& a) { return a.cout > 32 ? 4 : (a.cout > 16 ? 2 : 1); }
 
+// the generic kernel takes operands at any address
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
 bool uses_brick(const ConvArgs& a) {
-  return (a.geo == kConv3 || a.geo == kConv3T) && a.cin % kBK == 0;
+  return (a.geo == kConv3 || a.geo == kConv3T) && a.cin % kBK == 0 && aligned16(a.x);
+}
+
+bool uses_up(const ConvArgs& a) {
+  return a.geo == kUp && a.cin % kBK == 0 && a.cout % 8 == 0 && aligned16(a.x) &&
+         aligned16(a.y) && aligned16(a.skip);
+}
+
+// 64 voxels a wave where that leaves 512 workgroups, the classes apart if
+// need be, else 32; the classes split until there are 512.  Measured (us, 256 /
+// 512 / 1024 / 2048 workgroups): 32^3 64 -> 32 14.9 / 12.4 / 13.5 / 15.3, eight
+// images of 16^3 128 -> 64 37.0 / 29.5 / 32.3 / 38.6; eight of 8^3 256 -> 128
+// with 64 voxels 17.9, with 32 20.9.
+template <int KC>
+void launch_up(const ConvArgs& a, hipStream_t s) {
+  const int64_t M = static_cast<int64_t>(a.batch) * a.d * a.h * a.w;
+  const int nb = (a.cout + 31) / 32;
+  const bool wide = (M + 255) / 256 * nb * 8 >= 512;
+  const int64_t rows = (M + (wide ? 255 : 127)) / (wide ? 256 : 128);
+  int z = 1;
+  while (z < 8 && rows * nb * z < 512) z *= 2;
+  const dim3 grid(static_cast<unsigned>(rows), static_cast<unsigned>(nb), static_cast<unsigned>(z));
+  if (wide)
+    up_kernel<KC, 4><<<grid, 256, 0, s>>>(a);
+  else
+    up_kernel<KC, 2><<<grid, 256, 0, s>>>(a);
 }
 
 // The resident-weights kernel: 3x3x3 layers gathering exactly 32 channels,
@@ -1904,7 +2046,7 @@ bool uses_brick(const ConvArgs& a) {
 constexpr int64_t kResidentTiles = 1024;
 int64_t brick_tiles(const ConvArgs& a, int mz);
 bool uses_resident(const ConvArgs& a) {
-  return (a.geo == kConv3 || a.geo == kConv3T) && a.cin == 32 && !a.skip &&
+  return (a.geo == kConv3 || a.geo == kConv3T) && a.cin == 32 && !a.skip && aligned16(a.x) &&
          brick_tiles(a, 2) >= kResidentTiles;
 }
 
@@ -2051,6 +2193,19 @@ hipError_t launch_conv(const ConvArgs& args, hipStream_t s) {
     if (sp > 1) split_reduce_kernel<<<blocks_for(out_floats(a)), 256, 0, s>>>(a, sp);
     return hipGetLastError();
   }
+  if (uses_up(a)) {
+    if (a.cin == 32)
+      launch_up<1>(a, s);
+    else if (a.cin == 64)
+      launch_up<2>(a, s);
+    else if (a.cin == 128)
+      launch_up<4>(a, s);
+    else if (a.cin == 256)
+      launch_up<8>(a, s);
+    else
+      launch_up<0>(a, s);
+    return hipGetLastError();
+  }
   a.ranges = generic_ranges(a);
   const int sp = spread_ranges(a, a.ranges) && a.part && a.part_cap >= a.ranges * out_floats(a)
                      ? a.ranges
@@ -2059,7 +2214,7 @@ hipError_t launch_conv(const ConvArgs& args, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>((M + kBM - 1) / kBM),
                   static_cast<unsigned>((a.cout + 16 * nb - 1) / (16 * nb)),
                   a.geo == kUp ? 8 : static_cast<unsigned>(sp));
-  const bool vec = a.cin % 8 == 0;
+  const bool vec = a.cin % 8 == 0 && aligned16(a.x);
   const bool deep = a.k >= 4 * kBK;  // four reduction steps per stage
 #define MCX_CONV(NB)                                                   \
   if (vec && deep)                                                     \
@@ -2264,7 +2419,7 @@ hipError_t launch_mse(const float* out, const float* target_u, const float* targ
 hipError_t launch_bias_grad(const uint16_t* gy, int64_t m, int cout, float* gb, hipStream_t s) {
   const int64_t blocks = m < 512 ? 1 : (m / 256 < 256 ? m / 256 : 256);
   const int64_t per = (m + blocks - 1) / blocks;
-  if (cout % 8 == 0)
+  if (cout % 8 == 0 && aligned16(gy))
     bias_grad_kernel<true><<<static_cast<int>(blocks), 256, 0, s>>>(gy, m, cout, per, gb);
   else
     bias_grad_kernel<false><<<static_cast<int>(blocks), 256, 0, s>>>(gy, m, cout, per, gb);

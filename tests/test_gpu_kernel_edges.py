@@ -154,3 +154,46 @@ def test_images_in_one_launch_equal_one_by_one(channels, shape, nsym):
         d.forward(x, u_out=u_sym, symmetries=nsym)
         t.cuda.synchronize()
     assert t.equal(u_sym, acc / nsym)
+
+
+@pytest.mark.parametrize("shape,ci,co,skip,relu,f32,shift", [
+    ((2, 2, 2), 32, 8, True, True, False, 0),      # fewer voxels than a wave's
+    ((3, 5, 7), 64, 40, True, False, False, 0),    # remainders of voxels and of channels
+    ((4, 6, 10), 128, 24, False, True, True, 0),   # FP32 output
+    ((2, 4, 4), 256, 64, True, True, False, 0),
+    ((3, 3, 5), 96, 32, True, True, True, 0),      # channel chunks read again for each class
+    ((16, 24, 24), 64, 128, True, True, False, 0),  # 64 voxels a wave, remainder
+    ((3, 5, 7), 64, 40, True, True, False, 3),     # operands off 16-byte alignment
+    ((3, 5, 7), 64, 12, True, True, False, 0),     # channels not a multiple of 8
+])
+def test_up_layer_edges(shape, ci, co, skip, relu, f32, shift):
+    """Stride-2 up layers against the oracle on BF16 operands: FP32 sums of ci
+    products (1e-5 of the sum of their sizes), then one BF16 rounding (2^-8)
+    unless the output is FP32."""
+    import test_gpu_nn as T
+    t = T.torch()
+    say("[gpu] up", shape, ci, co, skip, relu, f32, shift)
+    x, w, b = T.layer_case("up", shape, ci, co, 41)
+    big = tuple(2 * s for s in shape)
+    sk = T.O.bf16(np.random.default_rng(42).standard_normal(big + (co,))) if skip else None
+    wq = T.O.bf16(w)
+
+    def placed(a, dtype):
+        buf = t.zeros(a.size + shift, dtype=dtype, device="cuda")
+        v = buf[shift:].view(a.shape)
+        v.copy_(t.from_numpy(np.ascontiguousarray(a)))
+        return v
+
+    y = placed(np.zeros(big + (co,), np.float32), t.float32 if f32 else t.bfloat16)
+    T.nn.mcx_nn_layer_forward(T.nn.MCX_NN_UP, shape, ci, co, placed(x, t.bfloat16), T.dev_f32(w),
+                              T.dev_f32(b), y=y, y_f32=f32, relu=relu,
+                              skip=None if sk is None else placed(sk, t.bfloat16))
+    ref = T.FWD["up"](x, wq, b)
+    size = T.FWD["up"](np.abs(x), np.abs(wq), np.abs(b))
+    if skip:
+        ref, size = ref + sk, size + np.abs(sk)
+    if relu:
+        ref = np.maximum(ref, 0)
+    got = y.float().cpu().numpy()
+    lim = 1e-5 * size + (0 if f32 else 2.0 ** -8 * np.abs(ref))
+    assert np.all(np.abs(got - ref) <= lim + 1e-30)
