@@ -24,10 +24,11 @@
 // conv3_resident_kernel (exactly 32 gathered channels on large grids: the
 // weights stay in LDS, input planes stream in by direct global-to-LDS
 // loads), conv3_brick_kernel (other multiples of 32 gathered channels),
-// conv3_scalar_kernel (one gathered channel), wgrad_slab_kernel and
-// wgrad_onechannel_kernel
-// (weight gradients) -- and wgrad_kernel covers the remaining weight
-// gradients.  Products that launch too few workgroups split their
+// conv3_scalar_kernel (one gathered channel) -- and up_kernel the stride-2 up
+// products.  Weight gradients: wgrad_brick_kernel (3x3x3) and
+// wgrad_pair_kernel (stride 2) for channels in eights,
+// wgrad_onechannel_kernel, wgrad_slab_kernel for other output channels, and
+// wgrad_kernel for the rest.  Products that launch too few workgroups split their
 // reduction and finish in split_reduce_kernel / wgrad_reduce_kernel, which
 // add FP32 partial sums in a fixed order.
 //
@@ -1288,8 +1289,9 @@ __global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a) {
 }
 
 // ---------------------------------------- 3x3x3 weight gradient from a slab
-// kConv3 layers with cin a multiple of 32.  A workgroup owns one chunk of 32
-// input channels (blockIdx.y % chunks), one plane dz = blockIdx.y / chunks
+// kConv3 layers with cin a multiple of 32 whose other operands the kernels with
+// transposing reads below do not take (16-byte pieces of 8 output channels).
+// A workgroup owns one chunk of 32 input channels (blockIdx.y % chunks), one plane dz = blockIdx.y / chunks
 // of taps (the 9 taps t = 9 dz + 3 dy + dx) and 32 NBW output channels
 // (blockIdx.z), and walks the 4 x 4 x kSlabTZ voxel tiles blockIdx.x,
 // blockIdx.x + gridDim.x, ...  Per tile it stages the kSlabTZ x 6 x 6 slab of x
@@ -1460,6 +1462,352 @@ __global__ void __launch_bounds__(256) wgrad_slab_kernel(WgradArgs a) {
     }
 }
 
+// ------------------------------------ weight gradients, operands by transposing reads
+// gw[t][ci][n] = sum_m x(m, t, ci) gy(m, t, n): both operands of the matrix
+// product run along voxels, which are the slow axis of x and gy.  Tiles are
+// copied to LDS as they are, [voxel][32 channels], by loader waves with direct
+// global-to-LDS loads, and gfx950's transposing LDS reads form the fragments:
+// of 16 lanes, lane 4 a + b reads 8 bytes, channels 4 b .. 4 b + 3 of the
+// voxel given by its address, and lane i receives channel i of the four
+// voxels a.  The voxels' addresses are free, so taps and classes are
+// offsets.  A 16-byte piece j of voxel v is in slot j ^ 2 s(v), where s differs
+// between the voxels that a half-wave reads 256 bytes apart: the 32 lanes
+// fall on 64 different banks.
+__device__ __forceinline__ bf16x8 read_tr(const char* lo, const char* hi) {
+  typedef short shortx4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) shortx4* lds;
+  struct {
+    shortx4 a, b;
+  } v = {__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds)(lo)),
+         __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds)(hi))};
+  return __builtin_bit_cast(bf16x8, v);
+}
+
+// this lane's byte offset in a transposing read of voxels 64 bytes apart
+__device__ __forceinline__ int tr_lane(int lane) {
+  return ((lane >> 2) & 3) * 64 + (lane & 3) * 8;
+}
+
+// A workgroup's sums, N groups of four output channels at the elements
+// at(0) .. at(N - 1) of gw, or nowhere (-1).  Several workgroups along the
+// tiles store to part[blockIdx.x] for wgrad_reduce_kernel; a single one
+// finishes gw itself, reading all of it before it stores any.
+template <int N, typename At, typename Sum>
+__device__ __forceinline__ void wgrad_put(const WgradArgs& a, At at, Sum sum) {
+  if (gridDim.x > 1) {
+    float* out = a.part + blockIdx.x * (static_cast<int64_t>(a.taps) * a.cin * a.cout);
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (at(k) >= 0) *reinterpret_cast<floatx4*>(out + at(k)) = sum(k);
+    return;
+  }
+  float old[N][4];
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) old[k][i] = !a.overwrite && at(k) >= 0 ? a.gw[at(k) + i] : 0.f;
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    if (at(k) >= 0)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        a.gw[at(k) + i] = a.overwrite ? sum(k)[i] : old[k][i] + sum(k)[i];
+}
+
+// The loader waves' protocol: stage s of nt in slot s % 3 of the ring, two
+// stages ahead; kL loads a stage.  The compute waves meet the same barrier
+// before each stage.
+template <int kL, typename Load>
+__device__ __forceinline__ void stream_stages(int nt, Load load) {
+  load(0, 0);
+  if (nt > 1) load(1, 1);
+  for (int s = 0, slot = 2; s < nt; ++s) {
+    if (s + 1 < nt)
+      wait_vm<kL>();
+    else
+      wait_vm<0>();
+    barrier_lds();  // stage s has landed; the slot of stage s - 1 is free
+    if (s + 2 < nt) load(s + 2, slot);
+    slot = slot == 2 ? 0 : slot + 1;
+  }
+}
+
+// 3x3x3 layers with cin and cout multiples of 8.  A workgroup owns 32 input
+// channels, 32 output channels and all 27 taps, or with kPlane one plane dz
+// of 9 (three workgroups), and walks the 4 x 4 x 8-voxel tiles blockIdx.x,
+// + gridDim.x, ...: per tile the 6 x 6 x 10 brick of x and the tile of gy.
+// The compute waves share the taps.
+// What bounds it: a tile's 31 KB arrive in 1.2 us where its matrix
+// instructions take 0.75; below four tiles a workgroup the partial sums, 28 MB
+// for 256 workgroups with all taps.  The slab kernel copied the tiles through
+// registers, transposing 2 bytes at a time.  Measured with the reductions, slab
+// and this, us: 64^3 32 -> 32 33.0 + 11.7 and 21.7 + 6.4, 32^3 64 -> 64 23.1 +
+// 7.7 and 16.0 + 6.4, 16^3 128 -> 128 15.4 + 10.7 and 16.3 + 4.8, 8^3 256 -> 256
+// 12.5 + 10.1 and 15.7.  Voxel k = 8 g + j of reduction step ks is
+// (x, y, z) = (j & 3, 2 (g & 1) + (j >> 2), 2 ks + (g >> 1)).
+struct WBrick {
+  static constexpr int kPieces = 360 * 4;               // 16-byte pieces of a brick
+  static constexpr int kBrickLoads = 23, kLoads = 31;   // wave loads: brick, then gy
+  static constexpr int kStageBytes = kLoads * 1024;
+};
+
+// bits 0 .. n - 1: which of the positions p0 .. p0 + n - 1 are outside [0, size)
+__device__ __forceinline__ uint32_t outside(int p0, int n, int size) {
+  uint32_t m = 0;
+  for (int i = 0; i < n; ++i) m |= p0 + i < 0 || p0 + i >= size ? 1u << i : 0u;
+  return m;
+}
+
+template <int LW>
+__device__ __forceinline__ void wbrick_loader(const WgradArgs& a, char* s_st, int lane, int c0,
+                                              int n0, int tx_n, int ty_n, int nt) {
+  using K = WBrick;
+  constexpr int kL = (K::kLoads + 1 - LW) / 2;
+  const uint16_t* zero = reinterpret_cast<const uint16_t*>(g_zero16) +
+                         ((blockIdx.x * 64 + lane) & (kZeroChunks - 1)) * 8;
+  // Per load: the offset from the tile's first voxel, and the brick position
+  // as one bit for each of x, y and z (bit 31: no such piece), which a tile's
+  // mask of what lies outside the volume tells apart in two instructions.
+  int64_t rel[kL];
+  uint32_t pos[kL];
+#pragma unroll
+  for (int k = 0; k < kL; ++k) {
+    const int b = 2 * k + LW;
+    int x, y, z;
+    if (b < K::kBrickLoads) {
+      const int p = b * 64 + lane, v = p >> 2;
+      x = v % 6, y = (v / 6) % 6, z = v / 36;
+      const int c = c0 + (((p & 3) ^ (y & 2)) << 3);
+      rel[k] = ((static_cast<int64_t>(z - 1) * a.h + (y - 1)) * a.w + (x - 1)) * a.cin + c;
+      pos[k] = p < K::kPieces && c < a.cin ? 0u : 1u << 31;
+    } else {
+      const int p = (b - K::kBrickLoads) * 64 + lane, v = p >> 2;
+      x = v & 3, y = (v >> 2) & 3, z = v >> 4;
+      const int n = n0 + (((p & 3) ^ (y & 2)) << 3);
+      rel[k] = ((static_cast<int64_t>(z) * a.h + y) * a.w + x) * a.cout + n;
+      pos[k] = n < a.cout ? 0u : 1u << 31;
+      ++x, ++y, ++z;
+    }
+    if (!pos[k]) pos[k] = 1u << x | 1u << (6 + y) | 1u << (12 + z);
+  }
+  stream_stages<kL>(nt, [&](int s, int slot) {
+    const int tile = blockIdx.x + s * gridDim.x;
+    const int bx = (tile % tx_n) * 4, by = ((tile / tx_n) % ty_n) * 4, bz = (tile / (tx_n * ty_n)) * 8;
+    const uint32_t out = 1u << 31 | outside(bx - 1, 6, a.w) | outside(by - 1, 6, a.h) << 6 |
+                         outside(bz - 1, 10, a.d) << 12;
+    const int64_t v0 = (static_cast<int64_t>(bz) * a.h + by) * a.w + bx;
+    const uint16_t* x0 = a.x + v0 * a.cin;
+    const uint16_t* g0 = a.gy + v0 * a.cout;
+#pragma unroll
+    for (int k = 0; k < kL; ++k) {
+      const int b = 2 * k + LW;
+      load_lds16(pos[k] & out ? zero : (b < K::kBrickLoads ? x0 : g0) + rel[k],
+                 s_st + slot * K::kStageBytes + b * 1024);
+    }
+  });
+}
+
+template <bool kPlane, int W>
+__device__ __forceinline__ void wbrick_compute(const WgradArgs& a, const char* s_st, int lane,
+                                               int c0, int n0, int dz0, int nt) {
+  using K = WBrick;
+  constexpr int kT0 = kPlane ? (9 * W + 3) / 4 : 7 * W;  // the wave's taps kT0 .. kT0 + kNT - 1
+  constexpr int kNT = kPlane ? (9 * W + 12) / 4 - kT0 : (W < 3 ? 7 : 6);
+  const int r = lane & 15, g = lane >> 4;
+  const int xo = tr_lane(lane) + ((g >> 1) * 36 + (g & 1) * 12 + dz0 * 36) * 64;
+  const int go = tr_lane(lane) + ((g >> 1) * 16 + (g & 1) * 8) * 64 + K::kBrickLoads * 1024;
+  floatx4 acc[kNT][2][2];
+#pragma unroll
+  for (int t = 0; t < kNT; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[t][q >> 1][q & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int s = 0, slot = 0; s < nt; ++s) {
+    barrier_lds();  // stage s has landed
+    const char* st = s_st + slot * K::kStageBytes;
+    // the two 16-channel halves, as they lie for even y >> 1
+    const char* xh[2] = {st + xo + (g & 1) * 32, st + xo + ((g & 1) ^ 1) * 32};
+    const char* gh[2] = {st + go + (g & 1) * 32, st + go + ((g & 1) ^ 1) * 32};
+    auto read_x = [&](int i, bf16x8 (&f)[2]) {  // tap i % kNT of step i / kNT
+      const int ks = i / kNT, t = kT0 + i % kNT, dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
+      const int o = ((2 * ks + dz) * 36 + dy * 6 + dx) * 64;
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+        f[cb] = read_tr(xh[cb ^ (dy >> 1)] + o, xh[cb ^ ((dy + 1) >> 1)] + o + 6 * 64);
+    };
+    bf16x8 xf[2][2], gf[2];
+    read_x(0, xf[0]);
+#pragma unroll
+    for (int i = 0; i < 4 * kNT; ++i) {
+      const int t = i % kNT;
+      if (t == 0) {
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+          gf[nb] = read_tr(gh[nb] + (i / kNT) * 2048, gh[nb] + (i / kNT) * 2048 + 256);
+      }
+      if (i + 1 < 4 * kNT) read_x(i + 1, xf[(i + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);  // those reads ahead of the matrix instructions
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+          acc[t][nb][cb] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf[nb], xf[i & 1][cb], acc[t][nb][cb], 0, 0, 0);
+    }
+    slot = slot == 2 ? 0 : slot + 1;
+  }
+  // lane (r, g) holds output channels 16 nb + 4 g .. + 3 of input channel 16 cb + r
+  wgrad_put<4 * kNT>(
+      a,
+      [&](int k) -> int64_t {
+        const int n = n0 + ((k >> 1) & 1) * 16 + 4 * g, ci = c0 + (k & 1) * 16 + r;
+        return n < a.cout && ci < a.cin
+                   ? (static_cast<int64_t>(9 * dz0 + kT0 + (k >> 2)) * a.cin + ci) * a.cout + n
+                   : -1;
+      },
+      [&](int k) { return acc[k >> 2][(k >> 1) & 1][k & 1]; });
+}
+
+// blockIdx.y: 32 input channels (kPlane: times 3, plus dz), blockIdx.z: 32 output channels
+template <bool kPlane>
+__global__ void __launch_bounds__(384) wgrad_brick_kernel(WgradArgs a) {
+  __shared__ __align__(16) char s_st[3 * WBrick::kStageBytes];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tx_n = (a.w + 3) >> 2, ty_n = (a.h + 3) >> 2, tiles = tx_n * ty_n * ((a.d + 7) >> 3);
+  const int nt = (tiles - blockIdx.x + gridDim.x - 1) / gridDim.x;
+  const int dz0 = kPlane ? blockIdx.y % 3 : 0;
+  const int c0 = (kPlane ? blockIdx.y / 3 : blockIdx.y) * 32, n0 = blockIdx.z * 32;
+  switch (wave) {
+    case 0: wbrick_compute<kPlane, 0>(a, s_st, lane, c0, n0, dz0, nt); break;
+    case 1: wbrick_compute<kPlane, 1>(a, s_st, lane, c0, n0, dz0, nt); break;
+    case 2: wbrick_compute<kPlane, 2>(a, s_st, lane, c0, n0, dz0, nt); break;
+    case 3: wbrick_compute<kPlane, 3>(a, s_st, lane, c0, n0, dz0, nt); break;
+    case 4: wbrick_loader<0>(a, s_st, lane, c0, n0, tx_n, ty_n, nt); break;
+    default: wbrick_loader<1>(a, s_st, lane, c0, n0, tx_n, ty_n, nt); break;
+  }
+}
+
+// 2x2x2 stride-2 layers with cin and cout multiples of 8: of each voxel m of the
+// small grid, the operand on the large grid (kDown: x, kUp: gy) has the 8
+// voxels 2 m + e(t), one per tap.  A workgroup owns 32 channels of the large
+// operand (blockIdx.y), 16 NS of the small one (blockIdx.z) and all taps, and
+// walks the tiles of 64 consecutive m blockIdx.x, + gridDim.x, ...; the large
+// operand is staged by tap.  Compute wave w has taps 2 w and 2 w + 1; s(v) is
+// bit 3 of v = 32 ks + 8 g + j.
+// What bounds it: reading the large operand (17 MB at 64^3 x 32: 4 us) and the
+// partial sums (17 MB).  The generic kernel reads it again for every 64 rows of
+// gw and adds to gw with atomics.  Measured, generic and this with its
+// reduction, us: down 64^3 -> 32^3, 32 -> 64 30 and 9.7 + 4.7, 32^3 -> 16^3,
+// 64 -> 128 27 and 9.5 + 4.3, up 32^3 -> 64^3, 64 -> 32 41 and 9.5 + 4.7.
+template <int NS>
+struct WPair {
+  static constexpr int kStageBytes = 32768 + NS * 2048;  // [tap][64 voxels], [NS / 2][64 voxels]
+};
+
+template <bool kUpGeo, int NS, int LW>
+__device__ __forceinline__ void wpair_loader(const WgradArgs& a, char* s_st, int lane, int b0,
+                                             int s0, int nt) {
+  const uint16_t* zero = reinterpret_cast<const uint16_t*>(g_zero16) + lane * 8;
+  const int64_t M = static_cast<int64_t>(a.d) * a.h * a.w;
+  const uint16_t* big = kUpGeo ? a.gy : a.x;
+  const uint16_t* small = kUpGeo ? a.x : a.gy;
+  const int bc = kUpGeo ? a.cout : a.cin, sc = kUpGeo ? a.cin : a.cout;
+  const int64_t row = 2 * a.w, plane = row * (2 * a.h);
+  stream_stages<16 + NS>(nt, [&](int s, int slot) {
+    const int64_t m0 = (blockIdx.x + static_cast<int64_t>(s) * gridDim.x) * 64;
+    char* st = s_st + slot * WPair<NS>::kStageBytes;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int v = (2 * LW + q) * 16 + (lane >> 2);
+      const int j = (lane & 3) ^ ((v >> 2) & 2);
+      const int64_t m = m0 + v;
+      const uint32_t mm = static_cast<uint32_t>(m < M ? m : 0);  // at most 2^30 voxels
+      const uint32_t x = mm % static_cast<uint32_t>(a.w), t = mm / static_cast<uint32_t>(a.w);
+      const uint32_t y = t % static_cast<uint32_t>(a.h), z = t / static_cast<uint32_t>(a.h);
+      const uint16_t* pb = big + (2 * z * plane + 2 * y * row + 2 * x) * bc + b0 + 8 * j;
+      const uint16_t* ps = small + static_cast<int64_t>(mm) * sc + s0 + 8 * j;
+      const bool in_b = m < M && b0 + 8 * j < bc;
+      char* dst = st + (2 * LW + q) * 1024;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        load_lds16(in_b ? pb + ((e >> 2) * plane + ((e >> 1) & 1) * row + (e & 1)) * bc : zero,
+                   dst + e * 4096);
+#pragma unroll
+      for (int h = 0; h < NS / 2; ++h)
+        load_lds16(m < M && s0 + 32 * h + 8 * j < sc ? ps + 32 * h : zero, dst + (8 + h) * 4096);
+    }
+  });
+}
+
+template <bool kUpGeo, int NS>
+__global__ void __launch_bounds__(384) wgrad_pair_kernel(WgradArgs a) {
+  __shared__ __align__(16) char s_st[3 * WPair<NS>::kStageBytes];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t M = static_cast<int64_t>(a.d) * a.h * a.w;
+  const int tiles = static_cast<int>((M + 63) / 64);
+  const int nt = (tiles - blockIdx.x + gridDim.x - 1) / gridDim.x;
+  const int b0 = blockIdx.y * 32, s0 = blockIdx.z * 16 * NS;
+  if (wave == 4) {
+    wpair_loader<kUpGeo, NS, 0>(a, s_st, lane, b0, s0, nt);
+    return;
+  }
+  if (wave == 5) {
+    wpair_loader<kUpGeo, NS, 1>(a, s_st, lane, b0, s0, nt);
+    return;
+  }
+  const int r = lane & 15, g = lane >> 4;
+  const int lo = tr_lane(lane) + g * 512;
+  floatx4 acc[2][NS][2];  // tap, small and large 16-channel block
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+#pragma unroll
+    for (int q = 0; q < 2 * NS; ++q) acc[e][q >> 1][q & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int s = 0, slot = 0; s < nt; ++s) {
+    barrier_lds();  // stage s has landed
+    const char* st = s_st + slot * WPair<NS>::kStageBytes + lo;
+    const char* h[2] = {st + (g & 1) * 32, st + ((g & 1) ^ 1) * 32};
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      bf16x8 sf[NS], bf[2][2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const char* p = h[q] + (2 * wave + e) * 4096 + ks * 2048;
+          bf[e][q] = read_tr(p, p + 256);
+        }
+#pragma unroll
+      for (int q = 0; q < NS; ++q) {
+        const char* p = h[q & 1] + (8 + (q >> 1)) * 4096 + ks * 2048;
+        sf[q] = read_tr(p, p + 256);
+      }
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int q = 0; q < NS; ++q)
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+            acc[e][q][c] =
+                kUpGeo ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[e][c], sf[q], acc[e][q][c], 0, 0, 0)
+                       : __builtin_amdgcn_mfma_f32_16x16x32_bf16(sf[q], bf[e][c], acc[e][q][c], 0, 0, 0);
+    }
+    slot = slot == 2 ? 0 : slot + 1;
+  }
+  // lane (r, g): four output channels of one input channel, as above
+  wgrad_put<4 * NS>(
+      a,
+      [&](int k) -> int64_t {
+        const int e = k / (2 * NS), q = (k >> 1) % NS, c = k & 1;
+        const int n = (kUpGeo ? b0 + 16 * c : s0 + 16 * q) + 4 * g;
+        const int ci = (kUpGeo ? s0 + 16 * q : b0 + 16 * c) + r;
+        return n < a.cout && ci < a.cin
+                   ? (static_cast<int64_t>(2 * wave + e) * a.cin + ci) * a.cout + n
+                   : -1;
+      },
+      [&](int k) { return acc[k / (2 * NS)][(k >> 1) % NS][k & 1]; });
+}
+
 // ------------------------------------- 3x3x3 weight gradients with one channel
 // Taps as a matrix axis (27 of 32 used).  kConv3 layers with cin == 1:
 // gw[t][n] = sum_m x[m + d(t)] gy[m][n], rows t, columns n; with cout == 1:
@@ -1557,6 +1905,7 @@ __global__ void wgrad_reduce_few_kernel(const float* part, int groups, int64_t n
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     float v = part[i];
+#pragma unroll 7
     for (int k = 1; k < groups; ++k) v += part[k * n + i];
     gw[i] = overwrite ? v : gw[i] + v;
   }
@@ -1574,6 +1923,7 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float* part, in
   const int64_t i = static_cast<int64_t>(blockIdx.x) * E + il;
   float v = 0.f;
   if (i < n)
+#pragma unroll 8
     for (int k = q; k < groups; k += KL) v += part[k * n + i];
   sh[q][il] = v;
   __syncthreads();
@@ -2237,8 +2587,49 @@ constexpr int64_t kSlabMaxPart = int64_t(8) << 20;  // floats of partial sums at
 bool uses_onechannel(const WgradArgs& a) {
   return a.geo == kConv3 && (a.cin == 1 || (a.cout == 1 && a.cin > 1));
 }
+// the kernels with transposing reads take 16-byte pieces of both operands
+bool uses_tr(const WgradArgs& a) {
+  return !uses_onechannel(a) && a.cin % 8 == 0 && a.cout % 8 == 0 && aligned16(a.x) &&
+         aligned16(a.gy);
+}
 bool uses_slab(const WgradArgs& a) {
-  return a.geo == kConv3 && a.cin % kBK == 0 && !uses_onechannel(a);
+  return a.geo == kConv3 && a.cin % kBK == 0 && !uses_onechannel(a) && !uses_tr(a);
+}
+
+// their workgroups along the voxel tiles: one workgroup per CU in all
+// (kTrGroups), at most one per tile, with the partial sums within `cap` floats
+constexpr int64_t kTrGroups = 256;
+int tr_ns(const WgradArgs& a) { return (a.geo == kUp ? a.cin : a.cout) > 32 ? 4 : 2; }
+int64_t tr_tiles(const WgradArgs& a) {
+  return a.geo == kConv3
+             ? static_cast<int64_t>((a.w + 3) / 4) * ((a.h + 3) / 4) * ((a.d + 7) / 8)
+             : (static_cast<int64_t>(a.d) * a.h * a.w + 63) / 64;
+}
+// workgroups for one of the tile groups, each with all the taps
+int64_t tr_blocks(const WgradArgs& a) {
+  if (a.geo == kConv3) return static_cast<int64_t>((a.cin + 31) / 32) * ((a.cout + 31) / 32);
+  const int bc = a.geo == kUp ? a.cout : a.cin, sc = a.geo == kUp ? a.cin : a.cout;
+  const int ns = 16 * tr_ns(a);
+  return static_cast<int64_t>((bc + 31) / 32) * ((sc + ns - 1) / ns);
+}
+// A plane of taps per workgroup, a third of the partial sums for three times
+// the loads, where a workgroup has at most two tiles.  Measured with the
+// reduction, us, planes and not: 8^3 256 -> 256 15.7 and 24.3, 16^3 128 -> 128
+// 21.1 and 26.6, 32^3 64 -> 64 (four tiles) 23.8 and 22.7.
+bool tr_plane(const WgradArgs& a) {
+  return a.geo == kConv3 && tr_tiles(a) * tr_blocks(a) <= 2 * kTrGroups;
+}
+int tr_groups(const WgradArgs& a, int64_t cap) {
+  const int64_t other = tr_blocks(a) * (tr_plane(a) ? 3 : 1);
+  int64_t G = std::min<int64_t>(tr_tiles(a), std::max<int64_t>(1, kTrGroups / other));
+  const int64_t per = static_cast<int64_t>(a.taps) * a.cin * a.cout;
+  while (G > 1 && G * per > cap) G = (G + 1) / 2;
+  return static_cast<int>(G);
+}
+// floats of their partial sums (one group needs none)
+int64_t tr_part(const WgradArgs& a) {
+  const int G = tr_groups(a, kSlabMaxPart);
+  return G > 1 ? G * static_cast<int64_t>(a.taps) * a.cin * a.cout : 0;
 }
 
 // tile groups of the one-channel kernels: about kSlabTargetGroups in all
@@ -2290,12 +2681,13 @@ hipError_t launch_wgrad_reduce(const float* part, int G, int64_t n, float* gw, b
 int64_t wgrad_workspace_floats(const WgradArgs& a) {
   if (uses_onechannel(a))
     return onechannel_groups(a, kSlabMaxPart) * static_cast<int64_t>(a.taps) * a.cin * a.cout;
+  if (uses_tr(a)) return tr_part(a);
   if (!uses_slab(a)) return 0;
   return slab_groups(a, kSlabMaxPart) * static_cast<int64_t>(a.taps) * a.cin * a.cout;
 }
 
 bool wgrad_overwrites(const WgradArgs& a) {
-  return (uses_onechannel(a) || uses_slab(a)) && wgrad_workspace_floats(a) <= kSlabMaxPart;
+  return (uses_onechannel(a) || uses_tr(a) || uses_slab(a)) && wgrad_workspace_floats(a) <= kSlabMaxPart;
 }
 
 hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
@@ -2311,6 +2703,29 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
         wgrad_onechannel_kernel<false><<<grid, 256, 0, s>>>(a);
       return launch_wgrad_reduce(a.part, G, per, a.gw, a.overwrite, s);
     }
+  }
+  if (uses_tr(a)) {
+    const int64_t per = static_cast<int64_t>(a.taps) * a.cin * a.cout;
+    const int G = tr_groups(a, a.part ? a.part_cap : 0);
+    const auto g = [&](int rows, int cols) {
+      return dim3(static_cast<unsigned>(G), static_cast<unsigned>(rows),
+                  static_cast<unsigned>(cols));
+    };
+    const int ns = tr_ns(a), cb = (a.cin + 31) / 32, nb = (a.cout + 31) / 32;
+    if (a.geo == kConv3 && tr_plane(a))
+      wgrad_brick_kernel<true><<<g(3 * cb, nb), 384, 0, s>>>(a);
+    else if (a.geo == kConv3)
+      wgrad_brick_kernel<false><<<g(cb, nb), 384, 0, s>>>(a);
+    else if (a.geo == kUp && ns == 4)
+      wgrad_pair_kernel<true, 4><<<g(nb, (a.cin + 63) / 64), 384, 0, s>>>(a);
+    else if (a.geo == kUp)
+      wgrad_pair_kernel<true, 2><<<g(nb, 1), 384, 0, s>>>(a);
+    else if (ns == 4)
+      wgrad_pair_kernel<false, 4><<<g(cb, (a.cout + 63) / 64), 384, 0, s>>>(a);
+    else
+      wgrad_pair_kernel<false, 2><<<g(cb, 1), 384, 0, s>>>(a);
+    if (G == 1) return hipGetLastError();
+    return launch_wgrad_reduce(a.part, G, per, a.gw, a.overwrite, s);
   }
   if (uses_slab(a) && a.part) {
     const int64_t per = static_cast<int64_t>(a.taps) * a.cin * a.cout;

@@ -197,3 +197,64 @@ def test_up_layer_edges(shape, ci, co, skip, relu, f32, shift):
     got = y.float().cpu().numpy()
     lim = 1e-5 * size + (0 if f32 else 2.0 ** -8 * np.abs(ref))
     assert np.all(np.abs(got - ref) <= lim + 1e-30)
+
+
+@pytest.mark.parametrize("kind,shape,ci,co,shift", [
+    ("conv3", (3, 5, 7), 8, 8, 0),          # one partial tile, a quarter of the channel blocks
+    ("conv3", (9, 8, 5), 40, 24, 0),        # two tiles along z, remainders everywhere
+    ("conv3", (8, 8, 8), 72, 96, 0),        # planes of taps, one group: gw finished at once
+    ("conv3", (16, 24, 28), 32, 40, 0),     # planes of taps, several groups
+    ("conv3", (24, 40, 44), 64, 32, 0),     # all taps, several tiles a workgroup
+    ("conv3", (8, 6, 10), 32, 12, 0),       # output channels not in eights
+    ("conv3", (6, 6, 6), 32, 32, 3),        # operands off 16-byte alignment
+    ("down", (2, 2, 2), 8, 8, 0),
+    ("down", (6, 10, 14), 24, 72, 0),
+    ("down", (32, 32, 40), 32, 24, 0),
+    ("up", (1, 1, 1), 8, 8, 0),
+    ("up", (5, 3, 7), 72, 24, 0),
+    ("up", (16, 20, 16), 24, 40, 0),
+    ("up", (4, 4, 4), 32, 32, 3),
+])
+def test_weight_gradient_edges(kind, shape, ci, co, shift):
+    """Weight gradients where tiles, channel blocks and groups of partial sums
+    have remainders, against the oracle on BF16 operands: FP32 sums over the
+    voxels, 1e-5 of the sum of the products' sizes."""
+    import test_gpu_nn as T
+    t = T.torch()
+    say("[gpu] weight gradient", kind, shape, ci, co, shift)
+    x, w, _ = T.layer_case(kind, shape, ci, co, 51)
+    gy = T.O.bf16(np.random.default_rng(52).normal(size=T.out_shape(kind, shape) + (co,)))
+
+    def placed(a):
+        buf = t.zeros(a.size + shift, dtype=t.bfloat16, device="cuda")
+        v = buf[shift:].view(a.shape)
+        v.copy_(t.from_numpy(np.ascontiguousarray(a)))
+        return v
+
+    gw = t.full(w.shape, float("nan"), dtype=t.float32, device="cuda")
+    T.nn.mcx_nn_layer_backward(T.KIND[kind], shape, ci, co, placed(x), T.dev_f32(w), placed(gy),
+                               None, gw, None)
+    ref = T.BWD[kind](x, T.O.bf16(w), gy)[1]
+    lim = T.BWD[kind](np.abs(x), np.abs(T.O.bf16(w)), np.abs(gy))[1]
+    assert np.all(np.abs(T.host(gw) - ref) <= 1e-5 * lim + 1e-30)
+
+
+def test_gradients_accumulate():
+    """A second pass over the same volume added to the gradients doubles them
+    exactly (their sums are taken in a fixed order): weight gradients that
+    go through partial sums and those finished in one launch."""
+    import test_gpu_nn as T
+    t = T.torch()
+    channels, shape = (32, 64, 128), (16, 32, 16)
+    _, flat = T.make_net(channels, shape, 61)
+    noisy, clean = T.fluence_pair(shape, 62)
+    say("[gpu] gradients", channels, shape)
+    with T.nn.Denoiser(channels, shape) as d:
+        d.set_params(flat)
+        x, y = T.dev_f32(noisy), T.dev_f32(clean)
+        d.loss_grad(x, y, want_loss=False)
+        once = d.grads().copy()
+        d.loss_grad(x, y, want_loss=False, accumulate=True)
+        twice = d.grads()
+    assert np.any(once)
+    assert np.array_equal(twice, 2 * once)
