@@ -1074,75 +1074,124 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
 // ------------------------------------------ 3x3x3 conv with one gathered channel
 // kConv3 / kConv3T with cin == 1 (the input layer's forward pass, the output
 // layer's input gradient): the 27 taps are the reduction axis (one MFMA
-// step, taps 27..31 zero).  A workgroup owns a 4 x 4 x 4 tile (wave w: the
-// z-slice w) and 16 NB output channels; the tile's 6 x 6 x 6 input brick is
-// staged in LDS and the B fragments Bt[n][t] are read once from the packed
-// weights (kpad >= 32, zero beyond tap 26).
-template <int NB>
-__global__ void __launch_bounds__(256) conv3_scalar_kernel(ConvArgs a) {
-  __shared__ uint16_t sB[216];
+// step, taps 27..31 zero).  A workgroup owns a 16 x 4 x 4 tile (wave w: the
+// z-slice w, four rows of 16 voxels) and 32 NP output channels; the tile's
+// 18 x 6 x 6 input brick is staged in LDS and the weights' fragments are read
+// once from the packed weights (kpad >= 32, zero beyond tap 26).  As in
+// up_kernel the voxels are the product's columns and a lane's sums 8 channels
+// of one voxel: with `vec` (channels in eights, aligned) 16 bytes are stored
+// at a time, 1 KB of consecutive memory per row and 32 channels.
+// What bounds it: writing the output.  With 2-byte stores of 4 x 4 patches 32
+// BF16 channels of eight 64^3 images took 94 us, one image 15.6; now 40 and
+// 10.5 (134 MB: 28 us at the rate of a large copy).
+template <int NP>
+__global__ void __launch_bounds__(256) conv3_scalar_kernel(ConvArgs a, int vec) {
+  __shared__ uint16_t sB[648];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int tx_n = (a.w + 3) >> 2, ty_n = (a.h + 3) >> 2;
+  const int tx_n = (a.w + 15) >> 4, ty_n = (a.h + 3) >> 2;
   const int ntile = tx_n * ty_n * ((a.d + 3) >> 2);
   const int img = blockIdx.x / ntile, tile = blockIdx.x - img * ntile;
-  const int bx = (tile % tx_n) * 4;
+  const int bx = (tile % tx_n) * 16;
   const int by = ((tile / tx_n) % ty_n) * 4;
   const int bz = (tile / (tx_n * ty_n)) * 4;
-  const int n0 = blockIdx.y * 16 * NB;
+  const int n0 = blockIdx.y * 32 * NP;
   const int sgn = a.geo == kConv3 ? 1 : -1;
   const int r = lane & 15, g = lane >> 4;
   const uint16_t* x_img = a.x + static_cast<int64_t>(img) * a.in_d * a.in_h * a.in_w;
   const int64_t o_img = static_cast<int64_t>(img) * a.d * a.h * a.w;
-  for (int v = tid; v < 216; v += 256) {
-    const int gx = bx + v % 6 - 1, gy = by + (v / 6) % 6 - 1, gz = bz + v / 36 - 1;
+  for (int v = tid; v < 648; v += 256) {
+    const int gx = bx + v % 18 - 1, gy = by + (v / 18) % 6 - 1, gz = bz + v / 108 - 1;
     uint16_t val = 0;
     if (gx >= 0 && gy >= 0 && gz >= 0 && gx < a.in_w && gy < a.in_h && gz < a.in_d)
       val = x_img[(static_cast<int64_t>(gz) * a.in_h + gy) * a.in_w + gx];
     sB[v] = val;
   }
-  bf16x8 bf[NB];
+  // rows 4 g' + i of product j are channels 8 g' + 4 j + i
+  bf16x8 wf[NP][2];
+  float bias[NP][8];
 #pragma unroll
-  for (int j = 0; j < NB; ++j)
-    bf[j] = *reinterpret_cast<const bf16x8*>(a.bt + static_cast<int64_t>(n0 + 16 * j + r) * a.kpad +
-                                            8 * g);
-  __syncthreads();
-  // A row r = voxel (r & 3, r >> 2, wave) of the tile; k = tap 8 g + j
-  bf16x8 af;
+  for (int p = 0; p < NP; ++p) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      wf[p][j] = *reinterpret_cast<const bf16x8*>(
+          a.bt + static_cast<int64_t>(n0 + 32 * p + 8 * (r >> 2) + 4 * j + (r & 3)) * a.kpad + 8 * g);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int n = n0 + 32 * p + 8 * g + i;
+      bias[p][i] = a.bias && n < a.cout ? a.bias[n] : 0.f;
+    }
+  }
+  int off[8];  // the brick positions of this lane's taps 8 g + j
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    const int t = 8 * g + j;
-    uint16_t e = 0;
-    if (t < 27) {
-      const int dz = sgn * (t / 9 - 1), dy = sgn * ((t / 3) % 3 - 1), dx = sgn * (t % 3 - 1);
-      e = sB[((wave + 1 + dz) * 6 + ((r >> 2) + 1 + dy)) * 6 + ((r & 3) + 1 + dx)];
-    }
-    af[j] = __builtin_bit_cast(__bf16, e);
+    const int t = min(8 * g + j, 26);
+    const int dz = sgn * (t / 9 - 1), dy = sgn * ((t / 3) % 3 - 1), dx = sgn * (t % 3 - 1);
+    off[j] = ((wave + 1 + dz) * 6 + 1 + dy) * 18 + r + 1 + dx;
   }
-  floatx4 acc[NB];
+  __syncthreads();
+  const int x = bx + r, z = bz + __builtin_amdgcn_readfirstlane(wave);
+  if (z >= a.d) return;
 #pragma unroll
-  for (int j = 0; j < NB; ++j)
-    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[j], floatx4{0.f, 0.f, 0.f, 0.f}, 0,
-                                                     0, 0);
+  for (int q = 0; q < 4; ++q) {
+    const int y = by + q;
+    if (y >= a.h) break;
+    bf16x8 vf;
 #pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const int n = n0 + j * 16 + r;
-    if (n >= a.cout) continue;
-    const float bias = a.bias ? a.bias[n] : 0.f;
+    for (int j = 0; j < 8; ++j) {
+      const uint16_t e = sB[off[j] + 18 * q];
+      vf[j] = __builtin_bit_cast(__bf16, 8 * g + j < 27 ? e : static_cast<uint16_t>(0));
+    }
+    const int64_t o = o_img + (static_cast<int64_t>(z) * a.h + y) * a.w + x;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int rr = 4 * g + e;
-      const int x = bx + (rr & 3), y = by + (rr >> 2), z = bz + wave;
-      if (x >= a.w || y >= a.h || z >= a.d) continue;
-      const int64_t o = o_img + (static_cast<int64_t>(z) * a.h + y) * a.w + x;
-      float v = acc[j][e] + bias;
-      if (a.skip) v += from_bf16(a.skip[o * a.cout + n]);
-      if (a.relu) v = fmaxf(v, 0.f);
-      if (a.y_f32)
-        static_cast<float*>(a.y)[o * a.cout + n] = v;
-      else
-        static_cast<uint16_t*>(a.y)[o * a.cout + n] = to_bf16(v);
+    for (int p = 0; p < NP; ++p) {
+      floatx4 acc[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[p][j], vf,
+                                                         floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      const int n = n0 + 32 * p + 8 * g;
+      const int64_t e0 = o * a.cout + n;
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = acc[i >> 2][i & 3] + bias[p][i];
+      if (x >= a.w) continue;  // (every lane takes part in the matrix products)
+      if (vec) {
+        if (n >= a.cout) continue;
+        if (a.skip) {
+          const uint4 sk = *reinterpret_cast<const uint4*>(a.skip + e0);
+          const uint16_t* sh = reinterpret_cast<const uint16_t*>(&sk);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) v[i] += from_bf16(sh[i]);
+        }
+        if (a.relu) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) v[i] = fmaxf(v[i], 0.f);
+        }
+        if (a.y_f32) {
+          float4* dst = reinterpret_cast<float4*>(static_cast<float*>(a.y) + e0);
+          dst[0] = make_float4(v[0], v[1], v[2], v[3]);
+          dst[1] = make_float4(v[4], v[5], v[6], v[7]);
+        } else {
+          uint4 u;
+          uint16_t* uh = reinterpret_cast<uint16_t*>(&u);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) uh[i] = to_bf16(v[i]);
+          *reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.y) + e0) = u;
+        }
+        continue;
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (n + i >= a.cout) continue;
+        if (a.skip) v[i] += from_bf16(a.skip[e0 + i]);
+        if (a.relu) v[i] = fmaxf(v[i], 0.f);
+        if (a.y_f32)
+          static_cast<float*>(a.y)[e0 + i] = v[i];
+        else
+          static_cast<uint16_t*>(a.y)[e0 + i] = to_bf16(v[i]);
+      }
     }
   }
 }
@@ -2498,14 +2547,16 @@ hipError_t launch_conv(const ConvArgs& args, hipStream_t s) {
   ConvArgs a = args;
   const int nb = conv_nb(a);
   if ((a.geo == kConv3 || a.geo == kConv3T) && a.cin == 1) {
-    const dim3 grid(static_cast<unsigned>(brick_tiles(a, 1)),
-                    static_cast<unsigned>(brick_ngroups(a)), 1);
-    if (nb == 4)
-      conv3_scalar_kernel<4><<<grid, 256, 0, s>>>(a);
-    else if (nb == 2)
-      conv3_scalar_kernel<2><<<grid, 256, 0, s>>>(a);
+    const int64_t tiles = static_cast<int64_t>(a.batch) * ((a.w + 15) / 16) * ((a.h + 3) / 4) *
+                          ((a.d + 3) / 4);
+    const int np = a.cout > 32 ? 2 : 1;
+    const dim3 grid(static_cast<unsigned>(tiles),
+                    static_cast<unsigned>((a.cout + 32 * np - 1) / (32 * np)), 1);
+    const int vec = a.cout % 8 == 0 && aligned16(a.y) && aligned16(a.skip);
+    if (np == 2)
+      conv3_scalar_kernel<2><<<grid, 256, 0, s>>>(a, vec);
     else
-      conv3_scalar_kernel<1><<<grid, 256, 0, s>>>(a);
+      conv3_scalar_kernel<1><<<grid, 256, 0, s>>>(a, vec);
     return hipGetLastError();
   }
   if (a.gmask && (!conv_folds_grad(a) || !a.gpart)) return hipErrorInvalidValue;

@@ -258,3 +258,43 @@ def test_gradients_accumulate():
         twice = d.grads()
     assert np.any(once)
     assert np.array_equal(twice, 2 * once)
+
+
+@pytest.mark.parametrize("shape,co,skip,relu,f32,shift", [
+    ((3, 5, 7), 8, False, True, False, 0),     # less than a tile, a quarter of the channels
+    ((5, 9, 17), 40, True, True, False, 0),    # one voxel past a tile, skip
+    ((4, 4, 16), 64, False, False, True, 0),   # exactly a tile, FP32
+    ((6, 7, 33), 100, True, True, True, 0),    # channels in fours
+    ((4, 5, 20), 33, True, False, False, 0),
+    ((4, 5, 20), 32, True, True, False, 3),    # operands off 16-byte alignment
+])
+def test_one_channel_layer_edges(shape, co, skip, relu, f32, shift):
+    """3x3x3 layers of one input channel against the oracle on BF16 operands:
+    FP32 sums of 27 products (1e-5 of the sum of their sizes), then one BF16
+    rounding (2^-8) unless the output is FP32."""
+    import test_gpu_nn as T
+    t = T.torch()
+    say("[gpu] one channel", shape, co, skip, relu, f32, shift)
+    x, w, b = T.layer_case("conv3", shape, 1, co, 71)
+    wq = T.O.bf16(w)
+    sk = T.O.bf16(np.random.default_rng(72).standard_normal(shape + (co,))) if skip else None
+
+    def placed(a, dtype):
+        buf = t.zeros(a.size + shift, dtype=dtype, device="cuda")
+        v = buf[shift:].view(a.shape)
+        v.copy_(t.from_numpy(np.ascontiguousarray(a)))
+        return v
+
+    y = placed(np.zeros(shape + (co,), np.float32), t.float32 if f32 else t.bfloat16)
+    T.nn.mcx_nn_layer_forward(T.nn.MCX_NN_CONV3, shape, 1, co, placed(x, t.bfloat16), T.dev_f32(w),
+                              T.dev_f32(b), y=y, y_f32=f32, relu=relu,
+                              skip=None if sk is None else placed(sk, t.bfloat16))
+    ref = T.FWD["conv3"](x, wq, b)
+    size = T.FWD["conv3"](np.abs(x), np.abs(wq), np.abs(b))
+    if skip:
+        ref, size = ref + sk, size + np.abs(sk)
+    if relu:
+        ref = np.maximum(ref, 0)
+    got = y.float().cpu().numpy()
+    lim = 1e-5 * size + (0 if f32 else 2.0 ** -8 * np.abs(ref))
+    assert np.all(np.abs(got - ref) <= lim + 1e-30)
