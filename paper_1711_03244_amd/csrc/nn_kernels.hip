@@ -402,6 +402,16 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// Where the 16-byte chunk j of a row of 64 bytes lies: slot j ^ row_slot(row
+// index / 4) for weight rows, j ^ plane_slot(y) for voxel rows of planes 6
+// voxels wide.  16-byte LDS reads are served 16 lanes at a time (lanes 0-3,
+// 12-15, 20-27, then 4-11, 16-19, 28-31, and so in the upper half: measured,
+// no bank conflicts this way against one in two reads when the slots follow
+// the rows as if lanes 0-15 went together), and these spread each such group
+// over all 64 banks.
+__device__ __forceinline__ int row_slot(int q) { return ((q ^ (q >> 1)) & 1) << 1 | ((q >> 1) & 1); }
+__device__ __forceinline__ int plane_slot(int y) { return (y & 1) << 1; }
+
 // A workgroup barrier that waits for this wave's LDS operations but not, as
 // __syncthreads does, for all its global loads: those in flight towards LDS
 // are waited for by count (wait_vm) where they are due.
@@ -412,30 +422,42 @@ __device__ __forceinline__ void barrier_lds() {
   asm volatile("" ::: "memory");
 }
 
-// kConv3 / kConv3T with cin a multiple of 32: a workgroup owns a 4 x 4 x 4MZ
-// tile of output voxels and 16 NB output channels.  Per chunk of 32 input
-// channels the 6 x 6 x (4MZ + 2) input brick (tile plus halo, zero outside
-// the volume) is staged in LDS, and the chunk's weights pass through a ring
-// of stages of three taps (one dz, dy).  Four compute waves, kWN of them side
-// by side along the channels, take their A fragments from the brick and their
-// B fragments from the stage and issue no global memory operation; two
-// loader waves stream the weights (three stages ahead) and the next chunk's
-// brick by direct global-to-LDS loads, each waiting only for the loads of
-// the stage that is due.  One barrier per stage.
-// What bounds it: staging.  Loading a plane's weights, a barrier, 9 taps,
-// a barrier left the waves waiting for loads 54-74 % of their cycles; with
-// the loads ahead the LDS reads of the fragments are next (two waves side by
-// side read 4 fragments for 4 matrix instructions, four in a column 5).
-// 32^3 64 -> 64: 30 -> 20 us (eight images in a launch: 17 us each), 16^3
-// 128 -> 128 and 8^3 256 -> 256 17 and 15 us (eight: 8 and 4 us each).
-// Layouts as in the resident kernel: brick voxel v at v * 64 bytes, its
-// 16-byte chunk j in slot j ^ (y & 3); weight row n at n * 64 bytes, chunk j
-// in slot j ^ ((n >> 2) & 3).
+// bits 0 .. n - 1: which of the positions p0 .. p0 + n - 1 are outside [0, size)
+__device__ __forceinline__ uint32_t outside(int p0, int n, int size) {
+  uint32_t m = 0;
+  for (int i = 0; i < n; ++i) m |= p0 + i < 0 || p0 + i >= size ? 1u << i : 0u;
+  return m;
+}
+
+// kConv3 / kConv3T with cin a multiple of 32: a workgroup owns 16 NB output
+// channels and walks the 4 x 4 x 4MZ tiles of output voxels blockIdx.x,
+// + gridDim.x, ... of all images.  Per chunk of 32 input channels the
+// 6 x 6 x (4MZ + 2) input brick (tile plus halo, zero outside the volume) is
+// staged in LDS, and the chunk's weights pass through a ring of stages of
+// three taps (one dz, dy).  Four compute waves, kWN of them side by side along
+// the channels, take their fragments of voxels from the brick and of weights
+// from the stage and issue no global loads; two loader waves stream the
+// weights (three stages ahead) and the next chunk's brick, also across tiles,
+// by direct global-to-LDS loads, each waiting only for the loads of the stage
+// that is due.  One barrier per stage.
+// What bounds it: for many images the matrix instructions, 0.73 of the 1.12
+// PFLOP/s that a large matrix product reaches; for one image filling and
+// draining the pipeline.  Measured: a barrier for every plane of 9 taps and
+// weights loaded by the waves that compute, 32^3 64 -> 64 30 us; the loader
+// waves 20.2; eight images with a workgroup for each tile 134, walking the tiles
+// (the next one's bricks loading meanwhile) with 4 x 4 x 16 voxels, 16-byte stores
+// and fragments read across the stages 79.  16^3 128 -> 128: 63 -> 39 for
+// eight, 16.6 for one; 8^3 256 -> 256: 34 and 10.3 + 4.6.
+// Layouts: brick voxel v at v * 64 bytes, its 16-byte chunk j in slot
+// j ^ plane_slot(y); weight row n at n * 64 bytes, chunk j in slot
+// j ^ row_slot((n >> kShift) & 3).  The channels are the product's rows and the voxels
+// its columns, as in up_kernel: with two channel blocks per wave a lane's sums
+// are 8 consecutive channels of one voxel (row 4 g + i of block j of a pair is
+// channel 8 g + 4 j + i), with one block 4.
 // The chunks are reduced in a.ranges equal ranges whose sums are added in
 // order.  With gridDim.z = a.ranges > 1 each grid z index takes one of them
 // and stores its raw sums to the workspace part[z][out voxel][cout] for
 // split_reduce_kernel to finish; with gridDim.z == 1 a workgroup takes all.
-// Tiles of a.batch images follow one another along the grid.
 template <int NB, int MZ>
 struct Brick {
   static constexpr int kBZ = 4 * MZ + 2;
@@ -445,76 +467,116 @@ struct Brick {
   static constexpr int kStageLoads = 3 * NB;                 // wave loads of a stage
   static constexpr int kStageBytes = kStageLoads * 1024;
   static constexpr int kRing = 4;
-  static constexpr int kWN = NB >= 2 ? 2 : 1;                // compute waves along the channels
-  static constexpr int kSW = 4 * MZ * kWN / 4;               // z-slices per wave
+  static constexpr int kWN = NB == 4 && MZ < 4 ? 2 : 1;      // compute waves along the channels
+  static constexpr int kSW = MZ * kWN;                       // z-slices per wave
   static constexpr int kCW = NB / kWN;                       // 16-channel blocks per wave
+  static constexpr int kShift = kCW >= 2 ? 3 : 2;
 };
+
+// The workgroup's i-th tile: its first voxel (bx, by, bz) and image
+template <int MZ>
+__device__ __forceinline__ void brick_tile(const ConvArgs& a, int i, int& img, int& bx, int& by,
+                                           int& bz) {
+  const int tx_n = (a.w + 3) >> 2, ty_n = (a.h + 3) >> 2;
+  const int ntile = tx_n * ty_n * ((a.d + 4 * MZ - 1) / (4 * MZ));
+  const int t = blockIdx.x + i * gridDim.x;
+  img = t / ntile;
+  const int tile = t - img * ntile;
+  bx = (tile % tx_n) * 4;
+  by = ((tile / tx_n) % ty_n) * 4;
+  bz = (tile / (tx_n * ty_n)) * (4 * MZ);
+}
 
 // Loader wave LW (0 or 1) of a workgroup: every other wave load.
 template <int NB, int MZ, int LW>
-__device__ __forceinline__ void brick_loader(const ConvArgs& a, const uint16_t* x, char* s_br,
-                                             char* s_w, int lane, int bx, int by, int bz, int n0,
-                                             int c_begin, int nchunks) {
+__device__ __forceinline__ void brick_loader(const ConvArgs& a, char* s_br, char* s_w, int lane,
+                                             int n0, int c_begin, int nchunks, int ntiles) {
   using K = Brick<NB, MZ>;
   constexpr int kB = (K::kBrickLoads + 1 - LW) / 2;  // this wave's loads of a brick
   constexpr int kW = (K::kStageLoads + 1 - LW) / 2;  // and of a stage
-  // brick: source of this lane's piece of each load at the first chunk
-  const uint16_t* zero = reinterpret_cast<const uint16_t*>(g_zero16);
-  const uint16_t* src[kB];
-  uint32_t inside = 0;
+  // Per brick load: this lane's offset from the tile's first voxel, and the
+  // brick position as one bit for each of x, y and z (bit 31: no such
+  // piece), which a tile's mask of what lies outside the volume tells apart
+  // in two instructions.
+  const uint16_t* zero = reinterpret_cast<const uint16_t*>(g_zero16) +
+                         ((blockIdx.x * 64 + lane) & (kZeroChunks - 1)) * 8;
+  int64_t rel[kB];
+  uint32_t pos[kB];
 #pragma unroll
   for (int k = 0; k < kB; ++k) {
     const int p = (2 * k + LW) * 64 + lane;
-    const int v = p >> 2, vx = v % 6, vy = (v / 6) % 6, vz = v / 36;
-    const int gx = bx + vx - 1, gy = by + vy - 1, gz = bz + vz - 1;
-    const bool in = p < K::kPieces && gx >= 0 && gy >= 0 && gz >= 0 && gx < a.in_w &&
-                    gy < a.in_h && gz < a.in_d;
-    const int j = (p & 3) ^ (vy & 3);
-    src[k] = in ? x + ((static_cast<int64_t>(gz) * a.in_h + gy) * a.in_w + gx) * a.cin +
-                      c_begin + j * 8
-                : zero + ((blockIdx.x * 192 + k * 64 + lane) & (kZeroChunks - 1)) * 8;
-    inside |= in ? 1u << k : 0u;
+    const int v = p >> 2, x = v % 6, y = (v / 6) % 6, z = v / 36;
+    const int j = (p & 3) ^ plane_slot(y);
+    rel[k] = ((static_cast<int64_t>(z - 1) * a.in_h + (y - 1)) * a.in_w + (x - 1)) * a.cin + j * 8;
+    pos[k] = p < K::kPieces ? 1u << x | 1u << (6 + y) | 1u << (12 + z) : 1u << 31;
   }
-  auto load_brick = [&](int chunk) {
-    char* dst = s_br + (chunk & 1) * K::kBrickBytes;
+  // the next brick: chunk b_chunk of tile b_tile, into buffer b_buf
+  const uint16_t* x0 = nullptr;
+  uint32_t out = 0;
+  int b_tile = 0, b_chunk = 0, b_buf = 0;
+  auto load_brick = [&]() {
+    if (b_chunk == 0) {
+      int img, bx, by, bz;
+      brick_tile<MZ>(a, b_tile, img, bx, by, bz);
+      x0 = a.x + (((static_cast<int64_t>(img) * a.in_d + bz) * a.in_h + by) * a.in_w + bx) * a.cin +
+           c_begin;
+      out = 1u << 31 | outside(bx - 1, 6, a.in_w) | outside(by - 1, 6, a.in_h) << 6 |
+            outside(bz - 1, K::kBZ, a.in_d) << 12;
+    }
+    const uint16_t* xc = x0 + b_chunk * 32;
+    char* dst = s_br + b_buf * K::kBrickBytes;
 #pragma unroll
     for (int k = 0; k < kB; ++k)
-      load_lds16(src[k] + ((inside >> k) & 1u ? chunk * 32 : 0), dst + (2 * k + LW) * 1024);
+      load_lds16(pos[k] & out ? zero : xc + rel[k], dst + (2 * k + LW) * 1024);
+    b_buf ^= 1;
+    if (++b_chunk == nchunks) {
+      b_chunk = 0;
+      ++b_tile;
+    }
   };
-  // weights: rows 16 rb + lane / 4 of the workgroup's 16 NB rows
-  const int row = lane >> 2, j = (lane & 3) ^ ((row >> 2) & 3);
+  // weights: row lane / 4 of each 16 of the workgroup's 16 NB rows
   uint32_t off[NB];
 #pragma unroll
-  for (int rb = 0; rb < NB; ++rb)
-    off[rb] = static_cast<uint32_t>(n0 + 16 * rb + row) * static_cast<uint32_t>(a.kpad) + j * 8;
-  auto load_stage = [&](int s) {
-    const int chunk = s / 9, t0 = (s - chunk * 9) * 3;
-    char* dst = s_w + (s & (K::kRing - 1)) * K::kStageBytes;
+  for (int rb = 0; rb < NB; ++rb) {
+    const int n = 16 * rb + (lane >> 2);
+    off[rb] = static_cast<uint32_t>(n0 + n) * static_cast<uint32_t>(a.kpad) +
+              ((lane & 3) ^ row_slot((n >> K::kShift) & 3)) * 8;
+  }
+  // the next stage: taps 3 w_row .. of chunk w_chunk, into slot w_slot
+  int w_row = 0, w_chunk = 0, w_slot = 0;
+  auto load_stage = [&]() {
+    char* dst = s_w + w_slot * K::kStageBytes;
 #pragma unroll
     for (int k = 0; k < kW; ++k) {
       const int b = 2 * k + LW, dx = b / NB, rb = b % NB;
-      const uint16_t* base = a.bt + (t0 + dx) * a.cin + c_begin + chunk * 32;
+      const uint16_t* base = a.bt + (3 * w_row + dx) * a.cin + c_begin + w_chunk * 32;
       load_lds16(base + off[rb], dst + b * 1024);
     }
-  };
-  const int S = 9 * nchunks;
-  load_brick(0);
-#pragma unroll
-  for (int s = 0; s < 3; ++s) load_stage(s);
-  int chunk = 0, js = 0;  // s = 9 chunk + js
-  for (int s = 0; s < S; ++s) {
-    // stage s has landed once at most the loads of the two stages after it,
-    // and of a brick asked for after it (at js == 0), are outstanding
-    if (s + 2 >= S) {
-      if (s + 1 < S) wait_vm<kW>(); else wait_vm<0>();
-    } else if ((js == 1 || js == 2) && chunk + 1 < nchunks) {
-      wait_vm<2 * kW + kB>();
-    } else {
-      wait_vm<2 * kW>();
+    w_slot = (w_slot + 1) & (K::kRing - 1);
+    if (++w_row == 9) {
+      w_row = 0;
+      if (++w_chunk == nchunks) w_chunk = 0;
     }
+  };
+  const int C = ntiles * nchunks, S = 9 * C;
+  load_brick();
+#pragma unroll
+  for (int s = 0; s < 3; ++s) load_stage();
+  wait_vm<2 * kW>();
+  barrier_lds();  // the first stage has landed
+  int chunk = 0, js = 0;  // s = 9 chunk + js, chunks counted over all tiles
+  for (int s = 0; s < S; ++s) {
+    // stages up to s + 1 have landed once at most the loads of stage s + 2,
+    // and of a brick asked for just before it (at js == 0), are outstanding
+    if (s + 2 >= S)
+      wait_vm<0>();
+    else if (js == 1 && chunk + 1 < C)
+      wait_vm<kW + kB>();
+    else
+      wait_vm<kW>();
     barrier_lds();
-    if (js == 0 && chunk + 1 < nchunks) load_brick(chunk + 1);
-    if (s + 3 < S) load_stage(s + 3);
+    if (js == 0 && chunk + 1 < C) load_brick();
+    if (s + 3 < S) load_stage();
     if (++js == 9) {
       js = 0;
       ++chunk;
@@ -522,126 +584,199 @@ __device__ __forceinline__ void brick_loader(const ConvArgs& a, const uint16_t* 
   }
 }
 
+// N (4 or 8) consecutive channels of output voxel o: bias, skip, ReLU and
+// store, or the raw sums to part.  vec: channels in eights, aligned operands.
+template <int N>
+__device__ __forceinline__ void put_channels(const ConvArgs& a, const floatx4 (&sum)[N / 4],
+                                             int64_t o, int n, float* part, bool vec) {
+  const int64_t e0 = o * a.cout + n;
+  if (vec) {
+    if (n >= a.cout) return;
+    if (part) {
+#pragma unroll
+      for (int j = 0; j < N / 4; ++j) *reinterpret_cast<floatx4*>(part + e0 + 4 * j) = sum[j];
+      return;
+    }
+    float v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = sum[i >> 2][i & 3] + (a.bias ? a.bias[n + i] : 0.f);
+    typedef uint32_t words __attribute__((ext_vector_type(N / 2)));
+    if (a.skip) {
+      const words sk = *reinterpret_cast<const words*>(a.skip + e0);
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        v[i] += from_bf16(static_cast<uint16_t>(i & 1 ? sk[i >> 1] >> 16 : sk[i >> 1] & 0xffffu));
+    }
+    if (a.relu) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[i] = fmaxf(v[i], 0.f);
+    }
+    if (a.y_f32) {
+#pragma unroll
+      for (int j = 0; j < N / 4; ++j)
+        *reinterpret_cast<floatx4*>(static_cast<float*>(a.y) + e0 + 4 * j) =
+            floatx4{v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]};
+    } else {
+      words u;
+#pragma unroll
+      for (int i = 0; i < N; i += 2) u[i >> 1] = to_bf16(v[i]) | uint32_t(to_bf16(v[i + 1])) << 16;
+      *reinterpret_cast<words*>(static_cast<uint16_t*>(a.y) + e0) = u;
+    }
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (n + i >= a.cout) return;
+    float v = sum[i >> 2][i & 3];
+    if (part) {
+      part[e0 + i] = v;
+      continue;
+    }
+    v += a.bias ? a.bias[n + i] : 0.f;
+    if (a.skip) v += from_bf16(a.skip[e0 + i]);
+    if (a.relu) v = fmaxf(v, 0.f);
+    if (a.y_f32)
+      static_cast<float*>(a.y)[e0 + i] = v;
+    else
+      static_cast<uint16_t*>(a.y)[e0 + i] = to_bf16(v);
+  }
+}
+
 template <int NB, int MZ>
-__global__ void __launch_bounds__(384) conv3_brick_kernel(ConvArgs a) {
+__global__ void __launch_bounds__(384) conv3_brick_kernel(ConvArgs a, int vec) {
   using K = Brick<NB, MZ>;
   __shared__ __align__(16) char s_br[2 * K::kBrickBytes];
   __shared__ __align__(16) char s_w[K::kRing * K::kStageBytes];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int tx_n = (a.w + 3) >> 2, ty_n = (a.h + 3) >> 2;
-  const int ntile = tx_n * ty_n * ((a.d + 4 * MZ - 1) / (4 * MZ));
-  const int img = blockIdx.x / ntile, tile = blockIdx.x - img * ntile;
-  const int bx = (tile % tx_n) * 4;
-  const int by = ((tile / tx_n) % ty_n) * 4;
-  const int bz = (tile / (tx_n * ty_n)) * (4 * MZ);
+  const int tiles = a.batch * ((a.w + 3) >> 2) * ((a.h + 3) >> 2) * ((a.d + 4 * MZ - 1) / (4 * MZ));
+  const int ntiles = (tiles - blockIdx.x + gridDim.x - 1) / gridDim.x;
   const int n0 = blockIdx.y * 16 * NB;
   const int split_len = a.cin / static_cast<int>(gridDim.z);  // a multiple of kBK
   const int c_begin = static_cast<int>(blockIdx.z) * split_len;
   const int nchunks = split_len / kBK;
-  const uint16_t* x_img = a.x + static_cast<int64_t>(img) * a.in_d * a.in_h * a.in_w * a.cin;
   if (wave == 4) {
-    brick_loader<NB, MZ, 0>(a, x_img, s_br, s_w, lane, bx, by, bz, n0, c_begin, nchunks);
+    brick_loader<NB, MZ, 0>(a, s_br, s_w, lane, n0, c_begin, nchunks, ntiles);
     return;
   }
   if (wave == 5) {
-    brick_loader<NB, MZ, 1>(a, x_img, s_br, s_w, lane, bx, by, bz, n0, c_begin, nchunks);
+    brick_loader<NB, MZ, 1>(a, s_br, s_w, lane, n0, c_begin, nchunks, ntiles);
     return;
   }
 
   const int sgn = a.geo == kConv3 ? 1 : -1;
-  const int r = lane & 15;            // A row of this lane: voxel (r & 3, r >> 2) of a slice
+  const int r = lane & 15;            // this lane's voxel (r & 3, r >> 2) of a slice
   const int ox = r & 3, oy = r >> 2;
-  const int kq = lane >> 4;           // this lane's 16-byte chunk of the 32 channels
+  const int g = lane >> 4;            // and its 16-byte chunk of the 32 channels
   const int z0 = wave / K::kWN * K::kSW;          // the wave's first slice
   const int cb = wave % K::kWN * K::kCW;          // and 16-channel block
-  // the current range's sums, those of the ranges before it
-  floatx4 acc[K::kSW][K::kCW], tot[K::kSW][K::kCW];
+  // byte offsets in a stage of this lane's weight rows
+  int wo[K::kCW];
 #pragma unroll
-  for (int q = 0; q < K::kSW; ++q)
-#pragma unroll
-    for (int c = 0; c < K::kCW; ++c) acc[q][c] = tot[q][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < K::kCW; ++c) {
+    const int n = K::kCW >= 2 ? 16 * cb + 32 * (c >> 1) + 8 * (r >> 2) + 4 * (c & 1) + (r & 3)
+                              : 16 * cb + r;
+    wo[c] = n * 64 + ((g ^ row_slot((n >> K::kShift) & 3)) << 4);
+  }
+  const int64_t vox = static_cast<int64_t>(a.d) * a.h * a.w;
+  float* part = gridDim.z > 1 ? a.part + static_cast<int64_t>(blockIdx.z) * a.batch * vox * a.cout
+                              : nullptr;
   const int range_chunks = gridDim.z > 1 ? nchunks : nchunks / a.ranges;
 
-  int s = 0, range_left = range_chunks;
-  for (int chunk = 0; chunk < nchunks; ++chunk) {
-    if (range_left == 0) {  // the next range starts from zero
+  // this lane's voxel offset for dy = -1, 0, 1 (in the taps' order)
+  int ao[3];
 #pragma unroll
-      for (int q = 0; q < K::kSW; ++q)
+  for (int k = 0; k < 3; ++k) {
+    const int yy = oy + 1 + sgn * (k - 1);
+    ao[k] = ((z0 + 1) * 36 + yy * 6 + ox + 1) * 64 + ((g ^ plane_slot(yy)) << 4);
+  }
+  bf16x8 af[2][K::kSW], bf[2][K::kCW];
+  auto read = [&](const char* br, int slot, int t, bf16x8 (&fa)[K::kSW], bf16x8 (&fb)[K::kCW]) {
+    const char* wst = s_w + slot * K::kStageBytes + (t % 3) * 16 * NB * 64;
+    const char* ab = br + sgn * ((t / 9 - 1) * 36 + (t % 3 - 1)) * 64 + ao[(t / 3) % 3];
 #pragma unroll
-        for (int c = 0; c < K::kCW; ++c) {
-          tot[q][c] = chunk == range_chunks ? acc[q][c] : tot[q][c] + acc[q][c];
-          acc[q][c] = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
-      range_left = range_chunks;
-    }
-    --range_left;
-    const char* br = s_br + (chunk & 1) * K::kBrickBytes;
-    for (int row = 0; row < 9; ++row, ++s) {  // taps 3 row .. 3 row + 2
-      barrier_lds();  // stage s (and the chunk's brick) has landed
-      const char* wst = s_w + (s & (K::kRing - 1)) * K::kStageBytes;
-      const int dz = sgn * (row / 3 - 1), dy = sgn * (row % 3 - 1);
-      const int yy = oy + 1 + dy;
-      const char* ab = br + (((z0 + 1 + dz) * 6 + yy) * 6 + ox + 1) * 64 + ((kq ^ (yy & 3)) << 4);
-      const char* bb = wst + (16 * cb + r) * 64 + ((kq ^ ((r >> 2) & 3)) << 4);
-      bf16x8 af[3][K::kSW], bf[3][K::kCW];
+    for (int c = 0; c < K::kCW; ++c) fb[c] = *reinterpret_cast<const bf16x8*>(wst + wo[c]);
 #pragma unroll
-      for (int t = 0; t < 3; ++t) {
+    for (int q = 0; q < K::kSW; ++q) fa[q] = *reinterpret_cast<const bf16x8*>(ab + q * 36 * 64);
+  };
+  int slot = 0, buf = 0;
+  barrier_lds();  // the first stage has landed
+  read(s_br, 0, 0, af[0], bf[0]);
+  for (int ti = 0; ti < ntiles; ++ti) {
+    // the current range's sums, those of the ranges before it
+    floatx4 acc[K::kSW][K::kCW], tot[K::kSW][K::kCW];
 #pragma unroll
-        for (int c = 0; c < K::kCW; ++c)
-          bf[t][c] = *reinterpret_cast<const bf16x8*>(bb + (t * 16 * NB + 16 * c) * 64);
+    for (int q = 0; q < K::kSW; ++q)
+#pragma unroll
+      for (int c = 0; c < K::kCW; ++c) acc[q][c] = tot[q][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    int range_left = range_chunks;
+    for (int chunk = 0; chunk < nchunks; ++chunk) {
+      if (range_left == 0) {  // the next range starts from zero
 #pragma unroll
         for (int q = 0; q < K::kSW; ++q)
-          af[t][q] = *reinterpret_cast<const bf16x8*>(ab + (q * 36 + sgn * (t - 1)) * 64);
-      }
-      __builtin_amdgcn_sched_barrier(0);  // all reads ahead of the matrix instructions
 #pragma unroll
-      for (int t = 0; t < 3; ++t)
+          for (int c = 0; c < K::kCW; ++c) {
+            tot[q][c] = chunk == range_chunks ? acc[q][c] : tot[q][c] + acc[q][c];
+            acc[q][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+          }
+        range_left = range_chunks;
+      }
+      --range_left;
+      // taps t = 3 row + dx; each one's fragments are read while the tap
+      // before runs, across stages and chunks
+      const char* br = s_br + buf * K::kBrickBytes;
+#pragma unroll
+      for (int t = 0; t < 27; ++t) {
+        if (t % 3 == 0) barrier_lds();  // this stage and the next have landed
+        if (t < 26) {
+          if (t % 3 == 2) slot = (slot + 1) & (K::kRing - 1);
+          read(br, slot, t + 1, af[(t + 1) & 1], bf[(t + 1) & 1]);
+        } else {
+          slot = (slot + 1) & (K::kRing - 1);
+          buf ^= 1;
+          if (chunk + 1 < nchunks || ti + 1 < ntiles)
+            read(s_br + buf * K::kBrickBytes, slot, 0, af[1], bf[1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // those reads ahead of the matrix instructions
 #pragma unroll
         for (int q = 0; q < K::kSW; ++q)
 #pragma unroll
           for (int c = 0; c < K::kCW; ++c)
-            acc[q][c] =
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[t][q], bf[t][c], acc[q][c], 0, 0, 0);
+            acc[q][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[t & 1][c], af[t & 1][q],
+                                                                acc[q][c], 0, 0, 0);
+      }
+#pragma unroll
+      for (int q = 0; q < K::kSW; ++q) af[0][q] = af[1][q];
+#pragma unroll
+      for (int c = 0; c < K::kCW; ++c) bf[0][c] = bf[1][c];
     }
-  }
-
-  // epilogue: rows 4 (lane >> 4) + e of each of the wave's slices
-  if (range_chunks < nchunks) {  // several ranges, added in order
+    if (range_chunks < nchunks) {  // several ranges, added in order
 #pragma unroll
-    for (int q = 0; q < K::kSW; ++q)
+      for (int q = 0; q < K::kSW; ++q)
 #pragma unroll
-      for (int c = 0; c < K::kCW; ++c) acc[q][c] = tot[q][c] + acc[q][c];
-  }
-  const bool split = gridDim.z > 1;
-  const int64_t vox = static_cast<int64_t>(a.d) * a.h * a.w, o_img = img * vox;
-  float* part = split ? a.part + static_cast<int64_t>(blockIdx.z) * a.batch * vox * a.cout : nullptr;
+        for (int c = 0; c < K::kCW; ++c) acc[q][c] = tot[q][c] + acc[q][c];
+    }
+    // epilogue: this lane's voxel of each of the wave's slices
+    int img, bx, by, bz;
+    brick_tile<MZ>(a, ti, img, bx, by, bz);
+    const int x = bx + ox, y = by + oy;
 #pragma unroll
-  for (int q = 0; q < K::kSW; ++q)
+    for (int q = 0; q < K::kSW; ++q) {
+      const int z = bz + z0 + q;
+      if (x >= a.w || y >= a.h || z >= a.d) continue;
+      const int64_t o = img * vox + (static_cast<int64_t>(z) * a.h + y) * a.w + x;
+      if constexpr (K::kCW >= 2) {
 #pragma unroll
-    for (int c = 0; c < K::kCW; ++c) {
-      const int n = n0 + (cb + c) * 16 + (lane & 15);
-      if (n >= a.cout) continue;
-      const float bias = a.bias ? a.bias[n] : 0.f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int rr = (lane >> 4) * 4 + e;
-        const int x = bx + (rr & 3), y = by + (rr >> 2), z = bz + z0 + q;
-        if (x >= a.w || y >= a.h || z >= a.d) continue;
-        const int64_t o = o_img + (static_cast<int64_t>(z) * a.h + y) * a.w + x;
-        if (split) {
-          part[o * a.cout + n] = acc[q][c][e];
-          continue;
+        for (int c = 0; c < K::kCW; c += 2) {
+          const floatx4 v[2] = {acc[q][c], acc[q][c + 1]};
+          put_channels<8>(a, v, o, n0 + 16 * (cb + c) + 8 * g, part, vec);
         }
-        float v = acc[q][c][e] + bias;
-        if (a.skip) v += from_bf16(a.skip[o * a.cout + n]);
-        if (a.relu) v = fmaxf(v, 0.f);
-        if (a.y_f32)
-          static_cast<float*>(a.y)[o * a.cout + n] = v;
-        else
-          static_cast<uint16_t*>(a.y)[o * a.cout + n] = to_bf16(v);
+      } else {
+        const floatx4 v[1] = {acc[q][0]};
+        put_channels<4>(a, v, o, n0 + 16 * cb + 4 * g, part, vec);
       }
     }
+  }
 }
 
 // --------------------------------- 3x3x3 conv, 32 input channels, weights resident
@@ -662,15 +797,16 @@ __global__ void __launch_bounds__(384) conv3_brick_kernel(ConvArgs a) {
 // which complete in issue order): one barrier per tile, which does not wait
 // for transfers (barrier_lds).  What bounds a tile are the compute waves'
 // fragment reads from LDS, 4 KB per 4 matrix instructions with both operands
-// read for every tap, so the weights of most taps stay in registers.  Measured
-// at 64^3, 32 -> 32 channels: 24.5 -> 21.6 us (BF16 out), 26.1 -> 22.2 (input
-// gradient, FP32 out); 32 -> 16: 19.0 -> 17.0; kGrad 26.5 -> 26.7: there the
-// output waves' work is the longer.  Plane layout: voxel
+// read for every tap, so the weights of most taps stay in registers, and the
+// plane wave's address arithmetic, so a plane's addresses are the last ones'
+// plus a plane.  Measured at 64^3, 32 -> 32 channels: 24.5 -> 21.6 us with the
+// weights in registers, -> 21 with the cheap addresses; input gradient folded
+// (kGrad) 26.5 -> 25.3; eight images 148 -> 137, where the matrix instructions
+// alone take 103 at the rate of a large product; 32 -> 16 channels, eight images,
+// 116 -> 89.  Plane layout: voxel
 // (y, x) of the plane at (y * 6 + x) * 64 bytes, its 16-byte chunk j
-// (channels 8j .. 8j + 7) in slot j ^ (y & 3), so that the 16 rows of an A
-// fragment (a 4 x 4 patch of voxels) fall on 16 different bank groups; the
-// weights of output channel n likewise at n * 64 bytes, chunk j in slot
-// j ^ ((n >> 2) & 3).
+// (channels 8j .. 8j + 7) in slot j ^ plane_slot(y); the weights of output
+// channel n likewise at n * 64 bytes, chunk j in slot j ^ row_slot((n >> 2) & 3).
 constexpr int kResPlane = 36 * 64;  // bytes per plane slot
 
 // Byte offset of byte `byte` of local voxel vl's outputs in an output tile
@@ -706,7 +842,10 @@ __device__ __forceinline__ void pin(const uint4& v) {
 constexpr int res_ahead(int nb, bool f32) { return nb == 2 && f32 ? 2 : 3; }
 // taps whose weights the compute waves hold in registers: what 256 registers
 // per lane leave room for
-constexpr int res_taps(int nb) { return nb == 2 ? 22 : 27; }
+constexpr int res_taps(int nb) { return nb == 2 ? 18 : 27; }
+// taps between reading a fragment from LDS and using it: a tap's 2 NB matrix
+// instructions take 64 or 32 cycles, an LDS read about 150
+constexpr int kAhead = 3;
 
 // kGrad: an input gradient with the next backward step folded in
 // (ConvArgs::gmask): the compute waves leave FP32 sums in LDS, the output
@@ -737,12 +876,12 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
   // plane wave (which starts on the first column's planes meanwhile): lane
   // L of block bl fills slot 64 bl + L, i.e. row (16 bl + L / 4) of the
   // flattened [27][NC] rows, chunk slot L % 4, with the chunk
-  // (L % 4) ^ ((row >> 2) & 3) of that row.
+  // (L % 4) ^ row_slot((row >> 2) & 3) of that row.
   if (wave != 4) {
     const int w6 = wave < 4 ? wave : wave - 1;
     for (int bl = w6; bl < 27 * NC / 16; bl += 6) {
       const int fr = 16 * bl + (lane >> 2), tt = fr / NC, row = fr % NC;
-      const int j = (lane & 3) ^ ((row >> 2) & 3);
+      const int j = (lane & 3) ^ row_slot((row >> 2) & 3);
       __builtin_amdgcn_global_load_lds(
           (__attribute__((address_space(1))) void*)(a.bt + static_cast<int64_t>(n0 + row) * a.kpad +
                                                      tt * 32 + j * 8),
@@ -753,38 +892,46 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
   }
   for (int i = tid; i < NC; i += blockDim.x) sBias[i] = (a.bias && i < ncols) ? a.bias[n0 + i] : 0.f;
 
-  // wave 4: plane z of the column at (bx, by) into its ring slot, in three
-  // loads of 64 lanes (144 chunks: the last load has 16 lanes).  A chunk's
-  // offset and position in the plane are the same for every plane.
+  // wave 4: the planes of a column, z = -1, 0, ..., each into the next ring
+  // slot (z + 1) % kRing in three loads of 64 lanes (144 chunks: the last load
+  // has 16 lanes).  Per load the lane's address of the next plane; in the
+  // volume's x and y it moves by a plane, elsewhere it stays on zeros.
   int64_t rel[3];
-  int pos[3];  // x | y << 4 of the chunk's voxel in the plane, or -1 past it
+  uint32_t pos[3];  // the chunk's voxel in the plane, one bit for x and one for y
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const int c = k * 64 + lane;  // chunk slot within the plane
-    const int vp = c >> 2, y = vp / 6, x = vp % 6, j = (c & 3) ^ (y & 3);
+    const int vp = c >> 2, y = vp / 6, x = vp % 6, j = (c & 3) ^ plane_slot(y);
     rel[k] = (static_cast<int64_t>(y - 1) * a.in_w + (x - 1)) * 32 + j * 8;
-    pos[k] = c < 144 ? (x | y << 4) : -1;
+    pos[k] = 1u << x | 1u << (6 + y);
   }
-  const uint16_t* zero = reinterpret_cast<const uint16_t*>(g_zero16);
-  auto load_plane = [&](int64_t v0, int bx, int by, int z) {
-    const int64_t base = (v0 + (static_cast<int64_t>(z) * a.in_h + by) * a.in_w + bx) * 32;
-    const bool zin = z >= 0 && z < a.in_d;
-    const bool xyin = bx >= 1 && by >= 1 && bx + 5 <= a.in_w && by + 5 <= a.in_h;
-    char* slot = reinterpret_cast<char*>(sRing) + ((z + 1) % kRing) * kResPlane;
+  const uint16_t* zero = reinterpret_cast<const uint16_t*>(g_zero16) +
+                         ((blockIdx.x * 64 + lane) & (kZeroChunks - 1)) * 8;
+  const uint16_t* next[3];
+  int64_t step[3];
+  int p_z = 0, p_slot = 0;  // the next plane and its slot
+  auto start_column = [&](int64_t v0, int bx, int by) {
+    const uint32_t out = outside(bx - 1, 6, a.in_w) | outside(by - 1, 6, a.in_h) << 6;
+    const int64_t plane = static_cast<int64_t>(a.in_h) * a.in_w * 32;
+    const uint16_t* x0 = a.x + (v0 + static_cast<int64_t>(by) * a.in_w + bx) * 32 - plane;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      if (pos[k] < 0) continue;
-      bool in = zin && xyin;
-      if (zin && !xyin) {
-        const int gx = bx + (pos[k] & 15) - 1, gy = by + (pos[k] >> 4) - 1;
-        in = gx >= 0 && gy >= 0 && gx < a.in_w && gy < a.in_h;
-      }
-      const uint16_t* src =
-          in ? a.x + base + rel[k] : zero + ((blockIdx.x * 192 + k * 64 + lane) & (kZeroChunks - 1)) * 8;
-      __builtin_amdgcn_global_load_lds(
-          (__attribute__((address_space(1))) void*)(src),
-          (__attribute__((address_space(3))) void*)(slot + k * 1024), 16, 0, 0);
+      next[k] = pos[k] & out ? zero : x0 + rel[k];
+      step[k] = pos[k] & out ? 0 : plane;
     }
+    p_z = -1;
+    p_slot = 0;
+  };
+  auto load_plane = [&]() {
+    const bool zin = p_z >= 0 && p_z < a.in_d;
+    char* slot = reinterpret_cast<char*>(sRing) + p_slot * kResPlane;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      if (k < 2 || lane < 16) load_lds16(zin ? next[k] : zero, slot + k * 1024);
+      next[k] += step[k];
+    }
+    ++p_z;
+    if (++p_slot == kRing) p_slot = 0;
   };
   // waves 5 and 6: the outputs of the tile at (bx, by, bz) from sOut[b] to
   // y, every other 64 pieces each
@@ -905,11 +1052,11 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
     for (int gc = blockIdx.x; gc < ncol * a.batch; gc += gridDim.x) {
       const int img = gc / ncol, col = gc - img * ncol;
       const int bx = (col % tx_n) * 4, by = (col / tx_n) * 4;
-      const int64_t v0 = img * in_vox;
+      start_column(img * in_vox, bx, by);
       // planes -1 .. 8 min(tz_n, A): the first A tiles; wait for tile 0's
       // (all loads but those of the tiles after it, 24 per tile)
       const int zend = 8 * min(tz_n, A);
-      for (int z = -1; z <= zend; ++z) load_plane(v0, bx, by, z);
+      for (int z = -1; z <= zend; ++z) load_plane();
       const int first = min(tz_n, A) - 1;
       if (first >= 2)
         wait_vm<48>();
@@ -924,7 +1071,7 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
         // all loads but those of the tiles after it (24 per tile)
         const int last = min(k + A, tz_n - 1);  // the newest tile loaded
         if (k + A < tz_n)
-          for (int z = 8 * (k + A) + 1; z <= 8 * (k + A) + 8; ++z) load_plane(v0, bx, by, z);
+          for (int z = 0; z < 8; ++z) load_plane();
         const int pending = last - (k + 1);  // tiles whose loads may stay in flight
         if (pending >= 2)
           wait_vm<48>();
@@ -956,6 +1103,7 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
     const int r = lane & 15;
     const int ox = r & 3, oy = r >> 2;
     const int kq = lane >> 4;  // this lane's 16-byte chunk of the 32 channels
+    const int wslot = kq ^ row_slot(r >> 2);
     const char* ring = reinterpret_cast<const char*>(sRing);
     // The fragment reads bound the tile (4 KB per 4 matrix instructions of
     // a wave), so the B fragments of the first kRT taps stay in registers for
@@ -967,7 +1115,7 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
     for (int tt = 0; tt < kRT; ++tt)
 #pragma unroll
       for (int j = 0; j < NB; ++j)
-        breg[tt][j] = *reinterpret_cast<const bf16x8*>(&sW[tt][16 * j + r][kq ^ ((r >> 2) & 3)]);
+        breg[tt][j] = *reinterpret_cast<const bf16x8*>(&sW[tt][16 * j + r][wslot]);
     for (int gc = blockIdx.x; gc < ncol * a.batch; gc += gridDim.x) {
       barrier_lds();
       for (int k = 0; k < tz_n; ++k) {
@@ -977,8 +1125,8 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
 #pragma unroll
           for (int j = 0; j < NB; ++j) acc[q][j] = floatx4{0.f, 0.f, 0.f, 0.f};
         // fragments of tap tt: A from the planes (voxel of row r shifted by
-        // the tap), B from the weights; the next tap's are read while this
-        // tap's matrix instructions run
+        // the tap), B from the weights; those of the tap kAhead further on are
+        // read while this tap's matrix instructions run
         auto read_a = [&](int tt, bf16x8 (&af)[2]) {
           const int dz = sgn * (tt / 9 - 1), dy = sgn * ((tt / 3) % 3 - 1), dx = sgn * (tt % 3 - 1);
           const int yy = oy + 1 + dy;
@@ -986,23 +1134,24 @@ __global__ void __launch_bounds__(448) conv3_resident_kernel(ConvArgs a) {
           for (int q = 0; q < 2; ++q) {
             const int zs = (8 * k + wave * 2 + q + 1 + dz) % kRing;  // plane z = 8k + zi - 1
             af[q] = *reinterpret_cast<const bf16x8*>(
-                ring + zs * kResPlane + (yy * 6 + ox + 1 + dx) * 64 + ((kq ^ (yy & 3)) << 4));
+                ring + zs * kResPlane + (yy * 6 + ox + 1 + dx) * 64 + ((kq ^ plane_slot(yy)) << 4));
           }
         };
         auto read_b = [&](int tt, bf16x8 (&bc)[NB]) {
 #pragma unroll
           for (int j = 0; j < NB; ++j)
-            bc[j] = *reinterpret_cast<const bf16x8*>(&sW[tt][16 * j + r][kq ^ ((r >> 2) & 3)]);
+            bc[j] = *reinterpret_cast<const bf16x8*>(&sW[tt][16 * j + r][wslot]);
         };
-        bf16x8 bc[2][NB], af[2][2];
-        read_a(0, af[0]);
-        if constexpr (kRT == 0) read_b(0, bc[0]);
+        bf16x8 bc[kAhead + 1][NB], af[kAhead + 1][2];
+        static_assert(kRT >= kAhead, "the first taps' weights are in registers");
+#pragma unroll
+        for (int tt = 0; tt < kAhead; ++tt) read_a(tt, af[tt]);
 #pragma unroll
         for (int tt = 0; tt < 27; ++tt) {
-          const int cur = tt & 1;
-          if (tt + 1 < 27) {
-            read_a(tt + 1, af[cur ^ 1]);
-            if (tt + 1 >= kRT) read_b(tt + 1, bc[cur ^ 1]);
+          const int cur = tt % (kAhead + 1), next = tt + kAhead;
+          if (next < 27) {
+            read_a(next, af[next % (kAhead + 1)]);
+            if (next >= kRT) read_b(next, bc[next % (kAhead + 1)]);
           }
           __builtin_amdgcn_sched_barrier(0);  // keep those reads ahead of the MFMAs below
 #pragma unroll
@@ -1599,13 +1748,6 @@ struct WBrick {
   static constexpr int kBrickLoads = 23, kLoads = 31;   // wave loads: brick, then gy
   static constexpr int kStageBytes = kLoads * 1024;
 };
-
-// bits 0 .. n - 1: which of the positions p0 .. p0 + n - 1 are outside [0, size)
-__device__ __forceinline__ uint32_t outside(int p0, int n, int size) {
-  uint32_t m = 0;
-  for (int i = 0; i < n; ++i) m |= p0 + i < 0 || p0 + i >= size ? 1u << i : 0u;
-  return m;
-}
 
 template <int LW>
 __device__ __forceinline__ void wbrick_loader(const WgradArgs& a, char* s_st, int lane, int c0,
@@ -2478,10 +2620,19 @@ int64_t brick_ngroups(const ConvArgs& a) {
   return (a.cout + 16 * nb - 1) / (16 * nb);
 }
 
-// z-slices per wave: two when the launch keeps at least kDeepTileGroups
-// workgroups with them
-int brick_mz(const ConvArgs& a) {
+// z-slices of a tile in fours: two when the launch keeps at least
+// kDeepTileGroups workgroups with them
+int deep_mz(const ConvArgs& a) {
   return brick_tiles(a, 2) * brick_ngroups(a) >= kDeepTileGroups ? 2 : 1;
+}
+// four, for 64 channels, when every CU has a workgroup and at most a fifth of
+// the slices is padding (eight images of 16^3 128 -> 128: 59.9 us with one, 41.4
+// with four; of 32^3 64 -> 64 87.5 with two, 85.6)
+int brick_mz(const ConvArgs& a) {
+  if (conv_nb(a) == 4 && brick_tiles(a, 4) * brick_ngroups(a) >= 256 &&
+      5 * ((a.d + 15) / 16 * 16) <= 6 * a.d)
+    return 4;
+  return deep_mz(a);
 }
 
 // Ranges of the brick kernel's input-channel chunks, whose sums are added in
@@ -2490,7 +2641,7 @@ int brick_mz(const ConvArgs& a) {
 // CU, enough ranges to fill the chip, a divisor of the chunk count.
 int brick_ranges(ConvArgs a) {
   a.batch = 1;
-  const int64_t groups = brick_tiles(a, brick_mz(a)) * brick_ngroups(a);
+  const int64_t groups = brick_tiles(a, deep_mz(a)) * brick_ngroups(a);
   if (groups >= kSplitBelowGroups) return 1;
   const int chunks = a.cin / kBK;
   int sp = static_cast<int>(std::min<int64_t>(chunks, (kSplitTargetGroups + groups - 1) / groups));
@@ -2582,15 +2733,28 @@ hipError_t launch_conv(const ConvArgs& args, hipStream_t s) {
     const int sp = spread_ranges(a, a.ranges) && a.part && a.part_cap >= a.ranges * out_floats(a)
                        ? a.ranges
                        : 1;
-    const dim3 grid(static_cast<unsigned>(brick_tiles(a, mz)),
+    // as many workgroups as the chip holds at once (by LDS two per CU, one with
+    // deeper tiles of 64 channels), each with its share of the tiles
+    const int64_t slots = device_cus() * (nb == 4 && mz > 1 ? 1 : 2);
+    const int64_t others = brick_ngroups(a) * sp;
+    const dim3 grid(static_cast<unsigned>(std::min<int64_t>(
+                        brick_tiles(a, mz), std::max<int64_t>(1, slots / others))),
                     static_cast<unsigned>(brick_ngroups(a)), static_cast<unsigned>(sp));
-#define MCX_BRICK(NB)                                                  \
-  if (mz == 2)                                                         \
-    conv3_brick_kernel<NB, 2><<<grid, 384, 0, s>>>(a);                 \
-  else                                                                 \
-    conv3_brick_kernel<NB, 1><<<grid, 384, 0, s>>>(a);
-    if (nb == 4) { MCX_BRICK(4) } else if (nb == 2) { MCX_BRICK(2) } else { MCX_BRICK(1) }
-#undef MCX_BRICK
+    const int vec = a.cout % 8 == 0 && aligned16(a.y) && aligned16(a.skip);
+    if (nb == 4 && mz == 4)
+      conv3_brick_kernel<4, 4><<<grid, 384, 0, s>>>(a, vec);
+    else if (nb == 4 && mz == 2)
+      conv3_brick_kernel<4, 2><<<grid, 384, 0, s>>>(a, vec);
+    else if (nb == 4)
+      conv3_brick_kernel<4, 1><<<grid, 384, 0, s>>>(a, vec);
+    else if (nb == 2 && mz == 2)
+      conv3_brick_kernel<2, 2><<<grid, 384, 0, s>>>(a, vec);
+    else if (nb == 2)
+      conv3_brick_kernel<2, 1><<<grid, 384, 0, s>>>(a, vec);
+    else if (mz == 2)
+      conv3_brick_kernel<1, 2><<<grid, 384, 0, s>>>(a, vec);
+    else
+      conv3_brick_kernel<1, 1><<<grid, 384, 0, s>>>(a, vec);
     if (sp > 1) split_reduce_kernel<<<blocks_for(out_floats(a)), 256, 0, s>>>(a, sp);
     return hipGetLastError();
   }

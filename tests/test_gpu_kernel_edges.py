@@ -298,3 +298,45 @@ def test_one_channel_layer_edges(shape, co, skip, relu, f32, shift):
     got = y.float().cpu().numpy()
     lim = 1e-5 * size + (0 if f32 else 2.0 ** -8 * np.abs(ref))
     assert np.all(np.abs(got - ref) <= lim + 1e-30)
+
+
+@pytest.mark.parametrize("shape,ci,co,skip,f32,shift", [
+    ((5, 6, 7), 64, 40, True, False, 0),       # remainders of tiles and channels
+    ((16, 36, 40), 96, 64, True, False, 0),    # deep tiles
+    ((30, 64, 66), 64, 72, False, True, 0),    # deep tiles with padding, more tiles than workgroups
+    ((20, 68, 72), 64, 64, False, False, 0),   # two slices, more tiles than workgroups
+    ((9, 40, 44), 64, 24, True, False, 0),     # 32-channel tiles
+    ((9, 10, 11), 64, 16, False, True, 0),     # four channels a lane
+    ((9, 10, 11), 64, 12, True, False, 0),     # channels not in eights
+    ((5, 6, 7), 64, 64, True, False, 3),       # operands off 16-byte alignment
+    ((33, 40, 36), 32, 32, False, False, 0),   # weights in registers, remainders
+])
+def test_3x3x3_layer_edges(shape, ci, co, skip, f32, shift):
+    """3x3x3 layers at the edges of their tilings against the oracle on BF16
+    operands: FP32 sums (1e-5 of the sum of the products' sizes), then one BF16
+    rounding (2^-8) unless the output is FP32."""
+    import test_gpu_nn as T
+    t = T.torch()
+    say("[gpu] 3x3x3", shape, ci, co, skip, f32, shift)
+    x, w, b = T.layer_case("conv3", shape, ci, co, 81)
+    wq = T.O.bf16(w)
+    sk = T.O.bf16(np.random.default_rng(82).standard_normal(shape + (co,))) if skip else None
+
+    def placed(a, dtype):
+        buf = t.zeros(a.size + shift, dtype=dtype, device="cuda")
+        v = buf[shift:].view(a.shape)
+        v.copy_(t.from_numpy(np.ascontiguousarray(a)))
+        return v
+
+    y = placed(np.zeros(shape + (co,), np.float32), t.float32 if f32 else t.bfloat16)
+    T.nn.mcx_nn_layer_forward(T.nn.MCX_NN_CONV3, shape, ci, co, placed(x, t.bfloat16),
+                              T.dev_f32(w), T.dev_f32(b), y=y, y_f32=f32, relu=True,
+                              skip=None if sk is None else placed(sk, t.bfloat16))
+    ref = T.FWD["conv3"](x, wq, b)
+    size = T.FWD["conv3"](np.abs(x), np.abs(wq), np.abs(b))
+    if skip:
+        ref, size = ref + sk, size + np.abs(sk)
+    ref = np.maximum(ref, 0)
+    got = y.float().cpu().numpy()
+    lim = 1e-5 * size + (0 if f32 else 2.0 ** -8 * np.abs(ref))
+    assert np.all(np.abs(got - ref) <= lim + 1e-30)
