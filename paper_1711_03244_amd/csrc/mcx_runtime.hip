@@ -1581,8 +1581,9 @@ mcx_status mcx_autotune(mcx_ctx* c, const uint64_t* pilot_photons, const uint64_
     int block, chunk, window, adds;
   };
   std::vector<Cand> timed;
-  timed.push_back({ms, c->block, kDefaultChunk, kDefaultWindow,
-                   map32_large(c) ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64});
+  const Cand untuned{ms, c->block, ns > 1 ? kBatchChunk : kDefaultChunk, kDefaultWindow,
+                     map32_large(c) ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64};
+  timed.push_back(untuned);
   for (int wi = 0; wi < nwin; ++wi) {
     for (int b : blocks) {
       for (int ch : chunks) {
@@ -1631,6 +1632,8 @@ mcx_status mcx_autotune(mcx_ctx* c, const uint64_t* pilot_photons, const uint64_
     best.adds = keep ? rule : other;
     best.ms = keep ? t_rule : t_other;
   }
+  // a shape that won its one pilot by chance is not kept over the default
+  if (best.ms > untuned.ms) best = untuned;
   out->block_size = best.block;
   out->refill_chunk = best.chunk;
   out->lds_window_cells = best.window;
