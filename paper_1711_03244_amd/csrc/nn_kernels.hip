@@ -1345,6 +1345,98 @@ __global__ void __launch_bounds__(256) conv3_scalar_kernel(ConvArgs a, int vec) 
   }
 }
 
+// ------------------------------------- 3x3x3 conv with few channels in eights
+// kConv3 / kConv3T with cin = 8, 16, 24, 40, 48 or 56: the reduction runs over
+// (tap, channel) in steps of 32, lane group g of step s taking the 8 channels
+// q % (cin / 8) of tap q / (cin / 8), q = 4 s + g.  A workgroup owns a 4 x 4 x 4
+// tile (wave w: the z-slice w) and 16 NB output channels; the tile's brick is
+// staged in LDS, where those 8 channels of a shifted voxel are 16 bytes, and
+// the weights' fragments of kSteps steps at a time are read straight from the
+// packed weights, all in flight together.  Rows and columns as in the brick
+// kernel.
+// What bounds it: on small grids the latency of its one or two rounds of loads,
+// where the generic kernel waits for each of its stages.  Measured, generic and
+// this, us: 24^3 8 -> 8 7.0 and 4.5, 12^3 16 -> 16 9.9 and 6.0, 40 x 44 x 50
+// 24 -> 40 31 and 28.
+template <int NB>
+__global__ void __launch_bounds__(256) conv3_eights_kernel(ConvArgs a, int vec) {
+  constexpr int kSteps = 7;
+  __shared__ uint4 s_br[216 * 7];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tx_n = (a.w + 3) >> 2, ty_n = (a.h + 3) >> 2;
+  const int ntile = tx_n * ty_n * ((a.d + 3) >> 2);
+  const int img = blockIdx.x / ntile, tile = blockIdx.x - img * ntile;
+  const int bx = (tile % tx_n) * 4;
+  const int by = ((tile / tx_n) % ty_n) * 4;
+  const int bz = (tile / (tx_n * ty_n)) * 4;
+  const int n0 = blockIdx.y * 16 * NB;
+  const int sgn = a.geo == kConv3 ? 1 : -1;
+  const int r = lane & 15, g = lane >> 4;
+  const int c8 = a.cin >> 3;                 // 1 .. 7
+  const int inv = 65536 / c8 + 1;            // (n * inv) >> 16 = n / c8 for n < 1512
+  const int steps = (27 * c8 + 3) >> 2;
+  const uint16_t* x_img = a.x + static_cast<int64_t>(img) * a.in_d * a.in_h * a.in_w * a.cin;
+
+  const uint16_t* wp[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int n = NB >= 2 ? 32 * (j >> 1) + 8 * (r >> 2) + 4 * (j & 1) + (r & 3) : r;
+    wp[j] = a.bt + static_cast<int64_t>(n0 + n) * a.kpad + 8 * g;
+  }
+  bf16x8 wf[kSteps][NB];
+  auto load_w = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        wf[u][j] = *reinterpret_cast<const bf16x8*>(wp[j] + min(s0 + u, steps - 1) * kBK);
+  };
+  load_w(0);
+  for (int p = tid; p < 216 * c8; p += 256) {
+    const int v = (p * inv) >> 16, c = p - v * c8;
+    const int gx = bx + v % 6 - 1, gy = by + (v / 6) % 6 - 1, gz = bz + v / 36 - 1;
+    uint4 val = make_uint4(0u, 0u, 0u, 0u);
+    if (gx >= 0 && gy >= 0 && gz >= 0 && gx < a.in_w && gy < a.in_h && gz < a.in_d)
+      val = *reinterpret_cast<const uint4*>(
+          x_img + ((static_cast<int64_t>(gz) * a.in_h + gy) * a.in_w + gx) * a.cin + c * 8);
+    s_br[p] = val;
+  }
+  __syncthreads();
+  const int center = ((wave + 1) * 6 + (r >> 2) + 1) * 6 + (r & 3) + 1;
+  floatx4 acc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < steps; s0 += kSteps) {
+    if (s0 > 0) load_w(s0);
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+      if (s0 + u >= steps) break;
+      const int q = 4 * (s0 + u) + g, t = (q * inv) >> 16, c = q - t * c8;
+      uint4 xv = make_uint4(0u, 0u, 0u, 0u);
+      if (t < 27)
+        xv = s_br[(center + sgn * ((t / 9 - 1) * 36 + ((t / 3) % 3 - 1) * 6 + t % 3 - 1)) * c8 + c];
+      const bf16x8 xf = __builtin_bit_cast(bf16x8, xv);
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[u][j], xf, acc[j], 0, 0, 0);
+    }
+  }
+  const int x = bx + (r & 3), y = by + (r >> 2), z = bz + wave;
+  if (x >= a.w || y >= a.h || z >= a.d) return;
+  const int64_t o = ((static_cast<int64_t>(img) * a.d + z) * a.h + y) * a.w + x;
+  if constexpr (NB >= 2) {
+#pragma unroll
+    for (int j = 0; j < NB; j += 2) {
+      const floatx4 v[2] = {acc[j], acc[j + 1]};
+      put_channels<8>(a, v, o, n0 + 16 * j + 8 * g, nullptr, vec);
+    }
+  } else {
+    const floatx4 v[1] = {acc[0]};
+    put_channels<4>(a, v, o, n0 + 4 * g, nullptr, vec);
+  }
+}
+
 // Finish a split product: y[o][n] = [relu](sum over splits of part[s][o][n]
 // + bias[n] [+ skip[o][n]]), splits summed in order.
 __global__ void __launch_bounds__(256) split_reduce_kernel(ConvArgs a, int nsplit) {
@@ -2555,6 +2647,11 @@ bool uses_brick(const ConvArgs& a) {
   return (a.geo == kConv3 || a.geo == kConv3T) && a.cin % kBK == 0 && aligned16(a.x);
 }
 
+bool uses_eights(const ConvArgs& a) {
+  return (a.geo == kConv3 || a.geo == kConv3T) && a.cin % 8 == 0 && a.cin % kBK != 0 &&
+         a.cin <= 56 && aligned16(a.x);
+}
+
 bool uses_up(const ConvArgs& a) {
   return a.geo == kUp && a.cin % kBK == 0 && a.cout % 8 == 0 && aligned16(a.x) &&
          aligned16(a.y) && aligned16(a.skip);
@@ -2756,6 +2853,18 @@ hipError_t launch_conv(const ConvArgs& args, hipStream_t s) {
     else
       conv3_brick_kernel<1, 1><<<grid, 384, 0, s>>>(a, vec);
     if (sp > 1) split_reduce_kernel<<<blocks_for(out_floats(a)), 256, 0, s>>>(a, sp);
+    return hipGetLastError();
+  }
+  if (uses_eights(a)) {
+    const dim3 grid(static_cast<unsigned>(brick_tiles(a, 1)),
+                    static_cast<unsigned>(brick_ngroups(a)), 1);
+    const int vec = a.cout % 8 == 0 && aligned16(a.y) && aligned16(a.skip);
+    if (nb == 4)
+      conv3_eights_kernel<4><<<grid, 256, 0, s>>>(a, vec);
+    else if (nb == 2)
+      conv3_eights_kernel<2><<<grid, 256, 0, s>>>(a, vec);
+    else
+      conv3_eights_kernel<1><<<grid, 256, 0, s>>>(a, vec);
     return hipGetLastError();
   }
   if (uses_up(a)) {

@@ -340,3 +340,14 @@ def test_3x3x3_layer_edges(shape, ci, co, skip, f32, shift):
     got = y.float().cpu().numpy()
     lim = 1e-5 * size + (0 if f32 else 2.0 ** -8 * np.abs(ref))
     assert np.all(np.abs(got - ref) <= lim + 1e-30)
+
+
+@pytest.mark.parametrize("shape,ci,co", [((4, 4, 4), 8, 8), ((5, 6, 7), 16, 20), ((9, 4, 5), 24, 40),
+                                         ((6, 5, 13), 40, 72), ((7, 8, 9), 56, 33),
+                                         ((12, 14, 10), 48, 16)])
+def test_few_channels_in_eights(shape, ci, co):
+    """3x3x3 layers of 8 to 56 channels in eights, forward and the gradients
+    (the input gradient gathers co channels), against the oracle."""
+    say("[gpu] eights", shape, ci, co)
+    layer_forward_backward("conv3", shape, ci, co, 91)
+    layer_forward_backward("conv3", shape, 8 * (co // 8), ci, 92)
