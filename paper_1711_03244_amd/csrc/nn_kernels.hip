@@ -1356,8 +1356,7 @@ __global__ void __launch_bounds__(256) conv3_scalar_kernel(ConvArgs a, int vec) 
 // kernel.
 // What bounds it: on small grids the latency of its one or two rounds of loads,
 // where the generic kernel waits for each of its stages.  Measured, generic and
-// this, us: 24^3 8 -> 8 7.0 and 4.5, 12^3 16 -> 16 9.9 and 6.0, 40 x 44 x 50
-// 24 -> 40 31 and 28.
+// this, us: 24^3 8 -> 8 7.0 and 4.5, 12^3 16 -> 16 9.9 and 6.0.
 template <int NB>
 __global__ void __launch_bounds__(256) conv3_eights_kernel(ConvArgs a, int vec) {
   constexpr int kSteps = 7;
@@ -2647,9 +2646,20 @@ bool uses_brick(const ConvArgs& a) {
   return (a.geo == kConv3 || a.geo == kConv3T) && a.cin % kBK == 0 && aligned16(a.x);
 }
 
+int64_t brick_tiles(const ConvArgs& a, int mz);
+int64_t brick_ngroups(const ConvArgs& a);
+// Few channels, whose weights a workgroup reads for its 64 voxels alone: where
+// these are few (blocks of 8 channels x 16), or the reads of the whole launch.
+// Measured, single layers, us, generic and this: 64^3 24 -> 16 (3 blocks) 78 and
+// 53, 8 -> 64 68 and 59, 16 -> 32 (4) 71 and 77; 24^3 56 -> 56 (216 workgroups, 28
+// blocks) 53 and 46, 32^3 56 -> 32 (512, 14) 51 and 46, 40 -> 64 (512, 20) 49 and 55.
 bool uses_eights(const ConvArgs& a) {
-  return (a.geo == kConv3 || a.geo == kConv3T) && a.cin % 8 == 0 && a.cin % kBK != 0 &&
-         a.cin <= 56 && aligned16(a.x);
+  if ((a.geo != kConv3 && a.geo != kConv3T) || a.cin % 8 != 0 || a.cin % kBK == 0 || a.cin > 56 ||
+      !aligned16(a.x))
+    return false;
+  const int blocks = a.cin / 8 * conv_nb(a);
+  return a.cin == 8 || blocks <= 3 ||
+         brick_tiles(a, 1) * brick_ngroups(a) * blocks <= 512 * 14;
 }
 
 bool uses_up(const ConvArgs& a) {
@@ -2682,7 +2692,6 @@ void launch_up(const ConvArgs& a, hipStream_t s) {
 // (the full-resolution layers; smaller grids keep the brick kernel, whose
 // split reductions fill the chip).
 constexpr int64_t kResidentTiles = 1024;
-int64_t brick_tiles(const ConvArgs& a, int mz);
 bool uses_resident(const ConvArgs& a) {
   return (a.geo == kConv3 || a.geo == kConv3T) && a.cin == 32 && !a.skip && aligned16(a.x) &&
          brick_tiles(a, 2) >= kResidentTiles;
