@@ -62,7 +62,8 @@ struct WgradArgs {
   float* gw;                  // FP32 [taps][cin][cout], accumulated
   float* part;                // FP32 workspace for per-workgroup partial sums, or null
   int64_t part_cap;           // its size in floats
-  bool overwrite = false;     // gw receives the sum instead (wgrad_overwrites)
+  bool overwrite = false;     // gw (and gb) receive the sum instead (wgrad_overwrites)
+  float* gb = nullptr;        // also gb[n] += sum_m gy(m, n), where wgrad_folds_bias
 };
 
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
@@ -72,6 +73,9 @@ int64_t conv_workspace_floats(const ConvArgs& a);
 hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s);
 // floats of workspace launch_wgrad uses for `a` (0: it needs none)
 int64_t wgrad_workspace_floats(const WgradArgs& a);
+// whether launch_wgrad can take the bias gradient along (WgradArgs::gb; to be
+// set before wgrad_workspace_floats)
+bool wgrad_folds_bias(const WgradArgs& a);
 // whether launch_wgrad with its workspace can store to gw instead of adding
 bool wgrad_overwrites(const WgradArgs& a);
 // One layer's weights w[taps][cin][cout] (FP32) to pack into BF16 rows:

@@ -1777,6 +1777,26 @@ __device__ __forceinline__ int tr_lane(int lane) {
   return ((lane >> 2) & 3) * 64 + (lane & 3) * 8;
 }
 
+// floats of one group's sums: the weights' and, with gb, the bias gradient
+__host__ __device__ __forceinline__ int64_t wgrad_floats(const WgradArgs& a) {
+  return static_cast<int64_t>(a.taps) * a.cin * a.cout + (a.gb ? a.cout : 0);
+}
+
+// Output channel n's sum over the workgroup's tiles of gy.  It comes from the
+// matrix products with a fragment of ones beside gy's, where each column is
+// the sum; a kernel of its own read gy again, 10 us at 64^3 x 32.
+__device__ __forceinline__ void wgrad_put_bias(const WgradArgs& a, int n, float v) {
+  if (n >= a.cout) return;
+  if (gridDim.x > 1)
+    a.part[blockIdx.x * wgrad_floats(a) + static_cast<int64_t>(a.taps) * a.cin * a.cout + n] = v;
+  else
+    a.gb[n] = a.overwrite ? v : a.gb[n] + v;
+}
+__device__ __forceinline__ bf16x8 ones8() {
+  const uint32_t two = 0x3f803f80u;  // 1.0 twice
+  return __builtin_bit_cast(bf16x8, make_uint4(two, two, two, two));
+}
+
 // A workgroup's sums, N groups of four output channels at the elements
 // at(0) .. at(N - 1) of gw, or nowhere (-1).  Several workgroups along the
 // tiles store to part[blockIdx.x] for wgrad_reduce_kernel; a single one
@@ -1784,7 +1804,7 @@ __device__ __forceinline__ int tr_lane(int lane) {
 template <int N, typename At, typename Sum>
 __device__ __forceinline__ void wgrad_put(const WgradArgs& a, At at, Sum sum) {
   if (gridDim.x > 1) {
-    float* out = a.part + blockIdx.x * (static_cast<int64_t>(a.taps) * a.cin * a.cout);
+    float* out = a.part + blockIdx.x * wgrad_floats(a);
 #pragma unroll
     for (int k = 0; k < N; ++k)
       if (at(k) >= 0) *reinterpret_cast<floatx4*>(out + at(k)) = sum(k);
@@ -1893,6 +1913,9 @@ template <bool kPlane, int W>
 __device__ __forceinline__ void wbrick_compute(const WgradArgs& a, const char* s_st, int lane,
                                                int c0, int n0, int dz0, int nt) {
   using K = WBrick;
+  // the last wave, which has the fewest taps, sums gy for the bias gradient
+  const bool bias = W == 3 && a.gb && c0 == 0 && dz0 == 0;
+  floatx4 sum[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
   constexpr int kT0 = kPlane ? (9 * W + 3) / 4 : 7 * W;  // the wave's taps kT0 .. kT0 + kNT - 1
   constexpr int kNT = kPlane ? (9 * W + 12) / 4 - kT0 : (W < 3 ? 7 : 6);
   const int r = lane & 15, g = lane >> 4;
@@ -1925,6 +1948,11 @@ __device__ __forceinline__ void wbrick_compute(const WgradArgs& a, const char* s
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
           gf[nb] = read_tr(gh[nb] + (i / kNT) * 2048, gh[nb] + (i / kNT) * 2048 + 256);
+        if (bias) {
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb)
+            sum[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf[nb], ones8(), sum[nb], 0, 0, 0);
+        }
       }
       if (i + 1 < 4 * kNT) read_x(i + 1, xf[(i + 1) & 1]);
       __builtin_amdgcn_sched_barrier(0);  // those reads ahead of the matrix instructions
@@ -1936,6 +1964,10 @@ __device__ __forceinline__ void wbrick_compute(const WgradArgs& a, const char* s
               __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf[nb], xf[i & 1][cb], acc[t][nb][cb], 0, 0, 0);
     }
     slot = slot == 2 ? 0 : slot + 1;
+  }
+  if (bias && r == 0) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) wgrad_put_bias(a, n0 + (i >> 2) * 16 + 4 * g + (i & 3), sum[i >> 2][i & 3]);
   }
   // lane (r, g) holds output channels 16 nb + 4 g .. + 3 of input channel 16 cb + r
   wgrad_put<4 * kNT>(
@@ -2040,6 +2072,13 @@ __global__ void __launch_bounds__(384) wgrad_pair_kernel(WgradArgs a) {
   }
   const int r = lane & 15, g = lane >> 4;
   const int lo = tr_lane(lane) + g * 512;
+  // the bias gradient: gy is the large operand (each wave sums its taps') or
+  // the small one (the first wave does)
+  constexpr int kSums = kUpGeo ? 2 : NS;
+  const bool bias = a.gb && (kUpGeo ? s0 == 0 : b0 == 0 && wave == 0);
+  floatx4 sum[kSums];
+#pragma unroll
+  for (int q = 0; q < kSums; ++q) sum[q] = floatx4{0.f, 0.f, 0.f, 0.f};
   floatx4 acc[2][NS][2];  // tap, small and large 16-channel block
 #pragma unroll
   for (int e = 0; e < 2; ++e)
@@ -2064,6 +2103,18 @@ __global__ void __launch_bounds__(384) wgrad_pair_kernel(WgradArgs a) {
         const char* p = h[q & 1] + (8 + (q >> 1)) * 4096 + ks * 2048;
         sf[q] = read_tr(p, p + 256);
       }
+      if (bias) {
+#pragma unroll
+        for (int q = 0; q < kSums; ++q) {
+          if constexpr (kUpGeo) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+              sum[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[e][q], ones8(), sum[q], 0, 0, 0);
+          } else {
+            sum[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sf[q], ones8(), sum[q], 0, 0, 0);
+          }
+        }
+      }
 #pragma unroll
       for (int e = 0; e < 2; ++e)
 #pragma unroll
@@ -2075,6 +2126,29 @@ __global__ void __launch_bounds__(384) wgrad_pair_kernel(WgradArgs a) {
                        : __builtin_amdgcn_mfma_f32_16x16x32_bf16(sf[q], bf[e][c], acc[e][q][c], 0, 0, 0);
     }
     slot = slot == 2 ? 0 : slot + 1;
+  }
+  if constexpr (kUpGeo) {
+    // the waves' sums in order, through the first stage's memory: the loader
+    // waves have ended, every compute wave has read its last fragments
+    if (a.gb && s0 == 0) {
+      float* sh = reinterpret_cast<float*>(s_st);
+      barrier_lds();
+      if (r == 0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          sh[wave * 32 + (i >> 2) * 16 + 4 * g + (i & 3)] = sum[i >> 2][i & 3];
+      }
+      barrier_lds();
+      if (wave == 0 && lane < 32) {
+        float t = sh[lane];
+        for (int w = 1; w < 4; ++w) t += sh[w * 32 + lane];
+        wgrad_put_bias(a, b0 + lane, t);
+      }
+    }
+  } else if (bias && r == 0) {
+#pragma unroll
+    for (int i = 0; i < 4 * NS; ++i)
+      wgrad_put_bias(a, s0 + (i >> 2) * 16 + 4 * g + (i & 3), sum[i >> 2][i & 3]);
   }
   // lane (r, g): four output channels of one input channel, as above
   wgrad_put<4 * NS>(
@@ -2181,15 +2255,22 @@ __global__ void __launch_bounds__(256) wgrad_onechannel_kernel(WgradArgs a) {
   }
 }
 
+// sum i of a reduction: of the weights' (i < nw) or of the bias gradient
+__device__ __forceinline__ void wgrad_finish(float* gw, int64_t nw, float* gb, int64_t i, float v,
+                                             int overwrite) {
+  float* p = i < nw ? gw + i : gb + (i - nw);
+  *p = overwrite ? v : *p + v;
+}
+
 // the same for fewer than 8 workgroups: one thread per i
 __global__ void wgrad_reduce_few_kernel(const float* part, int groups, int64_t n, float* gw,
-                                        int overwrite) {
+                                        int64_t nw, float* gb, int overwrite) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     float v = part[i];
 #pragma unroll 7
     for (int k = 1; k < groups; ++k) v += part[k * n + i];
-    gw[i] = overwrite ? v : gw[i] + v;
+    wgrad_finish(gw, nw, gb, i, v, overwrite);
   }
 }
 
@@ -2198,7 +2279,8 @@ __global__ void wgrad_reduce_few_kernel(const float* part, int groups, int64_t n
 // for i = E blockIdx.x + il, and the KL sums of each i are added in q order
 template <int KL>
 __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float* part, int groups,
-                                                           int64_t n, float* gw, int overwrite) {
+                                                           int64_t n, float* gw, int64_t nw,
+                                                           float* gb, int overwrite) {
   constexpr int E = 256 / KL;
   __shared__ float sh[KL][E + 1];
   const int il = threadIdx.x % E, q = threadIdx.x / E;
@@ -2213,7 +2295,7 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float* part, in
     float t = sh[0][il];
 #pragma unroll
     for (int k = 1; k < KL; ++k) t += sh[k][il];
-    gw[i] = overwrite ? t : gw[i] + t;
+    wgrad_finish(gw, nw, gb, i, t, overwrite);
   }
 }
 
@@ -2955,14 +3037,14 @@ bool tr_plane(const WgradArgs& a) {
 int tr_groups(const WgradArgs& a, int64_t cap) {
   const int64_t other = tr_blocks(a) * (tr_plane(a) ? 3 : 1);
   int64_t G = std::min<int64_t>(tr_tiles(a), std::max<int64_t>(1, kTrGroups / other));
-  const int64_t per = static_cast<int64_t>(a.taps) * a.cin * a.cout;
+  const int64_t per = wgrad_floats(a);
   while (G > 1 && G * per > cap) G = (G + 1) / 2;
   return static_cast<int>(G);
 }
 // floats of their partial sums (one group needs none)
 int64_t tr_part(const WgradArgs& a) {
   const int G = tr_groups(a, kSlabMaxPart);
-  return G > 1 ? G * static_cast<int64_t>(a.taps) * a.cin * a.cout : 0;
+  return G > 1 ? G * wgrad_floats(a) : 0;
 }
 
 // tile groups of the one-channel kernels: about kSlabTargetGroups in all
@@ -2996,16 +3078,18 @@ int slab_groups(const WgradArgs& a, int64_t cap) {
 
 namespace {
 
-// the reduction of G partial sums of n floats into gw
-hipError_t launch_wgrad_reduce(const float* part, int G, int64_t n, float* gw, bool overwrite,
-                               hipStream_t s) {
-  const int ow = overwrite ? 1 : 0;
+// the reduction of a's partial sums of G groups into gw and gb
+hipError_t launch_wgrad_reduce(const WgradArgs& a, int G, hipStream_t s) {
+  const int ow = a.overwrite ? 1 : 0;
+  const int64_t n = wgrad_floats(a), nw = static_cast<int64_t>(a.taps) * a.cin * a.cout;
   if (G < 8)
-    wgrad_reduce_few_kernel<<<blocks_for(n), 256, 0, s>>>(part, G, n, gw, ow);
+    wgrad_reduce_few_kernel<<<blocks_for(n), 256, 0, s>>>(a.part, G, n, a.gw, nw, a.gb, ow);
   else if (G >= 64 && n < 8192)  // fewer than 256 workgroups with 8 lanes per i
-    wgrad_reduce_kernel<32><<<static_cast<unsigned>((n + 7) / 8), 256, 0, s>>>(part, G, n, gw, ow);
+    wgrad_reduce_kernel<32><<<static_cast<unsigned>((n + 7) / 8), 256, 0, s>>>(a.part, G, n, a.gw,
+                                                                              nw, a.gb, ow);
   else
-    wgrad_reduce_kernel<8><<<static_cast<unsigned>((n + 31) / 32), 256, 0, s>>>(part, G, n, gw, ow);
+    wgrad_reduce_kernel<8><<<static_cast<unsigned>((n + 31) / 32), 256, 0, s>>>(a.part, G, n, a.gw,
+                                                                              nw, a.gb, ow);
   return hipGetLastError();
 }
 
@@ -3018,6 +3102,8 @@ int64_t wgrad_workspace_floats(const WgradArgs& a) {
   if (!uses_slab(a)) return 0;
   return slab_groups(a, kSlabMaxPart) * static_cast<int64_t>(a.taps) * a.cin * a.cout;
 }
+
+bool wgrad_folds_bias(const WgradArgs& a) { return uses_tr(a); }
 
 bool wgrad_overwrites(const WgradArgs& a) {
   return (uses_onechannel(a) || uses_tr(a) || uses_slab(a)) && wgrad_workspace_floats(a) <= kSlabMaxPart;
@@ -3034,11 +3120,10 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
         wgrad_onechannel_kernel<true><<<grid, 256, 0, s>>>(a);
       else
         wgrad_onechannel_kernel<false><<<grid, 256, 0, s>>>(a);
-      return launch_wgrad_reduce(a.part, G, per, a.gw, a.overwrite, s);
+      return launch_wgrad_reduce(a, G, s);
     }
   }
   if (uses_tr(a)) {
-    const int64_t per = static_cast<int64_t>(a.taps) * a.cin * a.cout;
     const int G = tr_groups(a, a.part ? a.part_cap : 0);
     const auto g = [&](int rows, int cols) {
       return dim3(static_cast<unsigned>(G), static_cast<unsigned>(rows),
@@ -3058,7 +3143,7 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
     else
       wgrad_pair_kernel<false, 2><<<g(cb, 1), 384, 0, s>>>(a);
     if (G == 1) return hipGetLastError();
-    return launch_wgrad_reduce(a.part, G, per, a.gw, a.overwrite, s);
+    return launch_wgrad_reduce(a, G, s);
   }
   if (uses_slab(a) && a.part) {
     const int64_t per = static_cast<int64_t>(a.taps) * a.cin * a.cout;
@@ -3071,7 +3156,7 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
         wgrad_slab_kernel<2><<<grid, 256, 0, s>>>(a);
       else
         wgrad_slab_kernel<1><<<grid, 256, 0, s>>>(a);
-      return launch_wgrad_reduce(a.part, G, per, a.gw, a.overwrite, s);
+      return launch_wgrad_reduce(a, G, s);
     }
   }
   const int64_t M = static_cast<int64_t>(a.d) * a.h * a.w;

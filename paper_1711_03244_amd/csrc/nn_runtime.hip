@@ -758,6 +758,7 @@ mcx_status mcx_nn_layer_backward(int32_t kind, int32_t nx, int32_t ny, int32_t n
   describe_layer(L, kind, cin, cout, Grid{nz, ny, nx});
   hipStream_t s = static_cast<hipStream_t>(stream);
   WgradArgs wa = wgrad_args(L, x, gy, gw);
+  if (wgrad_folds_bias(wa)) wa.gb = gb;
   wa.part_cap = wgrad_workspace_floats(wa);
   wa.overwrite = wgrad_overwrites(wa);
   ConvArgs da = dgrad_args(L, gy, gx);
@@ -775,9 +776,9 @@ mcx_status mcx_nn_layer_backward(int32_t kind, int32_t nx, int32_t ny, int32_t n
   wa.part = wa.part_cap > 0 ? part : nullptr;
   da.part = da.part_cap > 0 ? part : nullptr;
   const int64_t nw = wa.overwrite ? 0 : static_cast<int64_t>(L.taps) * cin * cout;
-  hipError_t e = launch_fill2(gw, nw, gb, gb ? cout : 0, s);
+  hipError_t e = launch_fill2(gw, nw, gb, gb && !(wa.gb && wa.overwrite) ? cout : 0, s);
   if (e == hipSuccess) e = launch_wgrad(wa, s);
-  if (e == hipSuccess && gb) e = launch_bias_grad(gy, L.out.vox(), cout, gb, s);
+  if (e == hipSuccess && gb && !wa.gb) e = launch_bias_grad(gy, L.out.vox(), cout, gb, s);
   if (e == hipSuccess && gx) e = launch_pack(pack_job(L, w, nullptr, L.bwd), s);
   if (e == hipSuccess && gx) e = launch_conv(da, s);
   const hipError_t w8 = hipStreamSynchronize(s);

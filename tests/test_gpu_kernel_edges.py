@@ -217,8 +217,9 @@ def test_up_layer_edges(shape, ci, co, skip, relu, f32, shift):
 ])
 def test_weight_gradient_edges(kind, shape, ci, co, shift):
     """Weight gradients where tiles, channel blocks and groups of partial sums
-    have remainders, against the oracle on BF16 operands: FP32 sums over the
-    voxels, 1e-5 of the sum of the products' sizes."""
+    have remainders, with and without the bias gradient, against the oracle
+    on BF16 operands: FP32 sums over the voxels, 1e-5 of the sum of the products'
+    sizes."""
     import test_gpu_nn as T
     t = T.torch()
     say("[gpu] weight gradient", kind, shape, ci, co, shift)
@@ -231,12 +232,17 @@ def test_weight_gradient_edges(kind, shape, ci, co, shift):
         v.copy_(t.from_numpy(np.ascontiguousarray(a)))
         return v
 
-    gw = t.full(w.shape, float("nan"), dtype=t.float32, device="cuda")
-    T.nn.mcx_nn_layer_backward(T.KIND[kind], shape, ci, co, placed(x), T.dev_f32(w), placed(gy),
-                               None, gw, None)
-    ref = T.BWD[kind](x, T.O.bf16(w), gy)[1]
-    lim = T.BWD[kind](np.abs(x), np.abs(T.O.bf16(w)), np.abs(gy))[1]
-    assert np.all(np.abs(T.host(gw) - ref) <= 1e-5 * lim + 1e-30)
+    ref = T.BWD[kind](x, T.O.bf16(w), gy)
+    lim = T.BWD[kind](np.abs(x), np.abs(T.O.bf16(w)), np.abs(gy))
+    for with_bias in (False, True):
+        gw = t.full(w.shape, float("nan"), dtype=t.float32, device="cuda")
+        gb = t.full((co,), float("nan"), dtype=t.float32, device="cuda") if with_bias else None
+        T.nn.mcx_nn_layer_backward(T.KIND[kind], shape, ci, co, placed(x), T.dev_f32(w), placed(gy),
+                                   None, gw, gb)
+        assert np.all(np.abs(T.host(gw) - ref[1]) <= 1e-5 * lim[1] + 1e-30)
+        if with_bias:
+            size = np.abs(gy).reshape(-1, co).sum(0)
+            assert np.all(np.abs(T.host(gb) - ref[2]) <= 1e-5 * size + 1e-30)
 
 
 def test_gradients_accumulate():
