@@ -24,10 +24,11 @@
 // register and flushed once when it leaves the cell.  Flushes into the
 // densest cells of the workgroup's window simulation (the home simulation
 // of its first wave) -- per early gate a box of cells, the "window" -- go to
-// integer partial sums in LDS (visit sums are rounded to a fixed deposit
-// unit, see deposit()), added to the map once when the workgroup finishes
-// (or earlier, by the lane whose addition takes a sum past 2^31 units).  All
-// other flushes are one atomic add to the map's integer counts (map_add).
+// 32-bit integer partial sums in LDS (visit sums are rounded to a fixed
+// deposit unit, see deposit()), added to the map once when the workgroup
+// finishes; a carry out of a sum is added to the map by the lane whose
+// addition made it (settle()).  All other flushes are one atomic add to the
+// map's integer counts.
 // Device-memory atomics on gfx950 execute at the memory side at a fixed
 // aggregate rate, which binds this kernel wherever photons spread out, so
 // the window is what keeps the cells that most photons of a workgroup visit
