@@ -126,7 +126,8 @@ typedef struct {
 typedef struct {
   uint64_t launched, escaped, detected, timeout, rr_dead, capped;
   uint64_t scatters, face_events, fresnel_draws, reflections, rr_tests, rr_survived;
-  uint64_t events;          /* segments simulated (lane iterations with a live photon) */
+  uint64_t events;          /* lane iterations with a live photon: the segments simulated,
+                               and one more for each capped photon */
   uint64_t lane_slots;      /* wave iterations x 64 (events / lane_slots = lane utilisation) */
   uint64_t flushes;         /* cell visits added to the map by a global atomic (not via LDS) */
   uint64_t det_records;     /* records written (<= max_detected) */
