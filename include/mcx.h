@@ -238,10 +238,12 @@ mcx_status mcx_batch_detected(mcx_ctx *ctx, int32_t sim, float *host_rec, uint64
 mcx_status mcx_batch_digest(mcx_ctx *ctx, int32_t sim, double *host_out, uint64_t nrows);
 
 /* Launch shape: threads per workgroup (0 = the size that keeps the most waves
- * resident, with fewer waves for launches of few photons per lane), photons
+ * resident and, unless mcx_options.blocks_per_cu asks for a number of
+ * workgroups, fewer waves for launches of few photons per lane), photons
  * per job (0 = 64, in a batch 256, fewer for launches of fewer photons than
- * lanes), LDS window cells (0 = default 16384, < 0 = none, at most 36864; in a batch each workgroup keeps the window
- * of the simulation its first wave starts on).  The window covers, per early
+ * lanes), LDS window cells (0 = default 16384, < 0 = none, at most 36864; in
+ * a batch each workgroup keeps the window of the simulation its first wave
+ * starts on).  The window covers, per early
  * gate, a box of cells: by default one box round the source over the gates of
  * the first ~0.5 ns; after mcx_autotune on a single simulation, the boxes
  * its flush census shaped for that cell count.  Waits for the stream. */

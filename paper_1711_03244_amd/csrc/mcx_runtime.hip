@@ -196,7 +196,8 @@ struct mcx_ctx {
   bool detect = false, diag = false;
   int block = 256, grid = 0, cus = 0;
   int chunk = 0;             // photons per job; 0: by the launch's photons
-  bool fit_shape = true;     // no block size asked for: small launches use fewer waves
+  bool fit_shape = true;     // neither block size nor workgroups per CU asked for: small
+                             // launches use fewer waves
   bool full_shape = false;   // pilots that stand for large launches: no such fit
   int last_block = 0, last_grid = 0;  // the last launch's shape
   int window_budget = 0;
@@ -774,7 +775,7 @@ static mcx_status setup(mcx_ctx* c, const mcx_sim* sims) {
   MCX_TRY(clear_all(c, c->stream));
   set_window(c, c->opt.lds_window_cells == 0 ? kDefaultWindow : c->opt.lds_window_cells);
   c->chunk = c->opt.refill_chunk;
-  c->fit_shape = c->opt.block_size == 0;
+  c->fit_shape = c->opt.block_size == 0 && c->opt.blocks_per_cu == 0;
   MCX_TRY(set_shape(c, c->opt.block_size));
   HIP_TRY(hipStreamSynchronize(c->stream));
   return MCX_OK;
@@ -1473,7 +1474,7 @@ mcx_status mcx_set_launch(mcx_ctx* c, int32_t block_size, int32_t refill_chunk,
   MCX_TRY(host_wait(c));
   set_window(c, lds_window_cells == 0 ? kDefaultWindow : lds_window_cells);
   c->chunk = refill_chunk;
-  c->fit_shape = block_size == 0;
+  c->fit_shape = block_size == 0 && c->opt.blocks_per_cu == 0;
   return set_shape(c, block_size);
 }
 

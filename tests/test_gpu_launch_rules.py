@@ -32,3 +32,51 @@ def test_events_count_every_live_iteration(cap, variant):
     assert st["events"] == o["events"] + o["capped"]
     assert st["scatters"] == o["scatters"] and st["face_events"] == o["face_events"]
     assert st["events"] == st["scatters"] + st["face_events"] + st["timeout"] + st["capped"]
+
+
+def cus():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def shape_of(sim, n):
+    """(workgroups per compute unit, threads per workgroup) of a run of n photons"""
+    sim.run(n, 5)
+    st = sim.stats()
+    assert st["launched"] == n and st["grid_blocks"] % cus() == 0
+    return st["grid_blocks"] // cus(), st["block_size"]
+
+
+@pytest.mark.parametrize("per_cu,window", [(2, 0), (2, -1), (3, -1)])
+def test_small_launches_keep_the_workgroups_asked_for(per_cu, window):
+    """With blocks_per_cu set a small launch has that many workgroups per
+    compute unit, like a large one."""
+    p = W.cube_homogeneous(n=20).replace(src_pos=(9.5, 9.5, 0.0))
+    say(f"[gpu] blocks_per_cu {per_cu} window {window}")
+    with mcx.Simulation(p, blocks_per_cu=per_cu, lds_window_cells=window) as sim:
+        large = shape_of(sim, 9 * 1024 * cus())
+        assert large[0] == per_cu
+        assert shape_of(sim, 1000) == large
+        sim.set_launch(0, 0, window)
+        assert shape_of(sim, 1000) == large
+
+
+@pytest.mark.parametrize("mus,waves", [(1.0, {0.4: 4, 0.6: 8, 7.9: 8, 8.1: 16}),
+                                       (5.0, {0.4: 4, 0.6: 8, 1.9: 8, 2.1: 16})])
+def test_waves_follow_the_photons_per_lane(mus, waves):
+    """Launches of few photons per lane of a full launch get 4 or 8 waves per
+    compute unit, where voxels are thin (mus h below 2) up to more photons;
+    the kind of map add follows the photons, the thickness and the waves."""
+    p = W.with_medium(W.cube_homogeneous(n=20), 1, (0.05, mus, 0.01, 1.37))
+    p = p.replace(src_pos=(9.5, 9.5, 0.0))
+    with mcx.Simulation(p) as sim:
+        full = shape_of(sim, 20 * 1024 * cus())
+        for per_lane, want in waves.items():
+            n = int(per_lane * 1024 * cus())
+            say(f"[gpu] mus {mus} photons {n}")
+            groups, block = shape_of(sim, n)
+            assert groups * block // 64 == min(want, full[0] * full[1] // 64)
+            adds = mcx.MAP_ADDS_32 if mus == 1.0 and per_lane > 8 else mcx.MAP_ADDS_64
+            assert sim.stats()["map_adds"] == adds
+        sim.set_launch(256, 64, 0)  # a block size asked for is kept
+        assert shape_of(sim, 1000)[1] == 256
