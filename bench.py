@@ -426,10 +426,12 @@ def batch_leg(mcx, W):
             b.run([max(1, x // 100) for x in n], [s + 1 for s in seeds])  # warm-up
             b.run(n, seeds)
             st = b.stats(0)
+            kinds = {b.stats(i)["map_adds"] for i in range(len(b))}
             out[label] = {"photons_per_ms": total / st["run_ms"], "run_ms": st["run_ms"],
                           "kernel_ms": st["kernel_ms"], "block_size": st["block_size"],
                           "grid_blocks": st["grid_blocks"],
-                          "map_adds": {1: "64-bit", 2: "32-bit with carry"}[st["map_adds"]]}
+                          "map_adds": "by simulation" if len(kinds) > 1 else
+                          {1: "64-bit", 2: "32-bit with carry"}[kinds.pop()]}
         b.set_launch(64, 64, -1)
         b.set_map_adds(mcx.MAP_ADDS_64)  # the fixed baseline: plain 64-bit atomic adds
         timed("fixed")

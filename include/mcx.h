@@ -138,7 +138,8 @@ typedef struct {
   double kernel_ms;         /* transport kernel time of the last run (HIP events) */
   double run_ms;            /* whole last run: clear + transport + reductions */
   int32_t grid_blocks, block_size;
-  int32_t map_adds;         /* MCX_MAP_ADDS_64 or MCX_MAP_ADDS_32: the last launch's map adds */
+  int32_t map_adds;         /* MCX_MAP_ADDS_64 or MCX_MAP_ADDS_32: the last launch's map adds
+                               of this simulation */
   int32_t reserved;
 } mcx_run_stats;
 

@@ -172,6 +172,7 @@ struct SimHost {
   // map's atomics bind rather than instruction issue
   bool thin = false;
   double events = 1.0;  // estimated segments per photon (describe)
+  bool last_map32 = false;  // the last launch's kind of map add
   int rec_len = 0;
   uint64_t label_off = 0, tally_off = 0, table_off = 0;
   uint64_t rec_off = 0;    // first record row (photon-index array)
@@ -207,7 +208,6 @@ struct mcx_ctx {
   std::vector<std::pair<int, std::vector<std::array<int, 6>>>> shaped;
   int force_variant = -1;  // kernel variant of the next launches (-1: opt.kernel_variant)
   int map_adds = MCX_MAP_ADDS_AUTO;  // how the kernel adds to map cells (mcx_set_map_adds)
-  bool last_map32 = false;           // the last launch's choice
   int table_rows = 0, nmedia_max = 0;
   uint64_t total_cells = 0, max_cells = 0;
 
@@ -881,7 +881,7 @@ static mcx_status enqueue(mcx_ctx* c, const uint64_t* first, const uint64_t* n,
   }
   const LaunchShape shape = launch_shape(c, photons, thin);
   for (size_t i = 0; i < ns; ++i) {
-    const SimHost& sh = c->sims[i];
+    SimHost& sh = c->sims[i];
     mcx::SimDesc& d = desc[i];
     memset(&d, 0, sizeof(d));
     d.labels = c->d_labels + sh.label_off;
@@ -941,7 +941,8 @@ static mcx_status enqueue(mcx_ctx* c, const uint64_t* first, const uint64_t* n,
     d.q_inv = 1.f / d.q_unit;
     std::copy(sh.wbox.begin(), sh.wbox.end(),
               reinterpret_cast<int32_t*>(wbox.data() + i * 2 * mcx::kMaxWinGates));
-    d.map32 = map32(c, shape, sh.thin) ? 1 : 0;
+    sh.last_map32 = map32(c, shape, sh.thin);
+    d.map32 = sh.last_map32 ? 1 : 0;
     job_start[i + 1] = job_start[i] + (n[i] + shape.chunk - 1) / shape.chunk;
   }
   // Home-wave shares: each simulation's estimated work, scaled to integers
@@ -981,7 +982,6 @@ static mcx_status enqueue(mcx_ctx* c, const uint64_t* first, const uint64_t* n,
   lp.table_rows = c->table_rows;
   lp.nmedia_max = c->nmedia_max;
   lp.window_cells = c->win_cells;
-  c->last_map32 = desc[0].map32 != 0;
   c->last_grid = shape.grid;
   c->last_block = shape.block;
 
@@ -1199,7 +1199,7 @@ static mcx_status stats_of(mcx_ctx* c, int32_t sim, mcx_run_stats* o) {
   }
   o->grid_blocks = c->last_grid ? c->last_grid : c->grid;
   o->block_size = c->last_block ? c->last_block : c->block;
-  o->map_adds = c->last_map32 ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64;
+  o->map_adds = sh.last_map32 ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64;
   return MCX_OK;
 }
 

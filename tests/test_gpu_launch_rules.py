@@ -80,3 +80,34 @@ def test_waves_follow_the_photons_per_lane(mus, waves):
             assert sim.stats()["map_adds"] == adds
         sim.set_launch(256, 64, 0)  # a block size asked for is kept
         assert shape_of(sim, 1000)[1] == 256
+
+
+def thin_and_thick():
+    """Two cubes in one batch, the first of thin voxels (mus h = 1), the
+    second of thick ones (5), with enough photons for 32-bit map adds."""
+    thin = W.cube_homogeneous(n=24).replace(src_pos=(11.5, 11.5, 0.0))
+    thick = W.with_medium(thin, 1, (0.05, 5.0, 0.5, 1.37)).replace(ngates=3, dt=1.0)
+    return [thin, thick], [5 * 1024 * cus()] * 2, [3, 4]
+
+
+@pytest.mark.parametrize("order", [(0, 1), (1, 0)])
+def test_kinds_of_map_add_in_a_mixed_batch(order):
+    """Waves that move between simulations whose maps take 32-bit adds and
+    ones that take 64-bit adds: the maps are those of either kind for all,
+    bit for bit, and each simulation's statistics report its own kind."""
+    probs, n, seeds = thin_and_thick()
+    probs = [probs[i] for i in order]
+    say(f"[gpu] mixed kinds, order {order}, {n} photons")
+    maps, kinds = [], []
+    with mcx.Batch(probs) as b:
+        for adds in (mcx.MAP_ADDS_AUTO, mcx.MAP_ADDS_32, mcx.MAP_ADDS_64):
+            b.set_map_adds(adds)
+            b.run(n, seeds)
+            maps.append([b.fluence(i, mcx.MCX_RAW, f64=True) for i in range(2)])
+            kinds.append([b.stats(i)["map_adds"] for i in range(2)])
+    for m in maps[1:]:
+        for i in range(2):
+            assert np.array_equal(m[i], maps[0][i])
+    by_rule = [mcx.MAP_ADDS_32, mcx.MAP_ADDS_64]  # thin, thick
+    assert kinds[0] == [by_rule[i] for i in order]
+    assert kinds[1] == [mcx.MAP_ADDS_32] * 2 and kinds[2] == [mcx.MAP_ADDS_64] * 2
