@@ -165,7 +165,8 @@ typedef struct {
   double best_ms;           /* pilot kernel time with the chosen shape */
   double ms_per_photon;     /* slope a of T = a n + T0 fitted from two pilot sizes */
   double overhead_ms;       /* intercept T0 of that fit */
-  int32_t map_adds;         /* chosen MCX_MAP_ADDS_64 or MCX_MAP_ADDS_32 */
+  int32_t map_adds;         /* chosen MCX_MAP_ADDS_64 or MCX_MAP_ADDS_32; where each simulation
+                               of a batch keeps its own, that of most pilot photons */
   int32_t reserved;
 } mcx_tune_result;
 

@@ -677,9 +677,14 @@ static bool map32(const mcx_ctx* c, const LaunchShape& s, bool thin) {
   return thin && s.many && c->cus > 0 && (s.grid / c->cus) * (s.block / 64) >= 16;
 }
 
-// The same for the context's shape and large launches of its simulations.
-static bool map32_large(const mcx_ctx* c) {
-  return map32(c, LaunchShape{c->grid, c->block, c->chunk, true}, c->sims[0].thin);
+// The kind large launches take at the context's shape: MCX_MAP_ADDS_32 or
+// MCX_MAP_ADDS_64, or MCX_MAP_ADDS_AUTO where its simulations differ.
+static int map_adds_large(const mcx_ctx* c) {
+  const LaunchShape s{c->grid, c->block, c->chunk, true};
+  const bool first = map32(c, s, c->sims[0].thin);
+  for (const SimHost& sh : c->sims)
+    if (map32(c, s, sh.thin) != first) return MCX_MAP_ADDS_AUTO;
+  return first ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64;
 }
 
 // Make stream st wait for the context's last clear or launch.
@@ -1581,68 +1586,88 @@ mcx_status mcx_autotune(mcx_ctx* c, const uint64_t* pilot_photons, const uint64_
     float ms;
     int block, chunk, window, adds;
   };
+  // the rule's map adds at the shape just set: in a batch the rule itself, by
+  // which each simulation takes its own kind
+  auto rule = [&]() { return ns > 1 ? MCX_MAP_ADDS_AUTO : map_adds_large(c); };
+  // and the kinds that are not it
+  auto others = [&]() -> std::vector<int> {
+    const int kind = map_adds_large(c);
+    if (kind == MCX_MAP_ADDS_32) return {MCX_MAP_ADDS_64};
+    if (kind == MCX_MAP_ADDS_64) return {MCX_MAP_ADDS_32};
+    return {MCX_MAP_ADDS_64, MCX_MAP_ADDS_32};
+  };
   std::vector<Cand> timed;
   const Cand untuned{ms, c->block, ns > 1 ? kBatchChunk : kDefaultChunk, kDefaultWindow,
-                     map32_large(c) ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64};
+                     rule()};
   timed.push_back(untuned);
   for (int wi = 0; wi < nwin; ++wi) {
     for (int b : blocks) {
       for (int ch : chunks) {
         if (mcx_set_launch(c, b, ch, windows[wi]) != MCX_OK) continue;
         MCX_TRY(pilot(pilot_photons, &ms));
-        timed.push_back({ms, c->block, ch, windows[wi],
-                         map32_large(c) ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64});
+        timed.push_back({ms, c->block, ch, windows[wi], rule()});
       }
     }
   }
-  // the four fastest shapes again with the other kind of map add
+  // the fastest shapes again with the other kinds of map add, four pilots
   std::sort(timed.begin(), timed.end(), [](const Cand& x, const Cand& y) { return x.ms < y.ms; });
   const size_t nshape = timed.size();
-  for (size_t k = 0; k < std::min<size_t>(4, nshape); ++k) {
+  size_t again = 0;
+  for (size_t k = 0; k < nshape && again < 4; ++k) {
     Cand t = timed[k];
-    t.adds = t.adds == MCX_MAP_ADDS_32 ? MCX_MAP_ADDS_64 : MCX_MAP_ADDS_32;
     if (mcx_set_launch(c, t.block, t.chunk, t.window) != MCX_OK) continue;
-    c->map_adds = t.adds;
-    MCX_TRY(pilot(pilot_photons, &t.ms));
-    c->map_adds = MCX_MAP_ADDS_AUTO;
-    timed.push_back(t);
+    for (int kind : others()) {
+      if (again++ == 4) break;
+      t.adds = kind;
+      c->map_adds = kind;
+      MCX_TRY(pilot(pilot_photons, &t.ms));
+      c->map_adds = MCX_MAP_ADDS_AUTO;
+      timed.push_back(t);
+    }
   }
   Cand best = *std::min_element(
       timed.begin(), timed.end(), [](const Cand& x, const Cand& y) { return x.ms < y.ms; });
-  // the kind of map add at that shape, from both kinds timed again three
-  // times, alternately: on pilots the two kinds are within the timing noise
+  // the kind of map add at that shape, from the kinds timed again three
+  // times, alternately: on pilots the kinds are within the timing noise
   // of each other where at full size the rule's kind is ahead (sphere
   // benchmark, 1e8 photons: 32-bit adds 6.5 % faster; head phantom: 64-bit
   // adds 7 % faster, where pilots had favoured 32-bit ones by 3 %), so the
-  // rule's kind stays unless the other is more than 10 % faster
+  // rule's kind (in a batch the rule) stays unless another is more than 10 %
+  // faster
   if (mcx_set_launch(c, best.block, best.chunk, best.window) == MCX_OK) {
     c->map_adds = MCX_MAP_ADDS_AUTO;
-    const int rule = map32_large(c) ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64;
-    const int other = rule == MCX_MAP_ADDS_32 ? MCX_MAP_ADDS_64 : MCX_MAP_ADDS_32;
-    float t_rule = 3.4e38f, t_other = 3.4e38f;
-    for (int rep = 0; rep < 3; ++rep) {
-      c->map_adds = rule;
-      MCX_TRY(pilot(pilot_photons, &ms));
-      t_rule = std::min(t_rule, ms);
-      c->map_adds = other;
-      MCX_TRY(pilot(pilot_photons, &ms));
-      t_other = std::min(t_other, ms);
-    }
+    std::vector<int> kinds{rule()};
+    for (int kind : others()) kinds.push_back(kind);
+    std::vector<float> t(kinds.size(), 3.4e38f);
+    for (int rep = 0; rep < 3; ++rep)
+      for (size_t k = 0; k < kinds.size(); ++k) {
+        c->map_adds = kinds[k];
+        MCX_TRY(pilot(pilot_photons, &ms));
+        t[k] = std::min(t[k], ms);
+      }
     c->map_adds = MCX_MAP_ADDS_AUTO;
-    const bool keep = !(t_other < 0.90f * t_rule);
-    best.adds = keep ? rule : other;
-    best.ms = keep ? t_rule : t_other;
+    size_t pick = 0;
+    for (size_t k = 1; k < kinds.size(); ++k)
+      if (t[k] < 0.90f * t[0] && t[k] < t[pick]) pick = k;
+    best.adds = kinds[pick];
+    best.ms = t[pick];
   }
   // a shape that won its one pilot by chance is not kept over the default
   if (best.ms > untuned.ms) best = untuned;
   out->block_size = best.block;
   out->refill_chunk = best.chunk;
   out->lds_window_cells = best.window;
-  out->map_adds = best.adds;
   out->candidates = static_cast<int32_t>(timed.size());
   out->best_ms = best.ms;
   MCX_TRY(mcx_set_launch(c, out->block_size, out->refill_chunk, out->lds_window_cells));
   c->map_adds = best.adds;
+  uint64_t thin = 0, all = 0;
+  for (size_t i = 0; i < ns; ++i) {
+    all += pilot_photons[i];
+    if (c->sims[i].thin) thin += pilot_photons[i];
+  }
+  out->map_adds = map32(c, LaunchShape{c->grid, c->block, c->chunk, true}, 2 * thin > all)
+                      ? MCX_MAP_ADDS_32 : MCX_MAP_ADDS_64;
   float t_full = 0.f, t_half = 0.f;
   MCX_TRY(pilot(pilot_photons, &t_full));
   MCX_TRY(pilot(half.data(), &t_half));

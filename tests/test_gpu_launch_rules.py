@@ -111,3 +111,20 @@ def test_kinds_of_map_add_in_a_mixed_batch(order):
     by_rule = [mcx.MAP_ADDS_32, mcx.MAP_ADDS_64]  # thin, thick
     assert kinds[0] == [by_rule[i] for i in order]
     assert kinds[1] == [mcx.MAP_ADDS_32] * 2 and kinds[2] == [mcx.MAP_ADDS_64] * 2
+
+
+@pytest.mark.parametrize("order", [(0, 1), (1, 0)])
+def test_tuning_a_mixed_batch_keeps_the_rule(order):
+    """Pilots too short for the kind of map add to matter: the autotuner
+    leaves each simulation of the batch its own kind, whichever is first."""
+    probs, n, seeds = thin_and_thick()
+    probs = [probs[i] for i in order]
+    with mcx.Batch(probs) as b:
+        tune = b.autotune([20000, 20000], seeds)
+        say("[gpu] tuned a mixed batch", order, tune)
+        assert tune["map_adds"] in (mcx.MAP_ADDS_64, mcx.MAP_ADDS_32)
+        b.set_launch(0, 0, 0)  # the kinds of map add stay
+        b.run(n, seeds)
+        kinds = [b.stats(i)["map_adds"] for i in range(2)]
+    by_rule = [mcx.MAP_ADDS_32, mcx.MAP_ADDS_64]
+    assert kinds == [by_rule[i] for i in order]
