@@ -161,8 +161,8 @@ typedef struct {
   int32_t refill_chunk;     /* chosen photons per job */
   int32_t lds_window_cells; /* chosen LDS window (-1 = none) */
   int32_t candidates;       /* launch shapes timed */
-  double default_ms;        /* pilot kernel time with the default shape */
-  double best_ms;           /* pilot kernel time with the chosen shape */
+  double default_ms;        /* pilot kernel time with the default shape, the best of three */
+  double best_ms;           /* and with the chosen shape; equal where the default is kept */
   double ms_per_photon;     /* slope a of T = a n + T0 fitted from two pilot sizes */
   double overhead_ms;       /* intercept T0 of that fit */
   int32_t map_adds;         /* chosen MCX_MAP_ADDS_64 or MCX_MAP_ADDS_32; where each simulation
@@ -274,14 +274,17 @@ mcx_status mcx_shape_window(mcx_ctx *ctx, const uint64_t *pilot_photons, const u
  * 256, 1024} photons (1 to 16 photons per lane) x deposit schemes {direct
  * global atomics, LDS window of 8192, 16384, 32768 or 36864 cells} (shapes that
  * do not fit on a compute unit are skipped; each timed with the map adds
- * MCX_MAP_ADDS_AUTO picks for it, and the four fastest again with the other
- * kind), keeps the fastest shape -- with the map adds MCX_MAP_ADDS_AUTO picks
- * for it unless the other kind is more than 10 % faster over three alternate
- * re-timings of both -- and fits
- * (single simulations without digests and with hardware math: the window boxes
- * are first shaped by a flush census -- one pilot counting, per map cell, the
- * cell visits the kernel adds to the map -- per gate the box grown from its
- * busiest cell by the densest slabs that fit the candidate's cell count),
+ * MCX_MAP_ADDS_AUTO picks for it, and the fastest again with the other kinds,
+ * four pilots).  Single simulations without digests and with hardware math: the
+ * window boxes are first shaped by a flush census -- one pilot counting, per
+ * map cell, the cell visits the kernel adds to the map -- per gate the box grown
+ * from its busiest cell by the densest slabs that fit the candidate's cell
+ * count.  The fastest shape and the default shape (with its own window box)
+ * are then timed three times, alternately, and the faster is kept, with the map
+ * adds MCX_MAP_ADDS_AUTO picks for it unless another kind is more than 10 %
+ * faster.  What is kept is an explicit shape: later launches of any size use
+ * it, as after mcx_set_launch (mcx_set_launch(ctx, 0, 0, 0) goes back to
+ * shapes by the photons of each launch).  Last, fits
  * the linear device runtime model T = a n + T0 of the paper's device-level
  * load balancing (the study of Fig. 3(b)) from pilots of n and n/2 photons.
  * Results do not depend on the shape (the random numbers are keyed by photon

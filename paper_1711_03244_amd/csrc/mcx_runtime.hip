@@ -1579,12 +1579,22 @@ mcx_status mcx_autotune(mcx_ctx* c, const uint64_t* pilot_photons, const uint64_
   float ms = 0.f;
   MCX_TRY(pilot(pilot_photons, &ms));
   MCX_TRY(pilot(pilot_photons, &ms));
-  out->default_ms = ms;
+  const int default_block = c->block;
   // then window boxes shaped by a flush census for the candidates below
   MCX_TRY(census(c, pilot_photons, seed, windows, nwin));
+  const auto boxes = c->shaped;
   struct Cand {
     float ms;
     int block, chunk, window, adds;
+    bool shaped;  // with the census's boxes for its window, or the default box
+  };
+  auto use = [&](const Cand& k) -> mcx_status {
+    c->shaped = boxes;
+    if (!k.shaped)
+      c->shaped.erase(std::remove_if(c->shaped.begin(), c->shaped.end(),
+                                     [&](const auto& e) { return e.first == k.window; }),
+                      c->shaped.end());
+    return mcx_set_launch(c, k.block, k.chunk, k.window);
   };
   // the rule's map adds at the shape just set: in a batch the rule itself, by
   // which each simulation takes its own kind
@@ -1597,15 +1607,17 @@ mcx_status mcx_autotune(mcx_ctx* c, const uint64_t* pilot_photons, const uint64_
     return {MCX_MAP_ADDS_64, MCX_MAP_ADDS_32};
   };
   std::vector<Cand> timed;
-  const Cand untuned{ms, c->block, ns > 1 ? kBatchChunk : kDefaultChunk, kDefaultWindow,
-                     rule()};
+  Cand untuned{ms, default_block, ns > 1 ? kBatchChunk : kDefaultChunk, kDefaultWindow, rule(),
+               false};
   timed.push_back(untuned);
   for (int wi = 0; wi < nwin; ++wi) {
     for (int b : blocks) {
       for (int ch : chunks) {
-        if (mcx_set_launch(c, b, ch, windows[wi]) != MCX_OK) continue;
-        MCX_TRY(pilot(pilot_photons, &ms));
-        timed.push_back({ms, c->block, ch, windows[wi], rule()});
+        Cand t{0.f, b, ch, windows[wi], 0, true};
+        if (use(t) != MCX_OK) continue;
+        t.adds = rule();
+        MCX_TRY(pilot(pilot_photons, &t.ms));
+        timed.push_back(t);
       }
     }
   }
@@ -1615,7 +1627,7 @@ mcx_status mcx_autotune(mcx_ctx* c, const uint64_t* pilot_photons, const uint64_
   size_t again = 0;
   for (size_t k = 0; k < nshape && again < 4; ++k) {
     Cand t = timed[k];
-    if (mcx_set_launch(c, t.block, t.chunk, t.window) != MCX_OK) continue;
+    if (use(t) != MCX_OK) continue;
     for (int kind : others()) {
       if (again++ == 4) break;
       t.adds = kind;
@@ -1634,32 +1646,38 @@ mcx_status mcx_autotune(mcx_ctx* c, const uint64_t* pilot_photons, const uint64_
   // adds 7 % faster, where pilots had favoured 32-bit ones by 3 %), so the
   // rule's kind (in a batch the rule) stays unless another is more than 10 %
   // faster
-  if (mcx_set_launch(c, best.block, best.chunk, best.window) == MCX_OK) {
-    c->map_adds = MCX_MAP_ADDS_AUTO;
-    std::vector<int> kinds{rule()};
-    for (int kind : others()) kinds.push_back(kind);
-    std::vector<float> t(kinds.size(), 3.4e38f);
-    for (int rep = 0; rep < 3; ++rep)
-      for (size_t k = 0; k < kinds.size(); ++k) {
-        c->map_adds = kinds[k];
-        MCX_TRY(pilot(pilot_photons, &ms));
-        t[k] = std::min(t[k], ms);
-      }
-    c->map_adds = MCX_MAP_ADDS_AUTO;
-    size_t pick = 0;
-    for (size_t k = 1; k < kinds.size(); ++k)
-      if (t[k] < 0.90f * t[0] && t[k] < t[pick]) pick = k;
-    best.adds = kinds[pick];
-    best.ms = t[pick];
+  MCX_TRY(use(best));
+  std::vector<int> kinds{rule()};
+  for (int kind : others()) kinds.push_back(kind);
+  std::vector<float> t(kinds.size(), 3.4e38f);
+  untuned.ms = 3.4e38f;
+  for (int rep = 0; rep < 3; ++rep) {
+    MCX_TRY(use(best));
+    for (size_t k = 0; k < kinds.size(); ++k) {
+      c->map_adds = kinds[k];
+      MCX_TRY(pilot(pilot_photons, &ms));
+      t[k] = std::min(t[k], ms);
+    }
+    // the default beside them, as often and as it would be kept
+    MCX_TRY(use(untuned));
+    c->map_adds = untuned.adds;
+    MCX_TRY(pilot(pilot_photons, &ms));
+    untuned.ms = std::min(untuned.ms, ms);
   }
+  size_t pick = 0;
+  for (size_t k = 1; k < kinds.size(); ++k)
+    if (t[k] < 0.90f * t[0] && t[k] < t[pick]) pick = k;
+  best.adds = kinds[pick];
+  best.ms = t[pick];
   // a shape that won its one pilot by chance is not kept over the default
-  if (best.ms > untuned.ms) best = untuned;
+  if (best.ms >= untuned.ms) best = untuned;
+  out->default_ms = untuned.ms;
   out->block_size = best.block;
   out->refill_chunk = best.chunk;
   out->lds_window_cells = best.window;
   out->candidates = static_cast<int32_t>(timed.size());
   out->best_ms = best.ms;
-  MCX_TRY(mcx_set_launch(c, out->block_size, out->refill_chunk, out->lds_window_cells));
+  MCX_TRY(use(best));
   c->map_adds = best.adds;
   uint64_t thin = 0, all = 0;
   for (size_t i = 0; i < ns; ++i) {

@@ -128,3 +128,32 @@ def test_tuning_a_mixed_batch_keeps_the_rule(order):
         kinds = [b.stats(i)["map_adds"] for i in range(2)]
     by_rule = [mcx.MAP_ADDS_32, mcx.MAP_ADDS_64]
     assert kinds == [by_rule[i] for i in order]
+
+
+def test_tuner_keeps_what_it_timed():
+    """Where no shape beats the default in the pilots, the kept shape is the
+    default's, its window boxes included: a run then flushes the same visits as
+    one with that shape in a context that was never tuned."""
+    p = W.cube_sphere(n=40, ngates=10, dt=0.5)
+    N = 20000
+    kept = 0
+    for pilot in (1, 64, 100, 150, 200, 250, 300, 400, 500):
+        with mcx.Simulation(p) as sim:
+            tune = sim.autotune(pilot, 9)
+            say("[gpu] tuned with", pilot, tune)
+            assert tune["best_ms"] <= tune["default_ms"]
+            sim.run(N, 3)
+            st = sim.stats()
+        assert st["block_size"] == tune["block_size"]
+        if tune["best_ms"] < tune["default_ms"]:
+            continue
+        kept += 1
+        with mcx.Simulation(p) as sim:
+            sim.set_launch(tune["block_size"], tune["refill_chunk"], tune["lds_window_cells"])
+            sim.set_map_adds(tune["map_adds"])
+            sim.run(N, 3)
+            assert sim.stats()["flushes"] == st["flushes"]
+        if kept == 2:
+            return
+    if not kept:
+        pytest.skip("another shape was faster in every pilot")
