@@ -1845,7 +1845,11 @@ __device__ __forceinline__ void stream_stages(int nt, Load load) {
 // channels, 32 output channels and all 27 taps, or with kPlane one plane dz
 // of 9 (three workgroups), and walks the 4 x 4 x 8-voxel tiles blockIdx.x,
 // + gridDim.x, ...: per tile the 6 x 6 x 10 brick of x and the tile of gy.
-// The compute waves share the taps.
+// The compute waves share the taps.  Where tiles end past the volume (kEdge), the
+// activations that the zero gradients there meet are read from a block of
+// zeros: an infinite one, inside the volume, would make sums NaN that it is no
+// part of.  That is a choice of address for each two slices (62 x 62 x 63, 32 -> 32:
+// 42.3 us a call with the zeros left out, 43.7; masking the fragments 48).
 // What bounds it: a tile's 31 KB arrive in 1.2 us where its matrix
 // instructions take 0.75; below four tiles a workgroup the partial sums, 28 MB
 // for 256 workgroups with all taps.  The slab kernel copied the tiles through
@@ -1858,6 +1862,9 @@ struct WBrick {
   static constexpr int kPieces = 360 * 4;               // 16-byte pieces of a brick
   static constexpr int kBrickLoads = 23, kLoads = 31;   // wave loads: brick, then gy
   static constexpr int kStageBytes = kLoads * 1024;
+  // zeros as far as a tap's reads reach: two planes, three rows and three voxels
+  static constexpr int kZeroBytes = 384 * 16;
+  static_assert((2 * 36 + 3 * 6 + 2 + 1) * 64 <= kZeroBytes, "one chunk a thread covers them");
 };
 
 template <int LW>
@@ -1909,9 +1916,10 @@ __device__ __forceinline__ void wbrick_loader(const WgradArgs& a, char* s_st, in
   });
 }
 
-template <bool kPlane, int W>
+template <bool kPlane, bool kEdge, int W>
 __device__ __forceinline__ void wbrick_compute(const WgradArgs& a, const char* s_st, int lane,
-                                               int c0, int n0, int dz0, int nt) {
+                                               int c0, int n0, int dz0, int tx_n, int ty_n,
+                                               int nt) {
   using K = WBrick;
   // the last wave, which has the fewest taps, sums gy for the bias gradient
   const bool bias = W == 3 && a.gb && c0 == 0 && dz0 == 0;
@@ -1932,12 +1940,31 @@ __device__ __forceinline__ void wbrick_compute(const WgradArgs& a, const char* s
     // the two 16-channel halves, as they lie for even y >> 1
     const char* xh[2] = {st + xo + (g & 1) * 32, st + xo + ((g & 1) ^ 1) * 32};
     const char* gh[2] = {st + go + (g & 1) * 32, st + go + ((g & 1) ^ 1) * 32};
+    // kEdge: whether the voxels this lane reads, of its two rows, and how many
+    // of the tile's slices lie in the volume; the others are read from the zeros
+    bool in_row[2] = {true, true};
+    int in_z = 8;
+    if constexpr (kEdge) {
+      const int tile = blockIdx.x + s * gridDim.x;
+      const int x = a.w - (tile % tx_n) * 4 - ((lane >> 2) & 3);
+      const int y = a.h - ((tile / tx_n) % ty_n) * 4 - 2 * (g & 1);
+      in_row[0] = x > 0 && y > 0;
+      in_row[1] = x > 0 && y > 1;
+      in_z = a.d - (tile / (tx_n * ty_n)) * 8 - (g >> 1);
+    }
+    const char* xr[2][2] = {{xh[0], xh[1]}, {xh[0], xh[1]}};  // row, half: of the step
     auto read_x = [&](int i, bf16x8 (&f)[2]) {  // tap i % kNT of step i / kNT
       const int ks = i / kNT, t = kT0 + i % kNT, dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
+      if (kEdge && i % kNT == 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          xr[q >> 1][q & 1] = in_row[q >> 1] && 2 * ks < in_z
+                                  ? xh[q & 1] : s_st + 3 * K::kStageBytes - 2 * ks * 36 * 64;
+      }
       const int o = ((2 * ks + dz) * 36 + dy * 6 + dx) * 64;
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb)
-        f[cb] = read_tr(xh[cb ^ (dy >> 1)] + o, xh[cb ^ ((dy + 1) >> 1)] + o + 6 * 64);
+        f[cb] = read_tr(xr[0][cb ^ (dy >> 1)] + o, xr[1][cb ^ ((dy + 1) >> 1)] + o + 6 * 64);
     };
     bf16x8 xf[2][2], gf[2];
     read_x(0, xf[0]);
@@ -1982,20 +2009,23 @@ __device__ __forceinline__ void wbrick_compute(const WgradArgs& a, const char* s
 }
 
 // blockIdx.y: 32 input channels (kPlane: times 3, plus dz), blockIdx.z: 32 output channels
-template <bool kPlane>
+template <bool kPlane, bool kEdge>
 __global__ void __launch_bounds__(384) wgrad_brick_kernel(WgradArgs a) {
-  __shared__ __align__(16) char s_st[3 * WBrick::kStageBytes];
+  __shared__ __align__(16) char s_st[3 * WBrick::kStageBytes + (kEdge ? WBrick::kZeroBytes : 0)];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tx_n = (a.w + 3) >> 2, ty_n = (a.h + 3) >> 2, tiles = tx_n * ty_n * ((a.d + 7) >> 3);
   const int nt = (tiles - blockIdx.x + gridDim.x - 1) / gridDim.x;
   const int dz0 = kPlane ? blockIdx.y % 3 : 0;
   const int c0 = (kPlane ? blockIdx.y / 3 : blockIdx.y) * 32, n0 = blockIdx.z * 32;
+  if constexpr (kEdge)  // ahead of the first stage's barrier
+    *reinterpret_cast<uint4*>(s_st + 3 * WBrick::kStageBytes + threadIdx.x * 16) =
+        make_uint4(0u, 0u, 0u, 0u);
   switch (wave) {
-    case 0: wbrick_compute<kPlane, 0>(a, s_st, lane, c0, n0, dz0, nt); break;
-    case 1: wbrick_compute<kPlane, 1>(a, s_st, lane, c0, n0, dz0, nt); break;
-    case 2: wbrick_compute<kPlane, 2>(a, s_st, lane, c0, n0, dz0, nt); break;
-    case 3: wbrick_compute<kPlane, 3>(a, s_st, lane, c0, n0, dz0, nt); break;
+    case 0: wbrick_compute<kPlane, kEdge, 0>(a, s_st, lane, c0, n0, dz0, tx_n, ty_n, nt); break;
+    case 1: wbrick_compute<kPlane, kEdge, 1>(a, s_st, lane, c0, n0, dz0, tx_n, ty_n, nt); break;
+    case 2: wbrick_compute<kPlane, kEdge, 2>(a, s_st, lane, c0, n0, dz0, tx_n, ty_n, nt); break;
+    case 3: wbrick_compute<kPlane, kEdge, 3>(a, s_st, lane, c0, n0, dz0, tx_n, ty_n, nt); break;
     case 4: wbrick_loader<0>(a, s_st, lane, c0, n0, tx_n, ty_n, nt); break;
     default: wbrick_loader<1>(a, s_st, lane, c0, n0, tx_n, ty_n, nt); break;
   }
@@ -3130,10 +3160,15 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
                   static_cast<unsigned>(cols));
     };
     const int ns = tr_ns(a), cb = (a.cin + 31) / 32, nb = (a.cout + 31) / 32;
-    if (a.geo == kConv3 && tr_plane(a))
-      wgrad_brick_kernel<true><<<g(3 * cb, nb), 384, 0, s>>>(a);
+    const bool edge = a.w % 4 != 0 || a.h % 4 != 0 || a.d % 8 != 0;
+    if (a.geo == kConv3 && tr_plane(a) && edge)
+      wgrad_brick_kernel<true, true><<<g(3 * cb, nb), 384, 0, s>>>(a);
+    else if (a.geo == kConv3 && tr_plane(a))
+      wgrad_brick_kernel<true, false><<<g(3 * cb, nb), 384, 0, s>>>(a);
+    else if (a.geo == kConv3 && edge)
+      wgrad_brick_kernel<false, true><<<g(cb, nb), 384, 0, s>>>(a);
     else if (a.geo == kConv3)
-      wgrad_brick_kernel<false><<<g(cb, nb), 384, 0, s>>>(a);
+      wgrad_brick_kernel<false, false><<<g(cb, nb), 384, 0, s>>>(a);
     else if (a.geo == kUp && ns == 4)
       wgrad_pair_kernel<true, 4><<<g(nb, (a.cin + 63) / 64), 384, 0, s>>>(a);
     else if (a.geo == kUp)
