@@ -1460,8 +1460,9 @@ __global__ void __launch_bounds__(256) split_reduce_kernel(ConvArgs a, int nspli
 // p = t * cin + ci.  kConv3 / kDown: m runs over the output grid, A is x
 // gathered at the tap; kUp: m runs over the input grid, A = x[m] and gy is
 // read at the parity-class position of tap t (all rows of a tile share t).
+// kVec, vec_gy: x, gy in 16-byte pieces (channels in eights, aligned).
 template <int NB, bool kVec>
-__global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a) {
+__global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a, bool vec_gy) {
   __shared__ uint16_t sA[kBM][kBK + kPadK];       // [p][m]
   __shared__ uint16_t sB[16 * NB][kBK + kPadK];   // [n][m]
   const int tid = threadIdx.x;
@@ -1543,7 +1544,7 @@ __global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a) {
                    (2 * a.w) + 2 * x + (t_up & 1);
         }
         const uint16_t* row = a.gy + gi * a.cout + n0 + nc;
-        if (a.cout % 8 == 0 && n0 + nc + 8 <= a.cout) {
+        if (vec_gy && n0 + nc + 8 <= a.cout) {
           const uint4 v = *reinterpret_cast<const uint4*>(row);
           e[0] = v.x & 0xffff; e[1] = v.x >> 16; e[2] = v.y & 0xffff; e[3] = v.y >> 16;
           e[4] = v.z & 0xffff; e[5] = v.z >> 16; e[6] = v.w & 0xffff; e[7] = v.w >> 16;
@@ -1596,10 +1597,16 @@ __global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a) {
 // matrix instruction against 4).  The sums are stored to
 // part[blockIdx.x][t][ci][n] and wgrad_reduce_kernel adds them to gw in a
 // fixed order.
+__device__ __forceinline__ uint4 load8(const uint16_t* p, bool vec) {
+  if (vec) return *reinterpret_cast<const uint4*>(p);
+  return make_uint4(p[0] | uint32_t(p[1]) << 16, p[2] | uint32_t(p[3]) << 16,
+                    p[4] | uint32_t(p[5]) << 16, p[6] | uint32_t(p[7]) << 16);
+}
 constexpr int kSlabTZ = 8;                     // z-slices per tile
 constexpr int kSlabRow = kSlabTZ * 6 * 4 + 4;  // one channel's (z, y, 4 x) of a copy, padded
+// vec_x: x aligned, and read in 16-byte pieces.
 template <int NBW>
-__global__ void __launch_bounds__(256) wgrad_slab_kernel(WgradArgs a) {
+__global__ void __launch_bounds__(256) wgrad_slab_kernel(WgradArgs a, bool vec_x) {
   __shared__ __align__(16) uint16_t sXT[3][32][kSlabRow];  // copy dx, channel, (z, y, x - dx)
   __shared__ uint16_t sG[32 * NBW][16 * kSlabTZ + kPadK];  // output channel, tile voxel
   const int tid = threadIdx.x;
@@ -1644,9 +1651,9 @@ __global__ void __launch_bounds__(256) wgrad_slab_kernel(WgradArgs a) {
         const int gx = bx + xx - 1;
         xv[xx] = make_uint4(0u, 0u, 0u, 0u);
         if (row_in && gx >= 0 && gx < a.g.in_w)
-          xv[xx] = *reinterpret_cast<const uint4*>(
+          xv[xx] = load8(
               a.x + ((static_cast<int64_t>(gz) * a.g.in_h + gy) * a.g.in_w + gx) * a.cin + c0 +
-              oc * 8);
+              oc * 8, vec_x);
       }
     }
 #pragma unroll
@@ -1658,15 +1665,11 @@ __global__ void __launch_bounds__(256) wgrad_slab_kernel(WgradArgs a) {
       if (x < a.w && y < a.h && z < a.d) {
         const uint16_t* row =
             a.gy + ((static_cast<int64_t>(z) * a.h + y) * a.w + x) * a.cout + n0 + nc;
-        if (a.cout % 8 == 0 && n0 + nc + 8 <= a.cout) {
-          gv[u] = *reinterpret_cast<const uint4*>(row);
-        } else {
-          uint32_t h[8];
+        uint32_t h[8];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) h[j] = (n0 + nc + j < a.cout) ? row[j] : 0u;
-          gv[u] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
-                             h[6] | (h[7] << 16));
-        }
+        for (int j = 0; j < 8; ++j) h[j] = (n0 + nc + j < a.cout) ? row[j] : 0u;
+        gv[u] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
+                           h[6] | (h[7] << 16));
       }
     }
   };
@@ -2802,11 +2805,13 @@ void launch_up(const ConvArgs& a, hipStream_t s) {
 // The resident-weights kernel: 3x3x3 layers gathering exactly 32 channels,
 // without a skip input, on grids of at least kResidentTiles 4 x 4 x 8 tiles
 // (the full-resolution layers; smaller grids keep the brick kernel, whose
-// split reductions fill the chip).
+// split reductions fill the chip).  Its output waves store 16-byte pieces: an
+// output off that alignment goes to the brick kernel (64^3 32 -> 32: 69 us for
+// 39, and 79 with this kernel's stores by element).
 constexpr int64_t kResidentTiles = 1024;
 bool uses_resident(const ConvArgs& a) {
   return (a.geo == kConv3 || a.geo == kConv3T) && a.cin == 32 && !a.skip && aligned16(a.x) &&
-         brick_tiles(a, 2) >= kResidentTiles;
+         aligned16(a.y) && aligned16(a.gmask) && brick_tiles(a, 2) >= kResidentTiles;
 }
 
 // 4 x 4 columns of all images, each a workgroup's unit of work
@@ -3188,9 +3193,9 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
       const dim3 grid(static_cast<unsigned>(G), static_cast<unsigned>(a.cin / kBK * 3),
                       static_cast<unsigned>((a.cout + 32 * nbw - 1) / (32 * nbw)));
       if (nbw == 2)
-        wgrad_slab_kernel<2><<<grid, 256, 0, s>>>(a);
+        wgrad_slab_kernel<2><<<grid, 256, 0, s>>>(a, aligned16(a.x));
       else
-        wgrad_slab_kernel<1><<<grid, 256, 0, s>>>(a);
+        wgrad_slab_kernel<1><<<grid, 256, 0, s>>>(a, aligned16(a.x));
       return launch_wgrad_reduce(a, G, s);
     }
   }
@@ -3201,12 +3206,13 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>((M + a.m_per_block - 1) / a.m_per_block),
                   static_cast<unsigned>(ptiles),
                   static_cast<unsigned>((a.cout + 16 * nb - 1) / (16 * nb)));
-  const bool vec = a.cin % 8 == 0;
+  const bool vec = a.cin % 8 == 0 && aligned16(a.x);
+  const bool vec_gy = a.cout % 8 == 0 && aligned16(a.gy);
 #define MCX_WG(NB)                                                     \
   if (vec)                                                             \
-    wgrad_kernel<NB, true><<<grid, 256, 0, s>>>(a);                    \
+    wgrad_kernel<NB, true><<<grid, 256, 0, s>>>(a, vec_gy);            \
   else                                                                 \
-    wgrad_kernel<NB, false><<<grid, 256, 0, s>>>(a);
+    wgrad_kernel<NB, false><<<grid, 256, 0, s>>>(a, vec_gy);
   if (nb == 4) { MCX_WG(4) } else if (nb == 2) { MCX_WG(2) } else { MCX_WG(1) }
 #undef MCX_WG
   return hipGetLastError();

@@ -62,3 +62,62 @@ def test_weight_gradient_of_activations_not_finite(shape, ci, co, value):
     assert np.all(np.abs(got - want)[ok] <= 1e-5 * want[ok] + 1e-30)
     size = gy.reshape(-1, co).sum(0)
     assert np.all(np.abs(T.host(gb) - size) <= 1e-5 * size)
+
+
+def placed(a, dtype, shift):
+    """`a` in device memory, `shift` elements past a 16-byte boundary"""
+    t = T.torch()
+    buf = t.zeros(a.size + shift, dtype=dtype, device="cuda")
+    v = buf[shift:].view(a.shape)
+    v.copy_(t.from_numpy(np.ascontiguousarray(a, np.float32)))
+    return v
+
+
+@pytest.mark.parametrize("co,f32,shift", [(32, False, 1), (32, True, 1), (16, False, 3),
+                                          (40, False, 4), (8, True, 2)])
+def test_resident_grids_with_outputs_off_alignment(co, f32, shift):
+    """3x3x3 layers of 32 channels on a grid of 1024 tiles whose output alone
+    is off 16-byte alignment: the same values as an aligned output (FP32 sums
+    in another order: 1e-5 of the sum of the products' sizes, and one BF16
+    rounding, 2^-7, where the output is BF16)."""
+    t = T.torch()
+    shape = (33, 64, 62)
+    say("[gpu] output off alignment", co, f32, shift)
+    x, w, b = T.layer_case("conv3", shape, 32, co, 5)
+    dt = t.float32 if f32 else t.bfloat16
+    xd, wd, bd = T.dev_bf16(x), T.dev_f32(w), T.dev_f32(b)
+    ys = []
+    for sh in (0, shift):
+        y = placed(np.full(shape + (co,), 7.0, np.float32), dt, sh)
+        T.nn.mcx_nn_layer_forward(T.nn.MCX_NN_CONV3, shape, 32, co, xd, wd, bd, relu=False, y=y,
+                                  y_f32=f32)
+        ys.append(T.host(y))
+    size = t.nn.functional.conv3d(
+        t.as_tensor(np.abs(x)).cuda().permute(3, 0, 1, 2)[None].float(),
+        t.as_tensor(np.abs(w)).cuda().reshape(3, 3, 3, 32, co).permute(4, 3, 0, 1, 2).float(),
+        padding=1)[0].permute(1, 2, 3, 0)
+    lim = 1e-5 * T.host(size) + (0 if f32 else 2.0 ** -7 * np.abs(ys[0])) + 1e-6
+    assert np.all(np.abs(ys[0] - ys[1]) <= lim)
+
+
+@pytest.mark.parametrize("xs,gs", [(3, 0), (0, 3), (1, 1)])
+@pytest.mark.parametrize("kind,shape,ci,co", [("conv3", (9, 8, 7), 32, 32), ("conv3", (6, 5, 7), 64, 12),
+                                              ("conv3", (6, 5, 7), 24, 8), ("down", (4, 6, 4), 32, 40),
+                                              ("up", (3, 4, 5), 8, 32)])
+def test_weight_gradients_of_operands_off_alignment(kind, shape, ci, co, xs, gs):
+    """Weight gradients where the activations, the output gradients or both
+    are off 16-byte alignment, against the oracle on BF16 operands: 1e-5 of the
+    sum of the products' sizes."""
+    t = T.torch()
+    say("[gpu] operands off alignment", kind, shape, ci, co, xs, gs)
+    x, w, _ = T.layer_case(kind, shape, ci, co, 51)
+    gy = T.O.bf16(np.random.default_rng(52).normal(size=T.out_shape(kind, shape) + (co,)))
+    ref = T.BWD[kind](x, T.O.bf16(w), gy)
+    lim = T.BWD[kind](np.abs(x), np.abs(T.O.bf16(w)), np.abs(gy))
+    gw = t.full(w.shape, float("nan"), device="cuda")
+    gb = t.full((co,), float("nan"), device="cuda")
+    T.nn.mcx_nn_layer_backward(T.KIND[kind], shape, ci, co, placed(x, t.bfloat16, xs), T.dev_f32(w),
+                               placed(gy, t.bfloat16, gs), None, gw, gb)
+    assert np.all(np.abs(T.host(gw) - ref[1]) <= 1e-5 * lim[1] + 1e-30)
+    size = np.abs(gy).reshape(-1, co).sum(0)
+    assert np.all(np.abs(T.host(gb) - ref[2]) <= 1e-5 * size + 1e-30)
