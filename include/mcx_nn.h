@@ -60,8 +60,7 @@ enum { MCX_NN_CONV3 = 0, MCX_NN_DOWN = 1, MCX_NN_UP = 2 };
  * not required) for volumes of nx x ny x nz voxels (each a multiple of
  * 2^(nlevels-1)); parameters start at zero (set them with
  * mcx_nn_set_params).  Allocates all activation, gradient and optimiser
- * buffers on `device`, and up to 2 GiB (at most an eighth of the free
- * memory) so that mcx_nn_forward_sym's volumes share launches.  MCX_EINVAL / MCX_ENODEV / MCX_ENOMEM. */
+ * buffers on `device`.  MCX_EINVAL / MCX_ENODEV / MCX_ENOMEM. */
 mcx_status mcx_nn_create(const int32_t *channels, int32_t nlevels, int32_t nx, int32_t ny,
                          int32_t nz, int32_t device, mcx_nn **out);
 void mcx_nn_destroy(mcx_nn *nn);
@@ -98,11 +97,13 @@ mcx_status mcx_nn_forward(mcx_nn *nn, const float *phi_in, float *phi_out, float
  * (phi_out).  For a source on the cross-section's centre line each
  * transformed input is the map of the mirrored volume, so every pass
  * estimates the same map (the training pairs are augmented with the same
- * symmetries).  nsym = 1 is mcx_nn_forward.  Costs nsym forward passes
- * (volumes share launches where memory for them was found, with the same
- * results); uses the network's loss buffers as scratch (do not overlap with
- * mcx_nn_loss_grad / mcx_nn_train_step on the same network).  MCX_EINVAL
- * for nsym not in {1, 2, 4, 8}, or 8 with nx != ny.  Async. */
+ * symmetries).  nsym = 1 is mcx_nn_forward.  Costs nsym forward passes.
+ * Volumes share launches, with the same results, where there is memory for
+ * them: a network's first call with nsym > 1 that is not being captured
+ * allocates it, up to 2 GiB and at most an eighth of what is free, and the
+ * network keeps it.  Uses the network's loss buffers as scratch (do not
+ * overlap with mcx_nn_loss_grad / mcx_nn_train_step on the same network).
+ * MCX_EINVAL for nsym not in {1, 2, 4, 8}, or 8 with nx != ny.  Async. */
 mcx_status mcx_nn_forward_sym(mcx_nn *nn, const float *phi_in, float *phi_out, float *u_out,
                               int32_t nsym, void *hip_stream);
 

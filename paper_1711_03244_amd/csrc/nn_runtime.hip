@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/mcx_nn.h"
@@ -242,9 +243,12 @@ struct mcx_nn {
   std::vector<char> fold;
   bool fuse = true;                // use the folds
   double* norm_partial = nullptr; // per-block sums of squares of the gradients
-  int batch = 1;                  // images that share a launch (alloc_images):
+  int batch = 1;                  // images that share a launch (take_images):
+  bool images_asked = false;      // memory for them was looked for
   uint16_t* u16s = nullptr;       // their inputs u16
   float* rs = nullptr;            // and outputs r
+  float* parts = nullptr;         // and workspace, as part
+  int64_t parts_cap = 0;
   float* part = nullptr;          // split-reduction workspace of the convolutions
   int64_t part_cap = 0;           // its size in floats
   std::vector<void*> owned;
@@ -261,38 +265,66 @@ mcx_status nn_alloc(mcx_nn* nn, T** p, size_t count) {
   return MCX_OK;
 }
 
-// Activations, inputs and outputs of images that share each layer's launch:
-// as many of the eight symmetries as fit in kBatchBytes (all eight of a 64^3
-// volume with 32 to 256 channels take 0.7 GB) and in an eighth of the memory
-// that is free.
+// Activations, inputs, outputs and workspace of images that share each layer's
+// launch: as many of the symmetries as the cross-section has (eight, or four
+// where nx != ny) and as fit in kBatchBytes (all eight of a 64^3 volume with 32
+// to 256 channels take 0.7 GB) and in an eighth of the memory that is free.
+// Taken once, by the network's first call over symmetries (networks that train
+// or infer without them do not hold it) and kept until the network goes: a
+// captured graph may hold its addresses.  A call under capture does not allocate;
+// then, and where there is no room, images go one at a time.
 // They are apart from those of one image, which training and plain inference
 // use, so that these stay close together.
 constexpr int64_t kBatchBytes = int64_t(2) << 30;
-mcx_status alloc_images(mcx_nn* nn) {
+void take_images(mcx_nn* nn, hipStream_t s) {
+  if (nn->images_asked) return;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  if (capture != hipStreamCaptureStatusNone) return;
+  nn->images_asked = true;
   const int64_t n0 = nn->g0.vox();
-  int64_t bytes = n0 * (sizeof(uint16_t) + sizeof(float));
-  for (const Layer& L : nn->layers) bytes += L.out.vox() * L.cout * sizeof(uint16_t);
-  nn->batch = 8;
+  int64_t at = 0;  // of the block laid out last
+  char* base = nullptr;
+  auto take = [&](auto** p, int64_t count) {
+    if (base) *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(base + at);
+    at += static_cast<int64_t>(mcx::Scratch::rounded(static_cast<size_t>(count) * sizeof(**p)));
+  };
+  auto lay_out = [&](int images) {
+    at = 0;
+    for (size_t i = 0; i + 1 < nn->layers.size(); ++i) {
+      Layer& L = nn->layers[i];
+      take(&L.acts, images * L.out.vox() * L.cout);
+    }
+    take(&nn->u16s, images * n0);
+    take(&nn->rs, images * n0);
+    nn->parts_cap = 0;
+    for (const Layer& L : nn->layers) {
+      ConvArgs fa = forward_args(L, nullptr, nullptr, nullptr, false, false, nullptr);
+      for (fa.batch = 2; fa.batch <= images; fa.batch *= 2)
+        nn->parts_cap = std::max(nn->parts_cap, conv_workspace_floats(fa));
+    }
+    take(&nn->parts, nn->parts_cap);
+  };
   size_t free = 0, total = 0;
   if (hipMemGetInfo(&free, &total) != hipSuccess) free = 0;
   const int64_t room = std::min<int64_t>(kBatchBytes, static_cast<int64_t>(free / 8));
-  while (nn->batch > 1 && nn->batch * bytes > room) nn->batch /= 2;
-  if (nn->batch == 1) return MCX_OK;
-  const size_t kept = nn->owned.size();
-  auto alloc = [&]() -> mcx_status {
-    for (size_t i = 0; i + 1 < nn->layers.size(); ++i) {
-      Layer& L = nn->layers[i];
-      NN_TRY(nn_alloc(nn, &L.acts, static_cast<size_t>(nn->batch * L.out.vox() * L.cout)));
-    }
-    NN_TRY(nn_alloc(nn, &nn->u16s, static_cast<size_t>(nn->batch * n0)));
-    return nn_alloc(nn, &nn->rs, static_cast<size_t>(nn->batch * n0));
-  };
-  if (alloc() != MCX_OK) {  // no room: one image at a time
+  int images = nn->g0.w == nn->g0.h ? 8 : 4;
+  for (lay_out(images); images > 1 && at > room; lay_out(images)) images /= 2;
+  if (images == 1) return;
+  // another thread's capture does not make this allocation one of its own
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (hipMalloc(&base, static_cast<size_t>(at)) == hipSuccess) {
+    nn->owned.push_back(base);  // reserved
+    lay_out(images);
+    nn->batch = images;
+  } else {
     (void)hipGetLastError();
-    for (; nn->owned.size() > kept; nn->owned.pop_back()) (void)hipFree(nn->owned.back());
-    nn->batch = 1;
   }
-  return MCX_OK;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
 }
 
 void nn_release(mcx_nn* nn) {
@@ -336,8 +368,8 @@ mcx_status run_layers(mcx_nn* nn, int images, hipStream_t s) {
     ConvArgs a = forward_args(L, x, nn->params + L.boff, skip, !out, out,
                               out ? static_cast<void*>(many ? nn->rs : nn->r)
                                   : static_cast<void*>(y));
-    a.part = nn->part;
-    a.part_cap = nn->part_cap;
+    a.part = many ? nn->parts : nn->part;
+    a.part_cap = many ? nn->parts_cap : nn->part_cap;
     a.batch = images;
     NN_HIP(launch_conv(a, s));
     x = y;
@@ -545,16 +577,16 @@ mcx_status mcx_nn_create(const int32_t* channels, int32_t nlevels, int32_t nx, i
     }
     NN_TRY(nn_alloc(nn, &nn->norm_partial, static_cast<size_t>(kNormBlocks)));
     NN_TRY(nn_alloc(nn, &nn->phimax, 1));
-    NN_TRY(alloc_images(nn));
     for (const Layer& Ly : nn->layers) {
-      ConvArgs fa = forward_args(Ly, nullptr, nullptr, nullptr, false, false, nullptr);
-      for (fa.batch = 1; fa.batch <= nn->batch; fa.batch *= 2)
-        nn->part_cap = std::max(nn->part_cap, conv_workspace_floats(fa));
+      nn->part_cap = std::max(nn->part_cap, conv_workspace_floats(
+                                                forward_args(Ly, nullptr, nullptr, nullptr, false,
+                                                             false, nullptr)));
       nn->part_cap = std::max(nn->part_cap, conv_workspace_floats(dgrad_args(Ly, nullptr, nullptr)));
       nn->part_cap =
           std::max(nn->part_cap, wgrad_workspace_floats(wgrad_args(Ly, nullptr, nullptr, nullptr)));
     }
     if (nn->part_cap > 0) NN_TRY(nn_alloc(nn, &nn->part, static_cast<size_t>(nn->part_cap)));
+    nn->owned.reserve(nn->owned.size() + 1);  // take_images'
     NN_HIP(launch_fill(nn->params, static_cast<int64_t>(nn->nparam), 0.f, nn->stream));
     NN_HIP(launch_fill(nn->adam_m, static_cast<int64_t>(nn->nparam), 0.f, nn->stream));
     NN_HIP(launch_fill(nn->adam_v, static_cast<int64_t>(nn->nparam), 0.f, nn->stream));
@@ -644,6 +676,7 @@ mcx_status mcx_nn_forward_sym(mcx_nn* nn, const float* phi_in, float* phi_out, f
   if (nsym == 1) return mcx_nn_forward(nn, phi_in, phi_out, u_out, stream);
   NN_HIP(hipSetDevice(nn->device));
   hipStream_t s = pick(nn, stream);
+  take_images(nn, s);
   NN_TRY(pack_all(nn, s));
   // groups of symmetries share each layer's launch; gout, idle outside
   // mcx_nn_loss_grad, holds the sum of the groups' outputs mapped back

@@ -121,3 +121,78 @@ def test_weight_gradients_of_operands_off_alignment(kind, shape, ci, co, xs, gs)
     assert np.all(np.abs(T.host(gw) - ref[1]) <= 1e-5 * lim[1] + 1e-30)
     size = np.abs(gy).reshape(-1, co).sum(0)
     assert np.all(np.abs(T.host(gb) - ref[2]) <= 1e-5 * size + 1e-30)
+
+
+def free_bytes():
+    t = T.torch()
+    t.cuda.synchronize()
+    return t.cuda.mem_get_info()[0]
+
+
+@pytest.mark.parametrize("shape,images", [((32, 32, 32), 8), ((32, 32, 48), 4)])
+def test_images_take_memory_with_the_first_symmetric_call(shape, images):
+    """The memory of images that share launches comes with the first call that
+    averages over symmetries, for as many as the cross-section has (four where
+    nx != ny), and not with every network."""
+    t = T.torch()
+    channels = (32, 64)
+    nz, ny, nx = shape
+    vox = nz * ny * nx
+    # the layers' outputs: four at full resolution, three at half, one voxel wide
+    # input and output
+    image = vox * (2 * (32 * 4 + 64 * 3 / 8) + 6)
+    _, flat = T.make_net(channels, shape, 31)
+    noisy, clean = T.fluence_pair(shape, 32)
+    x, y = T.dev_f32(noisy), T.dev_f32(clean)
+    u, u1 = t.empty_like(x), t.empty_like(x)
+    say("[gpu] memory of images", shape)
+    with T.nn.Denoiser(channels, shape) as d:
+        d.set_params(flat)
+        d.forward(x, u_out=u)
+        d.loss_grad(x, y, want_loss=False)
+        before = free_bytes()
+        d.forward(x, u_out=u, symmetries=2)
+        held = before - free_bytes()
+        d.forward(x, u_out=u1, symmetries=4)
+        d.forward(x, u_out=u1, symmetries=2)
+        assert before - free_bytes() == held  # once
+    assert t.equal(u, u1)
+    # allocations come in pages of 2 MiB, and a workspace of split sums with them
+    assert (images - 0.5) * image < held < (images + 0.5) * image + (40 << 20)
+
+
+def test_symmetric_call_captured_first():
+    """A graph that holds a network's first call over symmetries: its images go
+    one at a time, and every replay gives the bits of the images that share
+    launches, also after an eager call took memory for those."""
+    t = T.torch()
+    channels, shape = (16, 32), (12, 16, 16)
+    _, flat = T.make_net(channels, shape, 33)
+    x = T.dev_f32(T.fluence_pair(shape, 34)[0])
+    other = T.dev_f32(T.fluence_pair(shape, 35)[0])
+    say("[gpu] symmetric call under capture")
+    want = []
+    with T.nn.Denoiser(channels, shape) as d:
+        d.set_params(flat)
+        for v in (x, other):
+            u = t.empty_like(x)
+            d.forward(v, u_out=u, symmetries=8)
+            want.append(u)
+    with T.nn.Denoiser(channels, shape) as d:
+        d.set_params(flat)
+        d.forward(x, u_out=t.empty_like(x))  # packs the weights
+        t.cuda.synchronize()
+        inp, out = x.clone(), t.empty_like(x)
+        g = t.cuda.CUDAGraph()
+        with t.cuda.graph(g):
+            d.forward(inp, u_out=out, symmetries=8)
+        for k in (0, 1, 0, 1):
+            inp.copy_((x, other)[k])
+            out.zero_()
+            g.replay()
+            t.cuda.synchronize()
+            assert t.equal(out, want[k])
+            eager = t.empty_like(x)
+            d.forward(inp, u_out=eager, symmetries=8)
+            t.cuda.synchronize()
+            assert t.equal(eager, want[k])
