@@ -196,3 +196,60 @@ def test_symmetric_call_captured_first():
             d.forward(inp, u_out=eager, symmetries=8)
             t.cuda.synchronize()
             assert t.equal(eager, want[k])
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("kind,shape,ci,co", [
+    ("conv3", (5, 6, 19), 1, 40),        # one channel
+    ("conv3", (6, 5, 7), 8, 16), ("conv3", (5, 7, 6), 40, 24),   # few channels in eights
+    ("conv3", (9, 10, 11), 64, 40),      # bricks
+    ("conv3", (33, 64, 62), 32, 32),     # resident weights
+    ("up", (3, 5, 6), 64, 24), ("down", (6, 4, 10), 32, 16)])
+def test_outputs_of_activations_not_finite(kind, shape, ci, co, value):
+    """One activation that is not finite: the outputs it is part of are not
+    finite, all others keep the bits they have with a zero in its place."""
+    t = T.torch()
+    say("[gpu] not finite, forward", value, kind, shape, ci, co)
+    x, w, b = T.layer_case(kind, shape, ci, co, 9)
+    w = np.abs(w) + 0.01  # no product of infinity and zero
+    at = (shape[0] - 2, shape[1] - 1, 1)
+    out = T.out_shape(kind, shape) + (co,)
+    ys = []
+    for v in (0.0, value):
+        x[at + (ci // 2,)] = v
+        y = t.empty(out, device="cuda")
+        T.nn.mcx_nn_layer_forward(T.KIND[kind], shape, ci, co, T.dev_bf16(x), T.dev_f32(w),
+                                  T.dev_f32(b), relu=False, y=y, y_f32=True)
+        ys.append(T.host(y))
+    part = np.zeros(out, bool)
+    if kind == "conv3":
+        part[tuple(slice(max(k - 1, 0), k + 2) for k in at)] = True
+    elif kind == "up":
+        part[tuple(slice(2 * k, 2 * k + 2) for k in at)] = True
+    else:
+        part[tuple(k // 2 for k in at)] = True
+    assert np.all(np.isfinite(ys[0]))
+    assert np.array_equal(~np.isfinite(ys[1]), part)
+    assert np.array_equal(ys[1][~part], ys[0][~part])
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("kind,shape,ci,co", [("down", (6, 10, 14), 24, 72), ("down", (2, 2, 2), 8, 8),
+                                              ("up", (5, 3, 7), 72, 24), ("up", (1, 1, 1), 8, 8)])
+def test_stride_2_weight_gradients_not_finite(kind, shape, ci, co, value):
+    """The last voxel's activation of one channel is not finite: so are that
+    channel's weight gradients, of the one tap that reads it in a down layer
+    and of all in an up layer, and no other ones."""
+    t = T.torch()
+    say("[gpu] not finite, stride 2", value, kind, shape, ci, co)
+    rng = np.random.default_rng(8)
+    x = T.O.bf16(np.abs(rng.normal(size=shape + (ci,))))
+    gy = T.O.bf16(rng.uniform(0.5, 1.5, size=T.out_shape(kind, shape) + (co,)))
+    x[-1, -1, -1, 3] = value
+    gw = t.empty((8, ci, co), device="cuda")
+    w = t.zeros((8, ci, co), device="cuda")
+    T.nn.mcx_nn_layer_backward(T.KIND[kind], shape, ci, co, T.dev_bf16(x), w, T.dev_bf16(gy), None,
+                               gw, None)
+    part = np.zeros((8, ci, co), bool)
+    part[7 if kind == "down" else slice(None), 3] = True
+    assert np.array_equal(~np.isfinite(T.host(gw)), part)
