@@ -16,8 +16,8 @@ mcx_status report(mcx_status st, const char* message);
 // post-processing): blocks are kept for the next call instead of allocated
 // and freed each time (hipMalloc and hipFree of a few buffers cost such a
 // call 15 to 60 us).  At most kScratchIdleBytes and kScratchIdleBlocks stay
-// idle over all devices; they are given back when memory runs out and when
-// any context or network is destroyed.  Safe from several threads: a block
+// idle over all devices; they are given back when an allocation of the library
+// runs out of memory and when any context or network is destroyed.  Safe from several threads: a block
 // belongs to one call at a time, and that call's work on it has ended before
 // it is released.
 constexpr size_t kScratchIdleBytes = size_t(256) << 20;
@@ -44,6 +44,13 @@ class Scratch {
 };
 // Free every idle block.
 void scratch_trim();
+
+// hipMalloc; out of memory, again with every idle block freed.
+hipError_t device_malloc(void** p, size_t bytes);
+template <typename T>
+hipError_t device_malloc(T** p, size_t bytes) {
+  return device_malloc(reinterpret_cast<void**>(p), bytes);
+}
 
 // Ledger slots (FP64 weight sums) and counter slots accumulated per simulation.
 enum LedgerSlot {

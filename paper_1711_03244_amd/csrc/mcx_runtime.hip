@@ -77,6 +77,16 @@ void mcx::scratch_trim() {
   for (const IdleBlock& b : all) (void)hipFree(b.p);
 }
 
+hipError_t mcx::device_malloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    scratch_trim();
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
+
 hipError_t mcx::Scratch::acquire(size_t bytes) {
   hipError_t e = hipGetDevice(&device_);
   if (e != hipSuccess) return e;
@@ -99,12 +109,7 @@ hipError_t mcx::Scratch::acquire(size_t bytes) {
     }
   }
   size_ = std::max<size_t>(rounded(bytes), 1 << 16);
-  e = hipMalloc(&p_, size_);
-  if (e == hipErrorOutOfMemory) {
-    (void)hipGetLastError();
-    scratch_trim();
-    e = hipMalloc(&p_, size_);
-  }
+  e = device_malloc(&p_, size_);
   if (e != hipSuccess) {
     p_ = nullptr;
     size_ = 0;
@@ -752,24 +757,24 @@ static mcx_status setup(mcx_ctx* c, const mcx_sim* sims) {
       rec_rows += c->opt.max_detected;
     }
   }
-  HIP_TRY(hipMalloc(&c->d_labels, labels));
-  HIP_TRY(hipMalloc(&c->d_tables, tables * sizeof(float4)));
-  HIP_TRY(hipMalloc(&c->d_tally, c->total_cells * sizeof(uint64_t)));
-  HIP_TRY(hipMalloc(&c->d_ledger, n * mcx::kLedgerN * sizeof(double)));
-  HIP_TRY(hipMalloc(&c->d_counts, n * mcx::kCountN * sizeof(unsigned long long)));
-  HIP_TRY(hipMalloc(&c->d_det_count, n * sizeof(unsigned long long)));
-  HIP_TRY(hipMalloc(&c->d_reduce, n * 2 * sizeof(double)));
-  HIP_TRY(hipMalloc(&c->d_desc, n * sizeof(mcx::SimDesc)));
-  HIP_TRY(hipMalloc(&c->d_job_start, (n + 1) * sizeof(uint64_t)));
-  HIP_TRY(hipMalloc(&c->d_home_start, (n + 1) * sizeof(uint64_t)));
-  HIP_TRY(hipMalloc(&c->d_job_counter, n * sizeof(unsigned long long)));
-  HIP_TRY(hipMalloc(&c->d_wbox, n * 2 * mcx::kMaxWinGates * sizeof(int4)));
+  HIP_TRY(mcx::device_malloc(&c->d_labels, labels));
+  HIP_TRY(mcx::device_malloc(&c->d_tables, tables * sizeof(float4)));
+  HIP_TRY(mcx::device_malloc(&c->d_tally, c->total_cells * sizeof(uint64_t)));
+  HIP_TRY(mcx::device_malloc(&c->d_ledger, n * mcx::kLedgerN * sizeof(double)));
+  HIP_TRY(mcx::device_malloc(&c->d_counts, n * mcx::kCountN * sizeof(unsigned long long)));
+  HIP_TRY(mcx::device_malloc(&c->d_det_count, n * sizeof(unsigned long long)));
+  HIP_TRY(mcx::device_malloc(&c->d_reduce, n * 2 * sizeof(double)));
+  HIP_TRY(mcx::device_malloc(&c->d_desc, n * sizeof(mcx::SimDesc)));
+  HIP_TRY(mcx::device_malloc(&c->d_job_start, (n + 1) * sizeof(uint64_t)));
+  HIP_TRY(mcx::device_malloc(&c->d_home_start, (n + 1) * sizeof(uint64_t)));
+  HIP_TRY(mcx::device_malloc(&c->d_job_counter, n * sizeof(unsigned long long)));
+  HIP_TRY(mcx::device_malloc(&c->d_wbox, n * 2 * mcx::kMaxWinGates * sizeof(int4)));
   if (recs > 0) {
-    HIP_TRY(hipMalloc(&c->d_rec, recs * sizeof(float)));
-    HIP_TRY(hipMalloc(&c->d_rec_photon, rec_rows * sizeof(unsigned long long)));
+    HIP_TRY(mcx::device_malloc(&c->d_rec, recs * sizeof(float)));
+    HIP_TRY(mcx::device_malloc(&c->d_rec_photon, rec_rows * sizeof(unsigned long long)));
   }
   if (c->diag)
-    HIP_TRY(hipMalloc(&c->d_digest, n * c->opt.ndigest * mcx::kDigestN * sizeof(double)));
+    HIP_TRY(mcx::device_malloc(&c->d_digest, n * c->opt.ndigest * mcx::kDigestN * sizeof(double)));
   for (size_t i = 0; i < n; ++i) {
     const SimHost& sh = c->sims[i];
     HIP_TRY(hipMemcpyAsync(c->d_labels + sh.label_off, sims[i].vol.labels, sh.nvox,
@@ -1141,12 +1146,12 @@ static mcx_status fluence_host(mcx_ctx* c, int32_t sim, int32_t kind, void* host
   MCX_TRY(wait_done(c, c->stream));
   const uint64_t* tally = c->d_tally + sh.tally_off;
   if (f64) {
-    if (!c->d_stage64) HIP_TRY(hipMalloc(&c->d_stage64, c->max_cells * sizeof(double)));
+    if (!c->d_stage64) HIP_TRY(mcx::device_malloc(&c->d_stage64, c->max_cells * sizeof(double)));
     HIP_TRY(mcx::launch_normalise_f64(tally, sh.ncells(), scale, c->d_stage64, c->stream));
     HIP_TRY(hipMemcpyAsync(host_out, c->d_stage64, sh.ncells() * sizeof(double),
                            hipMemcpyDeviceToHost, c->stream));
   } else {
-    if (!c->d_stage32) HIP_TRY(hipMalloc(&c->d_stage32, c->max_cells * sizeof(float)));
+    if (!c->d_stage32) HIP_TRY(mcx::device_malloc(&c->d_stage32, c->max_cells * sizeof(float)));
     HIP_TRY(mcx::launch_normalise_f32(tally, sh.ncells(), scale, c->d_stage32, c->stream));
     HIP_TRY(hipMemcpyAsync(host_out, c->d_stage32, sh.ncells() * sizeof(float),
                            hipMemcpyDeviceToHost, c->stream));
@@ -1356,7 +1361,7 @@ static mcx_status ensure(T** p, uint64_t* cap, uint64_t n) {
   if (*p) HIP_TRY(hipFree(*p));
   *p = nullptr;
   *cap = 0;
-  HIP_TRY(hipMalloc(reinterpret_cast<void**>(p), std::max<uint64_t>(n, 1) * sizeof(T)));
+  HIP_TRY(mcx::device_malloc(p, std::max<uint64_t>(n, 1) * sizeof(T)));
   *cap = n;
   return MCX_OK;
 }
@@ -1433,7 +1438,7 @@ mcx_status mcx_detected_process(mcx_ctx* c, int32_t sim, const float* host_dmua,
                 static_cast<unsigned long long>(nweight), static_cast<unsigned long long>(nrec));
   const float* dmua = nullptr;
   if (host_dmua) {
-    if (!c->d_dmua) HIP_TRY(hipMalloc(&c->d_dmua, 256 * sizeof(float)));
+    if (!c->d_dmua) HIP_TRY(mcx::device_malloc(&c->d_dmua, 256 * sizeof(float)));
     HIP_TRY(hipMemcpyAsync(c->d_dmua, host_dmua, sp.npath * sizeof(float),
                            hipMemcpyHostToDevice, c->stream));
     dmua = c->d_dmua;

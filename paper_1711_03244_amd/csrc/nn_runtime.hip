@@ -259,7 +259,7 @@ namespace {
 template <typename T>
 mcx_status nn_alloc(mcx_nn* nn, T** p, size_t count) {
   void* q = nullptr;
-  NN_HIP(hipMalloc(&q, std::max<size_t>(count, 1) * sizeof(T)));
+  NN_HIP(mcx::device_malloc(&q, std::max<size_t>(count, 1) * sizeof(T)));
   nn->owned.push_back(q);
   *p = static_cast<T*>(q);
   return MCX_OK;
@@ -317,7 +317,7 @@ void take_images(mcx_nn* nn, hipStream_t s) {
   // another thread's capture does not make this allocation one of its own
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   (void)hipThreadExchangeStreamCaptureMode(&mode);
-  if (hipMalloc(&base, static_cast<size_t>(at)) == hipSuccess) {
+  if (mcx::device_malloc(&base, static_cast<size_t>(at)) == hipSuccess) {
     nn->owned.push_back(base);  // reserved
     lay_out(images);
     nn->batch = images;
