@@ -179,11 +179,11 @@ typedef struct {
  * do not depend on the order of the additions.  MCX_MAP_ADDS_64: one 64-bit
  * atomic add per visit.  MCX_MAP_ADDS_32: a 32-bit atomic add to the low
  * word whose returned value tells whether it carried into the high word
- * (then one more add); faster at the memory side, but the wave waits for
- * the returned value.  MCX_MAP_ADDS_AUTO: 32-bit adds where the memory
- * side's rate of atomics binds: large launches (16 waves per compute unit,
- * eight photons per lane) of simulations whose voxels are thin (mean mus h
- * below 2).  The maps are bit-identical. */
+ * (then one more add); faster at the memory side, but a lane has to have
+ * the returned value before its next add.  MCX_MAP_ADDS_AUTO: 32-bit adds,
+ * by simulation, where the memory side's rate of atomics binds: large launches
+ * (16 waves per compute unit, eight photons per lane) of voxels that are thin
+ * (mean mus h below 2).  The maps are bit-identical. */
 enum { MCX_MAP_ADDS_AUTO = 0, MCX_MAP_ADDS_64 = 1, MCX_MAP_ADDS_32 = 2 };
 
 /* Output kinds for mcx_fluence*. */

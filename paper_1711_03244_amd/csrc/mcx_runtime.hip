@@ -444,9 +444,11 @@ static void describe(SimHost& sh, const mcx_sim& sm) {
   if (seen > 0) {
     // segments per mm (scatterings, and three faces per two voxel edges of
     // path) over the rates at which paths end: absorption, leaving the grid,
-    // the last gate.  Over the 256 cubes of the batched workload (343 to 7000
-    // segments per photon) the estimate is off by a factor of 1.4 (one
-    // standard deviation), a constant by 1.9.
+    // the last gate (which few reach, unless paths of their mean length do: ten
+    // times 1 / reach).  The two factors are fitted.  Over the 256 cubes of the
+    // batched workload (108 to 2305 segments per photon) the estimate is off by
+    // a factor of 1.38 (one standard deviation), a constant by 1.93, with 0 for
+    // the 10 by 1.45, with 30 by 1.38, with 1 for the 1.5 by 1.43.
     const double k = static_cast<double>(seen);
     const double side = sh.h * std::min(sh.nx, std::min(sh.ny, sh.nz));
     const double reach = kCmmPerNs * k / index * sh.dt * sh.ngates;
@@ -642,8 +644,9 @@ struct LaunchShape {
 // / 5.3 / 5.8; sphere benchmark 1e5 7.0 / 7.2 / 6.9, 1e6 14.4 / 11.2 / 12.1,
 // 3e6 33 / 23.6 / 24.1; head 3e5 11.4 / 10.5 / 12.6, 1e6 24.7 / 17.1 /
 // 15.7): 4 below half a photon per lane of a full launch, 8 below eight (thin
-// voxels) or two.  Jobs of 64 photons, smaller where there are fewer photons
-// than lanes.
+// voxels) or two.  Of those figures the rule misses the best at 1e5 and 3e6
+// sphere photons, by 2 % at most.  Jobs of 64 photons, smaller where there are
+// fewer photons than lanes.
 static LaunchShape launch_shape(const mcx_ctx* c, uint64_t photons, uint64_t thin) {
   LaunchShape s{c->grid, c->block, c->chunk, true};
   const double lanes = c->cus * 1024.0;
@@ -673,7 +676,8 @@ static LaunchShape launch_shape(const mcx_ctx* c, uint64_t photons, uint64_t thi
 // than 64-bit adds: by the context's setting, or, for MCX_MAP_ADDS_AUTO,
 // where the memory side's rate of atomics binds -- thin voxels, at least
 // eight photons per lane of a full launch, and 16 waves per compute unit to
-// cover the returned value's latency.  Measured, ms with 64- / 32-bit adds:
+// cover the returned value's latency (a lane needs it before its next add).
+// Measured, ms with 64- / 32-bit adds:
 // sphere benchmark 1e6 photons 12.4 / 12.8, 3e6 24.3 / 22.9, 1e7 63.7 / 57.5;
 // homogeneous cube 1e6 5.8 / 6.3, 1e7 25.2 / 23.2; head (thick voxels) 1e7
 // 71.7 / 79.6.

@@ -348,7 +348,11 @@ __device__ __forceinline__ uint32_t window_cell(const int4* s_wbox, int wng, CSi
 // returning adds, branches per axis and ballots per count: homogeneous cube,
 // 1e4 photons 7.2 -> 5.1 ms; sphere benchmark, 1e6 photons 20.4 -> 14.0 ms,
 // 3e7 photons 162.5 -> 149.5 ms (bound by the map's atomics); head phantom,
-// 1e7 photons 100.9 -> 87.3 ms.
+// 1e7 photons 100.9 -> 87.3 ms.  All that takes 107 to 120 vector registers: four
+// waves per SIMD, 16 per CU, are resident at most, also without an LDS window,
+// where 67 to 71 registers allowed 28.  Those launches gain nevertheless (no
+// window: sphere, 5e6 photons 109.9 -> 104.7 ms, head, 2e6 photons 55.5 -> 45.8),
+// so the kernel keeps them.
 //
 // What the event loop reads of its simulation in every iteration, held in
 // scalar registers while the wave stays on that simulation (a scalar load
