@@ -444,11 +444,10 @@ static void describe(SimHost& sh, const mcx_sim& sm) {
   if (seen > 0) {
     // segments per mm (scatterings, and three faces per two voxel edges of
     // path) over the rates at which paths end: absorption, leaving the grid,
-    // the last gate (which few reach, unless paths of their mean length do: ten
-    // times 1 / reach).  The two factors are fitted.  Over the 256 cubes of the
-    // batched workload (108 to 2305 segments per photon) the estimate is off by
-    // a factor of 1.38 (one standard deviation), a constant by 1.93, with 0 for
-    // the 10 by 1.45, with 30 by 1.38, with 1 for the 1.5 by 1.43.
+    // the last gate (ten over the path to it; the ten is fitted).  Over the 256
+    // cubes of the batched workload (108 to 2305 segments per photon) the
+    // estimate is off by a factor of 1.38 (one standard deviation), with 0 for the
+    // ten by 1.45, with 30 by 1.38, a constant by 1.93.
     const double k = static_cast<double>(seen);
     const double side = sh.h * std::min(sh.nx, std::min(sh.ny, sh.nz));
     const double reach = kCmmPerNs * k / index * sh.dt * sh.ngates;
