@@ -1189,7 +1189,9 @@ static mcx_status stats_of(mcx_ctx* c, int32_t sim, mcx_run_stats* o) {
   o->reflections = cnt[mcx::kCntReflections];
   o->rr_tests = cnt[mcx::kCntRrTests];
   o->rr_survived = cnt[mcx::kCntRrSurvived];
-  o->events = cnt[mcx::kCntEvents];
+  // the kernel counts segments (a photon's at its end); the iteration in which
+  // a photon met the cap was none
+  o->events = cnt[mcx::kCntEvents] + cnt[mcx::kCntCapped];
   o->lane_slots = cnt[mcx::kCntLaneSlots];
   o->flushes = cnt[mcx::kCntFlushes];
   const SimHost& sh = c->sims[sim];

@@ -502,8 +502,8 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams L) {
   auto flush_wave = [&]() {
     spill_counts();
     if (lane == 0)  // a segment ends in a scattering, a face or the last gate's end
-      s_cnt[wid][kCntFaceEvents] = s_cnt[wid][kCntEvents] - s_cnt[wid][kCntScatters] -
-                                   s_cnt[wid][kCntTimeout] - s_cnt[wid][kCntCapped];
+      s_cnt[wid][kCntFaceEvents] =
+          s_cnt[wid][kCntEvents] - s_cnt[wid][kCntScatters] - s_cnt[wid][kCntTimeout];
     if (cur >= 0) {
       if (lane < kCountN && s_cnt[wid][lane]) atomicAdd(D->counts + lane, s_cnt[wid][lane]);
       if (lane < kLedgerN && s_led[wid][lane] != 0.0)
@@ -951,7 +951,7 @@ __global__ void __launch_bounds__(1024) transport_kernel(const LaunchParams L) {
           }
         }
         alive = false;
-        c_ev += nev + (end == kEndCapped ? 1u : 0u);  // the iteration that met the cap counts
+        c_ev += nev;
         c_scat += nscat;
         c_blk += blk - 1u;  // block 0 launched the photon
       }
