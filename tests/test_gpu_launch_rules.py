@@ -134,12 +134,13 @@ def test_tuner_keeps_what_it_timed():
     """Where no shape beats the default in the pilots, the kept shape is the
     default's, its window boxes included: a run then flushes the same visits as
     one with that shape in a context that was never tuned."""
-    p = W.cube_sphere(n=40, ngates=10, dt=0.5)
-    N = 20000
+    p = W.cube_homogeneous(n=20).replace(src_pos=(9.5, 9.5, 0.0), ngates=10, dt=1.5)
+    N = 100000
     kept = 0
-    for pilot in (1, 64, 100, 150, 200, 250, 300, 400, 500):
+    for k in range(40):  # few photons see a second gate, where the boxes differ: near ties
+        pilot = (3000, 30000)[k % 2]
         with mcx.Simulation(p) as sim:
-            tune = sim.autotune(pilot, 9)
+            tune = sim.autotune(pilot, 9 + k)
             say("[gpu] tuned with", pilot, tune)
             assert tune["best_ms"] <= tune["default_ms"]
             sim.run(N, 3)
